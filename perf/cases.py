@@ -127,10 +127,10 @@ def _positions(g, prompt, n):
 
 # ---------------------------------------------------------------- scores in plain torch, to place the cut
 
-def _attention(q, k, v, causal):
+def _attention(q, k, v, causal, dt=torch.float32):
     n, hq, dh = q.shape
     group = hq // k.shape[1]
-    q, k, v = q.float(), k.float(), v.float()
+    q, k, v = q.to(dt), k.to(dt), v.to(dt)
     out = torch.empty_like(q)
     rank = torch.arange(n, device=q.device)
     for h in range(hq):
@@ -147,11 +147,11 @@ def _attention(q, k, v, causal):
 
 def _scores(delta, x, kind):
     s = delta.norm(dim=1)
-    return s / x.float().norm(dim=1) if kind == "rel" else s
+    return s / x.to(s.dtype).norm(dim=1) if kind == "rel" else s
 
 
-def _rms(x):
-    x = x.float()
+def _rms(x, dt=torch.float32):
+    x = x.to(dt)
     return x * torch.rsqrt((x * x).mean(dim=1, keepdim=True) + 1e-6)
 
 
@@ -159,22 +159,23 @@ def _rope(u, pos):
     half = u.shape[2] // 2
     freq = THETA ** (-torch.arange(half, device=u.device, dtype=torch.float64) / half)
     a = pos.double()[:, None] * freq
-    c, s = torch.cos(a).float()[:, None], torch.sin(a).float()[:, None]
+    c, s = torch.cos(a).to(u.dtype)[:, None], torch.sin(a).to(u.dtype)[:, None]
     lo, hi = u[..., :half], u[..., half:]
     return torch.cat([lo * c - hi * s, lo * s + hi * c], dim=2)
 
 
-def _front(x, w_qkv, pos, hq, hkv, dh):
-    u = _rms(x) @ w_qkv.float()
+def _front(x, w_qkv, pos, hq, hkv, dh, dt=torch.float32):
+    u = _rms(x, dt) @ w_qkv.to(dt)
     q, k, v = (t.reshape(x.shape[0], -1, dh) for t in u.split([hq * dh, hkv * dh, hkv * dh], dim=1))
     return _rope(q, pos), _rope(k, pos), v
 
 
-def _ffn(x, gate, up, down):
+def _ffn(x, gate, up, down, dt=torch.float32):
     out = []
+    gate, up, down = gate.to(dt), up.to(dt), down.to(dt)
     for r in x.split(4096):
-        h = _rms(r)
-        out.append(r + (torch.nn.functional.silu(h @ gate.float()) * (h @ up.float())) @ down.float())
+        h = _rms(r, dt)
+        out.append(r + (torch.nn.functional.silu(h @ gate) * (h @ up)) @ down)
     return torch.cat(out)
 
 
@@ -265,7 +266,7 @@ def _prepare_schedule(case, g):
     if case["graph"]:
         prompt = x0.clone()
         return dict(graph=SS.GraphedSchedule(st, x0, weights, shots, rope_theta=THETA, final=final), x0=x0,
-                    prompt=prompt, final=final)
+                    prompt=prompt, final=final, weights=weights, shots=shots)
     return dict(args=(st, x0, weights, shots, THETA, final), final=final)
 
 
@@ -365,3 +366,71 @@ def tolerance(case):
     if case["path"] == "schedule":
         return dict(rel=1e-2, max=8e-2)
     return dict(rel=4e-3, max=3e-2)
+
+
+# ---------------------------------------------------------------- the same pass in 64 bits, in plain torch
+
+def _kept(scores, k_keep, first, last, low=False):
+    """TopK: the protected rows and the best of the others, k_keep in all, in their order."""
+    s = -scores if low else scores.clone()
+    s[:first] = float("inf")
+    s[s.numel() - last:] = float("inf")
+    return torch.sort(torch.topk(s, max(k_keep, min(first + last, s.numel()))).indices).values
+
+
+def _decided(scores, kept, idx, rows):
+    """The outputs that follow from which rows are kept: flags, compacted rows and positions, count."""
+    halt = torch.ones(scores.shape, dtype=torch.uint8, device="cuda")
+    halt[kept] = 0
+    compact, new_idx = torch.zeros_like(rows), torch.zeros_like(idx)
+    compact[:kept.numel()], new_idx[:kept.numel()] = rows[kept], idx[kept]
+    return [halt, compact, new_idx, torch.full((1,), kept.numel(), dtype=torch.int32, device="cuda")]
+
+
+def exact(case, seed):
+    f64 = torch.float64
+    d, hq, hkv, dh, m = SHAPES[case["shape"]]
+    state = prepare(case, seed)
+    if case["path"] == "layer":
+        p, x, q, k, v, w_o, idx, n, _ = state["args"]
+        delta = _attention(q, k, v, case["causal"], f64) @ w_o.to(f64)
+        scores, first, last = _scores(delta, x, case["score"]), case["first"], case["last"]
+        if case["rule"] == "topk":
+            kept = _kept(scores, int(p.k_keep), first, last)
+        else:
+            stays = scores >= (float(p.tau) if case["rule"] == "threshold" else 0.0)
+            stays[:first] = stays[n - last:] = True
+            kept = torch.nonzero(stays)[:, 0]
+        x_next = x.to(f64) + delta
+        return [x_next, scores] + _decided(scores, kept, idx, x_next)
+    if case["path"] == "chain":
+        _, x, idx, n, weights, halt = state["args"]
+        delta = _attention(*_front(x, weights[0]["w_qkv"], idx, hq, hkv, dh, f64), True, f64) @ weights[0]["w_o"].to(f64)
+        scores, x_next = _scores(delta, x, "rel"), x.to(f64) + delta
+        return [x_next, scores] + _decided(scores, _kept(scores, n - int(halt * n), 0, 0), idx, x_next)
+    if case["path"] == "schedule":
+        if case["graph"]:
+            x0, weights, shots = state["prompt"], state["weights"], state["shots"]
+        else:
+            _, x0, weights, shots, _, _ = state["args"]
+        x, pos = x0.to(f64), torch.arange(x0.shape[0], device="cuda")
+        final = torch.empty_like(x)
+        for l, w in enumerate(weights):
+            gate, up = (t.reshape(d, m) for t in w["w_gate_up"].reshape(d, m // 32, 2, 32).unbind(2))
+            delta = _attention(*_front(x, w["w_qkv"], pos, hq, hkv, dh, f64), True, f64) @ w["w_o"].to(f64)
+            done = _ffn(x + delta, gate, up, w["w_down"], f64)
+            if l in shots:
+                final[pos] = done
+                kept = _kept(_scores(delta, x, "rel"), shots[l], case["first"], case["last"])
+                done, pos = done[kept], pos[kept]
+            x = done
+        final[pos] = x
+        return [final] if case["graph"] else [final, x.shape[0]]
+    old, new, idx, low = state["old"], state["new"], state["idx"], state["low"]
+    scores = _scores(new.to(f64) - old.to(f64), old, "rel")
+    kept = _kept(scores, int(state["p"].k_keep), 0, 0, low)
+    out = _decided(scores, kept, idx, new.to(f64))
+    full = torch.zeros(state["full"].shape, dtype=f64, device="cuda")
+    gone = out[0] == 1
+    full[idx[gone].long()] = new[gone].to(f64)
+    return [scores] + out + [full]
