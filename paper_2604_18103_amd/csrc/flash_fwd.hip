@@ -8,7 +8,7 @@
 //
 // Two kernels:
 //   flash_fwd_mfma<DH>  bf16, MFMA 32x32x16, fp32 softmax and accumulation (the hot kernel)
-//   flash_fwd_simple<T> one wave per (row, head), plain FMA; the fp32 path
+//   flash_fwd_f32<DH> fp32, MFMA 16x16x4 fp32, keys split over the waves of a workgroup
 #include "common.h"
 #include "lds_ops.h"
 #include "staging_addr.h"
@@ -16,65 +16,214 @@
 namespace dash {
 
 // ------------------------------------------------------------------------------------------------
-// Plain kernel: one wave per (query row, head). Lane j scores key j of a 64-key block, then all
-// lanes accumulate their own head dims.
+// fp32 kernel: v_mfma_f32_16x16x4_f32 (fp32 operands, products and sums), exact expf.
+//
+// A workgroup owns 16 query rows of one head; its 8 waves split the KEYS (wave w takes the 32-key blocks w, w + 8,
+// ...) and meet once, at the end, in LDS. The prompts of this path are short (hundreds to a few thousand rows): with a
+// wave per query row and all of its keys in series the kernel waited for memory and for its own chain of adds. Splitting
+// the keys makes that chain eight times shorter and needs no barrier inside the loop.
+//
+// S^T = K Q^T, then O^T += V^T P^T: in the 16x16 accumulator layout (lane 16 g + i: rows 4 g .. 4 g + 3 of column i) lane
+// (i, g) holds the scores of query i for keys 4 g + r, and taking key 4 g + r as k-slot g of step r makes those registers
+// the B operand of the second product as they are. The contraction of the first product and the dims of the second are
+// numbered so that every operand is a 16-byte global load: step s of dim chunk c contracts dims 16 c + 4 g + s, and
+// output block (hf, e) holds dims 64 hf + 4 i + e. No LDS in the loop: K and V come from the L2.
+//
+// Bound by latency at a few hundred rows, by the fp32 matrix rate and the L2 from a few thousand on. Measured, causal, 4 / 1
+// heads of 64: n = 512 12 us, 2048 39 us, 8192 451 us (a wave per row and head: 72, 409, 5378 us); 4 / 2 heads of 128: 19,
+// 70, 868 us (96, 809, 11795 us). Error against 64 bits 2.2e-7 instead of 2.7e-7 at 512, 3.2e-7 instead of 6.3e-7 at 8192.
+// Two 16-row blocks per wave, which read K and V half as often, were 10 % faster from 4096 rows on, 40 % slower at 2048
+// and less, and spill at head_dim 128.
 // ------------------------------------------------------------------------------------------------
-template <typename T, int DH>
-__global__ __launch_bounds__(64) void flash_fwd_simple(const T* __restrict__ q, const T* __restrict__ k,
-                                                       const T* __restrict__ v,
-                                                       const int32_t* __restrict__ pos, T* __restrict__ o,
-                                                       int n, int Hq, int Hkv, float scale, int causal,
-                                                       uint32_t* __restrict__ clear_words, int n_clear) {
-    constexpr int DPL = DH / kWave;  // head dims per lane
-    if (blockIdx.x == 0 && blockIdx.y == 0)  // scratch of the kernels that follow in the layer call
-        for (int c = threadIdx.x; c < n_clear; c += kWave) clear_words[c] = 0u;
-    __shared__ float qs[DH];
-    const int i = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
-    const int g = h / (Hq / Hkv);
-    const T* qi = q + ((size_t)i * Hq + h) * DH;
-    for (int c = lane; c < DH; c += kWave) qs[c] = to_float(qi[c]);
-    __syncthreads();
-    const int limit = causal ? i + 1 : n;
-    const int pos_i = pos[i];
+constexpr int kF32Waves = 8;
+constexpr int kF32Keys = 32;  // keys per wave and step
+
+template <int DH>
+__global__ __launch_bounds__(kF32Waves * kWave) void flash_fwd_f32(
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
+    const int32_t* __restrict__ pos, float* __restrict__ o, int n, int Hq, int Hkv, float scale, int causal, int n_qtiles,
+    uint32_t* __restrict__ clear_words, int n_clear) {
+    constexpr int KC = DH / 16, HF = DH / 64, OSTR = DH + 4;
+    __shared__ float part_o[kF32Waves][16][OSTR];
+    __shared__ float part_m[kF32Waves][16], part_l[kF32Waves][16];
+    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    if (blockIdx.x == 0)  // scratch of the kernels that follow in the layer call
+        for (int c = tid; c < n_clear; c += kF32Waves * kWave) clear_words[c] = 0u;
+    const int qt = n_qtiles - 1 - (int)blockIdx.x / Hq, head = (int)blockIdx.x % Hq;  // longest rows first
+    const int kvh = head / (Hq / Hkv);
+    const int i = lane % 16, g = lane / 16;
+    const int row0 = qt * 16;
+    const size_t kv_stride = (size_t)Hkv * DH;
+    const float* kh = k + (size_t)kvh * DH;
+    const float* vh = v + (size_t)kvh * DH;
+
+    f32x4 Qf[KC], O[HF * 4];
     float m = -INFINITY, l = 0.f;
-    float acc[DPL];
+    const int row = min(row0 + i, n - 1);
+    {
+        const float* qp = q + ((size_t)row * Hq + head) * DH + 4 * g;
 #pragma unroll
-    for (int c = 0; c < DPL; ++c) acc[c] = 0.f;
-    for (int j0 = 0; j0 < limit; j0 += kWave) {
-        const int j = j0 + lane;
-        const bool valid = j < limit && (!causal || pos[j] <= pos_i);
-        float s = -INFINITY;
-        if (valid) {
-            const T* kj = k + ((size_t)j * Hkv + g) * DH;
-            float dot = 0.f;
-#pragma unroll 8
-            for (int c = 0; c < DH; ++c) dot = fmaf(qs[c], to_float(kj[c]), dot);
-            s = dot * scale;
-        }
-        float mx = s;
+        for (int c = 0; c < KC; ++c) Qf[c] = *reinterpret_cast<const f32x4*>(qp + 16 * c);
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-        const float m_new = fmaxf(m, mx);  // finite: key j0 (rank <= i) is always visible
-        const float alpha = expf(m - m_new);
-        const float p = valid ? expf(s - m_new) : 0.f;
-        float ps = p;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) ps += __shfl_xor(ps, off);
-        l = l * alpha + ps;
-#pragma unroll
-        for (int c = 0; c < DPL; ++c) acc[c] *= alpha;
-        const int cnt = min(kWave, limit - j0);
-        for (int jj = 0; jj < cnt; ++jj) {
-            const float pj = __shfl(p, jj);
-            const T* vj = v + ((size_t)(j0 + jj) * Hkv + g) * DH + lane * DPL;
-#pragma unroll
-            for (int c = 0; c < DPL; ++c) acc[c] = fmaf(pj, to_float(vj[c]), acc[c]);
-        }
-        m = m_new;
+        for (int d = 0; d < HF * 4; ++d) O[d] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    T* oi = o + ((size_t)i * Hq + h) * DH + lane * DPL;
+    const int pos_q = pos[row];
+    const int kend = causal ? min(n, row0 + 16) : n;
+    for (int key0 = wave * kF32Keys; key0 < kend; key0 += kF32Waves * kF32Keys) {
+        f32x4 S[2];
+        f32x4 Vf[2][4][HF];
+        {
+            f32x4 Kf[2][KC];
 #pragma unroll
-    for (int c = 0; c < DPL; ++c) oi[c] = from_float<T>(acc[c] / l);
+            for (int kb = 0; kb < 2; ++kb) {
+                const float* kp = kh + (size_t)min(key0 + 16 * kb + i, n - 1) * kv_stride + 4 * g;
+#pragma unroll
+                for (int c = 0; c < KC; ++c) Kf[kb][c] = *reinterpret_cast<const f32x4*>(kp + 16 * c);
+            }
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float* vp = vh + (size_t)min(key0 + 16 * kb + 4 * g + r, n - 1) * kv_stride + 4 * i;
+#pragma unroll
+                    for (int hf = 0; hf < HF; ++hf) Vf[kb][r][hf] = *reinterpret_cast<const f32x4*>(vp + 64 * hf);
+                }
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) S[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int c = 0; c < KC; ++c)
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb)
+                        S[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(Kf[kb][c][s], Qf[c][s], S[kb], 0, 0, 0);
+        }
+        // blocks that end beyond the first row's key, or beyond the last key: -inf where a key is not visible
+        const bool masked = (causal && key0 + kF32Keys - 1 > row0) || key0 + kF32Keys > n;
+        uint32_t seen = 0xFFu;  // bit 4 kb + r: the key is visible to this lane's query
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) S[kb] *= scale;
+        if (masked) {
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int key = key0 + 16 * kb + 4 * g + r;
+                    const int pos_k = pos[min(key, n - 1)];
+                    if (key >= n || (causal && (key > row0 + i || pos_k > pos_q))) {
+                        seen &= ~(1u << (4 * kb + r));
+                        S[kb][r] = -INFINITY;
+                    }
+                }
+        }
+        {
+            float mx = -INFINITY;
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) mx = fmaxf(mx, S[kb][r]);
+            mx = fmaxf(mx, __shfl_xor(mx, 16));
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float m_new = fmaxf(m, mx);
+            const float m_ref = m_new == -INFINITY ? 0.f : m_new;  // nothing visible to this query yet
+            const float alpha = expf(m - m_ref);
+            m = m_new;
+            float ps = 0.f;
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    S[kb][r] = (seen >> (4 * kb + r)) & 1u ? expf(S[kb][r] - m_ref) : 0.f;
+                    ps += S[kb][r];
+                }
+            l = l * alpha + ps;
+#pragma unroll
+            for (int d = 0; d < HF * 4; ++d) O[d] *= alpha;
+        }
+        // A key that a query does not see has probability 0, but 0 times an infinite or NaN value is NaN: such a block
+        // is added key by key, reading only what is visible. (Wave-uniform, never taken on finite values.)
+        bool odd = false;
+        if (masked) {
+            float t = 0.f;  // stays 0 unless some value is not finite
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int hf = 0; hf < HF; ++hf)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) t = fmaf(Vf[kb][r][hf][e], 0.f, t);
+            odd = __any(t != 0.f);  // NaN != 0
+        }
+        if (!odd) {
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int hf = 0; hf < HF; ++hf)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            O[4 * hf + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(Vf[kb][r][hf][e], S[kb][r], O[4 * hf + e], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll 1
+                    for (int gg = 0; gg < 4; ++gg) {
+                        const float* vp = vh + (size_t)min(key0 + 16 * kb + 4 * gg + r, n - 1) * kv_stride + 16 * g;
+                        const float p = __shfl(S[kb][r], 16 * gg + i);
+                        const uint32_t sees = __shfl(seen, 16 * gg + i);
+                        if ((sees >> (4 * kb + r)) & 1u)
+#pragma unroll
+                            for (int hf = 0; hf < HF; ++hf)
+#pragma unroll
+                                for (int rr = 0; rr < 4; ++rr)
+#pragma unroll
+                                    for (int e = 0; e < 4; ++e)
+                                        O[4 * hf + e][rr] = fmaf(p, vp[64 * hf + 4 * rr + e], O[4 * hf + e][rr]);
+                    }
+        }
+    }
+    // the eight partial results of each query meet: O = sum_w e^(m_w - M) O_w / sum_w e^(m_w - M) l_w, in the order of w
+    float lt = l;
+    lt += __shfl_xor(lt, 16);
+    lt += __shfl_xor(lt, 32);
+    if (g == 0) {
+        part_m[wave][i] = m;
+        part_l[wave][i] = lt;
+    }
+    // block (hf, e), register rr: dim 64 hf + 4 (4 g + rr) + e
+#pragma unroll
+    for (int hf = 0; hf < HF; ++hf)
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr)
+            *reinterpret_cast<f32x4*>(&part_o[wave][i][64 * hf + 16 * g + 4 * rr]) =
+                f32x4{O[4 * hf][rr], O[4 * hf + 1][rr], O[4 * hf + 2][rr], O[4 * hf + 3][rr]};
+    __syncthreads();
+    constexpr int PER = 16 * DH / (kF32Waves * kWave);  // dims per thread: 2 or 4
+    const int qi = tid / (DH / PER), d0 = (tid % (DH / PER)) * PER;
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < kF32Waves; ++w) M = fmaxf(M, part_m[w][qi]);
+    float L = 0.f, acc[PER];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) acc[e] = 0.f;
+#pragma unroll
+    for (int w = 0; w < kF32Waves; ++w) {
+        const float lw = part_l[w][qi];
+        if (lw == 0.f) continue;  // this wave saw no key of the query
+        const float f = expf(part_m[w][qi] - M);
+        L = fmaf(f, lw, L);
+#pragma unroll
+        for (int e = 0; e < PER; ++e) acc[e] = fmaf(f, part_o[w][qi][d0 + e], acc[e]);
+    }
+    if (row0 + qi < n) {
+        float* op = o + ((size_t)(row0 + qi) * Hq + head) * DH + d0;
+#pragma unroll
+        for (int e = 0; e < PER; ++e) op[e] = acc[e] / L;
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -505,17 +654,13 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
     }
 }
 
-template <typename T>
-static dash_status launch_simple(const dash_layer_params& p, const T* q, const T* k, const T* v,
-                                 const int32_t* pos, int n, T* o, float scale, uint32_t* clear_words, int n_clear,
-                                 hipStream_t s) {
-    dim3 grid(n, p.n_q_heads);
-    if (p.head_dim == 64)
-        hipLaunchKernelGGL((flash_fwd_simple<T, 64>), grid, dim3(64), 0, s, q, k, v, pos, o, n, p.n_q_heads,
-                           p.n_kv_heads, scale, p.causal, clear_words, n_clear);
-    else
-        hipLaunchKernelGGL((flash_fwd_simple<T, 128>), grid, dim3(64), 0, s, q, k, v, pos, o, n, p.n_q_heads,
-                           p.n_kv_heads, scale, p.causal, clear_words, n_clear);
+template <int DH>
+static dash_status launch_f32(const dash_layer_params& p, const float* q, const float* k, const float* v,
+                              const int32_t* pos, int n, float* o, float scale, uint32_t* clear_words, int n_clear,
+                              hipStream_t s) {
+    const int n_qtiles = (n + 15) / 16;
+    hipLaunchKernelGGL((flash_fwd_f32<DH>), dim3((unsigned)n_qtiles * p.n_q_heads), dim3(kF32Waves * kWave), 0, s, q, k, v,
+                       pos, o, n, p.n_q_heads, p.n_kv_heads, scale, p.causal, n_qtiles, clear_words, n_clear);
     return launch_status();
 }
 
@@ -536,9 +681,11 @@ dash_status launch_flash_fwd(const dash_layer_params& p, const void* q, const vo
                              hipStream_t s) {
     if (n == 0) return DASH_OK;
     const float scale = p.softmax_scale > 0.f ? p.softmax_scale : 1.0f / sqrtf((float)p.head_dim);
-    if (p.dtype == DASH_F32)
-        return launch_simple<float>(p, (const float*)q, (const float*)k, (const float*)v, active_idx, n,
-                                    (float*)o, scale, clear_words, n_clear, s);
+    if (p.dtype == DASH_F32) {
+        const float *fq = (const float*)q, *fk = (const float*)k, *fv = (const float*)v;
+        return p.head_dim == 64 ? launch_f32<64>(p, fq, fk, fv, active_idx, n, (float*)o, scale, clear_words, n_clear, s)
+                                : launch_f32<128>(p, fq, fk, fv, active_idx, n, (float*)o, scale, clear_words, n_clear, s);
+    }
     // the MFMA kernel addresses K and V with 32-bit byte offsets
     if ((size_t)n * p.n_kv_heads * p.head_dim * 2 >= (size_t)1 << 31) return DASH_ERR_UNSUPPORTED;
     const int n_qtiles = (n + kFaBM - 1) / kFaBM;
