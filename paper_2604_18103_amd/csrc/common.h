@@ -48,6 +48,7 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // one-time set-up of the MFMA kernels (idempotent; also run by the first launch)
 dash_status init_flash_kernels();
 dash_status init_gemm_kernels();
+int compute_units();  // of the current device, asked for once; 0 if that failed
 
 // flash_fwd.hip
 // clear_words / n_clear: optional device words the launch sets to zero (its first workgroup does it), for the

@@ -7,7 +7,7 @@
 // skipped by rank and the elements of diagonal tiles are masked by comparing positions.
 //
 // Two kernels:
-//   flash_fwd_mfma<DH>  bf16, MFMA 32x32x16, fp32 softmax and accumulation (the hot kernel)
+//   flash_fwd_mfma<DH, KG> bf16, MFMA 32x32x16, fp32 softmax and accumulation (the hot kernel)
 //   flash_fwd_f32<DH> fp32, MFMA 16x16x4 fp32, keys split over the waves of a workgroup
 #include "common.h"
 #include "lds_ops.h"
@@ -230,7 +230,8 @@ __global__ __launch_bounds__(kF32Waves * kWave) void flash_fwd_f32(
 // MFMA kernel.
 //
 // Workgroup = 8 waves = 256 query rows of one head; wave w owns rows 32w..32w+31. Keys/values come in
-// tiles of 64, staged through LDS in their natural [key][dim] layout (16-byte chunks swizzled).
+// tiles of 64, staged through LDS in their natural [key][dim] layout (16-byte chunks swizzled). (KG = 2, for short
+// sequences: 128 rows; waves w and w + 4 own the same rows and take every other key tile, see the launcher.)
 //
 //   S^T = K Q^T   (A = K fragment from LDS, B = Q fragment held in registers for the whole kernel):
 //         with the 32x32 accumulator layout each lane then holds 16 scores of ONE query per 32-key
@@ -301,13 +302,14 @@ struct FaSmem {
     static constexpr int CPR = DH / 8;             // 16-byte chunks per row
     static constexpr int RP = 256 / (DH * 2);      // rows per 256 bytes of LDS (one pass over all banks)
     static constexpr int STAGE_ELEMS = kFaBN * DH;
-    static constexpr size_t BYTES = 5 * STAGE_ELEMS * sizeof(__bf16);  // two stages of K, three of V
+    // one key group: two stages of K, three of V; two key groups: two of each for either group
+    static constexpr size_t bytes(int KG) { return (KG == 1 ? 5 : 8) * STAGE_ELEMS * sizeof(__bf16); }
     __device__ static constexpr int k_swz(int row) { return fa_k_swz(row, DH); }
     __device__ static constexpr int v_swz(int row) { return fa_v_swz(row, DH); }
 };
 
 
-template <int DH>
+template <int DH, int KG>
 __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __restrict__ q,
                                                                 const __bf16* __restrict__ k,
                                                                 const __bf16* __restrict__ v,
@@ -319,10 +321,10 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
     using SM = FaSmem<DH>;
     constexpr int KC = DH / 16;  // contraction chunks of Q K^T
     constexpr int DB = DH / 32;  // 32-wide output blocks of O^T
+    constexpr int BM = kFaBM / KG;            // query rows of the workgroup
+    constexpr int V_STAGES = KG == 1 ? 3 : 2;
     extern __shared__ __attribute__((aligned(16))) unsigned char fa_smem_raw[];
-    __bf16* Kst = reinterpret_cast<__bf16*>(fa_smem_raw);  // two K stages, then three V stages
-    __bf16* Vst = Kst + 2 * SM::STAGE_ELEMS;
-    __shared__ __attribute__((aligned(16))) int pos_blk[kFaBM];  // original positions of this workgroup's rows
+    __shared__ __attribute__((aligned(16))) int pos_blk[BM];  // original positions of this workgroup's rows
 
     if (blockIdx.x == 0)  // scratch of the kernels that follow in the layer call: cleared here, no launch of its own
         for (int c = threadIdx.x; c < n_clear; c += kFaThreads) clear_words[c] = 0u;
@@ -334,9 +336,12 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
     // exec-masked regions (MFMA ignores the exec mask)
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int grp = wave >> 2;
+    // two K stages, then the V stages; with two key groups either group has its own
+    __bf16* Kst = reinterpret_cast<__bf16*>(fa_smem_raw) + (KG == 1 ? 0 : grp * 4 * SM::STAGE_ELEMS);
+    __bf16* Vst = Kst + 2 * SM::STAGE_ELEMS;
     const int j = lane % 32, h = lane / 32;
     const int tg = lane / 16, ti = lane % 16;
-    const int q0 = qt * kFaBM + wave * 32;
+    const int q0 = qt * BM + (KG == 1 ? wave : wave & 3) * 32;
     const int qrow = q0 + j;
     const int qrow_c = min(qrow, n - 1);
     const int pos_q = pos[qrow_c];
@@ -388,9 +393,14 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
     for (int r = 0; r < 16; ++r) Cneg[r] = 0.f;
     asm volatile("" : "+v"(Cneg));
 
-    const int kv_end = causal ? min(n, qt * kFaBM + kFaBM) : n;
-    const int n_tiles = (kv_end + kFaBN - 1) / kFaBN;
-    const int wave_kend = causal ? min(n, q0 + 32) : n;  // keys at or beyond this rank are masked for the whole wave
+    const int kv_end = causal ? min(n, qt * BM + BM) : n;
+    const int all_tiles = (kv_end + kFaBN - 1) / kFaBN;
+    // tile t of this wave is key tile t, or, with two key groups, key tile 2 t + grp
+    const int n_tiles = KG == 1 ? all_tiles : (all_tiles - grp + 1) / 2;
+    const int n_rounds = KG == 1 ? all_tiles : (all_tiles + 1) / 2;
+    auto first_key = [&](int t) { return (KG == 1 ? t : 2 * t + grp) * kFaBN; };
+    // keys at or beyond this rank are masked for the whole wave; a wave whose rows all lie beyond the end does nothing
+    const int wave_kend = q0 >= n ? 0 : (causal ? min(n, q0 + 32) : n);
 
     // Staging by direct global->LDS loads, no registers in between: the four waves of group 0 fetch the K
     // tiles, those of group 1 the V tiles. One wave instruction moves 1 KB = ROWS_PER_DMA rows; lane l
@@ -401,26 +411,42 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
     constexpr int DMAS = fa_dmas(DH);                           // loads per wave and tile: 4 (DH 128) or 2 (DH 64)
     const int gw = wave & 3;                                    // wave inside its group
     const uint32_t tile_bytes = (uint32_t)fa_tile_bytes(Hkv, DH);
-    uint32_t dma_voff[DMAS];   // byte offset of this lane's 16 bytes from the start of a whole tile
+    // byte offset of this lane's 16 bytes from the start of a whole tile: this group's operand (one key group), or K and
+    // V (two key groups, either of which fetches its own tiles)
+    uint32_t dma_voff[KG][DMAS];
 #pragma unroll
-    for (int i = 0; i < DMAS; ++i) dma_voff[i] = fa_dma_voff(fa_dma_row(gw, i, lane, DH), lane, g, Hkv, DH, grp == 0);
-    const char* dma_base = reinterpret_cast<const char*>(grp == 0 ? k : v);
-    const uint32_t lds_stage0 = lds_addr(grp == 0 ? Kst : Vst) + (uint32_t)(gw * DMAS * 1024);
-    int dma_tile = 0;  // tiles are fetched strictly in order: 0, 1, 2, ...
-    auto dma_next_tile = [&](int stage) {
-        const char* tile_base = dma_base + (size_t)dma_tile * tile_bytes;
-        const int rows_left = n - dma_tile * kFaBN;  // >= 1: only tiles that hold a row are fetched
-        ++dma_tile;
+    for (int i = 0; i < DMAS; ++i) {
+        dma_voff[0][i] = fa_dma_voff(fa_dma_row(gw, i, lane, DH), lane, g, Hkv, DH, KG == 2 || grp == 0);
+        if (KG == 2) dma_voff[KG - 1][i] = fa_dma_voff(fa_dma_row(gw, i, lane, DH), lane, g, Hkv, DH, false);
+    }
+    auto fetch_tile = [&](const char* base, const uint32_t* voff, uint32_t lds, int key0) {
+        const char* tile_base = base + (size_t)(key0 / kFaBN) * tile_bytes;
+        const int rows_left = n - key0;  // >= 1: only tiles that hold a row are fetched
         if (rows_left >= kFaBN) {
 #pragma unroll
-            for (int i = 0; i < DMAS; ++i)
-                dma_load16(tile_base, dma_voff[i], lds_stage0 + (uint32_t)(stage * SM::STAGE_ELEMS * 2 + i * 1024));
+            for (int i = 0; i < DMAS; ++i) dma_load16(tile_base, voff[i], lds + (uint32_t)(i * 1024));
         } else {
 #pragma unroll
             for (int i = 0; i < DMAS; ++i)
-                dma_load16(tile_base, fa_dma_voff_tail(dma_voff[i], fa_dma_row(gw, i, lane, DH), rows_left, Hkv, DH),
-                           lds_stage0 + (uint32_t)(stage * SM::STAGE_ELEMS * 2 + i * 1024));
+                dma_load16(tile_base, fa_dma_voff_tail(voff[i], fa_dma_row(gw, i, lane, DH), rows_left, Hkv, DH),
+                           lds + (uint32_t)(i * 1024));
         }
+    };
+    // one key group: tiles of this group's operand are fetched strictly in order: 0, 1, 2, ...
+    const char* dma_base = reinterpret_cast<const char*>(grp == 0 ? k : v);
+    const uint32_t lds_stage0 = lds_addr(KG == 2 || grp == 0 ? Kst : Vst) + (uint32_t)(gw * DMAS * 1024);
+    int dma_tile = 0;
+    auto dma_next_tile = [&](int stage) {
+        fetch_tile(dma_base, dma_voff[0], lds_stage0 + (uint32_t)(stage * SM::STAGE_ELEMS * 2), dma_tile++ * kFaBN);
+    };
+    // two key groups: K or V of this group's tile t
+    auto fetch_k = [&](int t) {
+        fetch_tile(reinterpret_cast<const char*>(k), dma_voff[0], lds_stage0 + (uint32_t)((t & 1) * SM::STAGE_ELEMS * 2),
+                   first_key(t));
+    };
+    auto fetch_v = [&](int t) {
+        fetch_tile(reinterpret_cast<const char*>(v), dma_voff[KG - 1],
+                   lds_stage0 + (uint32_t)((2 + (t & 1)) * SM::STAGE_ELEMS * 2), first_key(t));
     };
 
     // A fragment of O^T += V^T P^T: V^T block (32 dims of block db) x (16 keys of chunk c) by transpose reads
@@ -437,13 +463,13 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
     // matrix-core phase, so that phase starts with MFMAs instead of an exposed LDS round trip.
     bf16x8 Vpre[DB];
     auto prefetch_v = [&](int t) {
-        const __bf16* Vs = Vst + (t % 3) * SM::STAGE_ELEMS;
+        const __bf16* Vs = Vst + (t % V_STAGES) * SM::STAGE_ELEMS;
 #pragma unroll
         for (int db = 0; db < DB; ++db) Vpre[db] = v_frag(Vs, 0, db);
     };
     // O^T += V^T(t) P^T(t): A = V^T fragment, B = packed P
     auto pv_mfma = [&](int t) {
-        const __bf16* Vs = Vst + (t % 3) * SM::STAGE_ELEMS;
+        const __bf16* Vs = Vst + (t % V_STAGES) * SM::STAGE_ELEMS;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const u32x4 pw = {Pw[c][0], Pw[c][1], Pw[c][2], Pw[c][3]};
@@ -492,14 +518,17 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
         }
         __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
     };
-    auto tile_active = [&](int t) { return t >= 0 && t < n_tiles && t * kFaBN < wave_kend; };  // wave-uniform
+    auto tile_active = [&](int t) { return t >= 0 && t < n_tiles && first_key(t) < wave_kend; };  // wave-uniform
 
     // matrix-core phase of tile t: finish the previous tile's P V, start this tile's scores
     auto mfma_phase = [&](int t) {
         // While a wave is in its matrix-core phase it gets issue priority over the wave of the other group
         // on the same SIMD: an MFMA is issued as soon as the pipe frees, VALU work fills the gaps.
         __builtin_amdgcn_s_setprio(3);
-        if (tile_active(t - 1)) pv_mfma(t - 1);
+        if (tile_active(t - 1)) {
+            if (KG == 2) prefetch_v(t - 1);
+            pv_mfma(t - 1);
+        }
         if (tile_active(t)) qk_mfma(t);
         __builtin_amdgcn_s_setprio(0);
     };
@@ -525,12 +554,12 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
     // VALU phase of tile t: softmax numerators in the log2 domain on S, leaves packed P in Pw
     auto valu_phase = [&](int t) {
         if (!tile_active(t)) return;
-        const int key0 = t * kFaBN;
+        const int key0 = first_key(t);
         // Causal masks are only ever needed on tiles that lie inside the workgroup's own row range, whose
         // original positions sit in LDS (pos_blk); masking compares positions, not ranks.
         const bool diag = causal && key0 + kFaBN - 1 > q0;  // wave-uniform
         if (diag || key0 + kFaBN > n) {
-            const int kl0 = key0 - qt * kFaBM;  // >= 0 whenever diag holds
+            const int kl0 = key0 - qt * BM;  // >= 0 whenever diag holds
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -552,7 +581,7 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
         // only if a sum is not a modest finite number (a score far above the reference), and always on
         // the first tile, the reference moves to the true running maximum, what was accumulated is
         // rescaled, and the tile's probabilities are redone.
-        prefetch_v(t);
+        if (KG == 1) prefetch_v(t);
         float psum = exp_pack(false, 0.f);
         if (t == 0 || __any(!(psum < kRowSumLimit))) {
             float c0 = fmaxf(S[0][0], S[1][0]), c1 = fmaxf(S[0][1], S[1][1]);
@@ -584,15 +613,28 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
         lsum += psum;
     };
 
-    // K(0) by group 0; V(0) and V(1) by group 1, which waits for V(0) only
-    dma_next_tile(0);
-    if (grp == 1 && n_tiles > 1) {
-        dma_next_tile(1);
-        dma_wait_keep<DMAS>();
+    if (KG == 2) {
+        // K(0) is waited for; group 1 has K(1) and V(0) in flight behind it
+        if (n_tiles > 0) fetch_k(0);
+        if (grp == 1 && n_tiles > 1) {
+            fetch_k(1);
+            fetch_v(0);
+            dma_wait_keep<2 * DMAS>();
+        } else {
+            if (grp == 1 && n_tiles > 0) fetch_v(0);
+            dma_wait();
+        }
     } else {
-        dma_wait();
+        // K(0) by group 0; V(0) and V(1) by group 1, which waits for V(0) only
+        dma_next_tile(0);
+        if (grp == 1 && n_tiles > 1) {
+            dma_next_tile(1);
+            dma_wait_keep<DMAS>();
+        } else {
+            dma_wait();
+        }
     }
-    if (tid < kFaBM) pos_blk[tid] = pos[min(qt * kFaBM + tid, n - 1)];
+    if (tid < BM) pos_blk[tid] = pos[min(qt * BM + tid, n - 1)];
     // The Q fragments have to be in registers before the loop: if their loads were still in flight at
     // loop entry, the first MFMAs of every tile would also wait for the staging loads (issued later,
     // returned in order). An empty asm that "uses" them pins the wait here.
@@ -619,27 +661,93 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
     //   requested by group 1 at the start of round r (V(0) and V(1) before the loop) and complete before barrier r;
     //   V(r) is read in round r (first fragments, group 0's softmax) and in round r+1 (P V of tile r, group 1's first
     //   fragments): three stages, and V(r-2) was last read before barrier r-1.
-    for (int t = 0; t <= n_tiles; ++t) {
-        mfma_phase(t);
-        if (grp == 1) {
-            dma_wait();  // V(t+1)
-            lds_barrier();
-            if (t + 2 < n_tiles) dma_next_tile((t + 2) % 3);  // V(t+2)
+    //
+    // Two key groups (KG = 2): the same rounds, but group grp works on the key tiles 2 t + grp of the workgroup's 128 rows
+    // and fetches its own K and V. Group 0 requests K(t+1) and V(t) at the start of softmax(t) - V(t-2) was last read
+    // before barrier t-1 - and waits for them before barrier t, the first reads of both following it. Group 1 requests
+    // K(t+2) and V(t+1) after barrier t and waits for them before barrier t+1: K(t) and V(t-1) were last read before
+    // barrier t. Two stages of each do for either group.
+    if (KG == 2) {
+        for (int t = 0; t <= n_rounds; ++t) {
+            mfma_phase(t);
+            if (grp == 1) {
+                dma_wait();
+                lds_barrier();
+                if (t + 2 < n_tiles) fetch_k(t + 2);
+                if (t + 1 < n_tiles) fetch_v(t + 1);
+            } else {
+                if (t + 1 < n_tiles) fetch_k(t + 1);
+                if (t < n_tiles) fetch_v(t);
+            }
+            valu_phase(t);
+            if (grp == 0) {
+                dma_wait();
+                lds_barrier();
+            }
         }
-        // Both groups request their tile at the START OF THEIR SOFTMAX PHASE, while the other group runs MFMAs: the
-        // compute unit's one address unit takes 16 cycles per request and holds few, so a wave queues behind its
-        // group's 16 requests, and ahead of a matrix-core phase that wait leaves the matrix pipe idle (K requested
-        // before group 0's matrix-core phase, where it also met group 1's V requests: 3 % slower).
-        if (grp == 0 && t + 1 < n_tiles) dma_next_tile((t + 1) & 1);  // K(t+1)
-        valu_phase(t);
-        if (grp == 0) {
-            dma_wait();  // K(t+1)
-            lds_barrier();
+    } else {
+        for (int t = 0; t <= n_rounds; ++t) {
+            mfma_phase(t);
+            if (grp == 1) {
+                dma_wait();  // V(t+1)
+                lds_barrier();
+                if (t + 2 < n_tiles) dma_next_tile((t + 2) % 3);  // V(t+2)
+            }
+            // Both groups request their tile at the START OF THEIR SOFTMAX PHASE, while the other group runs MFMAs: the
+            // compute unit's one address unit takes 16 cycles per request and holds few, so a wave queues behind its
+            // group's 16 requests, and ahead of a matrix-core phase that wait leaves the matrix pipe idle (K requested
+            // before group 0's matrix-core phase, where it also met group 1's V requests: 3 % slower).
+            if (grp == 0 && t + 1 < n_tiles) dma_next_tile((t + 1) & 1);  // K(t+1)
+            valu_phase(t);
+            if (grp == 0) {
+                dma_wait();  // K(t+1)
+                lds_barrier();
+            }
         }
     }
 
     lsum += __shfl_xor(lsum, 32);
-    const float inv = 1.0f / lsum;
+    float inv = 1.0f / lsum;
+    if (KG == 2) {
+        // The two key groups' results for the same rows meet in LDS (all tiles are read, nothing is in flight): group 0
+        // finishes the first half of the dims, group 1 the second, either with the other's half of its sums.
+        constexpr int HB = DB / 2;
+        f32x4* xo = reinterpret_cast<f32x4*>(fa_smem_raw);                                          // [4][2][4 HB][64]
+        float2* xm = reinterpret_cast<float2*>(fa_smem_raw + 4 * 2 * 4 * HB * kWave * sizeof(f32x4));  // [4][2][32]
+        const float m_own = lsum == 0.f ? -INFINITY : m;  // no key of this group is visible to the row
+#pragma unroll
+        for (int b = 0; b < HB; ++b)
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg) {
+                f32x4 t;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) t[e] = grp == 0 ? Oacc[HB + b][4 * rg + e] : Oacc[b][4 * rg + e];
+                xo[((gw * 2 + grp) * 4 * HB + 4 * b + rg) * kWave + lane] = t;
+            }
+        if (h == 0) xm[(gw * 2 + grp) * 32 + j] = make_float2(m_own, lsum);
+        __syncthreads();
+        const float2 other = xm[(gw * 2 + 1 - grp) * 32 + j];
+        const float M = fmaxf(m_own, other.x);
+        const float a_own = __builtin_amdgcn_exp2f(m_own - M), a_oth = __builtin_amdgcn_exp2f(other.x - M);
+        inv = grp == 0 ? 1.0f / (lsum * a_own + other.y * a_oth) : 1.0f / (other.y * a_oth + lsum * a_own);
+        if (qrow < n) {
+            __bf16* op = o + ((size_t)qrow * Hq + head) * DH + grp * 32 * HB;
+#pragma unroll
+            for (int b = 0; b < HB; ++b)
+#pragma unroll
+                for (int rg = 0; rg < 4; ++rg) {
+                    const f32x4 t = xo[((gw * 2 + 1 - grp) * 4 * HB + 4 * b + rg) * kWave + lane];
+                    bf16x4 ov;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float own = grp == 0 ? Oacc[b][4 * rg + e] : Oacc[HB + b][4 * rg + e];
+                        ov[e] = (__bf16)((own * a_own + t[e] * a_oth) * inv);
+                    }
+                    *reinterpret_cast<bf16x4*>(op + 32 * b + 8 * rg + 4 * h) = ov;
+                }
+        }
+        return;
+    }
     if (qrow < n) {
         __bf16* op = o + ((size_t)qrow * Hq + head) * DH;
 #pragma unroll
@@ -665,15 +773,59 @@ static dash_status launch_f32(const dash_layer_params& p, const float* q, const 
 }
 
 // One-time launch attribute of the MFMA kernels: their dynamic LDS size.
+template <int DH, int KG>
+static hipError_t set_flash_lds_size() {
+    return hipFuncSetAttribute((const void*)flash_fwd_mfma<DH, KG>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)FaSmem<DH>::bytes(KG));
+}
+
 dash_status init_flash_kernels() {
     static const hipError_t err = [] {
-        hipError_t e = hipFuncSetAttribute((const void*)flash_fwd_mfma<64>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)FaSmem<64>::BYTES);
-        if (e != hipSuccess) return e;
-        return hipFuncSetAttribute((const void*)flash_fwd_mfma<128>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   (int)FaSmem<128>::BYTES);
+        hipError_t e = set_flash_lds_size<64, 1>();
+        if (e == hipSuccess) e = set_flash_lds_size<64, 2>();
+        if (e == hipSuccess) e = set_flash_lds_size<128, 1>();
+        if (e == hipSuccess) e = set_flash_lds_size<128, 2>();
+        return e;
     }();
     return err == hipSuccess ? DASH_OK : DASH_ERR_HIP;
+}
+
+// Two key groups (128 query rows and half of the serial key loop per workgroup) where the loop's length or the last round
+// of workgroups decides the time; one (256 rows) where the chip is full anyway, because either group of the split form
+// fetches its own K and V tiles and its rounds take 14 % longer.
+//  - causal: while the 128-row workgroups number at most two per compute unit: the long ones start first, the short ones
+//    fill up behind them. 28 heads of 128, us, one group / two: n = 177 13.6 / 11.5, 804 26.8 / 19.7, 2304 (504
+//    workgroups) 58.7 / 54.2, 2432 (532) 60.3 / 66.3; 16 heads of 64: 4096 (512) 64 / 48, 4 heads of 128: 16384 (512) 328 / 263.
+//  - otherwise all workgroups are equally long, so whole rounds are counted, a round of the split form being half as many
+//    tiles: 28 heads of 128: 1152 (252 workgroups of 128 rows) 31 / 25, 1500 (336) 41 / 56; 16 heads of 64: 4300 (272 of 256
+//    rows, 544 of 128) 137 / 122.
+static bool fa_two_key_groups(int n, int Hq, bool causal) {
+    const int cu = compute_units();
+    const int64_t one = (int64_t)((n + kFaBM - 1) / kFaBM) * Hq, two = (int64_t)((n + kFaBM / 2 - 1) / (kFaBM / 2)) * Hq;
+    if (causal) return two <= 2 * cu;
+    return 0.57 * (double)((two + cu - 1) / cu) < (double)((one + cu - 1) / cu);
+}
+
+template <int DH, int KG>
+static dash_status launch_mfma(const dash_layer_params& p, const __bf16* q, const __bf16* k, const __bf16* v,
+                               const int32_t* pos, int n, __bf16* o, float scale_log2, uint32_t* clear_words, int n_clear,
+                               hipStream_t s) {
+    const int n_qtiles = (n + kFaBM / KG - 1) / (kFaBM / KG);
+    const int Hq = p.n_q_heads, Hkv = p.n_kv_heads, group = Hq / Hkv;
+    FaMap mp{0, 1, 1, n_qtiles * group};
+    unsigned blocks = (unsigned)n_qtiles * Hq;
+    if (Hkv <= 8 && 8 % Hkv == 0) {
+        mp.xcd_mode = 1;
+        mp.xcds_per_g = 8 / Hkv;
+        blocks = 8u * (unsigned)((mp.items_per_g + mp.xcds_per_g - 1) / mp.xcds_per_g);
+    } else if (Hkv % 8 == 0) {
+        mp.xcd_mode = 1;
+        mp.g_per_xcd = Hkv / 8;
+        blocks = 8u * (unsigned)(mp.items_per_g * mp.g_per_xcd);
+    }
+    hipLaunchKernelGGL((flash_fwd_mfma<DH, KG>), dim3(blocks), dim3(kFaThreads), FaSmem<DH>::bytes(KG), s, q, k, v, pos, o, n,
+                       Hq, Hkv, scale_log2, p.causal, n_qtiles, mp, clear_words, n_clear);
+    return launch_status();
 }
 
 dash_status launch_flash_fwd(const dash_layer_params& p, const void* q, const void* k, const void* v,
@@ -688,32 +840,15 @@ dash_status launch_flash_fwd(const dash_layer_params& p, const void* q, const vo
     }
     // the MFMA kernel addresses K and V with 32-bit byte offsets
     if ((size_t)n * p.n_kv_heads * p.head_dim * 2 >= (size_t)1 << 31) return DASH_ERR_UNSUPPORTED;
-    const int n_qtiles = (n + kFaBM - 1) / kFaBM;
+    if (init_flash_kernels() != DASH_OK || compute_units() <= 0) return DASH_ERR_HIP;
     const float scale_log2 = scale * 1.4426950408889634f;
-    const int Hq = p.n_q_heads, Hkv = p.n_kv_heads, group = Hq / Hkv;
-    FaMap mp{0, 1, 1, n_qtiles * group};
-    unsigned blocks = (unsigned)n_qtiles * Hq;
-    if (Hkv <= 8 && 8 % Hkv == 0) {
-        mp.xcd_mode = 1;
-        mp.xcds_per_g = 8 / Hkv;
-        blocks = 8u * (unsigned)((mp.items_per_g + mp.xcds_per_g - 1) / mp.xcds_per_g);
-    } else if (Hkv % 8 == 0) {
-        mp.xcd_mode = 1;
-        mp.g_per_xcd = Hkv / 8;
-        blocks = 8u * (unsigned)(mp.items_per_g * mp.g_per_xcd);
-    }
-    const dim3 grid(blocks);
-    if (init_flash_kernels() != DASH_OK) return DASH_ERR_HIP;
-    if (p.head_dim == 64) {
-        hipLaunchKernelGGL((flash_fwd_mfma<64>), grid, dim3(kFaThreads), FaSmem<64>::BYTES, s, (const __bf16*)q,
-                           (const __bf16*)k, (const __bf16*)v, active_idx, (__bf16*)o, n, Hq, Hkv, scale_log2,
-                           p.causal, n_qtiles, mp, clear_words, n_clear);
-    } else {
-        hipLaunchKernelGGL((flash_fwd_mfma<128>), grid, dim3(kFaThreads), FaSmem<128>::BYTES, s, (const __bf16*)q,
-                           (const __bf16*)k, (const __bf16*)v, active_idx, (__bf16*)o, n, Hq, Hkv, scale_log2,
-                           p.causal, n_qtiles, mp, clear_words, n_clear);
-    }
-    return launch_status();
+    const __bf16 *bq = (const __bf16*)q, *bk = (const __bf16*)k, *bv = (const __bf16*)v;
+    const bool split = fa_two_key_groups(n, p.n_q_heads, p.causal != 0);
+    if (p.head_dim == 64)
+        return split ? launch_mfma<64, 2>(p, bq, bk, bv, active_idx, n, (__bf16*)o, scale_log2, clear_words, n_clear, s)
+                     : launch_mfma<64, 1>(p, bq, bk, bv, active_idx, n, (__bf16*)o, scale_log2, clear_words, n_clear, s);
+    return split ? launch_mfma<128, 2>(p, bq, bk, bv, active_idx, n, (__bf16*)o, scale_log2, clear_words, n_clear, s)
+                 : launch_mfma<128, 1>(p, bq, bk, bv, active_idx, n, (__bf16*)o, scale_log2, clear_words, n_clear, s);
 }
 
 }  // namespace dash

@@ -671,7 +671,7 @@ int norm_partials_per_row(int d, int dtype) {
 }
 
 // Number of compute units of the current device (queried once; the library serves one GPU).
-static int compute_units() {
+int compute_units() {
     static const int n = [] {
         int dev = 0, cu = 0;
         if (hipGetDevice(&dev) != hipSuccess) return 0;

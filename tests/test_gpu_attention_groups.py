@@ -1,0 +1,45 @@
+"""The bf16 attention kernel's two forms (one key group per workgroup, two for short sequences) at the edges of their
+tiles, against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import reference as ref
+from paper_2604_18103_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(n, hq, hkv, dh, causal, seed, rows=None):
+    rng = np.random.default_rng(seed)
+    q, k, v = (torch.from_numpy(rng.standard_normal((n, h, dh)).astype(np.float32)).bfloat16() for h in (hq, hkv, hkv))
+    # keys in either group's tiles that lift the softmax reference late in the sequence
+    for row, f in ((70, 3.0), (130, 6.0), (n - 1, 5.0)):
+        if row < n:
+            k[row] *= f
+    pos = np.sort(rng.permutation(2 * n + 1)[:n]).astype(np.int32)
+    p = B.make_params(hq * dh, hq, hkv, dh, causal=causal)
+    o = torch.empty((n, hq * dh), dtype=torch.bfloat16, device="cuda")
+    B.dash_flash_fwd(p, q.cuda(), k.cuda(), v.cuda(), torch.from_numpy(pos).cuda(), n, o)
+    want = ref.attention_rows(*(t.float().numpy() for t in (q, k, v)), pos, rows=rows, causal=causal)
+    got = o.float().cpu().numpy()
+    got = got if rows is None else got[rows]
+    # Q, P and O are rounded to bf16 (2^-9 each). The scores reach about 6 * 4.5 * log2(e) = 40 in the log2 domain, where
+    # the rounding of Q (2^-9 per element, random over the head's 64 or 128 dims) moves a score by up to about 0.05.
+    err = np.abs(got - want).max(axis=1) / np.abs(want).max(axis=1)
+    assert np.isfinite(got).all() and err.max() <= 6e-2 and err.mean() <= 1e-2, (n, dh, causal, err.max(), err.mean())
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 96, 127, 128, 129, 192, 193, 257, 320])
+def test_two_key_groups_at_tile_edges(n, dh):
+    """128-row workgroups; group 1 has no tile up to 64 keys, one tile less than group 0 at odd tile counts."""
+    for causal in (True, False):
+        _run(n, 4, 2, dh, causal, seed=n + dh)
+
+
+@pytest.mark.parametrize("n,hq,hkv,dh,causal", [(4097, 16, 4, 64, True), (2433, 28, 4, 128, True), (1409, 28, 4, 128, False)])
+def test_one_key_group_with_a_nearly_empty_last_tile(n, hq, hkv, dh, causal):
+    """Lengths just past the split form's range whose last 256-row tile holds 1, 129 and 129 rows: waves beyond the end
+    do nothing."""
+    _run(n, hq, hkv, dh, causal, seed=n, rows=np.array([0, 1, 31, 32, 255, 256, n // 2, n - 130, n - 2, n - 1]))
