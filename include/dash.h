@@ -154,9 +154,10 @@ dash_status dash_flash_fwd(const dash_layer_params *params, const void *q, const
  * delta^2 and x^2 taken from the fp32 accumulators: norm_partials [P, n, 2] fp32 (P-major) with
  * P = dash_norm_partials_per_row(params). delta_dbg NULL or fp32 [n,d].
  * workspace: optional device scratch (NULL or 16-byte aligned). With few active rows the product has few
- * output tiles; given scratch it is then cut along the contraction into parts that run side by side and
- * are summed in a fixed order (as many parts as the scratch holds fp32 [n,d] sums; dash_workspace_bytes
- * reserves enough for dash_attn_layer). Results do not depend on other calls, only on n and the scratch size. */
+ * output tiles; given scratch it then runs on smaller tiles (8 ceil(d/64) n bytes for their row norms) or is cut along
+ * the contraction into parts that run side by side and are summed in a fixed order (as many parts as the scratch
+ * holds fp32 [n,d] sums); dash_workspace_bytes reserves enough for dash_attn_layer. Not with delta_dbg. Results do
+ * not depend on other calls, only on n and the scratch size. */
 dash_status dash_wo_residual_rownorm(const dash_layer_params *params, const void *o, const void *w_o,
                                      const void *x, int32_t n, void *x_next, float *norm_partials,
                                      float *delta_dbg, void *workspace, size_t workspace_bytes,

@@ -53,7 +53,7 @@ Workspace carve(const dash_layer_params& p, int64_t n) {
     w.published_off = off;  // words of the fused score + decision + compaction kernel
     off = align_up(off + published_bytes((int)n), 256);
     w.split_off = off;
-    w.split_bytes = wo_splitk_bytes(p, (int)n);  // split-K sums of the projection when few rows are active
+    w.split_bytes = wo_splitk_bytes(p, (int)n);  // split-K sums or fine row norms of the projection
     off += w.split_bytes;
     w.total = off;
     return w;
@@ -242,7 +242,7 @@ dash_status dash_wo_residual_rownorm(const dash_layer_params* p, const void* o, 
         return DASH_ERR_INVALID_ARG;
     // the scratch is optional here: without it the product is never split along K
     return launch_wo_residual_rownorm(*p, o, w_o, x, n, x_next, norm_partials, delta_dbg, workspace,
-                                      workspace ? workspace_bytes : 0, (hipStream_t)hip_stream);
+                                      workspace ? workspace_bytes : 0, nullptr, (hipStream_t)hip_stream);
 }
 
 dash_status dash_score_decide(const dash_layer_params* p, const float* norm_partials, int32_t n,
@@ -257,8 +257,8 @@ dash_status dash_score_decide(const dash_layer_params* p, const float* norm_part
     const size_t need = decide_workspace_bytes() + (size_t)((n + kChunkRows - 1) / kChunkRows) * 4;
     if (p->rule == DASH_RULE_TOPK && (!workspace || workspace_bytes < need || !aligned16(workspace)))
         return DASH_ERR_WORKSPACE;
-    return launch_score_decide(*p, norm_partials, norm_partials_per_row(p->d, p->dtype), n, scores,
-                               halt_mask, chunk_keep_counts, workspace, (hipStream_t)hip_stream);
+    return launch_score_decide(*p, NormSums{norm_partials, norm_partials_per_row(p->d, p->dtype), 1}, n, scores, halt_mask,
+                               chunk_keep_counts, workspace, (hipStream_t)hip_stream);
 }
 
 dash_status dash_decide_topk(const dash_layer_params* p, const float* scores, int32_t n, int32_t keep_low,
@@ -474,16 +474,16 @@ dash_status dash_attn_layer(const dash_layer_params* p, const void* x, const voi
     st = launch_flash_fwd(*p, q, k, v, active_idx, n, o, published, n_clear, s);
     if (st != DASH_OK) return st;
     if (profile) DASH_HIP_CHECK(hipEventRecord(profile->ev[1], s));
-    st = launch_wo_residual_rownorm(*p, o, w_o, x, n, x_next, partials, delta_dbg, ws + w.split_off, w.split_bytes, s);
+    NormSums sums{};
+    st = launch_wo_residual_rownorm(*p, o, w_o, x, n, x_next, partials, delta_dbg, ws + w.split_off, w.split_bytes, &sums, s);
     if (st != DASH_OK) return st;
     if (profile) DASH_HIP_CHECK(hipEventRecord(profile->ev[2], s));
     if (one_launch) {
-        st = launch_score_decide_compact(*p, partials, norm_partials_per_row(p->d, p->dtype), n, scores, halt_mask,
+        st = launch_score_decide_compact(*p, sums, n, scores, halt_mask,
                                          published, active_idx, x_next, p->d * (int)elem_size(p->dtype), x_compact,
                                          new_active_idx, n_active_out, s);
     } else {
-        st = launch_score_decide(*p, partials, norm_partials_per_row(p->d, p->dtype), n, scores, halt_mask,
-                                 counts, decide_ws, s);
+        st = launch_score_decide(*p, sums, n, scores, halt_mask, counts, decide_ws, s);
         if (st != DASH_OK) return st;
         if (profile) DASH_HIP_CHECK(hipEventRecord(profile->ev[3], s));
         st = launch_compact(halt_mask, counts, active_idx, x_next, n, p->d * (int)elem_size(p->dtype), x_compact,

@@ -58,11 +58,18 @@ dash_status launch_flash_fwd(const dash_layer_params& p, const void* q, const vo
                              hipStream_t s);
 // wo_gemm.hip
 int norm_partials_per_row(int d, int dtype);
+// Row norms as a product left them: `cols` pairs per row, of which `fold` neighbours make up one of the pairs that callers
+// of the library see (they are added in order before anything else, so a score has the same bits either way).
+struct NormSums {
+    const float* pairs;
+    int cols, fold;
+};
 // split_ws / split_bytes: optional device scratch that lets products with few output tiles split along K
 size_t wo_splitk_bytes(const dash_layer_params& p, int n);
 dash_status launch_wo_residual_rownorm(const dash_layer_params& p, const void* o, const void* w_o,
                                        const void* x, int n, void* x_next, float* partials,
-                                       float* delta_dbg, void* split_ws, size_t split_bytes, hipStream_t s);
+                                       float* delta_dbg, void* split_ws, size_t split_bytes, NormSums* sums,
+                                       hipStream_t s);
 size_t qkv_workspace_bytes(const dash_layer_params& p, int n);
 dash_status launch_rmsnorm_qkv(const dash_layer_params& p, const void* x, const void* w_q, const void* w_k,
                                const void* w_v, int n, void* q, void* k, void* v, void* h, void* split_ws,
@@ -73,15 +80,13 @@ dash_status launch_rmsnorm_qkv_fused(const dash_layer_params& p, const void* x, 
 size_t decide_workspace_bytes();
 constexpr int kStaticTopkMaxRows = 1 << 20;  // row limit of the allocation-free TopK entry point
 dash_status topk_static_scratch_ptr(void** out);  // this device's copy of its file-scope scratch array
-dash_status launch_score_decide(const dash_layer_params& p, const float* partials, int n_partials, int n,
-                                float* scores, uint8_t* halt, int32_t* chunk_counts, void* ws,
+dash_status launch_score_decide(const dash_layer_params& p, const NormSums& sums, int n, float* scores, uint8_t* halt, int32_t* chunk_counts, void* ws,
                                 hipStream_t s);
 dash_status launch_score_rows(const float* delta, const void* x, int n, int d, int dtype, int kind,
                               float* scores, hipStream_t s);
 // compact.hip
 size_t published_bytes(int n);  // words the fused score + decision + compaction kernel publishes its chunks through
-dash_status launch_score_decide_compact(const dash_layer_params& p, const float* partials, int n_partials, int n,
-                                        float* scores, uint8_t* halt, void* published, const int32_t* active_idx,
+dash_status launch_score_decide_compact(const dash_layer_params& p, const NormSums& sums, int n, float* scores, uint8_t* halt, void* published, const int32_t* active_idx,
                                         const void* x_next, int row_bytes, void* x_compact, int32_t* new_active_idx,
                                         int32_t* n_active_out, hipStream_t s);
 dash_status launch_chunk_counts(const uint8_t* halt, int n, int32_t* chunk_counts, hipStream_t s);

@@ -121,7 +121,7 @@ __device__ __forceinline__ unsigned long long wait_published(const unsigned long
 }
 
 __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
-    const float* __restrict__ partials, int P, int n, int score_kind, int rule, float tau, int n_first, int n_last,
+    const float* __restrict__ partials, int cols, int fold, int n, int score_kind, int rule, float tau, int n_first, int n_last,
     float* __restrict__ scores, uint8_t* __restrict__ halt, unsigned long long* __restrict__ published,
     const int32_t* __restrict__ active_idx, const uint4* __restrict__ x_next, int row_vecs, int vecs_per_split,
     uint4* __restrict__ x_compact, int32_t* __restrict__ new_idx, int32_t* __restrict__ n_out) {
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
     unsigned long long mask;
     if (blockIdx.y == 0) {
         // publisher: scores, flags, the chunk's kept mask
-        const float2 t = row_sums_256(partials, P, n, chunk * kChunkRows, red);
+        const float2 t = row_sums_256(partials, cols, fold, n, chunk * kChunkRows, red);
         bool keep = false;
         if (row < n) {  // every wave holds the sums of the chunk's rows (row = lane): every wave gets the same mask
             const float sc = score_from_sums(t, score_kind);
@@ -260,16 +260,15 @@ size_t published_bytes(int n) { return (size_t)((n + kChunkRows - 1) / kChunkRow
 
 // rules NONE and THRESHOLD: scores, decision and compaction in one launch. `published` (published_bytes(n), 8-byte
 // aligned) must have been cleared on this stream before (launch_flash_fwd does it for the layer call).
-dash_status launch_score_decide_compact(const dash_layer_params& p, const float* partials, int n_partials, int n,
-                                        float* scores, uint8_t* halt, void* published, const int32_t* active_idx,
+dash_status launch_score_decide_compact(const dash_layer_params& p, const NormSums& sums, int n, float* scores, uint8_t* halt, void* published, const int32_t* active_idx,
                                         const void* x_next, int row_bytes, void* x_compact, int32_t* new_active_idx,
                                         int32_t* n_active_out, hipStream_t s) {
     const int n_chunks = (n + kChunkRows - 1) / kChunkRows;
     const int row_vecs = row_bytes / 16;
     int splits, vecs_per_split;
     gather_splits(n_chunks, row_vecs, splits, vecs_per_split);
-    hipLaunchKernelGGL(score_decide_compact_kernel, dim3(n_chunks, splits), dim3(kCompactThreads), 0, s, partials,
-                       n_partials, n, p.score_kind, p.rule, p.tau, p.keep_first_n, p.keep_last_n, scores, halt,
+    hipLaunchKernelGGL(score_decide_compact_kernel, dim3(n_chunks, splits), dim3(kCompactThreads), 0, s, sums.pairs,
+                       sums.cols, sums.fold, n, p.score_kind, p.rule, p.tau, p.keep_first_n, p.keep_last_n, scores, halt,
                        (unsigned long long*)published, active_idx, (const uint4*)x_next, row_vecs, vecs_per_split,
                        (uint4*)x_compact, new_active_idx, n_active_out);
     return launch_status();

@@ -13,11 +13,11 @@ namespace dash {
 
 // rule NONE / THRESHOLD: score, flag and the chunk's kept count in one pass. One workgroup per 64-row chunk.
 __global__ __launch_bounds__(256) void score_threshold_kernel(
-    const float* __restrict__ partials, int P, int n, int score_kind, int rule, float tau, int n_first,
+    const float* __restrict__ partials, int cols, int fold, int n, int score_kind, int rule, float tau, int n_first,
     int n_last, float* __restrict__ scores, uint8_t* __restrict__ halt, int32_t* __restrict__ chunk_counts) {
     __shared__ float2 red[4][kChunkRows];
     const int row_base = blockIdx.x * kChunkRows;
-    const float2 t = row_sums_256(partials, P, n, row_base, red);
+    const float2 t = row_sums_256(partials, cols, fold, n, row_base, red);
     if (threadIdx.x >= kChunkRows) return;
     const int row = row_base + threadIdx.x;
     bool keep = false;
@@ -32,11 +32,11 @@ __global__ __launch_bounds__(256) void score_threshold_kernel(
     if (threadIdx.x == 0) chunk_counts[blockIdx.x] = __popcll(m);
 }
 
-__global__ __launch_bounds__(256) void score_only_kernel(const float* __restrict__ partials, int P, int n,
-                                                         int score_kind, float* __restrict__ scores) {
+__global__ __launch_bounds__(256) void score_only_kernel(const float* __restrict__ partials, int cols, int fold,
+                                                         int n, int score_kind, float* __restrict__ scores) {
     __shared__ float2 red[4][kChunkRows];
     const int row_base = blockIdx.x * kChunkRows;
-    const float2 t = row_sums_256(partials, P, n, row_base, red);
+    const float2 t = row_sums_256(partials, cols, fold, n, row_base, red);
     const int row = row_base + threadIdx.x;
     if (threadIdx.x < kChunkRows && row < n) scores[row] = score_from_sums(t, score_kind);
 }
@@ -451,13 +451,12 @@ static void launch_topk(const float* scores, int n, int n_first, int n_last, int
     }
 }
 
-dash_status launch_score_decide(const dash_layer_params& p, const float* partials, int n_partials, int n,
-                                float* scores, uint8_t* halt, int32_t* chunk_counts, void* ws,
+dash_status launch_score_decide(const dash_layer_params& p, const NormSums& sums, int n, float* scores, uint8_t* halt, int32_t* chunk_counts, void* ws,
                                 hipStream_t s) {
     if (n == 0) return DASH_OK;
     const int blocks = (n + kChunkRows - 1) / kChunkRows;
     if (p.rule != DASH_RULE_TOPK) {
-        hipLaunchKernelGGL(score_threshold_kernel, dim3(blocks), dim3(256), 0, s, partials, n_partials, n,
+        hipLaunchKernelGGL(score_threshold_kernel, dim3(blocks), dim3(256), 0, s, sums.pairs, sums.cols, sums.fold, n,
                            p.score_kind, p.rule, p.tau, p.keep_first_n, p.keep_last_n, scores, halt,
                            chunk_counts);
         return launch_status();
@@ -465,7 +464,7 @@ dash_status launch_score_decide(const dash_layer_params& p, const float* partial
     int64_t k_keep = p.k_keep;
     if (k_keep < 0) k_keep = dash_keep_count(n, p.rho, 0, 0, 0);
     if (k_keep > n) k_keep = n;
-    hipLaunchKernelGGL(score_only_kernel, dim3(blocks), dim3(256), 0, s, partials, n_partials, n,
+    hipLaunchKernelGGL(score_only_kernel, dim3(blocks), dim3(256), 0, s, sums.pairs, sums.cols, sums.fold, n,
                        p.score_kind, scores);
     launch_topk(scores, n, p.keep_first_n, p.keep_last_n, (int)k_keep, 0, halt, chunk_counts, ws, true, s);
     return launch_status();

@@ -140,6 +140,102 @@ DASH_HD int gemm_index_of(int b, int full, bool plain, int seg) {
 }
 
 // ------------------------------------------------------------------------------------------------
+// Small tiles: workgroup tile BM x BN (64 or 128 each), K step 64, 4 waves. A tile rows are 128 bytes (one load
+// instruction = 8 rows, swizzled as above), B tile rows 2 BN bytes (one instruction = 512 / BN rows). The bases and lane
+// offsets are those of the large tiles (gemm_a_base_elem, gemm_a_off, gemm_b_base_elem, gemm_b_off).
+// ------------------------------------------------------------------------------------------------
+constexpr int kSWaves = 4;
+DASH_HD constexpr int small_adma(int BM) { return BM / 8 / kSWaves; }
+DASH_HD constexpr int small_bdma(int BN) { return BN / 8 / kSWaves; }
+DASH_HD int small_a_row(int wave, int i, int lane, int BM) { return (wave * small_adma(BM) + i) * 8 + lane / 8; }
+DASH_HD int small_b_row(int wave, int i, int lane, int BN) {
+    return (wave * small_bdma(BN) + i) * (512 / BN) + lane / (BN / 8);
+}
+// 32 lanes of a transpose read touch rows r .. r + 3 and r + 8 .. r + 11, 32 bytes of each: the swizzle spreads these
+// eight pieces over the 256 bytes that the banks cover (one row of 128 columns, two rows of 64)
+DASH_HD int small_b_swz(int row, int BN) {
+    return BN == 64 ? 2 * ((row / 2) % 2) + 4 * ((row / 8) % 2) : 2 * (row % 4) + 8 * ((row / 8) % 2);
+}
+DASH_HD int small_b_lchunk(int row, int lane, int BN) { return (lane % (BN / 8)) ^ small_b_swz(row, BN); }
+// Tile of workgroup b: column tiles in order, row tiles of a column next to each other, dealt to the XCDs (b % 8) as 8
+// contiguous stretches, so that the row tiles of a weight column are read through one L2. -1: padding, no tile.
+DASH_HD int small_index_of(int b, int tiles) {
+    const int seg = (tiles + 7) / 8, idx = (b % 8) * seg + b / 8;
+    return b / 8 < seg && idx < tiles ? idx : -1;
+}
+
+// Which form a product takes: the large tiles (gemm_plan) or one of four small-tile forms, whichever is expected to be
+// faster. The expectation is a count of rounds over the compute units times the K steps times what one step was measured
+// to take, plus what a launch costs (us, 256 compute units at their usual clock under matrix work; the forms differ by
+// 10 to 300 %, so the figures only have to be roughly right):
+//   small form       KW NS  per unit  step alone, step of a full unit
+//   64 x  64          2  3     1        0.205
+//   64 x 128          2  3     1        0.31
+//  128 x 128          2  2     1        0.50
+//  128 x 128          1  2     2        0.64,  0.875 (two workgroups)
+//   large tile 1.35 (units two thirds busy or less) to 1.66 (all busy), half tile 0.65 to 0.98
+//   a second pass over K parts: 4 + 8 bytes per partial sum at 8 TB/s; several rounds of small tiles: a factor 1.3 (the L2)
+// Measured, large tiles / this choice, us, K = N = 3584: 64 rows 20.3 / 12, 177 25.9 / 15.5, 512 36.9 / 22.0, 804 42.8 / 32.6,
+// 1200 49.3 / 43.6, 2120 71.8 / 53.2, 3000 80 / 80 (large); K = N = 512: 333 rows 14.9 / 4.8, 2120 19.2 / 6.7.
+struct SmallForm {
+    int BM, BN, KW, NS, per_cu;
+    double step_us, full_us;
+};
+constexpr SmallForm kSmallForms[4] = {{64, 64, 2, 3, 1, 0.205, 0.205},
+                                      {64, 128, 2, 3, 1, 0.31, 0.31},
+                                      {128, 128, 2, 2, 1, 0.50, 0.50},
+                                      {128, 128, 1, 2, 2, 0.64, 0.875}};
+constexpr int kSmallSplitMinSteps = 6;  // K steps of a part, at least
+
+struct SmallPlan {
+    int form;                              // index into kSmallForms, -1: the large tiles
+    int mt, nt, tiles, grid;               // grid = workgroups per part, padded to a multiple of 8
+    int parts, ksteps_per_part;            // parts >= 2: fp32 sums and a second pass
+};
+inline double sa_busy(int wgs, int cu) {  // 0 up to two thirds of the units busy, 1 from all of them on
+    const double b = ((double)wgs / cu - 0.65) / 0.35;
+    return b < 0 ? 0 : (b > 1 ? 1 : b);
+}
+inline double second_pass_us(int parts, int M, int N) { return 4.0 + (double)parts * M * N * 8.0 / 8.0e6; }
+inline double large_tiles_us(const GemmPlan& g, int M, int N, int cu) {
+    if (g.parts >= 2) return g.ksteps_per_part * 1.35 + 9.0 + second_pass_us(g.parts, M, N);
+    const int rounds = (g.full + cu - 1) / cu;
+    double t = rounds * (g.ksteps * (1.35 + 0.31 * sa_busy(g.full, cu)) + 5.0);
+    if (g.rest > 0) t += g.ksteps * (0.65 + 0.33 * sa_busy(2 * g.rest, cu)) + 5.0;
+    return t;
+}
+// norms: the product returns row norms, whose fine pairs need scratch too. may_split: K parts are allowed.
+inline SmallPlan small_plan(int M, int K, int N, int cu, bool norms, bool may_split, size_t scratch_bytes, double large_us) {
+    SmallPlan best{};
+    best.form = -1;
+    if (cu <= 0) return best;
+    double best_us = 0.95 * large_us;
+    const int ksteps = K / kGK;
+    for (int f = 0; f < 4; ++f) {
+        const SmallForm& s = kSmallForms[f];
+        const int mt = (M + s.BM - 1) / s.BM, nt = (N + s.BN - 1) / s.BN;
+        const long long tiles = (long long)mt * nt;
+        if (tiles > 8LL * cu) continue;
+        const int most = f < 2 && may_split ? sa_min(cu / (int)tiles, ksteps / kSmallSplitMinSteps) : 1;
+        for (int parts = 1; parts <= sa_max(most, 1); ++parts) {
+            const int per = (ksteps + parts - 1) / parts;
+            if ((ksteps + per - 1) / per != parts) continue;  // every part has a K step, and no two plans are alike
+            const size_t need = parts > 1 ? (size_t)parts * M * N * sizeof(float) : (norms ? (size_t)((N + 63) / 64) * M * 2 * sizeof(float) : 0);
+            if (need > scratch_bytes) continue;
+            const int rounds = (int)((tiles + cu * s.per_cu - 1) / (cu * s.per_cu));
+            const double twice = tiles <= cu ? 0.0 : (tiles < 2LL * cu ? (double)(tiles - cu) / cu : 1.0);  // units with two
+            double t = rounds * per * (s.step_us + (s.full_us - s.step_us) * twice) * (rounds > 1 ? 1.3 : 1.0) + 4.0;
+            if (parts > 1) t += second_pass_us(parts, M, N);
+            if (t < best_us) {
+                best_us = t;
+                best = SmallPlan{f, mt, nt, (int)tiles, 8 * (((int)tiles + 7) / 8), parts, per};
+            }
+        }
+    }
+    return best;
+}
+
+// ------------------------------------------------------------------------------------------------
 // Attention: K/V tiles of 64 keys, rows of DH bf16, unpadded, 16-byte chunks XOR-swizzled inside a row. One
 // load instruction moves 1 KB = 64 / CPR rows; lane l lands in physical chunk l % CPR of row l / CPR. The four
 // waves of a group fetch a tile; a load's address is a uniform tile base plus a 32-bit lane offset that is the

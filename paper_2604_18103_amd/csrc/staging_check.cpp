@@ -147,6 +147,68 @@ void dash_gemm_launch_plan(int M, int K, int N, int cu, unsigned long long split
     out[5] = g.rest; out[6] = g.plain; out[7] = g.grid;
 }
 
+// Checks the small-tile product in form `form` on every shape: that the workgroups take every tile exactly once and that
+// every staging load of every K group fetches the clamped row and column its lane is meant to.
+int dash_check_small_staging(int M, int K, int N, int form, long long* n_loads) {
+    Counter c;
+    if (M <= 0 || K <= 0 || K % kGK != 0 || N <= 0 || N % 8 != 0 || form < 0 || form >= 4) return -1;
+    const SmallForm& f = kSmallForms[form];
+    const int mt = (M + f.BM - 1) / f.BM, nt = (N + f.BN - 1) / f.BN, tiles = mt * nt, grid = 8 * ((tiles + 7) / 8);
+    const uint64_t a_bytes = (uint64_t)M * K * 2, b_bytes = (uint64_t)K * N * 2;
+    std::vector<int> taken((size_t)tiles, 0);
+    for (int b = 0; b < grid; ++b) {
+        const int idx = small_index_of(b, tiles);
+        if (idx >= tiles) c.fail(1);
+        else if (idx >= 0) ++taken[(size_t)idx];
+    }
+    for (int t = 0; t < tiles; ++t)
+        if (taken[(size_t)t] != 1) c.fail(2);
+    std::vector<char> a_seen((size_t)f.BM * 8, 0), b_seen((size_t)kGK * (f.BN / 8), 0);
+    for (int tm = 0; tm < mt; ++tm)
+        for (int tn = 0; tn < nt; ++tn) {
+            if (tm != 0 && tm != mt - 1 && tn != 0 && tn != nt - 1) continue;  // the addresses are affine in the tile
+            const int m0 = tm * f.BM, n0 = tn * f.BN;
+            for (int wave = 0; wave < kSWaves; ++wave)
+                for (int lane = 0; lane < 64; ++lane) {
+                    for (int i = 0; i < small_adma(f.BM); ++i) {
+                        const int row = small_a_row(wave, i, lane, f.BM), lchunk = gemm_a_lchunk(row, lane);
+                        if (row < 0 || row >= f.BM || lchunk < 0 || lchunk >= 8) { c.fail(3); continue; }
+                        a_seen[(size_t)row * 8 + lchunk] = 1;
+                        const uint64_t off = gemm_a_off(m0, M, K, row, lchunk);
+                        for (int ks = 0; ks < K / kGK; ++ks) {
+                            const uint64_t addr = gemm_a_base_elem(m0, M, K, ks % f.KW) * 2 + (uint64_t)(ks - ks % f.KW) * gemm_a_step_bytes() + off;
+                            if (addr != ((uint64_t)sa_min(m0 + row, M - 1) * K + (uint64_t)ks * kGK + lchunk * 8) * 2) c.fail(4);
+                            if (addr + 16 > a_bytes) c.fail(5);
+                            ++c.loads;
+                        }
+                    }
+                    for (int i = 0; i < small_bdma(f.BN); ++i) {
+                        const int row = small_b_row(wave, i, lane, f.BN), lchunk = small_b_lchunk(row, lane, f.BN);
+                        if (row < 0 || row >= kGK || lchunk < 0 || lchunk >= f.BN / 8) { c.fail(6); continue; }
+                        b_seen[(size_t)row * (f.BN / 8) + lchunk] = 1;
+                        const uint64_t off = gemm_b_off(n0, N, row, lchunk);
+                        for (int ks = 0; ks < K / kGK; ++ks) {
+                            const uint64_t addr = gemm_b_base_elem(n0, N, ks % f.KW) * 2 + (uint64_t)(ks - ks % f.KW) * gemm_b_step_bytes(N) + off;
+                            if (addr != ((uint64_t)(ks * kGK + row) * N + sa_min(n0 + lchunk * 8, N - 8)) * 2) c.fail(7);
+                            if (addr + 16 > b_bytes) c.fail(8);
+                            ++c.loads;
+                        }
+                    }
+                }
+        }
+    for (char v : a_seen) if (!v) c.fail(9);
+    for (char v : b_seen) if (!v) c.fail(10);
+    if (n_loads) *n_loads = c.loads;
+    return c.status;
+}
+
+// The form a product takes: out[0..3] = form (-1: large tiles), tiles, parts, K steps per part.
+void dash_small_plan(int M, int K, int N, int cu, int norms, unsigned long long scratch, int* out) {
+    const GemmPlan g = gemm_plan(M, K, N, cu, scratch > 0, (size_t)scratch);
+    const SmallPlan p = small_plan(M, K, N, cu, norms != 0, scratch > 0, (size_t)scratch, large_tiles_us(g, M, N, cu));
+    out[0] = p.form; out[1] = p.tiles; out[2] = p.parts; out[3] = p.ksteps_per_part;
+}
+
 // Checks every K and V staging load of the attention launch over n rows (K, V: [n][Hkv][DH] bf16): for each
 // query tile of 256 rows, the tiles of 64 keys it fetches. Returns 0 when all loads are right.
 int dash_check_flash_staging(int n, int Hkv, int DH, int causal, long long* n_loads) {

@@ -513,6 +513,255 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// The same product on small tiles: BM x BN (64 or 128 each), 4 waves in 2 x 2, several workgroups per compute unit.
+// Few rows leave the 256 x 256 tiles with a handful of workgroups, which then have to be cut along K and summed in a
+// second pass: with 177 rows the fp32 sums written and read back were more bytes than the weight. Small tiles fill the
+// chip without that: 177 rows of K = N = 3584 take 15.5 us instead of 26, 333 rows of 512 4.8 instead of 15 (small_plan).
+// KW groups of 4 waves share a workgroup's tile and split its K steps (group kg: steps kg, kg + KW, ...), each with NS
+// operand stages of its own; their sums meet in the epilogue, in the order of kg. One barrier per round: a step is
+// multiplied from registers while the next one's fragments are read and the step NS ahead is requested. What bounds it: per
+// 64 x 64 step 48 KB through LDS (16 written, 32 read), 384 cycles of it, of the 500 that a step takes; more stages or K
+// groups do not shorten it.
+// Row norms (EPI_RESIDUAL_NORM) come as one pair per 64 columns, as a wave column of the large tiles sums them;
+// fold_partials_kernel adds them up to 256 columns for callers that see them.
+// ------------------------------------------------------------------------------------------------
+constexpr size_t small_smem_bytes(int BM, int BN, int KW, int NS) { return (size_t)KW * NS * (BM + BN) * kGK * sizeof(__bf16); }
+
+template <int EPI, int BM, int BN, int KW, int NS>
+__global__ __launch_bounds__(KW * kSWaves * kWave, KW == 4 ? 4 : 2) void gemm_small_kernel(const __bf16* __restrict__ A, const __bf16* __restrict__ B,
+                                                                  int M, int K, int N, const __bf16* __restrict__ x,
+                                                                  __bf16* __restrict__ out, float* __restrict__ partials,
+                                                                  float* __restrict__ split_sums, int mt, int tiles, int ksteps,
+                                                                  int ksteps_per_split, QkvOut qkv) {
+    constexpr int kThreads = KW * kSWaves * kWave;
+    constexpr int RB = BM / 32, CB = BN / 32;  // 16-row and 16-column blocks of a wave
+    constexpr int kAElems = BM * kGK, kStageElems = (BM + BN) * kGK;
+    constexpr int STR = BN + 4;
+    static_assert(small_smem_bytes(BM, BN, KW, NS) >= KW * 64 * STR * sizeof(float), "the epilogue's 64 staged rows fit");
+    extern __shared__ __attribute__((aligned(16))) unsigned char small_smem_raw[];
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int wave_all = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int kg = KW == 1 ? 0 : wave_all / kSWaves, wave = wave_all % kSWaves;  // K group, wave inside it
+    const int wm = wave / 2, wn = wave % 2;
+    __bf16* smem = reinterpret_cast<__bf16*>(small_smem_raw) + kg * NS * kStageElems;  // this group's stages
+    const int idx = small_index_of((int)blockIdx.x, tiles);
+    if (idx < 0) return;  // padding: the whole workgroup leaves
+    const int tile_m = idx % mt, tile_n = idx / mt;
+    const int m0 = tile_m * BM, n0 = tile_n * BN;
+    const int ks0 = EPI == EPI_SPLITK ? (int)blockIdx.y * ksteps_per_split : 0;
+    const int n_ksteps = EPI == EPI_SPLITK ? min(ksteps_per_split, ksteps - ks0) : ksteps;
+    const int n_rounds = (n_ksteps + KW - 1) / KW, n_mine = (n_ksteps - kg + KW - 1) / KW;  // group kg: steps kg, kg + KW, ...
+
+    f32x4 acc[RB][CB];
+#pragma unroll
+    for (int a = 0; a < RB; ++a)
+#pragma unroll
+        for (int b = 0; b < CB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    constexpr int ADMA = small_adma(BM), BDMA = small_bdma(BN);
+    uint32_t a_off[ADMA], b_off[BDMA];
+#pragma unroll
+    for (int i = 0; i < ADMA; ++i) {
+        const int row = small_a_row(wave, i, lane, BM);
+        a_off[i] = gemm_a_off(m0, M, K, row, gemm_a_lchunk(row, lane));
+    }
+#pragma unroll
+    for (int i = 0; i < BDMA; ++i) {
+        const int row = small_b_row(wave, i, lane, BN);
+        b_off[i] = gemm_b_off(n0, N, row, small_b_lchunk(row, lane, BN));
+    }
+    const char* a_base = reinterpret_cast<const char*>(A + gemm_a_base_elem(m0, M, K, ks0 + kg));
+    const char* b_base = reinterpret_cast<const char*>(B + gemm_b_base_elem(n0, N, ks0 + kg));
+    const size_t b_step = gemm_b_step_bytes(N);
+    const uint32_t lds_a = lds_addr(smem) + (uint32_t)(wave * ADMA * 1024);
+    const uint32_t lds_b = lds_addr(smem) + (uint32_t)(kAElems * 2 + wave * BDMA * 1024);
+    auto request = [&](int stage) {  // a group's K steps are requested strictly in order
+        const uint32_t so = (uint32_t)(stage * kStageElems * 2);
+#pragma unroll
+        for (int i = 0; i < ADMA; ++i) dma_load16(a_base, a_off[i], lds_a + so + i * 1024);
+#pragma unroll
+        for (int i = 0; i < BDMA; ++i) dma_load16(b_base, b_off[i], lds_b + so + i * 1024);
+        a_base += KW * gemm_a_step_bytes();
+        b_base += KW * b_step;
+    };
+    const int fi = lane % 16, fg = lane / 16;
+    struct Frags {  // operands of one K step
+        bf16x8 a[2][RB], b[2][CB];
+    };
+    auto read_frags = [&](int st, Frags& f) {
+        const __bf16* sa = smem + st * kStageElems;
+        const __bf16* sb = sa + kAElems;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+            for (int b = 0; b < CB; ++b) {
+                const int krow = 32 * ks + 8 * fg + fi / 4;  // and krow + 4: the same swizzle
+                const int col = wn * (BN / 2) + 16 * b + 4 * (fi % 4);
+                const int scol = ((col / 8) ^ small_b_swz(krow, BN)) * 8 + col % 8;
+                const s16x4 lo = lds_read_tr16(&sb[krow * BN + scol]);
+                const s16x4 hi = lds_read_tr16(&sb[(krow + 4) * BN + scol]);
+                f.b[ks][b] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            }
+#pragma unroll
+            for (int a = 0; a < RB; ++a) {
+                const int row = wm * (BM / 2) + 16 * a + fi;
+                f.a[ks][a] = *reinterpret_cast<const bf16x8*>(&sa[row * kGK + ((4 * ks + fg) ^ ((row / 2) % 8)) * 8]);
+            }
+        }
+    };
+    auto mfmas = [&](const Frags& f) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int a = 0; a < RB; ++a)
+#pragma unroll
+                for (int b = 0; b < CB; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[ks][a], f.b[ks][b], acc[a][b], 0, 0, 0);
+    };
+    // barrier that orders LDS traffic only: the tile requests in flight are not waited for
+    auto lds_barrier = [] {
+        asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");  // this wave's fragment reads are in registers
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    };
+    constexpr int kStepLoads = ADMA + BDMA;
+    for (int j = 0; j < min(NS, n_mine); ++j) request(j);
+    if (n_mine >= NS)
+        dma_wait_keep<(NS - 1) * kStepLoads>();  // the first step has landed
+    else
+        dma_wait();
+    lds_barrier();
+    // Round t multiplies its step from registers while the next step's fragments are read. Before barrier t this wave's
+    // part of step t + 1 has landed (the NS - 2 steps after it may be in flight) and its fragments of step t are in
+    // registers; so after it every wave's part of step t + 1 is there, and the stage of step t takes step t + NS.
+    // Every group passes the same number of barriers.
+    Frags f[2];
+    if (n_mine > 0) read_frags(0, f[0]);
+    int st = 0;  // t % NS
+    auto round = [&](int t, const Frags& cur, Frags& next) {
+        if (t + NS <= n_mine)
+            dma_wait_keep<(NS - 2) * kStepLoads>();
+        else
+            dma_wait();
+        lds_barrier();
+        if (t + NS < n_mine) request(st);
+        st = st + 1 == NS ? 0 : st + 1;
+        if (t + 1 < n_mine) read_frags(st, next);
+        if (t < n_mine) mfmas(cur);
+    };
+    for (int t = 0; t < n_rounds; t += 2) {
+        round(t, f[0], f[1]);
+        if (t + 1 < n_rounds) round(t + 1, f[1], f[0]);
+    }
+    __syncthreads();  // the operand stages are free and are reused
+
+    // Epilogue, 32 rows of either wave row at a time: the accumulators go to LDS, then a thread has 8 consecutive columns
+    // of one row (16-byte loads of x, 16-byte stores).
+    float* stage = reinterpret_cast<float*>(small_smem_raw);
+    auto sum8 = [&](const float* src, float* v) {  // eight columns, the K groups' parts in their order
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = src[e];
+#pragma unroll
+        for (int g = 1; g < KW; ++g)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] += src[g * 64 * STR + e];
+    };
+#pragma unroll
+    for (int a = 0; a < BM / 64; ++a) {
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+            for (int b = 0; b < CB; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)  // accumulator register r of a 16x16 block: row 4 g + r, column i
+                    stage[(64 * kg + 32 * wm + 16 * sb + 4 * fg + r) * STR + wn * (BN / 2) + 16 * b + fi] = acc[2 * a + sb][b][r];
+        __syncthreads();
+        if (EPI == EPI_SWIGLU) {
+            // lane group of 4 per row and 64 columns: lane c takes gate columns 8c..8c+7 and the up columns 32 + 8c..
+            constexpr int LPR = BN / 16, ROWS = kThreads / LPR;
+#pragma unroll
+            for (int p = 0; p < (64 + ROWS - 1) / ROWS; ++p) {
+                const int sr = p * ROWS + tid / LPR, l = tid % LPR;
+                if (sr >= 64) break;  // whole waves
+                const int gm = m0 + (sr / 32) * (BM / 2) + 32 * a + sr % 32;
+                const int gcol = (n0 + 64 * (l / 4)) / 2 + 8 * (l % 4);
+                float gv[8], uv[8];
+                sum8(&stage[sr * STR + 64 * (l / 4) + 8 * (l % 4)], gv);
+                sum8(&stage[sr * STR + 64 * (l / 4) + 8 * (l % 4) + 32], uv);
+                if (gm < M && gcol < N / 2) {
+                    bf16x8 ov;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) ov[e] = (__bf16)(gv[e] / (1.0f + __expf(-gv[e])) * uv[e]);
+                    *reinterpret_cast<bf16x8*>(out + (size_t)gm * (N / 2) + gcol) = ov;
+                }
+            }
+        } else {
+            constexpr int LPR = BN / 8, ROWS = kThreads / LPR;
+#pragma unroll
+            for (int p = 0; p < (64 + ROWS - 1) / ROWS; ++p) {
+                const int sr = p * ROWS + tid / LPR, l = tid % LPR;
+                if (sr >= 64) break;  // whole waves
+                const int gm = m0 + (sr / 32) * (BM / 2) + 32 * a + sr % 32, gn = n0 + 8 * l;
+                float dv[8];
+                sum8(&stage[sr * STR + 8 * l], dv);
+                const bool ok = gm < M && gn < N;
+                if (EPI == EPI_RESIDUAL_NORM) {
+                    float sd = 0.f, sx = 0.f;
+                    if (ok) {
+                        const bf16x8 xr = *reinterpret_cast<const bf16x8*>(x + (size_t)gm * N + gn);
+                        bf16x8 ov;
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            const float xf = (float)xr[e];
+                            ov[e] = (__bf16)(xf + dv[e]);
+                            sd = fmaf(dv[e], dv[e], sd);
+                            sx = fmaf(xf, xf, sx);
+                        }
+                        *reinterpret_cast<bf16x8*>(out + (size_t)gm * N + gn) = ov;
+                    }
+                    if (partials) {
+#pragma unroll
+                        for (int off = 4; off > 0; off >>= 1) {
+                            sd += __shfl_xor(sd, off);
+                            sx += __shfl_xor(sx, off);
+                        }
+                        if (l % 8 == 0 && ok)
+                            *reinterpret_cast<float2*>(partials + ((size_t)(gn / 64) * M + gm) * 2) = make_float2(sd, sx);
+                    }
+                } else if (EPI == EPI_SPLITK) {
+                    if (ok) {
+                        float* dst = split_sums + ((size_t)blockIdx.y * M + gm) * N + gn;
+                        *reinterpret_cast<f32x4*>(dst) = f32x4{dv[0], dv[1], dv[2], dv[3]};
+                        *reinterpret_cast<f32x4*>(dst + 4) = f32x4{dv[4], dv[5], dv[6], dv[7]};
+                    }
+                } else if (ok) {
+                    bf16x8 ov;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) ov[e] = (__bf16)dv[e];
+                    __bf16* dst = EPI == EPI_QKV ? qkv_dst(out, qkv, gm, gn) : out + (size_t)gm * N + gn;
+                    *reinterpret_cast<bf16x8*>(dst) = ov;
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// Row norms of a small-tile product, `fold` neighbouring columns of pairs to one: fine[cols][M] -> partials[P][M].
+__global__ __launch_bounds__(256) void fold_partials_kernel(const float2* __restrict__ fine, int cols, int fold, int M,
+                                                            float2* __restrict__ partials) {
+    const int row = blockIdx.x * 256 + threadIdx.x, c0 = blockIdx.y * fold;
+    if (row >= M) return;
+    float2 v = fine[(size_t)c0 * M + row];
+    for (int c = c0 + 1; c < min(c0 + fold, cols); ++c) {
+        v.x += fine[(size_t)c * M + row].x;
+        v.y += fine[(size_t)c * M + row].y;
+    }
+    partials[(size_t)blockIdx.y * M + row] = v;
+}
+
 // Second pass of a split-K product: adds the S split sums of sums[S][M][N] in the order s = 0..S-1 and applies
 // the epilogue EPI (same results layout as the one-pass kernel). A wave works on one row; a lane owns 8
 // consecutive columns, so the 32 lanes of a 256-column tile hold that tile's row sums for the norm partials.
@@ -691,6 +940,21 @@ static hipError_t set_gemm_lds_size() {
                                (int)gemm_smem_bytes(2));
 }
 
+template <int EPI, int F>
+static hipError_t set_small_lds_size() {
+    constexpr SmallForm f = kSmallForms[F];
+    return hipFuncSetAttribute((const void*)gemm_small_kernel<EPI, f.BM, f.BN, f.KW, f.NS>,
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)small_smem_bytes(f.BM, f.BN, f.KW, f.NS));
+}
+template <int EPI>
+static hipError_t set_small_lds_sizes() {
+    hipError_t e = set_small_lds_size<EPI, 0>();
+    if (e == hipSuccess) e = set_small_lds_size<EPI, 1>();
+    if (e == hipSuccess) e = set_small_lds_size<EPI, 2>();
+    if (e == hipSuccess) e = set_small_lds_size<EPI, 3>();
+    return e;
+}
+
 dash_status init_gemm_kernels() {
     static const hipError_t err = [] {
         hipError_t e = set_gemm_lds_size<EPI_RESIDUAL_NORM>();
@@ -698,6 +962,12 @@ dash_status init_gemm_kernels() {
         if (e == hipSuccess) e = set_gemm_lds_size<EPI_SWIGLU>();
         if (e == hipSuccess) e = set_gemm_lds_size<EPI_SPLITK>();
         if (e == hipSuccess) e = set_gemm_lds_size<EPI_QKV>();
+        if (e == hipSuccess) e = set_small_lds_sizes<EPI_RESIDUAL_NORM>();
+        if (e == hipSuccess) e = set_small_lds_sizes<EPI_STORE>();
+        if (e == hipSuccess) e = set_small_lds_sizes<EPI_SWIGLU>();
+        if (e == hipSuccess) e = set_small_lds_sizes<EPI_QKV>();
+        if (e == hipSuccess) e = set_small_lds_size<EPI_SPLITK, 0>();
+        if (e == hipSuccess) e = set_small_lds_size<EPI_SPLITK, 1>();
         return e;
     }();
     return err == hipSuccess && compute_units() > 0 ? DASH_OK : DASH_ERR_HIP;
@@ -720,6 +990,67 @@ size_t gemm_splitk_bytes(int M_cap, int K, int N) {
     return (best + 255) / 256 * 256;
 }
 
+struct GemmArgs {
+    const __bf16 *A, *B;
+    int M, K, N;
+    const __bf16* x;
+    __bf16* out;
+    float *partials, *split_sums;
+    QkvOut qkv;
+};
+
+template <int EPI, int F>
+static void launch_small_form(const SmallPlan& g, const GemmArgs& a, hipStream_t s) {
+    constexpr SmallForm f = kSmallForms[F];
+    hipLaunchKernelGGL((gemm_small_kernel<EPI, f.BM, f.BN, f.KW, f.NS>), dim3(g.grid, g.parts), dim3(f.KW * kSWaves * kWave),
+                       small_smem_bytes(f.BM, f.BN, f.KW, f.NS), s, a.A, a.B, a.M, a.K, a.N, a.x, a.out, a.partials,
+                       a.split_sums, g.mt, g.tiles, a.K / kGK, g.ksteps_per_part, a.qkv);
+}
+
+// Adds the K parts and applies the epilogue.
+template <int EPI>
+static void launch_splitk_reduce(const float* sums, int parts, const GemmArgs& a, hipStream_t s) {
+    const int cols_per_wave = EPI == EPI_SWIGLU ? 1024 : 512;
+    const size_t waves = (size_t)a.M * ((a.N + cols_per_wave - 1) / cols_per_wave);
+    hipLaunchKernelGGL((splitk_reduce_kernel<EPI>), dim3((unsigned)((waves * kWave + 255) / 256)), dim3(256), 0, s, sums,
+                       parts, a.M, a.N, a.x, a.out, a.partials, a.qkv);
+}
+
+// A small-tile product (g.form >= 0). scratch: the K parts' sums, or the fine row norms, which `sums` then describes or,
+// without it, are folded into a.partials; a.partials = nullptr: the caller has no use for row norms.
+template <int EPI>
+static dash_status launch_small(const SmallPlan& g, GemmArgs a, void* scratch, NormSums* sums, hipStream_t s) {
+    if (g.parts >= 2) {
+        GemmArgs part = a;
+        part.split_sums = reinterpret_cast<float*>(scratch);
+        if (g.form == 0)
+            launch_small_form<EPI_SPLITK, 0>(g, part, s);
+        else
+            launch_small_form<EPI_SPLITK, 1>(g, part, s);
+        launch_splitk_reduce<EPI>(part.split_sums, g.parts, a, s);
+        return launch_status();
+    }
+    float* coarse = a.partials;
+    if (EPI == EPI_RESIDUAL_NORM && coarse) a.partials = reinterpret_cast<float*>(scratch);
+    switch (g.form) {
+        case 0: launch_small_form<EPI, 0>(g, a, s); break;
+        case 1: launch_small_form<EPI, 1>(g, a, s); break;
+        case 2: launch_small_form<EPI, 2>(g, a, s); break;
+        default: launch_small_form<EPI, 3>(g, a, s); break;
+    }
+    if (EPI == EPI_RESIDUAL_NORM && coarse) {
+        constexpr int kFold = kGN / 64;
+        const int cols = (a.N + 63) / 64;
+        if (sums)
+            *sums = NormSums{a.partials, cols, kFold};
+        else
+            hipLaunchKernelGGL(fold_partials_kernel, dim3((a.M + 255) / 256, (cols + kFold - 1) / kFold), dim3(256), 0, s,
+                               (const float2*)a.partials, cols, kFold, a.M, (float2*)coarse);
+    }
+    return launch_status();
+}
+
+// Products of few rows: the small tiles (small_plan). Otherwise
 // 256x256 tiles for every whole round over the compute units, in an order that keeps the tiles an XCD runs at one
 // time close together (GemmPlan); if the tiles left over would occupy at most half of the units, they are run as
 // 128-row half tiles by a second launch (same kernel, MB = 2). Products with few tiles are split along K when
@@ -727,11 +1058,23 @@ size_t gemm_splitk_bytes(int M_cap, int K, int N) {
 template <int EPI>
 static dash_status launch_gemm(const __bf16* A, const __bf16* B, int M, int K, int N, const __bf16* x,
                                __bf16* out, float* partials, float* delta_dbg, void* split_ws, size_t split_bytes,
-                               hipStream_t s, QkvOut qkv = QkvOut{nullptr, nullptr, 0, 0}) {
+                               hipStream_t s, QkvOut qkv = QkvOut{nullptr, nullptr, 0, 0}, bool want_norms = true,
+                               NormSums* sums_out = nullptr) {
     // the staging loads address a tile with 32-bit lane offsets: 256 rows of A, 64 rows of B
     if ((size_t)kGM * K * 2 >= ((size_t)1 << 32) || (size_t)kGK * N * 2 + 2 * kGN >= ((size_t)1 << 32)) return DASH_ERR_UNSUPPORTED;
     if (init_gemm_kernels() != DASH_OK) return DASH_ERR_HIP;
     const GemmPlan g = gemm_plan(M, K, N, compute_units(), split_ws != nullptr && !delta_dbg, split_bytes);
+    const GemmArgs args{A, B, M, K, N, x, out, partials, nullptr, qkv};
+    const bool norms = EPI == EPI_RESIDUAL_NORM && want_norms;
+    if (sums_out) *sums_out = NormSums{partials, (N + kGN - 1) / kGN, 1};
+    // the debug output keeps the product off K parts and small tiles: with and without scratch it has the same bits
+    const SmallPlan small = small_plan(M, K, N, compute_units(), norms, split_ws != nullptr, split_ws ? split_bytes : 0,
+                                       large_tiles_us(g, M, N, compute_units()));
+    if (small.form >= 0 && !delta_dbg) {
+        GemmArgs a = args;
+        if (!norms && small.parts < 2) a.partials = nullptr;
+        return launch_small<EPI>(small, a, split_ws, sums_out, s);
+    }
     GemmLaunch L{};
     L.mt = g.mt;
     L.nt = g.nt;
@@ -742,10 +1085,7 @@ static dash_status launch_gemm(const __bf16* A, const __bf16* B, int M, int K, i
         L.ksteps_per_split = g.ksteps_per_part;
         hipLaunchKernelGGL((gemm_mfma_kernel<EPI_SPLITK, 4>), dim3(g.tiles, g.parts), dim3(kGThreads), gemm_smem_bytes(4), s,
                            A, B, M, K, N, nullptr, nullptr, nullptr, sums, L, qkv);
-        const int cols_per_wave = EPI == EPI_SWIGLU ? 1024 : 512;
-        const size_t waves = (size_t)M * ((N + cols_per_wave - 1) / cols_per_wave);
-        hipLaunchKernelGGL((splitk_reduce_kernel<EPI>), dim3((unsigned)((waves * kWave + 255) / 256)), dim3(256), 0,
-                           s, sums, g.parts, M, N, x, out, partials, qkv);
+        launch_splitk_reduce<EPI>(sums, g.parts, args, s);
         return launch_status();
     }
     L.full = g.full;
@@ -761,24 +1101,30 @@ static dash_status launch_gemm(const __bf16* A, const __bf16* B, int M, int K, i
     return launch_status();
 }
 
+// Fine row norms of a small-tile projection (one pair per row and 64 columns); products of more than 1 MB of them are no
+// small ones, and one that finds less scratch takes the large tiles.
 size_t wo_splitk_bytes(const dash_layer_params& p, int n) {
     if (p.dtype != DASH_BF16) return 0;
-    return gemm_splitk_bytes(n, p.n_q_heads * p.head_dim, p.d);
+    const size_t fine = (size_t)n * ((p.d + 63) / 64) * 2 * sizeof(float);
+    return max(gemm_splitk_bytes(n, p.n_q_heads * p.head_dim, p.d), min((fine + 255) / 256 * 256, (size_t)1 << 20));
 }
 
 dash_status launch_wo_residual_rownorm(const dash_layer_params& p, const void* o, const void* w_o,
                                        const void* x, int n, void* x_next, float* partials,
-                                       float* delta_dbg, void* split_ws, size_t split_bytes, hipStream_t s) {
+                                       float* delta_dbg, void* split_ws, size_t split_bytes, NormSums* sums,
+                                       hipStream_t s) {
     if (n == 0) return DASH_OK;
     const int K = p.n_q_heads * p.head_dim, N = p.d;
     if (p.dtype == DASH_F32) {
         dim3 grid((N + kF32TileN - 1) / kF32TileN, (n + kF32TileM - 1) / kF32TileM);
         hipLaunchKernelGGL(wo_f32_kernel, grid, dim3(kF32Split * kWave), 0, s, (const float*)o, (const float*)w_o,
                            (const float*)x, n, K, N, (float*)x_next, partials, delta_dbg);
+        if (sums) *sums = NormSums{partials, norm_partials_per_row(N, p.dtype), 1};
         return launch_status();
     }
     return launch_gemm<EPI_RESIDUAL_NORM>((const __bf16*)o, (const __bf16*)w_o, n, K, N, (const __bf16*)x,
-                                          (__bf16*)x_next, partials, delta_dbg, split_ws, split_bytes, s);
+                                          (__bf16*)x_next, partials, delta_dbg, split_ws, split_bytes, s,
+                                          QkvOut{nullptr, nullptr, 0, 0}, true, sums);
 }
 
 static size_t up256(size_t v) { return (v + 255) / 256 * 256; }
@@ -806,7 +1152,8 @@ dash_status launch_ffn_swiglu(const dash_layer_params& p, const void* x, const v
                                              nullptr, split_ws, split_bytes, s);
     if (st != DASH_OK) return st;
     return launch_gemm<EPI_RESIDUAL_NORM>(act, (const __bf16*)w_down, n, m, p.d, (const __bf16*)x,
-                                          (__bf16*)x_out, partials, nullptr, split_ws, split_bytes, s);
+                                          (__bf16*)x_out, partials, nullptr, split_ws, split_bytes, s,
+                                          QkvOut{nullptr, nullptr, 0, 0}, false);
 }
 
 size_t qkv_workspace_bytes(const dash_layer_params& p, int n) {

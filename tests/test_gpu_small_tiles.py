@@ -1,0 +1,83 @@
+"""The small-tile product in each of its forms, at the edges of the tiles and of the K groups, with every epilogue, against
+fp64 sums of the same bf16 operands."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2604_18103_amd import binding as B
+from test_small_tile_plan import _lib
+
+pytestmark = pytest.mark.gpu
+
+# (rows, query heads of 64, width, the form (64x64, 64x128, 128x128 with one and with two workgroups per unit), K parts)
+PROJECTIONS = [(1, 1, 64, 0, 1), (65, 3, 200, 0, 1), (129, 8, 512, 0, 1), (70, 56, 3584, 1, 4), (333, 56, 3584, 1, 1),
+               (1300, 16, 1000, 1, 1), (16, 300, 520, 1, 50), (804, 56, 3584, 2, 1), (2200, 8, 1032, 2, 1),
+               (1601, 56, 3584, 3, 1), (5003, 9, 1096, 3, 1)]
+
+
+def _plan(M, K, N, norms, scratch):
+    out = (ctypes.c_int * 4)()
+    _lib().dash_small_plan(M, K, N, torch.cuda.get_device_properties(0).multi_processor_count, norms, scratch, out)
+    return tuple(out)
+
+
+def _rand(rng, shape, scale=1.0):
+    return torch.from_numpy((rng.standard_normal(shape) * scale).astype(np.float32)).bfloat16().cuda()
+
+
+@pytest.mark.parametrize("n,heads,d,form,parts", PROJECTIONS)
+def test_projection(n, heads, d, form, parts):
+    """x_next: one bf16 rounding (2^-9 of the element; the bound is 2^-8 for a sum on the other side of a tie) beside fp32
+    sums of K products (1e-5 of the largest); norms: fp32 sums of d squares, 1e-4 covers K and d terms in any order. The
+    same call without scratch takes the large tiles: the same sums but for their order."""
+    K, rng = heads * 64, np.random.default_rng(n + d)
+    a, w, x = _rand(rng, (n, K)), _rand(rng, (K, d), K ** -0.5), _rand(rng, (n, d), 3.0)
+    p = B.make_params(d, heads, 1, 64, rule=B.RULE_NONE)
+    ws = torch.empty((64 << 20,), dtype=torch.uint8, device="cuda")
+    got_plan = _plan(n, K, d, 1, ws.numel())
+    assert (got_plan[0], got_plan[2]) == (form, parts)
+    P = B.norm_partials_per_row(p)
+    xn, xl, part, part_l = torch.zeros_like(x), torch.zeros_like(x), *(torch.zeros((P, n, 2), device="cuda") for _ in range(2))
+    B.dash_wo_residual_rownorm(p, a, w, x, n, xn, part, None, ws)
+    B.dash_wo_residual_rownorm(p, a, w, x, n, xl, part_l, None, None)
+    want = a.double() @ w.double()
+    assert float((part - part_l).abs().max()) <= 1e-5 * float(part_l.abs().max())
+    assert float((xn.double() - xl.double()).norm()) <= 1e-3 * float(xl.double().norm())
+    full = x.double() + want
+    assert bool(((xn.double() - full).abs() <= 2.0 ** -8 * full.abs() + 1e-5 * float(want.abs().max())).all())
+    for e, t in ((0, want), (1, x.double())):
+        blocks = torch.nn.functional.pad(t, (0, P * 256 - d)).reshape(n, P, 256).pow(2).sum(dim=2).t()
+        assert float((part[..., e].double() - blocks).abs().max()) <= 1e-4 * float(blocks.max())
+
+
+@pytest.mark.parametrize("n,d,hq,hkv,m", [(70, 512, 6, 2, 704), (333, 1024, 8, 4, 1408), (1205, 512, 12, 2, 1472), (2300, 512, 8, 2, 2816)])
+def test_front_end_and_feed_forward(n, d, hq, hkv, m):
+    """The q/k/v routing, plain store and gating epilogues at rows and widths that end inside tiles. h is rounded to bf16 on
+    the way as the library does it; results carry one bf16 rounding of a sum of d (or m) products."""
+    rng = np.random.default_rng(n)
+    dh = 64
+    p = B.make_params(d, hq, hkv, dh, rule=B.RULE_NONE)
+    x, w = _rand(rng, (n, d), 2.0), _rand(rng, (d, (hq + 2 * hkv) * dh), d ** -0.5)
+    ws = torch.empty((max(B.qkv_workspace_bytes(p, n), 256),), dtype=torch.uint8, device="cuda")
+    h = torch.empty_like(x)
+    new = lambda heads: torch.empty((n, heads, dh), dtype=torch.bfloat16, device="cuda")
+    q, k, v = new(hq), new(hkv), new(hkv)
+    B.dash_rmsnorm_qkv_fused(p, x, w, n, q, k, v, h, ws)
+    parts = [t.contiguous() for t in w.split([hq * dh, hkv * dh, hkv * dh], dim=1)]
+    q2, k2, v2 = new(hq), new(hkv), new(hkv)
+    B.dash_rmsnorm_qkv(p, x, *parts, n, q2, k2, v2, torch.empty_like(x), ws)
+    xd = x.double()
+    hd = (xd * torch.rsqrt(xd.pow(2).mean(dim=1, keepdim=True) + 1e-6)).bfloat16().double()
+    for got, wt in ((q, parts[0]), (k, parts[1]), (v, parts[2]), (q2, parts[0]), (k2, parts[1]), (v2, parts[2])):
+        want = hd @ wt.double()
+        # a row norm whose last fp32 bit differs may move a few of a row's h by one bf16 step: 2-norm, not elements
+        assert float((got.reshape(n, -1).double() - want).norm() / want.norm()) <= 4e-3
+    gate, up, down = _rand(rng, (d, m), d ** -0.5), _rand(rng, (d, m), d ** -0.5), _rand(rng, (m, d), m ** -0.5)
+    out = torch.empty_like(x)
+    fws = torch.empty((B.ffn_workspace_bytes(p, n, m),), dtype=torch.uint8, device="cuda")
+    B.dash_ffn_swiglu(p, x, B.interleave_gate_up(gate, up), down, n, m, out, fws)
+    act = (torch.nn.functional.silu(hd @ gate.double()) * (hd @ up.double())).bfloat16().double()
+    upd = act @ down.double()
+    assert float((out.double() - xd - upd).abs().max()) <= 2.0 ** -8 * float((xd + upd).abs().max()) + 4e-3 * float(upd.abs().max())

@@ -1,0 +1,59 @@
+"""CPU check of the small-tile product: its staging addresses and tile map, and the choice of a form."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from test_staging_addresses import _load
+
+FORMS = range(4)
+
+
+def _lib():
+    lib = _load()
+    lib.dash_check_small_staging.argtypes = [ctypes.c_int] * 4 + [ctypes.POINTER(ctypes.c_longlong)]
+    lib.dash_check_small_staging.restype = ctypes.c_int
+    lib.dash_small_plan.argtypes = [ctypes.c_int] * 5 + [ctypes.c_ulonglong, ctypes.POINTER(ctypes.c_int)]
+    lib.dash_small_plan.restype = None
+    return lib
+
+
+@pytest.mark.parametrize("form", FORMS)
+def test_staging_loads_fetch_the_clamped_rows_and_columns(form):
+    lib = _lib()
+    rng = np.random.default_rng(form)
+    shapes = [(1, 64, 8), (63, 128, 64), (64, 192, 72), (65, 64, 128), (127, 320, 136), (129, 128, 264), (177, 3584, 3584),
+              (333, 512, 512), (804, 3584, 4608), (64, 18944, 3584), (2120, 512, 1024)]
+    shapes += [(int(rng.integers(1, 900)), 64 * int(rng.integers(1, 12)), 8 * int(rng.integers(1, 90))) for _ in range(15)]
+    for M, K, N in shapes:
+        n = ctypes.c_longlong(0)
+        assert lib.dash_check_small_staging(M, K, N, form, ctypes.byref(n)) == 0, (M, K, N, form)
+        assert n.value > 0
+
+
+def test_choice_of_a_form():
+    """Large products keep the large tiles; short ones take small tiles, along K in parts only where the tiles alone leave
+    the chip idle; without scratch neither parts nor fine row norms."""
+    lib = _lib()
+
+    def plan(M, K, N, norms=1, scratch=1 << 30):
+        out = (ctypes.c_int * 4)()
+        lib.dash_small_plan(M, K, N, 256, norms, scratch, out)
+        return tuple(out)
+
+    for M, K, N in ((16384, 3584, 3584), (8192, 3584, 4608), (4097, 3584, 3584), (32768, 3584, 37888), (8192, 18944, 3584)):
+        assert plan(M, K, N)[0] == -1, (M, K, N)
+    assert plan(177, 3584, 3584)[0] >= 0 and plan(177, 3584, 3584)[2] == 1
+    assert plan(333, 512, 512)[0] >= 0 and plan(333, 512, 512)[2] == 1
+    assert plan(64, 18944, 3584)[2] > 1                       # a long contraction of few tiles: parts
+    assert plan(177, 3584, 3584, scratch=0)[0] == -1          # row norms need scratch
+    assert plan(177, 3584, 4608, norms=0, scratch=0)[0] >= 0  # a plain product does not
+    assert plan(64, 18944, 3584, norms=0, scratch=0)[2] == 1
+    rng = np.random.default_rng(7)
+    for _ in range(300):
+        M, K, N = int(rng.integers(1, 6000)), 64 * int(rng.integers(1, 300)), 8 * int(rng.integers(1, 5000))
+        scratch = int(rng.integers(0, 3)) * (8 << 20)
+        form, tiles, parts, per = plan(M, K, N, int(rng.integers(0, 2)), scratch)
+        if form >= 0:
+            assert parts >= 1 and (parts - 1) * per < K // 64 <= parts * per
+            assert parts == 1 or parts * M * N * 4 <= scratch
