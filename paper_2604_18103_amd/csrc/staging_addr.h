@@ -204,11 +204,12 @@ inline double large_tiles_us(const GemmPlan& g, int M, int N, int cu) {
     if (g.rest > 0) t += g.ksteps * (0.65 + 0.33 * sa_busy(2 * g.rest, cu)) + 5.0;
     return t;
 }
-// norms: the product returns row norms, whose fine pairs need scratch too. may_split: K parts are allowed.
-inline SmallPlan small_plan(int M, int K, int N, int cu, bool norms, bool may_split, size_t scratch_bytes, double large_us) {
+// norms: the product returns row norms, whose fine pairs need scratch too. Without scratch a product adds its K steps in
+// one order, whatever its width: large tiles.
+inline SmallPlan small_plan(int M, int K, int N, int cu, bool norms, bool scratch, size_t scratch_bytes, double large_us) {
     SmallPlan best{};
     best.form = -1;
-    if (cu <= 0) return best;
+    if (cu <= 0 || !scratch) return best;
     double best_us = 0.95 * large_us;
     const int ksteps = K / kGK;
     for (int f = 0; f < 4; ++f) {
@@ -216,7 +217,7 @@ inline SmallPlan small_plan(int M, int K, int N, int cu, bool norms, bool may_sp
         const int mt = (M + s.BM - 1) / s.BM, nt = (N + s.BN - 1) / s.BN;
         const long long tiles = (long long)mt * nt;
         if (tiles > 8LL * cu) continue;
-        const int most = f < 2 && may_split ? sa_min(cu / (int)tiles, ksteps / kSmallSplitMinSteps) : 1;
+        const int most = f < 2 ? sa_min(cu / (int)tiles, ksteps / kSmallSplitMinSteps) : 1;
         for (int parts = 1; parts <= sa_max(most, 1); ++parts) {
             const int per = (ksteps + parts - 1) / parts;
             if ((ksteps + per - 1) / per != parts) continue;  // every part has a K step, and no two plans are alike

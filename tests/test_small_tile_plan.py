@@ -33,7 +33,7 @@ def test_staging_loads_fetch_the_clamped_rows_and_columns(form):
 
 def test_choice_of_a_form():
     """Large products keep the large tiles; short ones take small tiles, along K in parts only where the tiles alone leave
-    the chip idle; without scratch neither parts nor fine row norms."""
+    the chip idle; without scratch none."""
     lib = _lib()
 
     def plan(M, K, N, norms=1, scratch=1 << 30):
@@ -47,8 +47,9 @@ def test_choice_of_a_form():
     assert plan(333, 512, 512)[0] >= 0 and plan(333, 512, 512)[2] == 1
     assert plan(64, 18944, 3584)[2] > 1                       # a long contraction of few tiles: parts
     assert plan(177, 3584, 3584, scratch=0)[0] == -1          # row norms need scratch
-    assert plan(177, 3584, 4608, norms=0, scratch=0)[0] >= 0  # a plain product does not
-    assert plan(64, 18944, 3584, norms=0, scratch=0)[2] == 1
+    assert plan(177, 3584, 4608, norms=0, scratch=0)[0] == -1  # one order of the K steps
+    assert plan(177, 3584, 4608, norms=0, scratch=1)[2] == 1   # room for nothing: no parts
+    assert plan(177, 3584, 3584, norms=1, scratch=1)[0] == -1  # nor for row norms
     rng = np.random.default_rng(7)
     for _ in range(300):
         M, K, N = int(rng.integers(1, 6000)), 64 * int(rng.integers(1, 300)), 8 * int(rng.integers(1, 5000))
