@@ -51,7 +51,7 @@ Workspace carve(const dash_layer_params& p, int64_t n) {
     w.decide_off = off;
     off = align_up(off + decide_workspace_bytes() + n_chunks * sizeof(int32_t), 256);
     w.published_off = off;  // words of the fused score + decision + compaction kernel
-    off = align_up(off + published_bytes((int)n), 256);
+    off = align_up(off + published_bytes((int)n, false) + (size_t)((n < kFusedTopkRows ? n : kFusedTopkRows) + 1) * sizeof(uint32_t), 256);
     w.split_off = off;
     w.split_bytes = wo_splitk_bytes(p, (int)n);  // split-K sums or fine row norms of the projection
     off += w.split_bytes;
@@ -465,11 +465,12 @@ dash_status dash_attn_layer(const dash_layer_params* p, const void* x, const voi
     int32_t* counts = reinterpret_cast<int32_t*>(ws + w.counts_off);
     void* decide_ws = ws + w.decide_off;
 
-    // NONE / THRESHOLD: scores, decision and compaction run as one launch whose workgroups hand each other the
-    // chunks' kept masks through words that have to start cleared: the attention kernel clears them on its way
-    const bool one_launch = p->rule != DASH_RULE_TOPK;
+    // NONE / THRESHOLD, and TOPK of few rows: scores, decision and compaction run as one launch whose workgroups hand
+    // each other keys and the chunks' kept masks through words that have to start cleared: the attention kernel clears
+    // them on its way
+    const bool topk = p->rule == DASH_RULE_TOPK, one_launch = !topk || n <= kFusedTopkRows;
     uint32_t* published = reinterpret_cast<uint32_t*>(ws + w.published_off);
-    const int n_clear = one_launch ? (int)(published_bytes(n) / sizeof(uint32_t)) : 0;
+    const int n_clear = one_launch ? (int)(published_bytes(n, topk) / sizeof(uint32_t)) : 0;
     if (profile) DASH_HIP_CHECK(hipEventRecord(profile->ev[0], s));
     st = launch_flash_fwd(*p, q, k, v, active_idx, n, o, published, n_clear, s);
     if (st != DASH_OK) return st;

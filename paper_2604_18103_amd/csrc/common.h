@@ -58,8 +58,10 @@ dash_status launch_flash_fwd(const dash_layer_params& p, const void* q, const vo
                              hipStream_t s);
 // wo_gemm.hip
 int norm_partials_per_row(int d, int dtype);
-// Row norms as a product left them: `cols` pairs per row, of which `fold` neighbours make up one of the pairs that callers
-// of the library see (they are added in order before anything else, so a score has the same bits either way).
+// Row norms as a product left them: `cols` pairs per row, of which `fold` (1 or kNormFold) neighbours make up one of the
+// pairs that callers of the library see (they are added in order before anything else, so a score has the same bits
+// either way).
+constexpr int kNormFold = 4;
 struct NormSums {
     const float* pairs;
     int cols, fold;
@@ -78,6 +80,7 @@ dash_status launch_rmsnorm_qkv_fused(const dash_layer_params& p, const void* x, 
                                      void* k, void* v, void* h, void* split_ws, size_t split_bytes, hipStream_t s);
 // score_decide.hip
 size_t decide_workspace_bytes();
+int topk_keep(const dash_layer_params& p, int n);  // rows TopK keeps of n
 constexpr int kStaticTopkMaxRows = 1 << 20;  // row limit of the allocation-free TopK entry point
 dash_status topk_static_scratch_ptr(void** out);  // this device's copy of its file-scope scratch array
 dash_status launch_score_decide(const dash_layer_params& p, const NormSums& sums, int n, float* scores, uint8_t* halt, int32_t* chunk_counts, void* ws,
@@ -85,7 +88,11 @@ dash_status launch_score_decide(const dash_layer_params& p, const NormSums& sums
 dash_status launch_score_rows(const float* delta, const void* x, int n, int d, int dtype, int kind,
                               float* scores, hipStream_t s);
 // compact.hip
-size_t published_bytes(int n);  // words the fused score + decision + compaction kernel publishes its chunks through
+// TOPK in one launch with score and compaction up to this many rows. Layer call in a graph, one launch / score, selection
+// and compaction one after the other, us: 64 rows of 28 x 128 heads 29.1 / 34.4, 512 51.3 / 54.9, 1500 93.5 / 94.6, 2120
+// 120.4 / 119.5; of 4 x 128 heads: 64 20.4 / 26.1, 1500 45.1 / 47.2, 2120 56.7 / 56.4.
+constexpr int kFusedTopkRows = 1536;
+size_t published_bytes(int n, bool topk);  // words the fused score + decision + compaction kernel publishes its chunks through
 dash_status launch_score_decide_compact(const dash_layer_params& p, const NormSums& sums, int n, float* scores, uint8_t* halt, void* published, const int32_t* active_idx,
                                         const void* x_next, int row_bytes, void* x_compact, int32_t* new_active_idx,
                                         int32_t* n_active_out, hipStream_t s);

@@ -87,7 +87,8 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(
 }
 
 // ------------------------------------------------------------------------------------------------
-// Score, threshold decision and compaction in ONE launch (rules NONE and THRESHOLD of the layer call).
+// Score, decision and compaction in ONE launch (rules NONE and THRESHOLD of the layer call, TOPK up to
+// kFusedTopkRows rows).
 //
 // Grid (chunks of 64 rows, column splits), 256 threads. Workgroup (c, 0) finishes the scores of chunk c from the
 // norm partials, writes scores and halt flags and PUBLISHES the chunk's kept mask and count; every workgroup
@@ -98,6 +99,15 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(
 // of one word: no fences, no ordering between words needed):
 //   word 0 = kept mask bits 0..31 | kept count << 32 | READY      word 1 = kept mask bits 32..63 | READY
 // They must be zero when the kernel starts (the attention kernel of the same layer call clears them).
+//
+// TOPK: a publisher first shares its rows' scores as order-preserving keys (one 32-bit word per row; no key is 0, so a
+// word is its own READY flag), takes everybody's, and ranks its 64 rows by counting: row r is kept when fewer than K
+// candidates come before it (a greater key, or the same key in an earlier row - the order of the selection kernels). That
+// is n^2 comparisons spread over the publishers, n / 4 per thread, in place of a radix selection that one workgroup does
+// behind a launch of its own. Bound by latency: the norms, one exchange through the last-level cache, the count, the
+// gather. The publishers wait for one another, so they have to be resident together: they are the first
+// n / 64 <= kFusedTopkRows / 64 workgroups of the grid, a fraction of what the chip holds. (Figures: kFusedTopkRows.)
+//
 // Waiting is safe: workgroups are dispatched in the order of their linear index (x fastest), a waiter (c, y) only
 // waits for publishers (c', 0) with c' <= c, which have a smaller linear index, are therefore resident or done, and
 // never wait themselves. The wait is bounded all the same: if a word never arrives the workgroup gives up, gathers
@@ -120,9 +130,10 @@ __device__ __forceinline__ unsigned long long wait_published(const unsigned long
     return v;
 }
 
+template <bool TOPK>
 __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
-    const float* __restrict__ partials, int cols, int fold, int n, int score_kind, int rule, float tau, int n_first, int n_last,
-    float* __restrict__ scores, uint8_t* __restrict__ halt, unsigned long long* __restrict__ published,
+    const float* __restrict__ partials, int cols, int fold, int n, int score_kind, int rule, float tau, int k_keep, int n_first,
+    int n_last, float* __restrict__ scores, uint8_t* __restrict__ halt, unsigned long long* __restrict__ published,
     const int32_t* __restrict__ active_idx, const uint4* __restrict__ x_next, int row_vecs, int vecs_per_split,
     uint4* __restrict__ x_compact, int32_t* __restrict__ new_idx, int32_t* __restrict__ n_out) {
     __shared__ float2 red[4][kChunkRows];
@@ -138,7 +149,84 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
         // publisher: scores, flags, the chunk's kept mask
         const float2 t = row_sums_256(partials, cols, fold, n, chunk * kChunkRows, red);
         bool keep = false;
-        if (row < n) {  // every wave holds the sums of the chunk's rows (row = lane): every wave gets the same mask
+        if (TOPK) {
+            __shared__ __attribute__((aligned(16))) uint32_t keys[kFusedTopkRows];
+            __shared__ int before[kCompactWaves][kChunkRows];
+            const float sc = score_from_sums(t, score_kind);
+            const uint32_t mine = order_key(sc);
+            uint32_t* words = reinterpret_cast<uint32_t*>(published + 2 * gridDim.x);
+            if (wave == 0 && row < n) {
+                __hip_atomic_store(words + row, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                scores[row] = sc;
+            }
+            const int lo = min(n_first, n), hi = max(lo, n - n_last);  // candidates are rows [lo, hi)
+            const int k_cand = max(0, min(k_keep - (n - (hi - lo)), hi - lo));
+            // everybody's keys, two per load, all of a thread's loads in flight at once; what has not arrived is asked for
+            // again together
+            constexpr int kLoads = kFusedTopkRows / 2 / kCompactThreads;
+            const int n_pairs = (n + 1) / 2;  // the last may reach one word beyond the n-th: padding, 0
+            const unsigned long long* pairs = reinterpret_cast<const unsigned long long*>(words);
+            uint2 kv[kLoads];
+            int spins = 0;
+            bool all = false;
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) kv[u] = make_uint2(0u, 0u);
+            while (!all) {
+#pragma unroll
+                for (int u = 0; u < kLoads; ++u) {
+                    const int i = u * kCompactThreads + tid;
+                    if (i < n_pairs && (kv[u].x == 0u || (kv[u].y == 0u && 2 * i + 1 < n))) {
+                        const unsigned long long w = __hip_atomic_load(pairs + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        kv[u] = make_uint2((uint32_t)w, (uint32_t)(w >> 32));
+                    }
+                }
+                all = true;
+#pragma unroll
+                for (int u = 0; u < kLoads; ++u) {
+                    const int i = u * kCompactThreads + tid;
+                    if (i < n_pairs && (kv[u].x == 0u || (kv[u].y == 0u && 2 * i + 1 < n))) all = false;
+                }
+                if (!all && ++spins > kPubSpinLimit) {
+                    bad = true;
+                    all = true;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) {
+                const int i = u * kCompactThreads + tid, r = 2 * i;
+                if (i >= (int)gridDim.x * (kChunkRows / 2)) continue;
+                uint2 c = kv[u];  // 0 comes before nothing: padding and protected rows
+                if (r < lo || r >= hi) c.x = 0u;
+                if (r + 1 < lo || r + 1 >= hi) c.y = 0u;
+                *reinterpret_cast<uint2*>(&keys[r]) = c;
+            }
+            __syncthreads();
+            int cnt_before = 0;
+            const uint32_t tie = mine - 1u;  // > tie: greater or the same
+            for (int c = wave; c < (int)gridDim.x; c += kCompactWaves) {
+                const uint4* src = reinterpret_cast<const uint4*>(keys + c * kChunkRows);
+                const uint32_t than = c < chunk ? tie : mine;
+                uint4 kv[kChunkRows / 4];
+#pragma unroll
+                for (int e = 0; e < kChunkRows / 4; ++e) kv[e] = src[e];
+#pragma unroll
+                for (int e = 0; e < kChunkRows / 4; ++e)
+                    cnt_before += (int)(kv[e].x > than) + (int)(kv[e].y > than) + (int)(kv[e].z > than) + (int)(kv[e].w > than);
+                if (c == chunk) {  // a row of the own chunk before this one counts on a tie too
+#pragma unroll
+                    for (int e = 0; e < kChunkRows / 4; ++e)
+                        cnt_before += (int)(kv[e].x == mine && 4 * e < lane) + (int)(kv[e].y == mine && 4 * e + 1 < lane) +
+                                      (int)(kv[e].z == mine && 4 * e + 2 < lane) + (int)(kv[e].w == mine && 4 * e + 3 < lane);
+                }
+            }
+            before[wave][lane] = cnt_before;
+            __syncthreads();
+            int rank = 0;
+#pragma unroll
+            for (int w = 0; w < kCompactWaves; ++w) rank += before[w][lane];
+            keep = row < n && (row_protected(row, n, n_first, n_last) || rank < k_cand);
+            if (wave == 0 && row < n) halt[row] = keep ? 0 : 1;
+        } else if (row < n) {  // every wave holds the sums of the chunk's rows (row = lane): every wave gets the same mask
             const float sc = score_from_sums(t, score_kind);
             const bool h = rule == DASH_RULE_THRESHOLD && !row_protected(row, n, n_first, n_last) && sc < tau;
             keep = !h;
@@ -156,7 +244,12 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
                                __HIP_MEMORY_SCOPE_AGENT);
         }
     } else {
-        // the chunk's mask from its publisher (every lane reads the same two words: one request per wave)
+        // the chunk's mask from its publisher (every lane reads the same two words: one request per wave; one wave asks
+        // until it is there, or the waiters' requests hold up the publishers' exchange)
+        if (TOPK) {
+            if (wave == 0) (void)wait_published(published + 2 * (gridDim.x - 1), bad);
+            __syncthreads();
+        }
         const unsigned long long w0 = wait_published(published + 2 * chunk, bad);
         const unsigned long long w1 = wait_published(published + 2 * chunk + 1, bad);
         mask = (w0 & 0xFFFFFFFFull) | ((w1 & 0xFFFFFFFFull) << 32);
@@ -256,10 +349,12 @@ dash_status launch_compact(const uint8_t* halt, const int32_t* chunk_counts, con
     return launch_status();
 }
 
-size_t published_bytes(int n) { return (size_t)((n + kChunkRows - 1) / kChunkRows) * 2 * sizeof(unsigned long long); }
+// words of the one-launch kernel: two per chunk, and for TOPK a key per row
+size_t published_bytes(int n, bool topk) {
+    return (size_t)((n + kChunkRows - 1) / kChunkRows) * 2 * sizeof(unsigned long long) + (topk ? (size_t)((n + 1) / 2) * 2 * sizeof(uint32_t) : 0);
+}
 
-// rules NONE and THRESHOLD: scores, decision and compaction in one launch. `published` (published_bytes(n), 8-byte
-// aligned) must have been cleared on this stream before (launch_flash_fwd does it for the layer call).
+// Scores, decision and compaction in one launch (TOPK: n <= kFusedTopkRows). `published` (published_bytes, 8-byte aligned) must have been cleared on this stream before (launch_flash_fwd does it for the layer call).
 dash_status launch_score_decide_compact(const dash_layer_params& p, const NormSums& sums, int n, float* scores, uint8_t* halt, void* published, const int32_t* active_idx,
                                         const void* x_next, int row_bytes, void* x_compact, int32_t* new_active_idx,
                                         int32_t* n_active_out, hipStream_t s) {
@@ -267,10 +362,12 @@ dash_status launch_score_decide_compact(const dash_layer_params& p, const NormSu
     const int row_vecs = row_bytes / 16;
     int splits, vecs_per_split;
     gather_splits(n_chunks, row_vecs, splits, vecs_per_split);
-    hipLaunchKernelGGL(score_decide_compact_kernel, dim3(n_chunks, splits), dim3(kCompactThreads), 0, s, sums.pairs,
-                       sums.cols, sums.fold, n, p.score_kind, p.rule, p.tau, p.keep_first_n, p.keep_last_n, scores, halt,
-                       (unsigned long long*)published, active_idx, (const uint4*)x_next, row_vecs, vecs_per_split,
-                       (uint4*)x_compact, new_active_idx, n_active_out);
+    const bool topk = p.rule == DASH_RULE_TOPK;
+    hipLaunchKernelGGL(topk ? score_decide_compact_kernel<true> : score_decide_compact_kernel<false>, dim3(n_chunks, splits),
+                       dim3(kCompactThreads), 0, s, sums.pairs, sums.cols, sums.fold, n, p.score_kind, p.rule, p.tau,
+                       topk ? topk_keep(p, n) : 0, p.keep_first_n, p.keep_last_n, scores, halt, (unsigned long long*)published,
+                       active_idx, (const uint4*)x_next, row_vecs, vecs_per_split, (uint4*)x_compact, new_active_idx,
+                       n_active_out);
     return launch_status();
 }
 

@@ -41,17 +41,6 @@ __global__ __launch_bounds__(256) void score_only_kernel(const float* __restrict
     if (threadIdx.x < kChunkRows && row < n) scores[row] = score_from_sums(t, score_kind);
 }
 
-// Order-preserving map from fp32 to uint32 for the total order in which TopK ranks scores:
-//   -inf < ... < -0.0 = +0.0 < ... < +inf < NaN   (every NaN, whatever its sign or payload, is one value).
-// Eq. 3 ranks real numbers; this is the reading for the other values a float can hold: a NaN score ranks highest
-// (the threshold rule keeps NaN rows as well, "score < tau" being false), the two zeros tie and are told apart
-// by row like any tie.
-__device__ __forceinline__ uint32_t order_key(float f) {
-    if (f != f) return 0xFFFFFFFFu;
-    const uint32_t b = __float_as_uint(f == 0.0f ? 0.0f : f);
-    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-}
-
 // Key under which TopK ranks a score: the order-preserving key, or its complement when the rows with the
 // LOWEST scores are to be kept (the direction control of Sec. 5.4).
 __device__ __forceinline__ uint32_t rank_key(float f, int keep_low) {
@@ -451,6 +440,12 @@ static void launch_topk(const float* scores, int n, int n_first, int n_last, int
     }
 }
 
+// Rows that TopK keeps of n: the requested count, or Eq. 3's for the ratio.
+int topk_keep(const dash_layer_params& p, int n) {
+    const int64_t k = p.k_keep < 0 ? dash_keep_count(n, p.rho, 0, 0, 0) : p.k_keep;
+    return (int)(k > n ? n : k);
+}
+
 dash_status launch_score_decide(const dash_layer_params& p, const NormSums& sums, int n, float* scores, uint8_t* halt, int32_t* chunk_counts, void* ws,
                                 hipStream_t s) {
     if (n == 0) return DASH_OK;
@@ -461,12 +456,9 @@ dash_status launch_score_decide(const dash_layer_params& p, const NormSums& sums
                            chunk_counts);
         return launch_status();
     }
-    int64_t k_keep = p.k_keep;
-    if (k_keep < 0) k_keep = dash_keep_count(n, p.rho, 0, 0, 0);
-    if (k_keep > n) k_keep = n;
     hipLaunchKernelGGL(score_only_kernel, dim3(blocks), dim3(256), 0, s, sums.pairs, sums.cols, sums.fold, n,
                        p.score_kind, scores);
-    launch_topk(scores, n, p.keep_first_n, p.keep_last_n, (int)k_keep, 0, halt, chunk_counts, ws, true, s);
+    launch_topk(scores, n, p.keep_first_n, p.keep_last_n, topk_keep(p, n), 0, halt, chunk_counts, ws, true, s);
     return launch_status();
 }
 
@@ -475,10 +467,7 @@ dash_status launch_score_decide(const dash_layer_params& p, const NormSums& sums
 dash_status launch_decide_topk(const dash_layer_params& p, const float* scores, int n, int keep_low, uint8_t* halt,
                                int32_t* chunk_counts, void* ws, bool one_launch_allowed, hipStream_t s) {
     if (n == 0) return DASH_OK;
-    int64_t k_keep = p.k_keep;
-    if (k_keep < 0) k_keep = dash_keep_count(n, p.rho, 0, 0, 0);
-    if (k_keep > n) k_keep = n;
-    launch_topk(scores, n, p.keep_first_n, p.keep_last_n, (int)k_keep, keep_low ? 1 : 0, halt, chunk_counts, ws,
+    launch_topk(scores, n, p.keep_first_n, p.keep_last_n, topk_keep(p, n), keep_low ? 1 : 0, halt, chunk_counts, ws,
                 one_launch_allowed, s);
     return launch_status();
 }

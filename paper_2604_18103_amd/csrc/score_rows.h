@@ -24,17 +24,22 @@ __device__ __forceinline__ float2 row_sums_256(const float* __restrict__ partial
                 sd += v.x;
                 sx += v.y;
             }
-        } else {  // partial p is the sum of `fold` neighbouring columns, in order
-#pragma unroll 2
-            for (int c0 = qd * fold; c0 < cols; c0 += 4 * fold) {
-                float2 v = src[(size_t)c0 * n];
-                for (int c = c0 + 1; c < min(c0 + fold, cols); ++c) {
-                    const float2 u = src[(size_t)c * n];
-                    v.x += u.x;
-                    v.y += u.y;
+        } else {  // kNormFold neighbouring columns make up a partial: added in order, all loads of a few partials in flight
+#pragma unroll 4
+            for (int c0 = qd * kNormFold; c0 < cols; c0 += 4 * kNormFold) {
+                float2 v[kNormFold];
+#pragma unroll
+                for (int c = 0; c < kNormFold; ++c) {
+                    v[c] = src[(size_t)min(c0 + c, cols - 1) * n];
+                    if (c0 + c >= cols) v[c] = make_float2(0.f, 0.f);
                 }
-                sd += v.x;
-                sx += v.y;
+#pragma unroll
+                for (int c = 1; c < kNormFold; ++c) {
+                    v[0].x += v[c].x;
+                    v[0].y += v[c].y;
+                }
+                sd += v[0].x;
+                sx += v[0].y;
             }
         }
     }
@@ -53,6 +58,17 @@ __device__ __forceinline__ float score_from_sums(float2 t, int score_kind) {
     const float nd = sqrtf(t.x);
     if (score_kind == DASH_SCORE_ABS) return nd;
     return nd / fmaxf(sqrtf(t.y), kNormEps);
+}
+
+// Order-preserving map from fp32 to uint32 for the total order in which TopK ranks scores:
+//   -inf < ... < -0.0 = +0.0 < ... < +inf < NaN   (every NaN, whatever its sign or payload, is one value).
+// Eq. 3 ranks real numbers; this is the reading for the other values a float can hold: a NaN score ranks highest
+// (the threshold rule keeps NaN rows as well, "score < tau" being false), the two zeros tie and are told apart
+// by row like any tie.
+__device__ __forceinline__ uint32_t order_key(float f) {
+    if (f != f) return 0xFFFFFFFFu;
+    const uint32_t b = __float_as_uint(f == 0.0f ? 0.0f : f);
+    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
 }  // namespace dash

@@ -749,17 +749,20 @@ __global__ __launch_bounds__(KW * kSWaves * kWave, KW == 4 ? 4 : 2) void gemm_sm
     }
 }
 
-// Row norms of a small-tile product, `fold` neighbouring columns of pairs to one: fine[cols][M] -> partials[P][M].
-__global__ __launch_bounds__(256) void fold_partials_kernel(const float2* __restrict__ fine, int cols, int fold, int M,
+// Row norms of a small-tile product, kNormFold neighbouring columns of pairs to one: fine[cols][M] -> partials[P][M].
+__global__ __launch_bounds__(256) void fold_partials_kernel(const float2* __restrict__ fine, int cols, int M,
                                                             float2* __restrict__ partials) {
-    const int row = blockIdx.x * 256 + threadIdx.x, c0 = blockIdx.y * fold;
+    const int row = blockIdx.x * 256 + threadIdx.x, c0 = blockIdx.y * kNormFold;
     if (row >= M) return;
-    float2 v = fine[(size_t)c0 * M + row];
-    for (int c = c0 + 1; c < min(c0 + fold, cols); ++c) {
-        v.x += fine[(size_t)c * M + row].x;
-        v.y += fine[(size_t)c * M + row].y;
+    float2 v[kNormFold];
+#pragma unroll
+    for (int c = 0; c < kNormFold; ++c) v[c] = c0 + c < cols ? fine[(size_t)(c0 + c) * M + row] : make_float2(0.f, 0.f);
+#pragma unroll
+    for (int c = 1; c < kNormFold; ++c) {
+        v[0].x += v[c].x;
+        v[0].y += v[c].y;
     }
-    partials[(size_t)blockIdx.y * M + row] = v;
+    partials[(size_t)blockIdx.y * M + row] = v[0];
 }
 
 // Second pass of a split-K product: adds the S split sums of sums[S][M][N] in the order s = 0..S-1 and applies
@@ -1039,13 +1042,13 @@ static dash_status launch_small(const SmallPlan& g, GemmArgs a, void* scratch, N
         default: launch_small_form<EPI, 3>(g, a, s); break;
     }
     if (EPI == EPI_RESIDUAL_NORM && coarse) {
-        constexpr int kFold = kGN / 64;
+        static_assert(kGN == 64 * kNormFold, "a fine pair covers 64 columns");
         const int cols = (a.N + 63) / 64;
         if (sums)
-            *sums = NormSums{a.partials, cols, kFold};
+            *sums = NormSums{a.partials, cols, kNormFold};
         else
-            hipLaunchKernelGGL(fold_partials_kernel, dim3((a.M + 255) / 256, (cols + kFold - 1) / kFold), dim3(256), 0, s,
-                               (const float2*)a.partials, cols, kFold, a.M, (float2*)coarse);
+            hipLaunchKernelGGL(fold_partials_kernel, dim3((a.M + 255) / 256, (cols + kNormFold - 1) / kNormFold), dim3(256), 0, s,
+                               (const float2*)a.partials, cols, a.M, (float2*)coarse);
     }
     return launch_status();
 }
