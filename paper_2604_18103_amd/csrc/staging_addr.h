@@ -201,8 +201,33 @@ inline double large_tiles_us(const GemmPlan& g, int M, int N, int cu) {
     if (g.parts >= 2) return g.ksteps_per_part * 1.35 + 9.0 + second_pass_us(g.parts, M, N);
     const int rounds = (g.full + cu - 1) / cu;
     double t = rounds * (g.ksteps * (1.35 + 0.31 * sa_busy(g.full, cu)) + 5.0);
-    if (g.rest > 0) t += g.ksteps * (0.65 + 0.33 * sa_busy(2 * g.rest, cu)) + 5.0;
+    if (g.rest > 0) t += g.ksteps * (0.65 + 0.33 * sa_busy(2 * g.rest, cu)) + 5.0;  // in one part
     return t;
+}
+// The tiles left over after the whole rounds (g.rest, run as 128-row half tiles on 2 g.rest units) cut along K as well when
+// that leaves units idle: fp32 sums [part][half tile][128][256] and a second pass over those tiles only. Returns the parts, 1
+// where the second pass costs more than it gives. Measured, whole product, one pass / cut, us: K = N = 3584 with 10
+// left-over tiles 140 / 125, 24 140 / 128, 38 143 / 137; K = 18944: 10 625 / 480, 38 644 / 534. From about 64 on (two parts) it
+// no longer pays.
+constexpr int kRestMinSteps = 4;
+DASH_HD constexpr size_t rest_sum_elems() { return (size_t)(kGM / 2) * kGN; }
+inline int rest_parts(const GemmPlan& g, int cu, size_t scratch_bytes) {
+    if (g.parts >= 2 || g.rest == 0 || cu <= 0) return 1;
+    auto launch_us = [&](int per, int parts) { return per * (0.65 + 0.33 * sa_busy(2 * g.rest * parts, cu)) + 5.0; };
+    int best = 1;
+    double best_us = 0.9 * launch_us(g.ksteps, 1);
+    const int most = sa_min(cu / (2 * g.rest), g.ksteps / kRestMinSteps);
+    for (int p = 2; p <= most; ++p) {
+        const int per = (g.ksteps + p - 1) / p;
+        const size_t need = (size_t)p * 2 * g.rest * rest_sum_elems() * sizeof(float);
+        if ((g.ksteps + per - 1) / per != p || need > scratch_bytes) continue;
+        const double t = launch_us(per, p) + 4.0 + 2.0 * (double)need / 8.0e6;
+        if (t < best_us) {
+            best_us = t;
+            best = p;
+        }
+    }
+    return best;
 }
 // norms: the product returns row norms, whose fine pairs need scratch too. Without scratch a product adds its K steps in
 // one order, whatever its width: large tiles.

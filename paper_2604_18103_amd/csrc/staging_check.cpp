@@ -128,10 +128,15 @@ int dash_check_gemm_staging(int M, int K, int N, int cu, unsigned long long spli
             if (taken[(size_t)t] != 1) c.fail(12);
         for (int x = 0; x < 8; ++x)  // no XCD has more than a stretch's worth, none is short by more than the padding
             if (per_xcd[x] > (g.full + 7) / 8 || per_xcd[x] + 8 < g.full / 8) c.fail(13);
+        const int rp = split_bytes > 0 ? rest_parts(g, cu, (size_t)split_bytes) : 1, per = (g.ksteps + rp - 1) / rp;
+        if (rp > 1 && (size_t)rp * 2 * g.rest * rest_sum_elems() * 4 > split_bytes) c.fail(14);
         for (int b = 0; b < 2 * g.rest; ++b) {  // half tiles: workgroup b handles half b % 2 of tile full + b / 2
             int tm, tn;
             gemm_tile_of(g.full + b / 2, g.mt, g.nt, plain, tm, tn);
-            check_gemm_workgroup(M, K, N, 2, tm, tn, b % 2, 0, g.ksteps, c);
+            for (int part = 0; part < rp; ++part) {
+                if (g.ksteps - part * per <= 0) c.fail(15);
+                check_gemm_workgroup(M, K, N, 2, tm, tn, b % 2, part * per, sa_min(per, g.ksteps - part * per), c);
+            }
         }
     }
     if (n_loads) *n_loads = c.loads;
@@ -200,6 +205,11 @@ int dash_check_small_staging(int M, int K, int N, int form, long long* n_loads) 
     for (char v : b_seen) if (!v) c.fail(10);
     if (n_loads) *n_loads = c.loads;
     return c.status;
+}
+
+// K parts of the left-over half tiles, 1: one pass.
+int dash_rest_parts(int M, int K, int N, int cu, unsigned long long scratch) {
+    return rest_parts(gemm_plan(M, K, N, cu, scratch > 0, (size_t)scratch), cu, (size_t)scratch);
 }
 
 // The form a product takes: out[0..3] = form (-1: large tiles), tiles, parts, K steps per part.

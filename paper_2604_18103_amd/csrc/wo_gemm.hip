@@ -191,7 +191,7 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
     // this workgroup's tile and K steps
     int tile_idx, ks0 = 0, n_ksteps = L.ksteps;
     if (EPI == EPI_SPLITK) {
-        tile_idx = (int)blockIdx.x;
+        tile_idx = MB == 2 ? L.first_tile + (int)blockIdx.x / 2 : (int)blockIdx.x;
         ks0 = (int)blockIdx.y * L.ksteps_per_split;
         n_ksteps = min(L.ksteps_per_split, L.ksteps - ks0);
     } else if (MB == 2) {
@@ -482,7 +482,10 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
                 if (e_c8 == 0) nrm[wn * BM + wm * WM + 32 * a + lr] = make_float2(sd, sx);
             } else if (EPI == EPI_SPLITK) {
                 if (ok) {
-                    float* dst = f32_out + ((size_t)blockIdx.y * M + gm) * N + gn_e;
+                    // whole products: [part][M][N]; left-over half tiles: [part][half tile][128][256]
+                    float* dst = MB == 2 ? f32_out + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * rest_sum_elems() +
+                                               (size_t)(gm - m0) * kGN + (gn_e - n0)
+                                         : f32_out + ((size_t)blockIdx.y * M + gm) * N + gn_e;
                     *reinterpret_cast<f32x4*>(dst) = d0;
                     *reinterpret_cast<f32x4*>(dst + 4) = d1;
                 }
@@ -853,6 +856,78 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
         *reinterpret_cast<float2*>(partials + ((size_t)tile * M + row) * 2) = make_float2(sd, sx);
 }
 
+// Second pass over left-over half tiles that were cut along K: adds sums[part][half tile][128][256] in the order of the
+// parts and applies the epilogue EPI. 8 columns per lane: 32 lanes per row (gating: 16, with the gate and up columns of 8
+// features each).
+template <int EPI>
+__global__ __launch_bounds__(256) void rest_reduce_kernel(const float* __restrict__ sums, int parts, int M, int N,
+                                                          const __bf16* __restrict__ x, __bf16* __restrict__ out,
+                                                          float* __restrict__ partials, GemmLaunch L, QkvOut qkv) {
+    constexpr int LPR = EPI == EPI_SWIGLU ? 16 : 32, ROWS = 256 / LPR;
+    const int half = (int)blockIdx.x, lr = (int)blockIdx.y * ROWS + (int)threadIdx.x / LPR, l = (int)threadIdx.x % LPR;
+    int tile_m, tile_n;
+    gemm_tile_of(L.first_tile + half / 2, L.mt, L.nt, L.plain != 0, tile_m, tile_n);
+    const int gm = tile_m * kGM + (half % 2) * (kGM / 2) + lr, n0 = tile_n * kGN;
+    const size_t part_stride = (size_t)gridDim.x * rest_sum_elems();
+    auto add_parts = [&](int col, float* v) {
+        const float* src = sums + (size_t)half * rest_sum_elems() + (size_t)lr * kGN + col;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = 0.f;
+#pragma unroll 4
+        for (int p = 0; p < parts; ++p) {
+            const f32x4 a0 = *reinterpret_cast<const f32x4*>(src + p * part_stride);
+            const f32x4 a1 = *reinterpret_cast<const f32x4*>(src + p * part_stride + 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                v[e] += a0[e];
+                v[4 + e] += a1[e];
+            }
+        }
+    };
+    if (EPI == EPI_SWIGLU) {
+        const int col = 64 * (l / 4) + 8 * (l % 4), gcol = (n0 + 64 * (l / 4)) / 2 + 8 * (l % 4);
+        if (gm >= M || gcol >= N / 2) return;
+        float g[8], u[8];
+        add_parts(col, g);
+        add_parts(col + 32, u);
+        bf16x8 ov;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) ov[e] = (__bf16)(g[e] / (1.0f + __expf(-g[e])) * u[e]);
+        *reinterpret_cast<bf16x8*>(out + (size_t)gm * (N / 2) + gcol) = ov;
+        return;
+    }
+    const int gn = n0 + 8 * l;
+    const bool ok = gm < M && gn < N;
+    float v[8], sd = 0.f, sx = 0.f;
+    if (ok) {
+        add_parts(8 * l, v);
+        bf16x8 ov;
+        if (EPI == EPI_RESIDUAL_NORM) {
+            const bf16x8 xr = *reinterpret_cast<const bf16x8*>(x + (size_t)gm * N + gn);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float xf = (float)xr[e];
+                ov[e] = (__bf16)(xf + v[e]);
+                sd = fmaf(v[e], v[e], sd);
+                sx = fmaf(xf, xf, sx);
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) ov[e] = (__bf16)v[e];
+        }
+        __bf16* dst = EPI == EPI_QKV ? qkv_dst(out, qkv, gm, gn) : out + (size_t)gm * N + gn;
+        *reinterpret_cast<bf16x8*>(dst) = ov;
+    }
+    if (EPI == EPI_RESIDUAL_NORM) {
+#pragma unroll
+        for (int off = 1; off < 32; off <<= 1) {
+            sd += __shfl_xor(sd, off);
+            sx += __shfl_xor(sx, off);
+        }
+        if (l == 0 && gm < M) *reinterpret_cast<float2*>(partials + ((size_t)tile_n * M + gm) * 2) = make_float2(sd, sx);
+    }
+}
+
 // h = x / sqrt(mean(x^2) + 1e-6), unit gain; one wave per row. Rows of up to 512 * CH elements are held in
 // registers between the two passes (one read of x); longer rows are read twice (CH = 0).
 template <int CH>
@@ -1098,6 +1173,17 @@ static dash_status launch_gemm(const __bf16* A, const __bf16* B, int M, int K, i
                            out, partials, delta_dbg, L, qkv);
     if (g.rest > 0) {
         L.first_tile = g.full;
+        const int parts = split_ws && !delta_dbg ? rest_parts(g, compute_units(), split_bytes) : 1;
+        if (parts >= 2) {
+            float* sums = reinterpret_cast<float*>(split_ws);
+            L.ksteps_per_split = (g.ksteps + parts - 1) / parts;
+            hipLaunchKernelGGL((gemm_mfma_kernel<EPI_SPLITK, 2>), dim3(2 * g.rest, parts), dim3(kGThreads), gemm_smem_bytes(2), s,
+                               A, B, M, K, N, nullptr, nullptr, nullptr, sums, L, qkv);
+            constexpr int kRows = 256 / (EPI == EPI_SWIGLU ? 16 : 32);
+            hipLaunchKernelGGL((rest_reduce_kernel<EPI>), dim3(2 * g.rest, kGM / 2 / kRows), dim3(256), 0, s, sums, parts, M, N,
+                               x, out, partials, L, qkv);
+            return launch_status();
+        }
         hipLaunchKernelGGL((gemm_mfma_kernel<EPI, 2>), dim3(2 * g.rest), dim3(kGThreads), gemm_smem_bytes(2), s, A, B, M, K, N,
                            x, out, partials, delta_dbg, L, qkv);
     }

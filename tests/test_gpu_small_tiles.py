@@ -81,3 +81,62 @@ def test_front_end_and_feed_forward(n, d, hq, hkv, m):
     act = (torch.nn.functional.silu(hd @ gate.double()) * (hd @ up.double())).bfloat16().double()
     upd = act @ down.double()
     assert float((out.double() - xd - upd).abs().max()) <= 2.0 ** -8 * float((xd + upd).abs().max()) + 4e-3 * float(upd.abs().max())
+
+
+def _rest_parts(M, K, N, scratch):
+    lib = _lib()
+    lib.dash_rest_parts.argtypes = [ctypes.c_int] * 4 + [ctypes.c_ulonglong]
+    return lib.dash_rest_parts(M, K, N, torch.cuda.get_device_properties(0).multi_processor_count, scratch)
+
+
+@pytest.mark.parametrize("n,K,d", [(4617, 3584, 3584), (4900, 3584, 3400)])
+def test_left_over_tiles_in_k_parts_projection(n, K, d):
+    """Products whose few left-over half tiles are cut along K (the last row tile holds 9 and 36 rows; the last column tile
+    whole and 72 columns): x_next and norms as in test_projection."""
+    rng = np.random.default_rng(n)
+    a, w, x = _rand(rng, (n, K)), _rand(rng, (K, d), K ** -0.5), _rand(rng, (n, d), 3.0)
+    p = B.make_params(d, K // 64, 1, 64, rule=B.RULE_NONE)
+    ws = torch.empty((64 << 20,), dtype=torch.uint8, device="cuda")
+    assert _plan(n, K, d, 1, ws.numel())[0] < 0 and _rest_parts(n, K, d, ws.numel()) > 1
+    P = B.norm_partials_per_row(p)
+    xn, part = torch.zeros_like(x), torch.zeros((P, n, 2), device="cuda")
+    B.dash_wo_residual_rownorm(p, a, w, x, n, xn, part, None, ws)
+    want = a.double() @ w.double()
+    full = x.double() + want
+    assert bool(((xn.double() - full).abs() <= 2.0 ** -8 * full.abs() + 1e-5 * float(want.abs().max())).all())
+    for e, t in ((0, want), (1, x.double())):
+        blocks = torch.nn.functional.pad(t, (0, P * 256 - d)).reshape(n, P, 256).pow(2).sum(dim=2).t()
+        assert float((part[..., e].double() - blocks).abs().max()) <= 1e-4 * float(blocks.max())
+
+
+def test_left_over_tiles_in_k_parts_front_end_and_feed_forward():
+    """The routing, store and gating epilogues of the second pass, and a long contraction."""
+    rng = np.random.default_rng(3)
+    d, hq, hkv, dh = 3584, 28, 4, 128
+    p = B.make_params(d, hq, hkv, dh, rule=B.RULE_NONE)
+    for n, fused in ((3612, True), (4617, False)):
+        x, w = _rand(rng, (n, d), 2.0), _rand(rng, (d, (hq + 2 * hkv) * dh), d ** -0.5)
+        ws = torch.empty((B.qkv_workspace_bytes(p, n),), dtype=torch.uint8, device="cuda")
+        assert _rest_parts(n, d, 4608 if fused else 3584, ws.numel()) > 1
+        q, k, v = (torch.zeros((n, h, dh), dtype=torch.bfloat16, device="cuda") for h in (hq, hkv, hkv))
+        parts = [t.contiguous() for t in w.split([hq * dh, hkv * dh, hkv * dh], dim=1)]
+        if fused:
+            B.dash_rmsnorm_qkv_fused(p, x, w, n, q, k, v, torch.empty_like(x), ws)
+        else:
+            B.dash_rmsnorm_qkv(p, x, *parts, n, q, k, v, torch.empty_like(x), ws)
+        hd = (x.double() * torch.rsqrt(x.double().pow(2).mean(dim=1, keepdim=True) + 1e-6)).bfloat16().double()
+        for got, wt in zip((q, k, v), parts):
+            want = hd @ wt.double()
+            row = (got.reshape(n, -1).double() - want).norm(dim=1) / want.norm(dim=1)
+            assert float(row.max()) <= 4e-3
+    n, m = 400, 18944
+    x = _rand(rng, (n, d), 2.0)
+    gate, up, down = _rand(rng, (d, m), d ** -0.5), _rand(rng, (d, m), d ** -0.5), _rand(rng, (m, d), m ** -0.5)
+    fws = torch.empty((B.ffn_workspace_bytes(p, n, m),), dtype=torch.uint8, device="cuda")
+    out = torch.empty_like(x)
+    B.dash_ffn_swiglu(p, x, B.interleave_gate_up(gate, up), down, n, m, out, fws)
+    xd = x.double()
+    hd = (xd * torch.rsqrt(xd.pow(2).mean(dim=1, keepdim=True) + 1e-6)).bfloat16().double()
+    act = (torch.nn.functional.silu(hd @ gate.double()) * (hd @ up.double())).bfloat16().double()
+    upd = act @ down.double()
+    assert float((out.double() - xd - upd).abs().max()) <= 2.0 ** -8 * float((xd + upd).abs().max()) + 4e-3 * float(upd.abs().max())

@@ -31,6 +31,22 @@ def test_staging_loads_fetch_the_clamped_rows_and_columns(form):
         assert n.value > 0
 
 
+def test_left_over_tiles_in_k_parts():
+    """Half tiles left over after the whole rounds are cut along K when there are few of them and scratch holds the sums."""
+    lib = _load()
+    lib.dash_rest_parts.argtypes = [ctypes.c_int] * 4 + [ctypes.c_ulonglong]
+    parts = lambda *a: lib.dash_rest_parts(*a)
+    assert parts(4700, 3584, 3584, 256, 1 << 26) > 2 and parts(4700, 18944, 3584, 256, 1 << 26) > 4
+    assert parts(16384, 3584, 3584, 256, 1 << 26) == 1          # 128 left over fill the units as they are
+    assert parts(4700, 3584, 3584, 256, 0) == 1                 # no scratch
+    assert parts(4700, 3584, 3584, 256, 3 * 20 * 131072) <= 3   # as many as the scratch holds
+    assert parts(4700, 512, 3584, 256, 1 << 26) == 1            # too few steps to cut
+    for M, K, N in ((4700, 3584, 3584), (4700, 18944, 3584), (9500, 3584, 3584), (400, 3584, 37888), (3700, 3584, 4608)):
+        n = ctypes.c_longlong(0)
+        assert parts(M, K, N, 256, 1 << 26) > 1
+        assert lib.dash_check_gemm_staging(M, K, N, 256, 1 << 26, ctypes.byref(n)) == 0
+
+
 def test_choice_of_a_form():
     """Large products keep the large tiles; short ones take small tiles, along K in parts only where the tiles alone leave
     the chip idle; without scratch none."""
