@@ -118,7 +118,9 @@ def _check(status: int, what: str):
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """Handle of the current device's current stream. Asked for in every call: torch.cuda.current_stream() builds a Stream
+    object each time, 2.8 us of the 6.9 that a call with one launch takes; the handle alone takes 0.2."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _p(t: torch.Tensor | None):
