@@ -239,6 +239,13 @@ dash_status dash_rmsnorm_qkv_fused(const dash_layer_params *params, const void *
 dash_status dash_rope_qk(const dash_layer_params *params, void *q, void *k, const int32_t *active_idx, int32_t n,
                          double theta_base, void *hip_stream);
 
+/* The two calls above as one: dash_rmsnorm_qkv_fused, then dash_rope_qk on its q and k. With a workspace of
+ * dash_qkv_workspace_bytes (which holds the rows' cosines and sines) the rotation happens in the product's epilogue, on
+ * the fp32 sums: q and k are rounded to bf16 once instead of twice and not read and written again. */
+dash_status dash_rmsnorm_qkv_rope(const dash_layer_params *params, const void *x, const void *w_qkv,
+                                  const int32_t *active_idx, int32_t n, double theta_base, void *q, void *k, void *v,
+                                  void *h_scratch, void *workspace, size_t workspace_bytes, void *hip_stream);
+
 /* Second half of a block (Alg. 1 step 7): x_out = x + FFN(LN(x)) on n rows, LN = RMS normalisation (unit gain,
  * eps 1e-6), FFN the gated feed-forward of the Qwen2.5 / Llama-3 backbones (Sec. 4.1):
  *   h = LN(x); a = silu(h W_gate) * (h W_up); x_out = x + a W_down.

@@ -88,6 +88,8 @@ def lib() -> C.CDLL:
     L.dash_rmsnorm_qkv.argtypes = [pp, _vp, _vp, _vp, _vp, C.c_int32, _vp, _vp, _vp, _vp, _vp, C.c_size_t, _vp]
     L.dash_rmsnorm_qkv_fused.argtypes = [pp, _vp, _vp, C.c_int32, _vp, _vp, _vp, _vp, _vp, C.c_size_t, _vp]
     L.dash_rmsnorm_qkv_fused.restype = C.c_int
+    L.dash_rmsnorm_qkv_rope.argtypes = [pp, _vp, _vp, _vp, C.c_int32, C.c_double, _vp, _vp, _vp, _vp, _vp, C.c_size_t, _vp]
+    L.dash_rmsnorm_qkv_rope.restype = C.c_int
     L.dash_qkv_workspace_bytes.restype = C.c_size_t
     L.dash_qkv_workspace_bytes.argtypes = [pp, C.c_int32]
     L.dash_rope_qk.argtypes = [pp, _vp, _vp, _vp, C.c_int32, C.c_double, _vp]
@@ -349,6 +351,13 @@ def interleave_gate_up(w_gate: torch.Tensor, w_up: torch.Tensor) -> torch.Tensor
 def dash_rope_qk(params, q, k, active_idx, n, theta_base) -> None:
     _check(lib().dash_rope_qk(C.byref(params), _p(q), _p(k), _p(active_idx), int(n), float(theta_base), _stream()),
            "dash_rope_qk")
+
+
+def dash_rmsnorm_qkv_rope(params, x, w_qkv, active_idx, n, theta_base, q, k, v, h_scratch, workspace=None) -> None:
+    """dash_rmsnorm_qkv_fused and dash_rope_qk in one call: the rotation in the product's epilogue."""
+    ws_n = workspace.numel() if workspace is not None else 0
+    _check(lib().dash_rmsnorm_qkv_rope(C.byref(params), _p(x), _p(w_qkv), _p(active_idx), int(n), float(theta_base), _p(q),
+                                       _p(k), _p(v), _p(h_scratch), _p(workspace), ws_n, _stream()), "dash_rmsnorm_qkv_rope")
 
 
 def qkv_workspace_bytes(params, n_capacity: int) -> int:

@@ -57,12 +57,14 @@ def run_chain(state: ChainState, x0: torch.Tensor, active_idx0: torch.Tensor, n0
         if time_layers:
             e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
             e0.record()
-        if "w_qkv" in W:      # one product over the concatenated weight
+        if "w_qkv" in W and rope_theta is not None:      # one product over the concatenated weight, rotated on the way
+            B.dash_rmsnorm_qkv_rope(p, x, W["w_qkv"], idx, n, rope_theta, state.q, state.k, state.v, state.h, state.qkv_ws)
+        elif "w_qkv" in W:
             B.dash_rmsnorm_qkv_fused(p, x, W["w_qkv"], n, state.q, state.k, state.v, state.h, state.qkv_ws)
         else:
             B.dash_rmsnorm_qkv(p, x, W["w_q"], W["w_k"], W["w_v"], n, state.q, state.k, state.v, state.h, state.qkv_ws)
-        if rope_theta is not None:
-            B.dash_rope_qk(p, state.q, state.k, idx, n, rope_theta)
+            if rope_theta is not None:
+                B.dash_rope_qk(p, state.q, state.k, idx, n, rope_theta)
         B.dash_attn_layer(p, x, state.q, state.k, state.v, W["w_o"], idx, n, buf)
         if time_layers:
             e1.record()

@@ -378,6 +378,26 @@ dash_status dash_rmsnorm_qkv_fused(const dash_layer_params* p, const void* x, co
                                     (hipStream_t)hip_stream);
 }
 
+dash_status dash_rmsnorm_qkv_rope(const dash_layer_params* p, const void* x, const void* w_qkv, const int32_t* active_idx,
+                                  int32_t n, double theta_base, void* q, void* k, void* v, void* h_scratch, void* workspace,
+                                  size_t workspace_bytes, void* hip_stream) {
+    if (!(theta_base > 1.0)) return DASH_ERR_INVALID_ARG;
+    if (n > 0 && !active_idx) return DASH_ERR_INVALID_ARG;
+    dash_status st = check_params(p);
+    if (st != DASH_OK) return st;
+    if (p->dtype != DASH_BF16 || p->d % 64 != 0) return DASH_ERR_UNSUPPORTED;
+    if (n > 0 && workspace && aligned16(workspace) && workspace_bytes >= rope_table_bytes(*p, n)) {
+        if (!x || !w_qkv || !q || !k || !v || !h_scratch) return DASH_ERR_INVALID_ARG;
+        if (!aligned16(x) || !aligned16(w_qkv) || !aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(h_scratch))
+            return DASH_ERR_INVALID_ARG;
+        return launch_rmsnorm_qkv_rope(*p, x, w_qkv, active_idx, theta_base, n, q, k, v, h_scratch, workspace, workspace_bytes,
+                                       (hipStream_t)hip_stream);
+    }
+    // no room for the table: the two calls
+    st = dash_rmsnorm_qkv_fused(p, x, w_qkv, n, q, k, v, h_scratch, workspace, workspace_bytes, hip_stream);
+    return st != DASH_OK ? st : dash_rope_qk(p, q, k, active_idx, n, theta_base, hip_stream);
+}
+
 size_t dash_ffn_workspace_bytes(const dash_layer_params* p, int32_t n_capacity, int32_t m) {
     if (check_params(p) != DASH_OK || n_capacity < 0 || m <= 0) return 0;
     return ffn_workspace_bytes(*p, n_capacity, m);

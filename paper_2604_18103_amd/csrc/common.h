@@ -78,6 +78,10 @@ dash_status launch_rmsnorm_qkv(const dash_layer_params& p, const void* x, const 
                                size_t split_bytes, hipStream_t s);
 dash_status launch_rmsnorm_qkv_fused(const dash_layer_params& p, const void* x, const void* w_qkv, int n, void* q,
                                      void* k, void* v, void* h, void* split_ws, size_t split_bytes, hipStream_t s);
+size_t rope_table_bytes(const dash_layer_params& p, int n);
+dash_status launch_rmsnorm_qkv_rope(const dash_layer_params& p, const void* x, const void* w_qkv, const int32_t* active_idx,
+                                    double theta, int n, void* q, void* k, void* v, void* h, void* ws, size_t ws_bytes,
+                                    hipStream_t s);
 // score_decide.hip
 size_t decide_workspace_bytes();
 int topk_keep(const dash_layer_params& p, int n);  // rows TopK keeps of n

@@ -231,7 +231,8 @@ inline int rest_parts(const GemmPlan& g, int cu, size_t scratch_bytes) {
 }
 // norms: the product returns row norms, whose fine pairs need scratch too. Without scratch a product adds its K steps in
 // one order, whatever its width: large tiles.
-inline SmallPlan small_plan(int M, int K, int N, int cu, bool norms, bool scratch, size_t scratch_bytes, double large_us) {
+// head: columns that have to lie in one tile unless a second pass follows (0: none).
+inline SmallPlan small_plan(int M, int K, int N, int cu, bool norms, int head, bool scratch, size_t scratch_bytes, double large_us) {
     SmallPlan best{};
     best.form = -1;
     if (cu <= 0 || !scratch) return best;
@@ -245,6 +246,7 @@ inline SmallPlan small_plan(int M, int K, int N, int cu, bool norms, bool scratc
         const int most = f < 2 ? sa_min(cu / (int)tiles, ksteps / kSmallSplitMinSteps) : 1;
         for (int parts = 1; parts <= sa_max(most, 1); ++parts) {
             const int per = (ksteps + parts - 1) / parts;
+            if (parts == 1 && head > s.BN) continue;
             if ((ksteps + per - 1) / per != parts) continue;  // every part has a K step, and no two plans are alike
             const size_t need = parts > 1 ? (size_t)parts * M * N * sizeof(float) : (norms ? (size_t)((N + 63) / 64) * M * 2 * sizeof(float) : 0);
             if (need > scratch_bytes) continue;

@@ -215,7 +215,7 @@ int dash_rest_parts(int M, int K, int N, int cu, unsigned long long scratch) {
 // The form a product takes: out[0..3] = form (-1: large tiles), tiles, parts, K steps per part.
 void dash_small_plan(int M, int K, int N, int cu, int norms, unsigned long long scratch, int* out) {
     const GemmPlan g = gemm_plan(M, K, N, cu, scratch > 0, (size_t)scratch);
-    const SmallPlan p = small_plan(M, K, N, cu, norms != 0, scratch > 0, (size_t)scratch, large_tiles_us(g, M, N, cu));
+    const SmallPlan p = small_plan(M, K, N, cu, norms != 0, 0, scratch > 0, (size_t)scratch, large_tiles_us(g, M, N, cu));
     out[0] = p.form; out[1] = p.tiles; out[2] = p.parts; out[3] = p.ksteps_per_part;
 }
 

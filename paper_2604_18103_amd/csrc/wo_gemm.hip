@@ -144,7 +144,10 @@ static_assert(gemm_smem_bytes(4) >= 8 * 32 * kEpiStr * sizeof(float) + 4 * kGM *
 // f32_out[split][M][N]; a reduction kernel adds the splits in order and applies one of the other epilogues.
 // EPI_QKV: a plain store whose columns are routed to three outputs (the q, k and v projections as one product
 // over the concatenated weight).
-enum { EPI_RESIDUAL_NORM = 0, EPI_STORE = 1, EPI_SWIGLU = 2, EPI_SPLITK = 3, EPI_QKV = 4 };
+// EPI_QKV_ROPE: the same with the q and k columns rotated on the way (rotary embedding), from the fp32 sums and a table
+// of cosines and sines that the row norm's launch leaves: q and k are not read and written once more.
+enum { EPI_RESIDUAL_NORM = 0, EPI_STORE = 1, EPI_SWIGLU = 2, EPI_SPLITK = 3, EPI_QKV = 4, EPI_QKV_ROPE = 5 };
+constexpr bool epi_qkv(int EPI) { return EPI == EPI_QKV || EPI == EPI_QKV_ROPE; }
 
 // Output routing of EPI_QKV: columns [0, Dq) go to `out` (row stride Dq), [Dq, Dq + Dkv) to k and the rest to v
 // (row stride Dkv). Dq and Dkv are multiples of 8, so the 8 columns a lane stores never straddle two outputs.
@@ -152,7 +155,22 @@ struct QkvOut {
     __bf16* k;
     __bf16* v;
     int Dq, Dkv;
+    const float2* table;  // EPI_QKV_ROPE: [n][half] cosine and sine of each row's angles
+    int half;             // head_dim / 2
 };
+// The 8 columns of a row that start at `col` (v) rotated with their partners `half` columns away in the same head.
+__device__ __forceinline__ void rope8(const QkvOut& o, int row, int col, const float* partner, float* v) {
+    const int i0 = col % o.half;  // col is a multiple of 8, half 32 or 64: the eight columns lie on one side
+    const bool hi = col % (2 * o.half) >= o.half;
+    const float4* t = reinterpret_cast<const float4*>(o.table + (size_t)row * o.half + i0);
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+        const float4 cs = t[e / 2];  // cos, sin of two neighbouring frequencies
+        const float s0 = hi ? cs.y : -cs.y, s1 = hi ? cs.w : -cs.w;
+        v[e] = fmaf(partner[e], s0, v[e] * cs.x);
+        v[e + 1] = fmaf(partner[e + 1], s1, v[e + 1] * cs.z);
+    }
+}
 __device__ __forceinline__ __bf16* qkv_dst(__bf16* q, const QkvOut& o, int row, int col) {
     if (col < o.Dq) return q + (size_t)row * o.Dq + col;
     col -= o.Dq;
@@ -490,10 +508,21 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
                     *reinterpret_cast<f32x4*>(dst + 4) = d1;
                 }
             } else if (ok) {
+                float v[8] = {dv[0], dv[1], dv[2], dv[3], dv[4], dv[5], dv[6], dv[7]};
+                if (EPI == EPI_QKV_ROPE && gn_e < qkv.Dq + qkv.Dkv) {
+                    // the partner columns: in the neighbouring wave's staged block (head size 128) or in this one (64)
+                    const float* src = qkv.half == 64 ? reinterpret_cast<const float*>(gemm_smem_raw) + (wave ^ 1) * 32 * kEpiStr +
+                                                            lr * kEpiStr + 8 * e_c8
+                                                      : stage + lr * kEpiStr + ((8 * e_c8) ^ 32);
+                    float partner[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) partner[e] = src[e];
+                    rope8(qkv, gm, gn_e, partner, v);
+                }
                 bf16x8 ov;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) ov[e] = (__bf16)dv[e];
-                __bf16* dst = EPI == EPI_QKV ? qkv_dst(out, qkv, gm, gn_e) : out + (size_t)gm * N + gn_e;
+                for (int e = 0; e < 8; ++e) ov[e] = (__bf16)v[e];
+                __bf16* dst = epi_qkv(EPI) ? qkv_dst(out, qkv, gm, gn_e) : out + (size_t)gm * N + gn_e;
                 *reinterpret_cast<bf16x8*>(dst) = ov;
             }
         }
@@ -740,10 +769,15 @@ __global__ __launch_bounds__(KW * kSWaves * kWave, KW == 4 ? 4 : 2) void gemm_sm
                         *reinterpret_cast<f32x4*>(dst + 4) = f32x4{dv[4], dv[5], dv[6], dv[7]};
                     }
                 } else if (ok) {
+                    if (EPI == EPI_QKV_ROPE && gn < qkv.Dq + qkv.Dkv) {  // a head lies in one tile (the launcher's choice)
+                        float partner[8];
+                        sum8(&stage[sr * STR + ((8 * l) ^ qkv.half)], partner);
+                        rope8(qkv, gm, gn, partner, dv);
+                    }
                     bf16x8 ov;
 #pragma unroll
                     for (int e = 0; e < 8; ++e) ov[e] = (__bf16)dv[e];
-                    __bf16* dst = EPI == EPI_QKV ? qkv_dst(out, qkv, gm, gn) : out + (size_t)gm * N + gn;
+                    __bf16* dst = epi_qkv(EPI) ? qkv_dst(out, qkv, gm, gn) : out + (size_t)gm * N + gn;
                     *reinterpret_cast<bf16x8*>(dst) = ov;
                 }
             }
@@ -822,12 +856,18 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
             }
         }
     }
-    if (EPI == EPI_STORE || EPI == EPI_QKV) {
+    if (EPI == EPI_STORE || epi_qkv(EPI)) {
+        if (EPI == EPI_QKV_ROPE) {  // the partner columns belong to the lane half / 8 away
+            float partner[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) partner[e] = __shfl_xor(acc[e], qkv.half / 8);
+            if (ok && col < qkv.Dq + qkv.Dkv) rope8(qkv, row, col, partner, acc);
+        }
         if (ok) {
             bf16x8 ov;
 #pragma unroll
             for (int e = 0; e < 8; ++e) ov[e] = (__bf16)acc[e];
-            __bf16* dst = EPI == EPI_QKV ? qkv_dst(out, qkv, row, col) : out + (size_t)row * N + col;
+            __bf16* dst = epi_qkv(EPI) ? qkv_dst(out, qkv, row, col) : out + (size_t)row * N + col;
             *reinterpret_cast<bf16x8*>(dst) = ov;
         }
         return;
@@ -898,9 +938,15 @@ __global__ __launch_bounds__(256) void rest_reduce_kernel(const float* __restric
     }
     const int gn = n0 + 8 * l;
     const bool ok = gm < M && gn < N;
-    float v[8], sd = 0.f, sx = 0.f;
+    float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, sd = 0.f, sx = 0.f;
+    if (ok) add_parts(8 * l, v);
+    if (EPI == EPI_QKV_ROPE) {  // the partner columns belong to the lane half / 8 away
+        float partner[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) partner[e] = __shfl_xor(v[e], qkv.half / 8);
+        if (ok && gn < qkv.Dq + qkv.Dkv) rope8(qkv, gm, gn, partner, v);
+    }
     if (ok) {
-        add_parts(8 * l, v);
         bf16x8 ov;
         if (EPI == EPI_RESIDUAL_NORM) {
             const bf16x8 xr = *reinterpret_cast<const bf16x8*>(x + (size_t)gm * N + gn);
@@ -915,7 +961,7 @@ __global__ __launch_bounds__(256) void rest_reduce_kernel(const float* __restric
 #pragma unroll
             for (int e = 0; e < 8; ++e) ov[e] = (__bf16)v[e];
         }
-        __bf16* dst = EPI == EPI_QKV ? qkv_dst(out, qkv, gm, gn) : out + (size_t)gm * N + gn;
+        __bf16* dst = epi_qkv(EPI) ? qkv_dst(out, qkv, gm, gn) : out + (size_t)gm * N + gn;
         *reinterpret_cast<bf16x8*>(dst) = ov;
     }
     if (EPI == EPI_RESIDUAL_NORM) {
@@ -930,22 +976,43 @@ __global__ __launch_bounds__(256) void rest_reduce_kernel(const float* __restric
 
 // h = x / sqrt(mean(x^2) + 1e-6), unit gain; one wave per row. Rows of up to 512 * CH elements are held in
 // registers between the two passes (one read of x); longer rows are read twice (CH = 0).
-template <int CH>
+// HALF > 0: the wave also leaves the cosine and sine of its row's HALF rotary angles pos * theta^(-2i / (2 HALF)) in
+// table[row][HALF], from fp64 angles as rope_qk_kernel forms them; the arithmetic hides behind the row's loads.
+struct RopeTable {
+    const int32_t* pos;
+    float2* table;
+    double neg_log2_theta_2_over_dh;
+};
+template <int CH, int HALF>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const __bf16* __restrict__ x, int n, int d,
-                                                      __bf16* __restrict__ hout) {
+                                                      __bf16* __restrict__ hout, RopeTable rope) {
     const int row = (blockIdx.x * blockDim.x + threadIdx.x) / kWave;
     const int lane = threadIdx.x % kWave;
     if (row >= n) return;
     const __bf16* xr = x + (size_t)row * d;
     __bf16* hr = hout + (size_t)row * d;
     float ss = 0.f;
+    auto leave_angles = [&] {
+        if (HALF > 0 && lane < HALF) {
+            double a = (double)rope.pos[row] * exp2((double)lane * rope.neg_log2_theta_2_over_dh);
+            a -= 6.283185307179586476925286766559 * rint(a * 0.15915494309189533576888376337251);
+            double s, c;
+            sincos(a, &s, &c);
+            rope.table[(size_t)row * HALF + lane] = make_float2((float)c, (float)s);
+        }
+    };
     if (CH > 0) {
         bf16x8 v[CH > 0 ? CH : 1];
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             const int c = (i * kWave + lane) * 8;
+            if (c < d) v[i] = *reinterpret_cast<const bf16x8*>(xr + c);
+        }
+        leave_angles();  // while the row is on its way
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int c = (i * kWave + lane) * 8;
             if (c < d) {
-                v[i] = *reinterpret_cast<const bf16x8*>(xr + c);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) ss = fmaf((float)v[i][e], (float)v[i][e], ss);
             }
@@ -965,6 +1032,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const __bf16* __restrict__
         }
         return;
     }
+    leave_angles();
     for (int c = lane * 8; c < d; c += kWave * 8) {
         const bf16x8 v = *reinterpret_cast<const bf16x8*>(xr + c);
 #pragma unroll
@@ -982,14 +1050,18 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const __bf16* __restrict__
     }
 }
 
-static void launch_rmsnorm(const __bf16* x, int n, int d, __bf16* h, hipStream_t s) {
+template <int HALF>
+static void launch_rmsnorm(const __bf16* x, int n, int d, __bf16* h, const RopeTable& rope, hipStream_t s) {
     const int blocks = (int)(((size_t)n * kWave + 255) / 256);
     if (d <= 512 * 4)
-        hipLaunchKernelGGL(rmsnorm_kernel<4>, dim3(blocks), dim3(256), 0, s, x, n, d, h);
+        hipLaunchKernelGGL((rmsnorm_kernel<4, HALF>), dim3(blocks), dim3(256), 0, s, x, n, d, h, rope);
     else if (d <= 512 * 8)
-        hipLaunchKernelGGL(rmsnorm_kernel<8>, dim3(blocks), dim3(256), 0, s, x, n, d, h);
+        hipLaunchKernelGGL((rmsnorm_kernel<8, HALF>), dim3(blocks), dim3(256), 0, s, x, n, d, h, rope);
     else
-        hipLaunchKernelGGL(rmsnorm_kernel<0>, dim3(blocks), dim3(256), 0, s, x, n, d, h);
+        hipLaunchKernelGGL((rmsnorm_kernel<0, HALF>), dim3(blocks), dim3(256), 0, s, x, n, d, h, rope);
+}
+static void launch_rmsnorm(const __bf16* x, int n, int d, __bf16* h, hipStream_t s) {
+    launch_rmsnorm<0>(x, n, d, h, RopeTable{nullptr, nullptr, 0.0}, s);
 }
 
 int norm_partials_per_row(int d, int dtype) {
@@ -1040,6 +1112,8 @@ dash_status init_gemm_kernels() {
         if (e == hipSuccess) e = set_gemm_lds_size<EPI_SWIGLU>();
         if (e == hipSuccess) e = set_gemm_lds_size<EPI_SPLITK>();
         if (e == hipSuccess) e = set_gemm_lds_size<EPI_QKV>();
+        if (e == hipSuccess) e = set_gemm_lds_size<EPI_QKV_ROPE>();
+        if (e == hipSuccess) e = set_small_lds_sizes<EPI_QKV_ROPE>();
         if (e == hipSuccess) e = set_small_lds_sizes<EPI_RESIDUAL_NORM>();
         if (e == hipSuccess) e = set_small_lds_sizes<EPI_STORE>();
         if (e == hipSuccess) e = set_small_lds_sizes<EPI_SWIGLU>();
@@ -1136,7 +1210,7 @@ static dash_status launch_small(const SmallPlan& g, GemmArgs a, void* scratch, N
 template <int EPI>
 static dash_status launch_gemm(const __bf16* A, const __bf16* B, int M, int K, int N, const __bf16* x,
                                __bf16* out, float* partials, float* delta_dbg, void* split_ws, size_t split_bytes,
-                               hipStream_t s, QkvOut qkv = QkvOut{nullptr, nullptr, 0, 0}, bool want_norms = true,
+                               hipStream_t s, QkvOut qkv = QkvOut{}, bool want_norms = true,
                                NormSums* sums_out = nullptr) {
     // the staging loads address a tile with 32-bit lane offsets: 256 rows of A, 64 rows of B
     if ((size_t)kGM * K * 2 >= ((size_t)1 << 32) || (size_t)kGK * N * 2 + 2 * kGN >= ((size_t)1 << 32)) return DASH_ERR_UNSUPPORTED;
@@ -1146,7 +1220,7 @@ static dash_status launch_gemm(const __bf16* A, const __bf16* B, int M, int K, i
     const bool norms = EPI == EPI_RESIDUAL_NORM && want_norms;
     if (sums_out) *sums_out = NormSums{partials, (N + kGN - 1) / kGN, 1};
     // the debug output keeps the product off K parts and small tiles: with and without scratch it has the same bits
-    const SmallPlan small = small_plan(M, K, N, compute_units(), norms, split_ws != nullptr, split_ws ? split_bytes : 0,
+    const SmallPlan small = small_plan(M, K, N, compute_units(), norms, EPI == EPI_QKV_ROPE ? 2 * qkv.half : 0, split_ws != nullptr, split_ws ? split_bytes : 0,
                                        large_tiles_us(g, M, N, compute_units()));
     if (small.form >= 0 && !delta_dbg) {
         GemmArgs a = args;
@@ -1213,7 +1287,7 @@ dash_status launch_wo_residual_rownorm(const dash_layer_params& p, const void* o
     }
     return launch_gemm<EPI_RESIDUAL_NORM>((const __bf16*)o, (const __bf16*)w_o, n, K, N, (const __bf16*)x,
                                           (__bf16*)x_next, partials, delta_dbg, split_ws, split_bytes, s,
-                                          QkvOut{nullptr, nullptr, 0, 0}, true, sums);
+                                          QkvOut{}, true, sums);
 }
 
 static size_t up256(size_t v) { return (v + 255) / 256 * 256; }
@@ -1242,14 +1316,16 @@ dash_status launch_ffn_swiglu(const dash_layer_params& p, const void* x, const v
     if (st != DASH_OK) return st;
     return launch_gemm<EPI_RESIDUAL_NORM>(act, (const __bf16*)w_down, n, m, p.d, (const __bf16*)x,
                                           (__bf16*)x_out, partials, nullptr, split_ws, split_bytes, s,
-                                          QkvOut{nullptr, nullptr, 0, 0}, false);
+                                          QkvOut{}, false);
 }
+
+size_t rope_table_bytes(const dash_layer_params& p, int n);
 
 size_t qkv_workspace_bytes(const dash_layer_params& p, int n) {
     if (p.dtype != DASH_BF16) return 0;
     const int Dq = p.n_q_heads * p.head_dim, Dkv = p.n_kv_heads * p.head_dim;
-    // the widest of the three separate projections, or the one product over the concatenated weight
-    return max(gemm_splitk_bytes(n, p.d, Dq), gemm_splitk_bytes(n, p.d, Dq + 2 * Dkv));
+    // the rotary table, and the widest of the three separate projections or the one product over the concatenated weight
+    return rope_table_bytes(p, n) + max(gemm_splitk_bytes(n, p.d, Dq), gemm_splitk_bytes(n, p.d, Dq + 2 * Dkv));
 }
 
 dash_status launch_rmsnorm_qkv(const dash_layer_params& p, const void* x, const void* w_q, const void* w_k,
@@ -1278,7 +1354,27 @@ dash_status launch_rmsnorm_qkv_fused(const dash_layer_params& p, const void* x, 
     const int d = p.d, Dq = p.n_q_heads * p.head_dim, Dkv = p.n_kv_heads * p.head_dim;
     launch_rmsnorm((const __bf16*)x, n, d, (__bf16*)hbuf, s);
     return launch_gemm<EPI_QKV>((const __bf16*)hbuf, (const __bf16*)w_qkv, n, d, Dq + 2 * Dkv, nullptr, (__bf16*)q,
-                                nullptr, nullptr, split_ws, split_bytes, s, QkvOut{(__bf16*)k, (__bf16*)v, Dq, Dkv});
+                                nullptr, nullptr, split_ws, split_bytes, s, QkvOut{(__bf16*)k, (__bf16*)v, Dq, Dkv, nullptr, 0});
+}
+
+// ... and with the rotary embedding of q and k in the product's epilogue: the row norm's launch leaves the angles' cosines
+// and sines at the start of the scratch, the rest of it serves the product.
+size_t rope_table_bytes(const dash_layer_params& p, int n) { return up256((size_t)n * (p.head_dim / 2) * sizeof(float2)); }
+
+dash_status launch_rmsnorm_qkv_rope(const dash_layer_params& p, const void* x, const void* w_qkv, const int32_t* active_idx,
+                                    double theta, int n, void* q, void* k, void* v, void* hbuf, void* ws, size_t ws_bytes,
+                                    hipStream_t s) {
+    if (n == 0) return DASH_OK;
+    const int d = p.d, Dq = p.n_q_heads * p.head_dim, Dkv = p.n_kv_heads * p.head_dim, half = p.head_dim / 2;
+    const size_t used = rope_table_bytes(p, n);
+    const RopeTable rope{active_idx, (float2*)ws, -log2(theta) * 2.0 / (double)p.head_dim};
+    if (half == 32)
+        launch_rmsnorm<32>((const __bf16*)x, n, d, (__bf16*)hbuf, rope, s);
+    else
+        launch_rmsnorm<64>((const __bf16*)x, n, d, (__bf16*)hbuf, rope, s);
+    return launch_gemm<EPI_QKV_ROPE>((const __bf16*)hbuf, (const __bf16*)w_qkv, n, d, Dq + 2 * Dkv, nullptr, (__bf16*)q, nullptr,
+                                     nullptr, (char*)ws + used, ws_bytes - used, s,
+                                     QkvOut{(__bf16*)k, (__bf16*)v, Dq, Dkv, rope.table, half});
 }
 
 }  // namespace dash

@@ -93,12 +93,14 @@ def run_schedule(st: BlockState, x0: torch.Tensor, weights: list, shots: dict, r
     spare = [st.x_a, st.x_b]
     for l, W in enumerate(weights):
         x_out = spare[l & 1]
-        if "w_qkv" in W:      # one product over the concatenated weight
+        if "w_qkv" in W and rope_theta is not None:      # one product over the concatenated weight, rotated on the way
+            B.dash_rmsnorm_qkv_rope(p, x, W["w_qkv"], idx, n, rope_theta, st.q, st.k, st.v, st.h, st.qkv_ws)
+        elif "w_qkv" in W:
             B.dash_rmsnorm_qkv_fused(p, x, W["w_qkv"], n, st.q, st.k, st.v, st.h, st.qkv_ws)
         else:
             B.dash_rmsnorm_qkv(p, x, W["w_q"], W["w_k"], W["w_v"], n, st.q, st.k, st.v, st.h, st.qkv_ws)
-        if rope_theta is not None:
-            B.dash_rope_qk(p, st.q, st.k, idx, n, rope_theta)
+            if rope_theta is not None:
+                B.dash_rope_qk(p, st.q, st.k, idx, n, rope_theta)
         if l in shots:
             p.rule, p.k_keep = B.RULE_TOPK, int(shots[l])
             B.dash_attn_layer(p, x, st.q, st.k, st.v, W["w_o"], idx, n, buf)     # H~ in buf.x_next, mask, S*
