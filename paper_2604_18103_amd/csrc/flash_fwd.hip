@@ -304,10 +304,28 @@ struct FaSmem {
     static constexpr int STAGE_ELEMS = kFaBN * DH;
     // one key group: two stages of K, three of V; two key groups: two of each for either group
     static constexpr size_t bytes(int KG) { return (KG == 1 ? 5 : 8) * STAGE_ELEMS * sizeof(__bf16); }
+    // the result rows of 8 waves, and with two key groups the halves they exchange before that, take the stages' place
+    static_assert(bytes(1) >= 8 * 32 * (DH + 8) * sizeof(__bf16), "result rows fit");
+    static_assert(bytes(2) >= 32 * DH * 16 + 2048 + 8 * 32 * (DH / 2 + 8) * sizeof(__bf16), "exchange and result rows fit");
     __device__ static constexpr int k_swz(int row) { return fa_k_swz(row, DH); }
     __device__ static constexpr int v_swz(int row) { return fa_v_swz(row, DH); }
 };
 
+
+// A wave's 32 result rows of W elements go out through LDS (rows of W + 8 elements, written 8 bytes per lane as the
+// accumulators lie): a store instruction then covers whole rows instead of 8-byte pieces of 32 of them.
+__device__ constexpr int out_row(int W) { return W + 8; }
+template <int W>
+__device__ __forceinline__ void store_rows(const __bf16* rows, int lane, int q0, int n, __bf16* o, size_t stride) {
+    constexpr int LPR = W / 8, RPI = kWave / LPR;  // lanes per row, rows per instruction
+    wave_sync_lds();
+#pragma unroll
+    for (int r0 = 0; r0 < 32; r0 += RPI) {
+        const int r = r0 + lane / LPR, c = 8 * (lane % LPR);
+        const bf16x8 v = *reinterpret_cast<const bf16x8*>(rows + r * out_row(W) + c);
+        if (q0 + r < n) *reinterpret_cast<bf16x8*>(o + (size_t)(q0 + r) * stride + c) = v;
+    }
+}
 
 template <int DH, int KG>
 __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __restrict__ q,
@@ -357,24 +375,49 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
         // and, for a fixed scale constant, has a common sign for most rows (measured: 3e-4 of systematic relative
         // error in ||delta||). The row is therefore rounded a second time from x scaled by the inverse of that
         // factor, which cancels the systematic part; what is left is the random part of one rounding.
-        float xs[KC][8];
-        float sxx = 0.f, srx = 0.f;
+        // Head size 128: the two sums are taken over bf16 pairs (fp32 products and sums): with q the unscaled row and s the
+        // scale, <x, x> = s^2 <q, q> and <r, x> = s <r, q>. A third of the prologue's instructions less: 1 % at 4096 rows. At
+        // head size 64 the same text leaves the compiler a main loop that is 3 % slower, so it keeps the plain form.
+        if constexpr (DH == 128) {
+            float qq = 0.f, rq = 0.f;
 #pragma unroll
-        for (int kc = 0; kc < KC; ++kc)
+            for (int kc = 0; kc < KC; ++kc)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float x = (float)Qf[kc][e] * scale_log2;
-                xs[kc][e] = x;
-                sxx = fmaf(x, x, sxx);
-                srx = fmaf((float)(__bf16)x, x, srx);
-            }
-        sxx += __shfl_xor(sxx, 32);  // lanes j and j + 32 hold the two halves of the row
-        srx += __shfl_xor(srx, 32);
-        const float comp = sxx > 0.f ? 2.0f - srx / sxx : 1.0f;  // 1 / (1 + a) to first order, a = srx / sxx - 1
+                for (int e = 0; e < 8; e += 2) {
+                    const bf16x2 qp2 = {Qf[kc][e], Qf[kc][e + 1]};
+                    const bf16x2 r2 = {(__bf16)((float)Qf[kc][e] * scale_log2), (__bf16)((float)Qf[kc][e + 1] * scale_log2)};
+                    qq = __builtin_amdgcn_fdot2_f32_bf16(qp2, qp2, qq, false);
+                    rq = __builtin_amdgcn_fdot2_f32_bf16(r2, qp2, rq, false);
+                }
+            qq += __shfl_xor(qq, 32);  // lanes j and j + 32 hold the two halves of the row
+            rq += __shfl_xor(rq, 32);
+            const float sqq = qq * scale_log2;
+            // 1 / (1 + a) to first order, a = rq / sqq - 1 (rows of zeros, or too long to measure: 1), and the scale itself
+            const float scale_comp = (sqq > 0.f && sqq < INFINITY ? 2.0f - rq / sqq : 1.0f) * scale_log2;
 #pragma unroll
-        for (int kc = 0; kc < KC; ++kc)
+            for (int kc = 0; kc < KC; ++kc)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) Qf[kc][e] = (__bf16)(xs[kc][e] * comp);
+                for (int e = 0; e < 8; ++e) Qf[kc][e] = (__bf16)((float)Qf[kc][e] * scale_comp);
+        } else {
+            float xs[KC][8];
+            float sxx = 0.f, srx = 0.f;
+#pragma unroll
+            for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float x = (float)Qf[kc][e] * scale_log2;
+                    xs[kc][e] = x;
+                    sxx = fmaf(x, x, sxx);
+                    srx = fmaf((float)(__bf16)x, x, srx);
+                }
+            sxx += __shfl_xor(sxx, 32);  // lanes j and j + 32 hold the two halves of the row
+            srx += __shfl_xor(srx, 32);
+            const float comp = sxx > 0.f ? 2.0f - srx / sxx : 1.0f;  // 1 / (1 + a) to first order, a = srx / sxx - 1
+#pragma unroll
+            for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) Qf[kc][e] = (__bf16)(xs[kc][e] * comp);
+        }
     }
     f32x16 Oacc[DB];
 #pragma unroll
@@ -730,8 +773,8 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
         const float M = fmaxf(m_own, other.x);
         const float a_own = __builtin_amdgcn_exp2f(m_own - M), a_oth = __builtin_amdgcn_exp2f(other.x - M);
         inv = grp == 0 ? 1.0f / (lsum * a_own + other.y * a_oth) : 1.0f / (other.y * a_oth + lsum * a_own);
-        if (qrow < n) {
-            __bf16* op = o + ((size_t)qrow * Hq + head) * DH + grp * 32 * HB;
+        __bf16* mine = reinterpret_cast<__bf16*>(xm + 4 * 2 * 32) + wave * 32 * out_row(32 * HB);
+        {
 #pragma unroll
             for (int b = 0; b < HB; ++b)
 #pragma unroll
@@ -743,23 +786,24 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
                         const float own = grp == 0 ? Oacc[b][4 * rg + e] : Oacc[HB + b][4 * rg + e];
                         ov[e] = (__bf16)((own * a_own + t[e] * a_oth) * inv);
                     }
-                    *reinterpret_cast<bf16x4*>(op + 32 * b + 8 * rg + 4 * h) = ov;
+                    *reinterpret_cast<bf16x4*>(mine + j * out_row(32 * HB) + 32 * b + 8 * rg + 4 * h) = ov;
                 }
         }
+        store_rows<32 * HB>(mine, lane, q0, n, o + (size_t)head * DH + grp * 32 * HB, (size_t)Hq * DH);
         return;
     }
-    if (qrow < n) {
-        __bf16* op = o + ((size_t)qrow * Hq + head) * DH;
+    // all tiles are read, nothing is in flight: every wave passes its rows through a piece of LDS of its own
+    __bf16* mine = reinterpret_cast<__bf16*>(fa_smem_raw) + wave * 32 * out_row(DH);
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+    for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int rg = 0; rg < 4; ++rg) {
-                bf16x4 ov;
+        for (int rg = 0; rg < 4; ++rg) {
+            bf16x4 ov;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) ov[e] = (__bf16)(Oacc[db][4 * rg + e] * inv);
-                *reinterpret_cast<bf16x4*>(op + 32 * db + 8 * rg + 4 * h) = ov;
-            }
-    }
+            for (int e = 0; e < 4; ++e) ov[e] = (__bf16)(Oacc[db][4 * rg + e] * inv);
+            *reinterpret_cast<bf16x4*>(mine + j * out_row(DH) + 32 * db + 8 * rg + 4 * h) = ov;
+        }
+    store_rows<DH>(mine, lane, q0, n, o + (size_t)head * DH, (size_t)Hq * DH);
 }
 
 template <int DH>
