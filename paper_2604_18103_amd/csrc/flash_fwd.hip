@@ -334,7 +334,7 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
                                                                 const int32_t* __restrict__ pos,
                                                                 __bf16* __restrict__ o, int n, int Hq,
                                                                 int Hkv, float scale_log2, int causal,
-                                                                int n_qtiles, FaMap mp,
+                                                                int row_base, int n_qtiles, FaMap mp,
                                                                 uint32_t* __restrict__ clear_words, int n_clear) {
     using SM = FaSmem<DH>;
     constexpr int KC = DH / 16;  // contraction chunks of Q K^T
@@ -359,7 +359,8 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
     __bf16* Vst = Kst + 2 * SM::STAGE_ELEMS;
     const int j = lane % 32, h = lane / 32;
     const int tg = lane / 16, ti = lane % 16;
-    const int q0 = qt * BM + (KG == 1 ? wave : wave & 3) * 32;
+    const int tile_row0 = (KG == 1 ? 0 : row_base) + qt * BM;  // this workgroup's first query row
+    const int q0 = tile_row0 + (KG == 1 ? wave : wave & 3) * 32;
     const int qrow = q0 + j;
     const int qrow_c = min(qrow, n - 1);
     const int pos_q = pos[qrow_c];
@@ -436,7 +437,7 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
     for (int r = 0; r < 16; ++r) Cneg[r] = 0.f;
     asm volatile("" : "+v"(Cneg));
 
-    const int kv_end = causal ? min(n, qt * BM + BM) : n;
+    const int kv_end = causal ? min(n, tile_row0 + BM) : n;
     const int all_tiles = (kv_end + kFaBN - 1) / kFaBN;
     // tile t of this wave is key tile t, or, with two key groups, key tile 2 t + grp
     const int n_tiles = KG == 1 ? all_tiles : (all_tiles - grp + 1) / 2;
@@ -602,7 +603,7 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
         // original positions sit in LDS (pos_blk); masking compares positions, not ranks.
         const bool diag = causal && key0 + kFaBN - 1 > q0;  // wave-uniform
         if (diag || key0 + kFaBN > n) {
-            const int kl0 = key0 - qt * BM;  // >= 0 whenever diag holds
+            const int kl0 = key0 - tile_row0;  // >= 0 whenever diag holds
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -677,7 +678,7 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
             dma_wait();
         }
     }
-    if (tid < BM) pos_blk[tid] = pos[min(qt * BM + tid, n - 1)];
+    if (tid < BM) pos_blk[tid] = pos[min(tile_row0 + tid, n - 1)];
     // The Q fragments have to be in registers before the loop: if their loads were still in flight at
     // loop entry, the first MFMAs of every tile would also wait for the staging loads (issued later,
     // returned in order). An empty asm that "uses" them pins the wait here.
@@ -837,24 +838,37 @@ dash_status init_flash_kernels() {
 // Two key groups (128 query rows and half of the serial key loop per workgroup) where the loop's length or the last round
 // of workgroups decides the time; one (256 rows) where the chip is full anyway, because either group of the split form
 // fetches its own K and V tiles and its rounds take 14 % longer.
-//  - causal: while the 128-row workgroups number at most two per compute unit: the long ones start first, the short ones
-//    fill up behind them. 28 heads of 128, us, one group / two: n = 177 13.6 / 11.5, 804 26.8 / 19.7, 2304 (504
-//    workgroups) 58.7 / 54.2, 2432 (532) 60.3 / 66.3; 16 heads of 64: 4096 (512) 64 / 48, 4 heads of 128: 16384 (512) 328 / 263.
+//  - causal: while the 128-row workgroups number at most two (head size 64: two and a half) per compute unit: the long ones
+//    start first, the short ones fill up behind them. 28 heads of 128, us, one group / two: n = 177 13.6 / 11.5, 804 26.8 /
+//    19.7, 2304 (504 workgroups) 56.4 / 51.6, 2400 (532) 56.0 / 59.2; 4 heads of 128: 16384 (512) 328 / 263; 16 heads of 64:
+//    4096 (512) 65 / 49, 5000 (640) 78 / 76.
 //  - otherwise all workgroups are equally long, so whole rounds are counted, a round of the split form being half as many
 //    tiles: 28 heads of 128: 1152 (252 workgroups of 128 rows) 31 / 25, 1500 (336) 41 / 56; 16 heads of 64: 4300 (272 of 256
-//    rows, 544 of 128) 137 / 122.
-static bool fa_two_key_groups(int n, int Hq, bool causal) {
+//    rows, 544 of 128) 137 / 122. The rows beyond the last whole 256-row tile may also run as a launch of their own in the
+//    split form, so that a few of them do not cost a round of
+//    all: 28 heads of 128: 2400 111 / 101; 32 of 128: 4100 298 / 270; 16 of 64: 4097 112 / 107, 8200 354 / 341.
+enum FaForm { FA_ONE = 0, FA_TWO = 1, FA_ONE_AND_TAIL = 2 };
+static FaForm fa_form(int n, int Hq, int head_dim, bool causal) {
     const int cu = compute_units();
+    auto rounds = [&](int64_t wgs) { return (double)((wgs + cu - 1) / cu); };
     const int64_t one = (int64_t)((n + kFaBM - 1) / kFaBM) * Hq, two = (int64_t)((n + kFaBM / 2 - 1) / (kFaBM / 2)) * Hq;
-    if (causal) return two <= 2 * cu;
-    return 0.57 * (double)((two + cu - 1) / cu) < (double)((one + cu - 1) / cu);
+    if (causal) return 2 * two <= (head_dim == 64 ? 5 : 4) * cu ? FA_TWO : FA_ONE;
+    const double t_one = rounds(one), t_two = 0.57 * rounds(two);
+    const int tail = n % kFaBM;
+    if (tail > 0 && n > kFaBM) {
+        // one active wave per key group (32 rows) takes about two thirds of a full workgroup's time
+        const double t_tail = rounds(one - Hq) + (tail <= 32 ? 0.4 : 0.57 * rounds(tail <= kFaBM / 2 ? Hq : 2 * Hq)) + 0.1;
+        if (t_tail < t_one && t_tail < t_two) return FA_ONE_AND_TAIL;
+    }
+    return t_two < t_one ? FA_TWO : FA_ONE;
 }
 
+// Query rows [row0, row1) against all keys (row0 = 0 with one key group).
 template <int DH, int KG>
 static dash_status launch_mfma(const dash_layer_params& p, const __bf16* q, const __bf16* k, const __bf16* v,
-                               const int32_t* pos, int n, __bf16* o, float scale_log2, uint32_t* clear_words, int n_clear,
-                               hipStream_t s) {
-    const int n_qtiles = (n + kFaBM / KG - 1) / (kFaBM / KG);
+                               const int32_t* pos, int n, int row0, int row1, __bf16* o, float scale_log2,
+                               uint32_t* clear_words, int n_clear, hipStream_t s) {
+    const int n_qtiles = (row1 - row0 + kFaBM / KG - 1) / (kFaBM / KG);
     const int Hq = p.n_q_heads, Hkv = p.n_kv_heads, group = Hq / Hkv;
     FaMap mp{0, 1, 1, n_qtiles * group};
     unsigned blocks = (unsigned)n_qtiles * Hq;
@@ -868,7 +882,7 @@ static dash_status launch_mfma(const dash_layer_params& p, const __bf16* q, cons
         blocks = 8u * (unsigned)(mp.items_per_g * mp.g_per_xcd);
     }
     hipLaunchKernelGGL((flash_fwd_mfma<DH, KG>), dim3(blocks), dim3(kFaThreads), FaSmem<DH>::bytes(KG), s, q, k, v, pos, o, n,
-                       Hq, Hkv, scale_log2, p.causal, n_qtiles, mp, clear_words, n_clear);
+                       Hq, Hkv, scale_log2, p.causal, row0, n_qtiles, mp, clear_words, n_clear);
     return launch_status();
 }
 
@@ -887,12 +901,16 @@ dash_status launch_flash_fwd(const dash_layer_params& p, const void* q, const vo
     if (init_flash_kernels() != DASH_OK || compute_units() <= 0) return DASH_ERR_HIP;
     const float scale_log2 = scale * 1.4426950408889634f;
     const __bf16 *bq = (const __bf16*)q, *bk = (const __bf16*)k, *bv = (const __bf16*)v;
-    const bool split = fa_two_key_groups(n, p.n_q_heads, p.causal != 0);
-    if (p.head_dim == 64)
-        return split ? launch_mfma<64, 2>(p, bq, bk, bv, active_idx, n, (__bf16*)o, scale_log2, clear_words, n_clear, s)
-                     : launch_mfma<64, 1>(p, bq, bk, bv, active_idx, n, (__bf16*)o, scale_log2, clear_words, n_clear, s);
-    return split ? launch_mfma<128, 2>(p, bq, bk, bv, active_idx, n, (__bf16*)o, scale_log2, clear_words, n_clear, s)
-                 : launch_mfma<128, 1>(p, bq, bk, bv, active_idx, n, (__bf16*)o, scale_log2, clear_words, n_clear, s);
+    const FaForm form = fa_form(n, p.n_q_heads, p.head_dim, p.causal != 0);
+    const int one_end = form == FA_TWO ? 0 : (form == FA_ONE ? n : n - n % kFaBM);  // rows of the one-group form
+    dash_status st = DASH_OK;
+    if (one_end > 0)
+        st = p.head_dim == 64 ? launch_mfma<64, 1>(p, bq, bk, bv, active_idx, n, 0, one_end, (__bf16*)o, scale_log2, clear_words, n_clear, s)
+                              : launch_mfma<128, 1>(p, bq, bk, bv, active_idx, n, 0, one_end, (__bf16*)o, scale_log2, clear_words, n_clear, s);
+    if (st != DASH_OK || one_end == n) return st;
+    if (one_end > 0) n_clear = 0;  // cleared by the first launch
+    return p.head_dim == 64 ? launch_mfma<64, 2>(p, bq, bk, bv, active_idx, n, one_end, n, (__bf16*)o, scale_log2, clear_words, n_clear, s)
+                            : launch_mfma<128, 2>(p, bq, bk, bv, active_idx, n, one_end, n, (__bf16*)o, scale_log2, clear_words, n_clear, s);
 }
 
 }  // namespace dash

@@ -38,8 +38,9 @@ def test_two_key_groups_at_tile_edges(n, dh):
         _run(n, 4, 2, dh, causal, seed=n + dh)
 
 
-@pytest.mark.parametrize("n,hq,hkv,dh,causal", [(4097, 16, 4, 64, True), (2433, 28, 4, 128, True), (1409, 28, 4, 128, False)])
+@pytest.mark.parametrize("n,hq,hkv,dh,causal", [(5377, 16, 4, 64, True), (2433, 28, 4, 128, True), (1409, 28, 4, 128, False),
+                                                (4097, 16, 4, 64, False), (4224, 16, 4, 64, False), (2400, 32, 8, 128, False)])
 def test_one_key_group_with_a_nearly_empty_last_tile(n, hq, hkv, dh, causal):
     """Lengths just past the split form's range whose last 256-row tile holds 1, 129 and 129 rows: waves beyond the end
-    do nothing."""
+    do nothing. Without a causal mask also lengths whose last 1, 128 and 96 rows run as a launch of their own."""
     _run(n, hq, hkv, dh, causal, seed=n, rows=np.array([0, 1, 31, 32, 255, 256, n // 2, n - 130, n - 2, n - 1]))
