@@ -334,8 +334,9 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
                                                                 const int32_t* __restrict__ pos,
                                                                 __bf16* __restrict__ o, int n, int Hq,
                                                                 int Hkv, float scale_log2, int causal,
-                                                                int row_base, int n_qtiles, FaMap mp,
-                                                                uint32_t* __restrict__ clear_words, int n_clear) {
+                                                                int n_qtiles, FaMap mp,
+                                                                uint32_t* __restrict__ clear_words, int n_clear,
+                                                                int row_base) {
     using SM = FaSmem<DH>;
     constexpr int KC = DH / 16;  // contraction chunks of Q K^T
     constexpr int DB = DH / 32;  // 32-wide output blocks of O^T
@@ -882,7 +883,7 @@ static dash_status launch_mfma(const dash_layer_params& p, const __bf16* q, cons
         blocks = 8u * (unsigned)(mp.items_per_g * mp.g_per_xcd);
     }
     hipLaunchKernelGGL((flash_fwd_mfma<DH, KG>), dim3(blocks), dim3(kFaThreads), FaSmem<DH>::bytes(KG), s, q, k, v, pos, o, n,
-                       Hq, Hkv, scale_log2, p.causal, row0, n_qtiles, mp, clear_words, n_clear);
+                       Hq, Hkv, scale_log2, p.causal, n_qtiles, mp, clear_words, n_clear, row0);
     return launch_status();
 }
 
