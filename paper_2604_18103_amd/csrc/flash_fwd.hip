@@ -256,7 +256,8 @@ constexpr int kFaBM = 256;  // query rows per workgroup
 // keys per tile: kFaBN = 64 (staging_addr.h)
 constexpr int kFaThreads = 512;
 constexpr float kMaskedScore = -1.0e30f;
-constexpr float kRowSumLimit = 1048576.0f;  // a lane's 32-key partial row sum above this moves the softmax reference
+// 2^20 as a float: a lane's 32-key partial row sum above this moves the softmax reference
+constexpr int kRowSumLimitBits = 0x49800000;
 
 // Work-item -> (query tile, head) map. Workgroups are handed to the 8 XCDs round-robin
 // (workgroup b runs on XCD b % 8) and each XCD has its own L2, so all workgroups of one XCD are given
@@ -311,6 +312,15 @@ struct FaSmem {
     __device__ static constexpr int v_swz(int row) { return fa_v_swz(row, DH); }
 };
 
+
+// Where the key loop lies in the code. The loop body is branches and short stretches between them, two waves per SIMD are
+// fetched from one instruction cache, and what a taken branch costs depends on where its target lies in a 32-byte fetch: the
+// same instructions shifted by 4 bytes at a time take from 0.98 to 1.10 times as long at head size 64 with one key group
+// (4097 to 12001 rows), up to 1.03 with two. So the loop starts at a stated distance from a 64-byte line (no-ops before
+// it), and so does what follows the rarely taken branch of the softmax (no-ops at its end). Steps of 4 bytes, measured; to be
+// measured again when the loop changes.
+constexpr int fa_loop_pad(int DH, int KG) { return KG == 2 ? (DH == 64 ? 8 : 2) : (DH == 64 ? 5 : 0); }
+constexpr int fa_branch_pad(int DH, int KG) { return DH == 64 && KG == 1 ? 3 : 4; }
 
 // A wave's 32 result rows of W elements go out through LDS (rows of W + 8 elements, written 8 bytes per lane as the
 // accumulators lie): a store instruction then covers whole rows instead of 8-byte pieces of 32 of them.
@@ -433,6 +443,7 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
     // It changes only when the reference moves; the empty asm keeps it a register block instead of 16
     // re-materialised moves per tile.
     float m = 0.f, lsum = 0.f;
+    int sum_limit = kRowSumLimitBits;  // wave-uniform; -1 (a NaN: no sum lies below it) while some row waits for a key that counts
     f32x16 Cneg;
 #pragma unroll
     for (int r = 0; r < 16; ++r) Cneg[r] = 0.f;
@@ -623,12 +634,12 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
         // Probabilities are taken against a reference m that is NOT the running maximum: any reference
         // gives the same O / sum, it only has to keep exp2 in range. The common tile therefore computes
         // no row maximum at all: it exponentiates S (already relative to m) and looks at the row sums;
-        // only if a sum is not a modest finite number (a score far above the reference), and always on
-        // the first tile, the reference moves to the true running maximum, what was accumulated is
+        // only if a sum is not a modest finite number (a score far above the reference), and always while a
+        // row of the wave has no reference yet, the reference moves to the true running maximum, what was accumulated is
         // rescaled, and the tile's probabilities are redone.
         if (KG == 1) prefetch_v(t);
         float psum = exp_pack(false, 0.f);
-        if (t == 0 || __any(!(psum < kRowSumLimit))) {
+        if (t == 0 || __any(!(psum < __builtin_bit_cast(float, sum_limit)))) {
             float c0 = fmaxf(S[0][0], S[1][0]), c1 = fmaxf(S[0][1], S[1][1]);
             float c2 = fmaxf(S[0][2], S[1][2]), c3 = fmaxf(S[0][3], S[1][3]);
 #pragma unroll
@@ -640,10 +651,14 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
             }
             float mx = fmaxf(fmaxf(c0, c1), fmaxf(c2, c3));  // tile maximum relative to m
             mx = fmaxf(mx, __shfl_xor(mx, 32));
-            // The first tile (key 0 is visible to every row, so mx is finite) sets the reference outright,
-            // nothing has been accumulated yet; later the reference only rises.
-            const float shift = t == 0 ? mx : fmaxf(mx, 0.f);
-            const float alpha = t == 0 ? 1.f : __builtin_amdgcn_exp2f(-shift);
+            // A row for which nothing has been accumulated takes the tile's maximum as its reference outright; later the
+            // reference only rises. A tile may hold no key that counts for a row (every score -inf, or masked): the row
+            // then keeps 0, adds nothing and waits for its next tile.
+            const bool first = t == 0 || lsum + __shfl_xor(lsum, 32) == 0.f;
+            const bool none = first && !(mx > 0.5f * kMaskedScore);
+            const float shift = none ? 0.f : (first ? mx : fmaxf(mx, 0.f));
+            const float alpha = first ? 1.f : __builtin_amdgcn_exp2f(-shift);
+            sum_limit = __builtin_amdgcn_readfirstlane(__any(none)) ? -1 : kRowSumLimitBits;
             m += shift;
 #pragma unroll
             for (int r = 0; r < 16; ++r) Cneg[r] = -m;
@@ -654,6 +669,7 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
 #pragma unroll
                 for (int r = 0; r < 16; ++r) Oacc[db][r] *= alpha;
             psum = exp_pack(true, shift);
+            asm volatile(".rept %0\n\ts_nop 0\n\t.endr" : : "n"(fa_branch_pad(DH, KG)));
         }
         lsum += psum;
     };
@@ -712,6 +728,7 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
     // before barrier t-1 - and waits for them before barrier t, the first reads of both following it. Group 1 requests
     // K(t+2) and V(t+1) after barrier t and waits for them before barrier t+1: K(t) and V(t-1) were last read before
     // barrier t. Two stages of each do for either group.
+    asm volatile(".p2align 6\n\t.rept %0\n\ts_nop 0\n\t.endr" : : "n"(fa_loop_pad(DH, KG)));
     if (KG == 2) {
         for (int t = 0; t <= n_rounds; ++t) {
             mfma_phase(t);
