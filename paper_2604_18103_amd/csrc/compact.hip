@@ -5,6 +5,8 @@
 // the kept counts of all earlier chunks (written by the decision kernel, one wave ballot each), so no
 // cross-workgroup waiting is needed; ranks inside the chunk come from ballot + popcount.
 #include "common.h"
+#include "lds_ops.h"
+#include "publish.h"
 #include "score_rows.h"
 
 namespace dash {
@@ -95,25 +97,31 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(
 // (c, y) takes its chunk's mask and the counts of all earlier chunks from the published words, then gathers its
 // columns of the kept rows as compact_kernel does. Nothing is computed twice and nothing waits for a kernel boundary.
 //
-// Published words: two 64-bit words per chunk, each valid on its own (a relaxed device-scope atomic store / load
-// of one word: no fences, no ordering between words needed):
-//   word 0 = kept mask bits 0..31 | kept count << 32 | READY      word 1 = kept mask bits 32..63 | READY
-// They must be zero when the kernel starts (the attention kernel of the same layer call clears them).
+// Published words: publish.h. They must be zero when the kernel starts (the attention kernel of the same layer call clears
+// them).
 //
 // TOPK: a publisher first shares its rows' scores as order-preserving keys (one 32-bit word per row; no key is 0, so a
 // word is its own READY flag), takes everybody's, and ranks its 64 rows by counting: row r is kept when fewer than K
 // candidates come before it (a greater key, or the same key in an earlier row - the order of the selection kernels). That
 // is n^2 comparisons spread over the publishers, n / 4 per thread, in place of a radix selection that one workgroup does
 // behind a launch of its own. Bound by latency: the norms, one exchange through the last-level cache, the count, the
-// gather. The publishers wait for one another, so they have to be resident together: they are the first
-// n / 64 <= kFusedTopkRows / 64 workgroups of the grid, a fraction of what the chip holds. (Figures: kFusedTopkRows.)
+// gather. (Figures: kFusedTopkRows.)
 //
-// Waiting is safe: workgroups are dispatched in the order of their linear index (x fastest), a waiter (c, y) only
-// waits for publishers (c', 0) with c' <= c, which have a smaller linear index, are therefore resident or done, and
-// never wait themselves. The wait is bounded all the same: if a word never arrives the workgroup gives up, gathers
-// nothing and the survivor count is written as -1.
+// Waiting. Workgroups are dispatched in the order of their linear index (x fastest), and the publishers (c, 0) are the first of
+// the grid.
+//  - NONE, THRESHOLD: a workgroup (c, y) waits for publishers (c', 0) with c' <= c only. They have a smaller linear index,
+//    are therefore resident or done, and publish without having waited.
+//  - TOPK: the publishers wait for one another, so they have to be resident together. They are at most
+//    kFusedTopkRows / 64 = 24 workgroups, a fraction of what the chip holds, but nothing reserves that room: beside
+//    kernels on other streams that fill the chip, the last of them may come late.
+// Every wait is bounded (kPubSpinLimit), and one that ends without its word fails the call: a publisher that gave up
+// publishes FAILED instead of a mask; whoever reads FAILED, or gives up itself, gathers nothing, sets the launch's own FAILED
+// word and then writes the survivor count -1. The count's writer is one thread of the last chunk's publisher: it writes 0
+// at the start, then looks at that word, and at the end exchanges the 0 for the count. So a workgroup that failed before the
+// look is seen, and one that fails after it leaves a -1 that the exchange does not replace. (Either side's first write is
+// acknowledged before its next step. The look is early, beside the norms, so that nothing waits for it: at the end,
+// after the count, it took 0.4 us of the call.)
 // ------------------------------------------------------------------------------------------------
-constexpr unsigned long long kPubReady = 1ull << 62;
 constexpr int kPubSpinLimit = 1 << 20;
 
 __device__ __forceinline__ unsigned long long wait_published(const unsigned long long* word, bool& bad) {
@@ -121,12 +129,10 @@ __device__ __forceinline__ unsigned long long wait_published(const unsigned long
     int spins = 0;
     while (!(v & kPubReady)) {
         __builtin_amdgcn_s_sleep(4);
-        if (++spins > kPubSpinLimit) {
-            bad = true;
-            break;
-        }
+        if (++spins > kPubSpinLimit) break;
         v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    if (pub_bad(v)) bad = true;
     return v;
 }
 
@@ -145,16 +151,26 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
     const int row = chunk * kChunkRows + lane;
     bool bad = false;
     unsigned long long mask;
+    unsigned long long* call_failed = published + 2 * gridDim.x;
+    // the thread that writes the survivor count, in a wave that publishes nothing
+    const bool counts = chunk == (int)gridDim.x - 1 && blockIdx.y == 0 && tid == kWave;
+    unsigned long long seen = 0;
+    if (counts) __hip_atomic_store(n_out, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (blockIdx.y == 0) {
         // publisher: scores, flags, the chunk's kept mask
         const float2 t = row_sums_256(partials, cols, fold, n, chunk * kChunkRows, red);
+        if (counts) {
+            dma_wait();  // the 0 is written
+            seen = __hip_atomic_load(call_failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
         bool keep = false;
         if (TOPK) {
             __shared__ __attribute__((aligned(16))) uint32_t keys[kFusedTopkRows];
             __shared__ int before[kCompactWaves][kChunkRows];
+            __shared__ int gave_up[kCompactWaves];
             const float sc = score_from_sums(t, score_kind);
             const uint32_t mine = order_key(sc);
-            uint32_t* words = reinterpret_cast<uint32_t*>(published + 2 * gridDim.x);
+            uint32_t* words = reinterpret_cast<uint32_t*>(call_failed + 1);
             if (wave == 0 && row < n) {
                 __hip_atomic_store(words + row, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 scores[row] = sc;
@@ -220,10 +236,15 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
                 }
             }
             before[wave][lane] = cnt_before;
+            const unsigned long long any_missing = __ballot(bad);
+            if (lane == 0) gave_up[wave] = any_missing != 0ull;
             __syncthreads();
             int rank = 0;
 #pragma unroll
-            for (int w = 0; w < kCompactWaves; ++w) rank += before[w][lane];
+            for (int w = 0; w < kCompactWaves; ++w) {
+                rank += before[w][lane];
+                bad = bad || gave_up[w] != 0;  // some key never came: the ranks mean nothing
+            }
             keep = row < n && (row_protected(row, n, n_first, n_last) || rank < k_cand);
             if (wave == 0 && row < n) halt[row] = keep ? 0 : 1;
         } else if (row < n) {  // every wave holds the sums of the chunk's rows (row = lane): every wave gets the same mask
@@ -237,11 +258,9 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
         }
         mask = __ballot(keep);
         if (tid == 0) {
-            const unsigned long long cnt = (unsigned long long)__popcll(mask);
-            __hip_atomic_store(published + 2 * chunk, (mask & 0xFFFFFFFFull) | (cnt << 32) | kPubReady, __ATOMIC_RELAXED,
+            __hip_atomic_store(published + 2 * chunk, pub_word0(mask, __popcll(mask), bad), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(published + 2 * chunk + 1, (mask >> 32) | kPubReady, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(published + 2 * chunk + 1, pub_word1(mask, bad), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     } else {
         // the chunk's mask from its publisher (every lane reads the same two words: one request per wave; one wave asks
@@ -252,12 +271,13 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
         }
         const unsigned long long w0 = wait_published(published + 2 * chunk, bad);
         const unsigned long long w1 = wait_published(published + 2 * chunk + 1, bad);
-        mask = (w0 & 0xFFFFFFFFull) | ((w1 & 0xFFFFFFFFull) << 32);
+        mask = pub_mask(w0, w1);
     }
     // exclusive offset of this chunk: kept counts of all earlier chunks (integer sum, order does not matter)
     int part = 0;
     for (int c = tid; c < chunk; c += kCompactThreads)
-        part += (int)((wait_published(published + 2 * c, bad) >> 32) & 0x7Full);
+        part += pub_count(wait_published(published + 2 * c, bad));
+    if (seen != 0) bad = true;
     part = wave_sum_int(part);
     const unsigned long long any_bad = __ballot(bad);
     if (lane == 0) {
@@ -275,11 +295,20 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
         base += wave_part[w];
         failed |= wave_bad[w];
     }
-    if (blockIdx.y == 0 && wave == 0) {
-        if (keep && !failed) new_idx[base + rank] = active_idx[row];
-        if (chunk == (int)gridDim.x - 1 && lane == 0) *n_out = failed ? -1 : base + cnt;
+    if (failed) {  // uniform: every thread read the same LDS words
+        if (tid == kWave) {
+            __hip_atomic_store(call_failed, kPubFailed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            dma_wait();
+            __hip_atomic_store(n_out, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        return;
     }
-    if (failed) return;  // uniform: every thread read the same LDS words
+    if (counts) {
+        int none = 0;
+        (void)__hip_atomic_compare_exchange_strong(n_out, &none, base + cnt, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (blockIdx.y == 0 && wave == 0 && keep) new_idx[base + rank] = active_idx[row];
     const int v0 = ((int)gridDim.y - 1 - (int)blockIdx.y) * vecs_per_split;
     const int v1 = min(row_vecs, v0 + vecs_per_split);
     constexpr int R = 4;
@@ -349,9 +378,9 @@ dash_status launch_compact(const uint8_t* halt, const int32_t* chunk_counts, con
     return launch_status();
 }
 
-// words of the one-launch kernel: two per chunk, and for TOPK a key per row
+// words of the one-launch kernel: two per chunk, FAILED of the launch, and for TOPK a key per row
 size_t published_bytes(int n, bool topk) {
-    return (size_t)((n + kChunkRows - 1) / kChunkRows) * 2 * sizeof(unsigned long long) + (topk ? (size_t)((n + 1) / 2) * 2 * sizeof(uint32_t) : 0);
+    return ((size_t)((n + kChunkRows - 1) / kChunkRows) * 2 + 1) * sizeof(unsigned long long) + (topk ? (size_t)((n + 1) / 2) * 2 * sizeof(uint32_t) : 0);
 }
 
 // Scores, decision and compaction in one launch (TOPK: n <= kFusedTopkRows). `published` (published_bytes, 8-byte aligned) must have been cleared on this stream before (launch_flash_fwd does it for the layer call).

@@ -1,0 +1,78 @@
+// Host-side check of the exchange between the workgroups of the one-launch score + decision + compaction kernel (test
+// infrastructure, CPU only; part of the same small library as staging_check.cpp). Steps the kernel's protocol with the words
+// that the kernel uses (publish.h).
+#include <vector>
+
+#include "publish.h"
+
+using namespace dash;
+
+extern "C" {
+
+// Steps the exchange of the one-launch TopK kernel over `chunks` chunks of 64 rows and `splits` column splits; chunk c keeps
+// c % 65 rows. late >= 0: that chunk's keys come only after every other publisher has given up waiting for them. Returns the
+// survivor count; gathered[c]: how many of chunk c's workgroups gathered rows.
+int dash_check_publish(int chunks, int splits, int late, int* gathered) {
+    std::vector<unsigned long long> words((size_t)chunks * 2, 0);
+    auto mask_of = [](int c) { return c % 65 == 64 ? ~0ull : (1ull << (c % 65)) - 1; };
+    for (int turn = 0; turn < 2; ++turn)  // the others first, then the late one, which finds every key
+        for (int c = 0; c < chunks; ++c) {
+            if ((c == late) != (turn == 1)) continue;
+            const bool missing = late >= 0 && c != late;
+            words[2 * c] |= pub_word0(mask_of(c), c % 65, missing);
+            words[2 * c + 1] |= pub_word1(mask_of(c), missing);
+        }
+    int n_out = 0;
+    bool call_failed = false;
+    for (int c = 0; c < chunks; ++c) {
+        gathered[c] = 0;
+        for (int y = 0; y < splits; ++y) {
+            // the publisher knows whether it gave up; the others ask for the last chunk's word first, then for their own
+            bool failed = y == 0 ? late >= 0 && c != late
+                                 : pub_bad(words[2 * (chunks - 1)]) || pub_bad(words[2 * c]) || pub_bad(words[2 * c + 1]);
+            int base = 0;
+            for (int e = 0; e < c; ++e) {
+                failed = failed || pub_bad(words[2 * e]);
+                base += pub_count(words[2 * e]);
+            }
+            if (failed) {
+                call_failed = true;
+            } else {
+                if (y > 0 && pub_mask(words[2 * c], words[2 * c + 1]) != mask_of(c)) return -100;
+                ++gathered[c];
+            }
+            if (c == chunks - 1 && y == 0) n_out = failed ? -1 : base + c % 65;
+        }
+    }
+    return call_failed ? -1 : n_out;
+}
+
+// A workgroup that gives up (sets the launch's FAILED word, then writes the count -1) beside the count's writer (writes
+// 0, looks at the word, then exchanges a 0 for the count, or writes -1 if it saw FAILED), in every order of their steps, after a
+// call that left any count. Returns the number of orders after which the count is not -1.
+int dash_check_publish_orders() {
+    int wrong = 0;
+    for (int pick = 0; pick < 32; ++pick) {  // bit i: step i of the five is the failing workgroup's
+        if (__builtin_popcount((unsigned)pick) != 2) continue;
+        for (int before : {-1, 0, 5}) {
+            unsigned long long word = 0;
+            int n_out = before, f = 0, w = 0;
+            bool seen = false;
+            for (int i = 0; i < 5; ++i) {
+                if ((pick >> i) & 1) {
+                    if (f++ == 0) word = kPubFailed;
+                    else n_out = -1;
+                    continue;
+                }
+                if (w == 0) n_out = 0;
+                if (w == 1) seen = word != 0;
+                if (w == 2 && (seen || n_out == 0)) n_out = seen ? -1 : 7;
+                ++w;
+            }
+            wrong += n_out != -1;
+        }
+    }
+    return wrong;
+}
+
+}  // extern "C"
