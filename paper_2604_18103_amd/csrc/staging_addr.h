@@ -157,11 +157,15 @@ DASH_HD int small_b_swz(int row, int BN) {
     return BN == 64 ? 2 * ((row / 2) % 2) + 4 * ((row / 8) % 2) : 2 * (row % 4) + 8 * ((row / 8) % 2);
 }
 DASH_HD int small_b_lchunk(int row, int lane, int BN) { return (lane % (BN / 8)) ^ small_b_swz(row, BN); }
-// Tile of workgroup b: column tiles in order, row tiles of a column next to each other, dealt to the XCDs (b % 8) as 8
-// contiguous stretches, so that the row tiles of a weight column are read through one L2. -1: padding, no tile.
-DASH_HD int small_index_of(int b, int tiles) {
-    const int seg = (tiles + 7) / 8, idx = (b % 8) * seg + b / 8;
-    return b / 8 < seg && idx < tiles ? idx : -1;
+// Tile (and K part) of workgroup b: the parts one after the other, in each the column tiles in order, row tiles of a column
+// next to each other; all of it dealt to the XCDs (b % 8) as 8 contiguous stretches, so that the row tiles of a weight column
+// are read through one L2 and no XCD gets more than an eighth of the workgroups. (Stretches of each part by itself, rounded up,
+// gave 33 workgroups to XCDs of 32 units where 84 tiles run in 3 parts, and the launch two rounds.) False: padding, no tile.
+DASH_HD bool small_work_of(int b, int tiles, int parts, int& tile, int& part) {
+    const int work = tiles * parts, seg = (work + 7) / 8, idx = (b % 8) * seg + b / 8;
+    part = parts == 1 ? 0 : idx / tiles;
+    tile = idx - part * tiles;
+    return b / 8 < seg && idx < work;
 }
 
 // Which form a product takes: the large tiles (gemm_plan) or one of four small-tile forms, whichever is expected to be
@@ -189,7 +193,7 @@ constexpr int kSmallSplitMinSteps = 6;  // K steps of a part, at least
 
 struct SmallPlan {
     int form;                              // index into kSmallForms, -1: the large tiles
-    int mt, nt, tiles, grid;               // grid = workgroups per part, padded to a multiple of 8
+    int mt, nt, tiles, grid;               // grid = workgroups of all parts, padded to a multiple of 8
     int parts, ksteps_per_part;            // parts >= 2: fp32 sums and a second pass
 };
 inline double sa_busy(int wgs, int cu) {  // 0 up to two thirds of the units busy, 1 from all of them on
@@ -256,7 +260,7 @@ inline SmallPlan small_plan(int M, int K, int N, int cu, bool norms, int head, b
             if (parts > 1) t += second_pass_us(parts, M, N);
             if (t < best_us) {
                 best_us = t;
-                best = SmallPlan{f, mt, nt, (int)tiles, 8 * (((int)tiles + 7) / 8), parts, per};
+                best = SmallPlan{f, mt, nt, (int)tiles, 8 * (((int)tiles * parts + 7) / 8), parts, per};
             }
         }
     }

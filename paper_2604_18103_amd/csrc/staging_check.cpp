@@ -5,6 +5,7 @@
 // the operand the lane is meant to fetch. A wrapped offset, a wrong clamp or a load outside the operand fails.
 #include <stdint.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "staging_addr.h"
@@ -152,22 +153,31 @@ void dash_gemm_launch_plan(int M, int K, int N, int cu, unsigned long long split
     out[5] = g.rest; out[6] = g.plain; out[7] = g.grid;
 }
 
+// The workgroups of a small-tile launch of `tiles` tiles in `parts` K parts: the most that one XCD gets, or -1 if some tile of
+// some part is not taken exactly once.
+int dash_small_deal(int tiles, int parts) {
+    std::vector<int> taken((size_t)tiles * parts, 0), xcd(8, 0);
+    for (int b = 0; b < 8 * ((tiles * parts + 7) / 8); ++b) {
+        int tile = -1, part = -1;
+        if (!small_work_of(b, tiles, parts, tile, part)) continue;
+        if (tile < 0 || tile >= tiles || part < 0 || part >= parts) return -1;
+        ++taken[(size_t)part * tiles + tile];
+        ++xcd[(size_t)(b % 8)];
+    }
+    for (const int t : taken)
+        if (t != 1) return -1;
+    return *std::max_element(xcd.begin(), xcd.end());
+}
+
 // Checks the small-tile product in form `form` on every shape: that the workgroups take every tile exactly once and that
 // every staging load of every K group fetches the clamped row and column its lane is meant to.
 int dash_check_small_staging(int M, int K, int N, int form, long long* n_loads) {
     Counter c;
     if (M <= 0 || K <= 0 || K % kGK != 0 || N <= 0 || N % 8 != 0 || form < 0 || form >= 4) return -1;
     const SmallForm& f = kSmallForms[form];
-    const int mt = (M + f.BM - 1) / f.BM, nt = (N + f.BN - 1) / f.BN, tiles = mt * nt, grid = 8 * ((tiles + 7) / 8);
+    const int mt = (M + f.BM - 1) / f.BM, nt = (N + f.BN - 1) / f.BN, tiles = mt * nt;
     const uint64_t a_bytes = (uint64_t)M * K * 2, b_bytes = (uint64_t)K * N * 2;
-    std::vector<int> taken((size_t)tiles, 0);
-    for (int b = 0; b < grid; ++b) {
-        const int idx = small_index_of(b, tiles);
-        if (idx >= tiles) c.fail(1);
-        else if (idx >= 0) ++taken[(size_t)idx];
-    }
-    for (int t = 0; t < tiles; ++t)
-        if (taken[(size_t)t] != 1) c.fail(2);
+    if (dash_small_deal(tiles, 1) < 0) c.fail(2);
     std::vector<char> a_seen((size_t)f.BM * 8, 0), b_seen((size_t)kGK * (f.BN / 8), 0);
     for (int tm = 0; tm < mt; ++tm)
         for (int tn = 0; tn < nt; ++tn) {

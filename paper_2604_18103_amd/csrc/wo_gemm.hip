@@ -564,8 +564,8 @@ template <int EPI, int BM, int BN, int KW, int NS>
 __global__ __launch_bounds__(KW * kSWaves * kWave, KW == 4 ? 4 : 2) void gemm_small_kernel(const __bf16* __restrict__ A, const __bf16* __restrict__ B,
                                                                   int M, int K, int N, const __bf16* __restrict__ x,
                                                                   __bf16* __restrict__ out, float* __restrict__ partials,
-                                                                  float* __restrict__ split_sums, int mt, int tiles, int ksteps,
-                                                                  int ksteps_per_split, QkvOut qkv) {
+                                                                  float* __restrict__ split_sums, int mt, int tiles, int parts,
+                                                                  int ksteps, int ksteps_per_split, QkvOut qkv) {
     constexpr int kThreads = KW * kSWaves * kWave;
     constexpr int RB = BM / 32, CB = BN / 32;  // 16-row and 16-column blocks of a wave
     constexpr int kAElems = BM * kGK, kStageElems = (BM + BN) * kGK;
@@ -577,11 +577,11 @@ __global__ __launch_bounds__(KW * kSWaves * kWave, KW == 4 ? 4 : 2) void gemm_sm
     const int kg = KW == 1 ? 0 : wave_all / kSWaves, wave = wave_all % kSWaves;  // K group, wave inside it
     const int wm = wave / 2, wn = wave % 2;
     __bf16* smem = reinterpret_cast<__bf16*>(small_smem_raw) + kg * NS * kStageElems;  // this group's stages
-    const int idx = small_index_of((int)blockIdx.x, tiles);
-    if (idx < 0) return;  // padding: the whole workgroup leaves
+    int idx, part;
+    if (!small_work_of((int)blockIdx.x, tiles, EPI == EPI_SPLITK ? parts : 1, idx, part)) return;  // padding: the whole workgroup
     const int tile_m = idx % mt, tile_n = idx / mt;
     const int m0 = tile_m * BM, n0 = tile_n * BN;
-    const int ks0 = EPI == EPI_SPLITK ? (int)blockIdx.y * ksteps_per_split : 0;
+    const int ks0 = EPI == EPI_SPLITK ? part * ksteps_per_split : 0;
     const int n_ksteps = EPI == EPI_SPLITK ? min(ksteps_per_split, ksteps - ks0) : ksteps;
     const int n_rounds = (n_ksteps + KW - 1) / KW, n_mine = (n_ksteps - kg + KW - 1) / KW;  // group kg: steps kg, kg + KW, ...
 
@@ -764,7 +764,7 @@ __global__ __launch_bounds__(KW * kSWaves * kWave, KW == 4 ? 4 : 2) void gemm_sm
                     }
                 } else if (EPI == EPI_SPLITK) {
                     if (ok) {
-                        float* dst = split_sums + ((size_t)blockIdx.y * M + gm) * N + gn;
+                        float* dst = split_sums + ((size_t)part * M + gm) * N + gn;
                         *reinterpret_cast<f32x4*>(dst) = f32x4{dv[0], dv[1], dv[2], dv[3]};
                         *reinterpret_cast<f32x4*>(dst + 4) = f32x4{dv[4], dv[5], dv[6], dv[7]};
                     }
@@ -1154,9 +1154,9 @@ struct GemmArgs {
 template <int EPI, int F>
 static void launch_small_form(const SmallPlan& g, const GemmArgs& a, hipStream_t s) {
     constexpr SmallForm f = kSmallForms[F];
-    hipLaunchKernelGGL((gemm_small_kernel<EPI, f.BM, f.BN, f.KW, f.NS>), dim3(g.grid, g.parts), dim3(f.KW * kSWaves * kWave),
+    hipLaunchKernelGGL((gemm_small_kernel<EPI, f.BM, f.BN, f.KW, f.NS>), dim3(g.grid), dim3(f.KW * kSWaves * kWave),
                        small_smem_bytes(f.BM, f.BN, f.KW, f.NS), s, a.A, a.B, a.M, a.K, a.N, a.x, a.out, a.partials,
-                       a.split_sums, g.mt, g.tiles, a.K / kGK, g.ksteps_per_part, a.qkv);
+                       a.split_sums, g.mt, g.tiles, g.parts, a.K / kGK, g.ksteps_per_part, a.qkv);
 }
 
 // Adds the K parts and applies the epilogue.

@@ -74,3 +74,16 @@ def test_choice_of_a_form():
         if form >= 0:
             assert parts >= 1 and (parts - 1) * per < K // 64 <= parts * per
             assert parts == 1 or parts * M * N * 4 <= scratch
+
+
+def test_no_xcd_gets_more_than_an_eighth():
+    """A launch in K parts is planned to fit the units in one round; with workgroup b on XCD b % 8, that holds only if no
+    XCD gets more workgroups than it has units."""
+    lib = _lib()
+    lib.dash_small_deal.argtypes = [ctypes.c_int] * 2
+    lib.dash_small_deal.restype = ctypes.c_int
+    for tiles in range(1, 257):
+        for parts in range(1, 256 // tiles + 1):
+            assert lib.dash_small_deal(tiles, parts) == (tiles * parts + 7) // 8, (tiles, parts)
+    for tiles in (300, 476, 512, 1000, 2047):
+        assert lib.dash_small_deal(tiles, 1) == (tiles + 7) // 8
