@@ -168,19 +168,31 @@ DASH_HD bool small_work_of(int b, int tiles, int parts, int& tile, int& part) {
     return b / 8 < seg && idx < work;
 }
 
-// Which form a product takes: the large tiles (gemm_plan) or one of four small-tile forms, whichever is expected to be
-// faster. The expectation is a count of rounds over the compute units times the K steps times what one step was measured
-// to take, plus what a launch costs (us, 256 compute units at their usual clock under matrix work; the forms differ by
-// 10 to 300 %, so the figures only have to be roughly right):
-//   small form       KW NS  per unit  step alone, step of a full unit
-//   64 x  64          2  3     1        0.205
-//   64 x 128          2  3     1        0.31
-//  128 x 128          2  2     1        0.50
-//  128 x 128          1  2     2        0.64,  0.875 (two workgroups)
+// Which form a product takes: the large tiles (gemm_plan) or one of four small-tile forms. Small tiles are for products of few
+// rows (at most two large row tiles), and for others while the large tiles would occupy at most half of the units (their
+// alternative is then K parts and a second pass). From there on they save nothing worth a second rule: of 300 products
+// measured beyond that line, small tiles were up to 1.3 times as slow where they had been chosen, and never more than 8 %
+// faster. Otherwise the form expected to be fastest is taken. (With few rows of a wide product the large form may also
+// cut its left-over half tiles along K, which large_tiles_us leaves out: at 257 to 384 rows of 3584 x 37888 that estimate would
+// turn to the large tiles, which measured 3 to 4 % slower.) The
+// expectation is a count of rounds over the compute units times the K steps times what one step was measured to take, plus
+// what a launch costs (us, 256 compute units at their usual clock under matrix work; the forms differ by 10 to 300 %, so
+// the figures only have to be roughly right):
+//   small form       KW NS  per unit  step alone, step of a full unit   (weight from memory, not from the last-level cache)
+//   64 x  64          2  3     1        0.205                             0.23
+//   64 x 128          2  3     1        0.31                              0.35
+//  128 x 128          2  2     1        0.50                              0.70
+//  128 x 128          1  2     2        0.64,  0.875 (two workgroups)     0.80, 0.95
 //   large tile 1.35 (units two thirds busy or less) to 1.66 (all busy), half tile 0.65 to 0.98
 //   a second pass over K parts: 4 + 8 bytes per partial sum at 8 TB/s; several rounds of small tiles: a factor 1.3 (the L2)
-// Measured, large tiles / this choice, us, K = N = 3584: 64 rows 20.3 / 12, 177 25.9 / 15.5, 512 36.9 / 22.0, 804 42.8 / 32.6,
-// 1200 49.3 / 43.6, 2120 71.8 / 53.2, 3000 80 / 80 (large); K = N = 512: 333 rows 14.9 / 4.8, 2120 19.2 / 6.7.
+// The launcher cannot know where the weight is, and the figures taken are the cached ones: with those of the last column the
+// choice gains 1 % on weights from memory and loses 1 % on cached ones.
+// Measured over 916 products (17 to 12001 rows, K 512 to 4096, N 512 to 6144; each repeated on one weight, and the shorter ones
+// on weights from memory): below the line 0.62 and 0.64 times the large tiles' time on average; at worst 1.09 times on cached
+// weights and, at K = 4096 on weights from memory, 1.18. (Beyond those ranges: five K steps, 2201 x 320 x 3584, 14 / 18; a column
+// tile for 8 columns, 6600 x 3584 x 520, 50 / 66.) Feed-forward of 17 and 63 rows, 3584 x 18944: 133 / 103, 133 / 113. Large tiles / this choice, us, K = N = 3584 (with a row norm's launch,
+// about 5), cached and from memory: 63 rows 24.6 / 14.9 and 25.1 / 17.7, 511 40 / 28 and 41 / 35, 901 48 / 38 and 48 / 46, 1401
+// 58 / 49.5 and 58 / 58.6, 2201 75 / 60 and 75 / 65; from 2305 on large.
 struct SmallForm {
     int BM, BN, KW, NS, per_cu;
     double step_us, full_us;
@@ -239,8 +251,9 @@ inline int rest_parts(const GemmPlan& g, int cu, size_t scratch_bytes) {
 inline SmallPlan small_plan(int M, int K, int N, int cu, bool norms, int head, bool scratch, size_t scratch_bytes, double large_us) {
     SmallPlan best{};
     best.form = -1;
-    if (cu <= 0 || !scratch) return best;
-    double best_us = 0.95 * large_us;
+    const long long large_tiles = (long long)((M + kGM - 1) / kGM) * ((N + kGN - 1) / kGN);
+    if (cu <= 0 || !scratch || (M > 2 * kGM && 2 * large_tiles > cu)) return best;
+    double best_us = 0.95 * large_us - 0.5;  // so close, the large tiles were the faster ones (few K steps)
     const int ksteps = K / kGK;
     for (int f = 0; f < 4; ++f) {
         const SmallForm& s = kSmallForms[f];

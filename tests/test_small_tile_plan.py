@@ -87,3 +87,19 @@ def test_no_xcd_gets_more_than_an_eighth():
             assert lib.dash_small_deal(tiles, parts) == (tiles * parts + 7) // 8, (tiles, parts)
     for tiles in (300, 476, 512, 1000, 2047):
         assert lib.dash_small_deal(tiles, 1) == (tiles + 7) // 8
+
+
+def test_small_tiles_only_for_products_of_few_large_tiles():
+    """Products of more than two large row tiles whose large tiles occupy more than half of the units keep them: several
+    rounds of small tiles were up to 1.3 times as slow."""
+    lib = _lib()
+    out = (ctypes.c_int * 4)()
+    rng = np.random.default_rng(11)
+    shapes = [(513, 3584, 18944), (4700, 320, 3584), (8001, 320, 2112), (6600, 3584, 2080), (12001, 512, 6144)]
+    shapes += [(int(rng.integers(1, 20000)), 64 * int(rng.integers(1, 300)), 8 * int(rng.integers(1, 5000))) for _ in range(400)]
+    for M, K, N in shapes:
+        lib.dash_small_plan(M, K, N, 256, 1, 1 << 30, out)
+        if M > 512 and 2 * (-(-M // 256)) * (-(-N // 256)) > 256:
+            assert out[0] == -1, (M, K, N, tuple(out))
+    lib.dash_small_plan(17, 3584, 37888, 256, 0, 1 << 30, out)
+    assert out[0] >= 0
