@@ -252,8 +252,7 @@ __global__ __launch_bounds__(kF32Waves * kWave) void flash_fwd_f32(
 // MFMA 32x32x16 operand layout (lane l, i = l%32, h = l/32): A holds row i, k-slots 8h..8h+7;
 // B holds column i, k-slots 8h..8h+7; D register r holds row 8*(r/4) + 4h + r%4 of column i.
 // ------------------------------------------------------------------------------------------------
-constexpr int kFaBM = 256;  // query rows per workgroup
-// keys per tile: kFaBN = 64 (staging_addr.h)
+// query rows per workgroup: kFaBM = 256, keys per tile: kFaBN = 64 (staging_addr.h)
 constexpr int kFaThreads = 512;
 constexpr float kMaskedScore = -1.0e30f;
 // 2^20 as a float: a lane's 32-key partial row sum above this moves the softmax reference
@@ -853,34 +852,6 @@ dash_status init_flash_kernels() {
     return err == hipSuccess ? DASH_OK : DASH_ERR_HIP;
 }
 
-// Two key groups (128 query rows and half of the serial key loop per workgroup) where the loop's length or the last round
-// of workgroups decides the time; one (256 rows) where the chip is full anyway, because either group of the split form
-// fetches its own K and V tiles and its rounds take 14 % longer.
-//  - causal: while the 128-row workgroups number at most two (head size 64: two and a half) per compute unit: the long ones
-//    start first, the short ones fill up behind them. 28 heads of 128, us, one group / two: n = 177 13.6 / 11.5, 804 26.8 /
-//    19.7, 2304 (504 workgroups) 56.4 / 51.6, 2400 (532) 56.0 / 59.2; 4 heads of 128: 16384 (512) 328 / 263; 16 heads of 64:
-//    4096 (512) 65 / 49, 5000 (640) 78 / 76.
-//  - otherwise all workgroups are equally long, so whole rounds are counted, a round of the split form being half as many
-//    tiles: 28 heads of 128: 1152 (252 workgroups of 128 rows) 31 / 25, 1500 (336) 41 / 56; 16 heads of 64: 4300 (272 of 256
-//    rows, 544 of 128) 137 / 122. The rows beyond the last whole 256-row tile may also run as a launch of their own in the
-//    split form, so that a few of them do not cost a round of
-//    all: 28 heads of 128: 2400 111 / 101; 32 of 128: 4100 298 / 270; 16 of 64: 4097 112 / 107, 8200 354 / 341.
-enum FaForm { FA_ONE = 0, FA_TWO = 1, FA_ONE_AND_TAIL = 2 };
-static FaForm fa_form(int n, int Hq, int head_dim, bool causal) {
-    const int cu = compute_units();
-    auto rounds = [&](int64_t wgs) { return (double)((wgs + cu - 1) / cu); };
-    const int64_t one = (int64_t)((n + kFaBM - 1) / kFaBM) * Hq, two = (int64_t)((n + kFaBM / 2 - 1) / (kFaBM / 2)) * Hq;
-    if (causal) return 2 * two <= (head_dim == 64 ? 5 : 4) * cu ? FA_TWO : FA_ONE;
-    const double t_one = rounds(one), t_two = 0.57 * rounds(two);
-    const int tail = n % kFaBM;
-    if (tail > 0 && n > kFaBM) {
-        // one active wave per key group (32 rows) takes about two thirds of a full workgroup's time
-        const double t_tail = rounds(one - Hq) + (tail <= 32 ? 0.4 : 0.57 * rounds(tail <= kFaBM / 2 ? Hq : 2 * Hq)) + 0.1;
-        if (t_tail < t_one && t_tail < t_two) return FA_ONE_AND_TAIL;
-    }
-    return t_two < t_one ? FA_TWO : FA_ONE;
-}
-
 // Query rows [row0, row1) against all keys (row0 = 0 with one key group).
 template <int DH, int KG>
 static dash_status launch_mfma(const dash_layer_params& p, const __bf16* q, const __bf16* k, const __bf16* v,
@@ -919,7 +890,7 @@ dash_status launch_flash_fwd(const dash_layer_params& p, const void* q, const vo
     if (init_flash_kernels() != DASH_OK || compute_units() <= 0) return DASH_ERR_HIP;
     const float scale_log2 = scale * 1.4426950408889634f;
     const __bf16 *bq = (const __bf16*)q, *bk = (const __bf16*)k, *bv = (const __bf16*)v;
-    const FaForm form = fa_form(n, p.n_q_heads, p.head_dim, p.causal != 0);
+    const FaForm form = fa_form(n, p.n_q_heads, p.head_dim, p.causal != 0, compute_units());  // staging_addr.h
     const int one_end = form == FA_TWO ? 0 : (form == FA_ONE ? n : n - n % kFaBM);  // rows of the one-group form
     dash_status st = DASH_OK;
     if (one_end > 0)

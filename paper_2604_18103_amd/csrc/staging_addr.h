@@ -286,7 +286,8 @@ inline SmallPlan small_plan(int M, int K, int N, int cu, bool norms, int head, b
 // waves of a group fetch a tile; a load's address is a uniform tile base plus a 32-bit lane offset that is the
 // same for every whole tile; in the last, partly filled tile rows beyond the end are clamped to the last row.
 // ------------------------------------------------------------------------------------------------
-constexpr int kFaBN = 64;  // keys per tile
+constexpr int kFaBM = 256;  // query rows per workgroup (two key groups: 128)
+constexpr int kFaBN = 64;   // keys per tile
 
 DASH_HD constexpr int fa_cpr(int DH) { return DH / 8; }            // 16-byte chunks per row
 DASH_HD constexpr int fa_rp(int DH) { return 256 / (DH * 2); }     // rows per 256 bytes of LDS
@@ -312,5 +313,35 @@ DASH_HD uint32_t fa_dma_voff_tail(uint32_t voff, int r, int rows_left, int Hkv, 
     return voff - (uint32_t)beyond * ((uint32_t)Hkv * DH * 2u);
 }
 DASH_HD size_t fa_tile_bytes(int Hkv, int DH) { return (size_t)kFaBN * Hkv * DH * 2; }
+
+// Two key groups (128 query rows and half of the serial key loop per workgroup) where the loop's length or the last round
+// of workgroups decides the time; one (256 rows) where the chip is full anyway, because either group of the split form
+// fetches its own K and V tiles and its rounds take 14 % longer.
+//  - causal: while the 128-row workgroups number at most two (head size 64: two and a half) per compute unit: the long ones
+//    start first, the short ones fill up behind them. 28 heads of 128, us, one group / two: n = 177 13.6 / 11.5, 804 26.8 /
+//    19.7, 2304 (504 workgroups) 56.4 / 51.6, 2400 (532) 56.0 / 59.2; 4 heads of 128: 16384 (512) 328 / 263; 16 heads of 64:
+//    4096 (512) 65 / 49, 5000 (640) 78 / 76.
+//  - otherwise all workgroups are equally long, so whole rounds are counted, a round of the split form being half as many
+//    tiles: 28 heads of 128: 1152 (252 workgroups of 128 rows) 31 / 25, 1500 (336) 41 / 56; 16 heads of 64: 4300 (272 of 256
+//    rows, 544 of 128) 137 / 122. A form whose count is less than 6 % (head size 64: 4 %) lower is not the faster one,
+//    its last round being as likely a nearly empty one: 28 heads of 128, counts 4 / 3.99, 8001 758 / 823; 3 / 2.85, 5500 384 /
+//    406; 16 heads of 64, 3 / 2.85, 9700 433 / 418; 4 / 3.99, 14001 1 / 1.03. The rows beyond the
+//    last whole 256-row tile may also run as a launch of their own in the split form, so that a few of them do not cost a
+//    round of all (4 % lower will do: the whole tiles keep their form): 28 heads of 128: 2400 111 / 101, 14001 7 / 6.67
+//    rounds, 0.967 times; 32 of 128: 4100 298 / 270; 16 of 64: 4097 112 / 107, 8200 354 / 341.
+enum FaForm { FA_ONE = 0, FA_TWO = 1, FA_ONE_AND_TAIL = 2 };
+inline FaForm fa_form(int n, int Hq, int head_dim, bool causal, int cu) {
+    auto rounds = [&](long long wgs) { return (double)((wgs + cu - 1) / cu); };
+    const long long one = (long long)((n + kFaBM - 1) / kFaBM) * Hq, two = (long long)((n + kFaBM / 2 - 1) / (kFaBM / 2)) * Hq;
+    if (causal) return 2 * two <= (head_dim == 64 ? 5 : 4) * cu ? FA_TWO : FA_ONE;
+    const double t_one = rounds(one), t_two = 0.57 * rounds(two);
+    const int tail = n % kFaBM;
+    if (tail > 0 && n > kFaBM) {
+        // one active wave per key group (32 rows) takes about two thirds of a full workgroup's time
+        const double t_tail = rounds(one - Hq) + (tail <= 32 ? 0.4 : 0.57 * rounds(tail <= kFaBM / 2 ? Hq : 2 * Hq)) + 0.1;
+        if (t_tail < 0.96 * t_one && t_tail < t_two) return FA_ONE_AND_TAIL;
+    }
+    return t_two < (head_dim == 64 ? 0.96 : 0.94) * t_one ? FA_TWO : FA_ONE;
+}
 
 }  // namespace dash

@@ -229,6 +229,9 @@ void dash_small_plan(int M, int K, int N, int cu, int norms, unsigned long long 
     out[0] = p.form; out[1] = p.tiles; out[2] = p.parts; out[3] = p.ksteps_per_part;
 }
 
+// The form attention takes: 0 one key group, 1 two, 2 one with the rows beyond the last whole tile as a launch of their own.
+int dash_fa_form(int n, int Hq, int head_dim, int causal, int cu) { return (int)fa_form(n, Hq, head_dim, causal != 0, cu); }
+
 // Checks every K and V staging load of the attention launch over n rows (K, V: [n][Hkv][DH] bf16): for each
 // query tile of 256 rows, the tiles of 64 keys it fetches. Returns 0 when all loads are right.
 int dash_check_flash_staging(int n, int Hkv, int DH, int causal, long long* n_loads) {
