@@ -116,13 +116,13 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(
 //    kernels on other streams that fill the chip, the last of them may come late.
 // Every wait is bounded (kPubSpinLimit), and one that ends without its word fails the call: a publisher that gave up
 // publishes FAILED instead of a mask; whoever reads FAILED, or gives up itself, gathers nothing, sets the launch's own FAILED
-// word and then writes the survivor count -1. The count's writer is one thread of the last chunk's publisher: it writes 0
-// at the start, then looks at that word, and at the end exchanges the 0 for the count. So a workgroup that failed before the
-// look is seen, and one that fails after it leaves a -1 that the exchange does not replace. (Either side's first write is
-// acknowledged before its next step. The look is early, beside the norms, so that nothing waits for it: at the end,
-// after the count, it took 0.4 us of the call.)
+// word and then writes the survivor count -1. The count is 0 when the kernel starts (cleared with the words), and its writer,
+// one thread of the last chunk's publisher, looks at that word early and at the end exchanges the 0 for the count. So a
+// workgroup that failed before the look is seen, and one that fails after it leaves a -1 that the exchange does not replace,
+// or replaces the count. (Nothing waits for the early look; one after the count took 0.4 us of the call.)
 // ------------------------------------------------------------------------------------------------
 constexpr int kPubSpinLimit = 1 << 20;
+constexpr int kKeyMissing = 1 << 20;  // in place of a count of keys
 
 __device__ __forceinline__ unsigned long long wait_published(const unsigned long long* word, bool& bad) {
     unsigned long long v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -155,19 +155,14 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
     // the thread that writes the survivor count, in a wave that publishes nothing
     const bool counts = chunk == (int)gridDim.x - 1 && blockIdx.y == 0 && tid == kWave;
     unsigned long long seen = 0;
-    if (counts) __hip_atomic_store(n_out, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (blockIdx.y == 0) {
         // publisher: scores, flags, the chunk's kept mask
         const float2 t = row_sums_256(partials, cols, fold, n, chunk * kChunkRows, red);
-        if (counts) {
-            dma_wait();  // the 0 is written
-            seen = __hip_atomic_load(call_failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        if (counts) seen = __hip_atomic_load(call_failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         bool keep = false;
         if (TOPK) {
             __shared__ __attribute__((aligned(16))) uint32_t keys[kFusedTopkRows];
             __shared__ int before[kCompactWaves][kChunkRows];
-            __shared__ int gave_up[kCompactWaves];
             const float sc = score_from_sums(t, score_kind);
             const uint32_t mine = order_key(sc);
             uint32_t* words = reinterpret_cast<uint32_t*>(call_failed + 1);
@@ -235,16 +230,12 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
                                       (int)(kv[e].z == mine && 4 * e + 2 < lane) + (int)(kv[e].w == mine && 4 * e + 3 < lane);
                 }
             }
-            before[wave][lane] = cnt_before;
-            const unsigned long long any_missing = __ballot(bad);
-            if (lane == 0) gave_up[wave] = any_missing != 0ull;
+            before[wave][lane] = bad ? kKeyMissing : cnt_before;
             __syncthreads();
             int rank = 0;
 #pragma unroll
-            for (int w = 0; w < kCompactWaves; ++w) {
-                rank += before[w][lane];
-                bad = bad || gave_up[w] != 0;  // some key never came: the ranks mean nothing
-            }
+            for (int w = 0; w < kCompactWaves; ++w) rank += before[w][lane];
+            bad = __any(rank >= kKeyMissing);  // some thread's key never came: the ranks mean nothing
             keep = row < n && (row_protected(row, n, n_first, n_last) || rank < k_cand);
             if (wave == 0 && row < n) halt[row] = keep ? 0 : 1;
         } else if (row < n) {  // every wave holds the sums of the chunk's rows (row = lane): every wave gets the same mask
@@ -304,8 +295,8 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
         return;
     }
     if (counts) {
-        int none = 0;
-        (void)__hip_atomic_compare_exchange_strong(n_out, &none, base + cnt, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+        int cleared = 0;
+        (void)__hip_atomic_compare_exchange_strong(n_out, &cleared, base + cnt, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                    __HIP_MEMORY_SCOPE_AGENT);
     }
     if (blockIdx.y == 0 && wave == 0 && keep) new_idx[base + rank] = active_idx[row];
@@ -383,7 +374,7 @@ size_t published_bytes(int n, bool topk) {
     return ((size_t)((n + kChunkRows - 1) / kChunkRows) * 2 + 1) * sizeof(unsigned long long) + (topk ? (size_t)((n + 1) / 2) * 2 * sizeof(uint32_t) : 0);
 }
 
-// Scores, decision and compaction in one launch (TOPK: n <= kFusedTopkRows). `published` (published_bytes, 8-byte aligned) must have been cleared on this stream before (launch_flash_fwd does it for the layer call).
+// Scores, decision and compaction in one launch (TOPK: n <= kFusedTopkRows). `published` (published_bytes, 8-byte aligned) and the count must have been cleared on this stream before (launch_flash_fwd does it for the layer call).
 dash_status launch_score_decide_compact(const dash_layer_params& p, const NormSums& sums, int n, float* scores, uint8_t* halt, void* published, const int32_t* active_idx,
                                         const void* x_next, int row_bytes, void* x_compact, int32_t* new_active_idx,
                                         int32_t* n_active_out, hipStream_t s) {

@@ -42,13 +42,16 @@ template <int DH>
 __global__ __launch_bounds__(kF32Waves * kWave) void flash_fwd_f32(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
     const int32_t* __restrict__ pos, float* __restrict__ o, int n, int Hq, int Hkv, float scale, int causal, int n_qtiles,
-    uint32_t* __restrict__ clear_words, int n_clear) {
+    uint32_t* __restrict__ clear_words, int n_clear, int32_t* __restrict__ clear_count) {
     constexpr int KC = DH / 16, HF = DH / 64, OSTR = DH + 4;
     __shared__ float part_o[kF32Waves][16][OSTR];
     __shared__ float part_m[kF32Waves][16], part_l[kF32Waves][16];
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     if (blockIdx.x == 0)  // scratch of the kernels that follow in the layer call
-        for (int c = tid; c < n_clear; c += kF32Waves * kWave) clear_words[c] = 0u;
+        for (int c = tid; c <= n_clear; c += kF32Waves * kWave) {
+            if (c < n_clear) clear_words[c] = 0u;
+            else if (clear_count) *clear_count = 0;
+        }
     const int qt = n_qtiles - 1 - (int)blockIdx.x / Hq, head = (int)blockIdx.x % Hq;  // longest rows first
     const int kvh = head / (Hq / Hkv);
     const int i = lane % 16, g = lane / 16;
@@ -318,7 +321,7 @@ struct FaSmem {
 // (4097 to 12001 rows), up to 1.03 with two. So the loop starts at a stated distance from a 64-byte line (no-ops before
 // it), and so does what follows the rarely taken branch of the softmax (no-ops at its end). Steps of 4 bytes, measured; to be
 // measured again when the loop changes.
-constexpr int fa_loop_pad(int DH, int KG) { return KG == 2 ? (DH == 64 ? 8 : 2) : (DH == 64 ? 5 : 0); }
+constexpr int fa_loop_pad(int DH, int KG) { return KG == 2 ? (DH == 64 ? 10 : 4) : (DH == 64 ? 6 : 1); }
 constexpr int fa_branch_pad(int DH, int KG) { return DH == 64 && KG == 1 ? 3 : 4; }
 
 // A wave's 32 result rows of W elements go out through LDS (rows of W + 8 elements, written 8 bytes per lane as the
@@ -345,7 +348,7 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
                                                                 int Hkv, float scale_log2, int causal,
                                                                 int n_qtiles, FaMap mp,
                                                                 uint32_t* __restrict__ clear_words, int n_clear,
-                                                                int row_base) {
+                                                                int row_base, int32_t* __restrict__ clear_count) {
     using SM = FaSmem<DH>;
     constexpr int KC = DH / 16;  // contraction chunks of Q K^T
     constexpr int DB = DH / 32;  // 32-wide output blocks of O^T
@@ -355,7 +358,10 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
     __shared__ __attribute__((aligned(16))) int pos_blk[BM];  // original positions of this workgroup's rows
 
     if (blockIdx.x == 0)  // scratch of the kernels that follow in the layer call: cleared here, no launch of its own
-        for (int c = threadIdx.x; c < n_clear; c += kFaThreads) clear_words[c] = 0u;
+        for (int c = threadIdx.x; c <= n_clear; c += kFaThreads) {
+            if (c < n_clear) clear_words[c] = 0u;
+            else if (clear_count) *clear_count = 0;
+        }
     int qt, head;
     if (!fa_map_block(mp, (int)blockIdx.x, n_qtiles, Hq, Hkv, qt, head)) return;  // whole workgroup exits
     const int g = head / (Hq / Hkv);
@@ -826,11 +832,11 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
 
 template <int DH>
 static dash_status launch_f32(const dash_layer_params& p, const float* q, const float* k, const float* v,
-                              const int32_t* pos, int n, float* o, float scale, uint32_t* clear_words, int n_clear,
+                              const int32_t* pos, int n, float* o, float scale, uint32_t* clear_words, int n_clear, int32_t* clear_count,
                               hipStream_t s) {
     const int n_qtiles = (n + 15) / 16;
     hipLaunchKernelGGL((flash_fwd_f32<DH>), dim3((unsigned)n_qtiles * p.n_q_heads), dim3(kF32Waves * kWave), 0, s, q, k, v,
-                       pos, o, n, p.n_q_heads, p.n_kv_heads, scale, p.causal, n_qtiles, clear_words, n_clear);
+                       pos, o, n, p.n_q_heads, p.n_kv_heads, scale, p.causal, n_qtiles, clear_words, n_clear, clear_count);
     return launch_status();
 }
 
@@ -856,7 +862,7 @@ dash_status init_flash_kernels() {
 template <int DH, int KG>
 static dash_status launch_mfma(const dash_layer_params& p, const __bf16* q, const __bf16* k, const __bf16* v,
                                const int32_t* pos, int n, int row0, int row1, __bf16* o, float scale_log2,
-                               uint32_t* clear_words, int n_clear, hipStream_t s) {
+                               uint32_t* clear_words, int n_clear, int32_t* clear_count, hipStream_t s) {
     const int n_qtiles = (row1 - row0 + kFaBM / KG - 1) / (kFaBM / KG);
     const int Hq = p.n_q_heads, Hkv = p.n_kv_heads, group = Hq / Hkv;
     FaMap mp{0, 1, 1, n_qtiles * group};
@@ -871,19 +877,19 @@ static dash_status launch_mfma(const dash_layer_params& p, const __bf16* q, cons
         blocks = 8u * (unsigned)(mp.items_per_g * mp.g_per_xcd);
     }
     hipLaunchKernelGGL((flash_fwd_mfma<DH, KG>), dim3(blocks), dim3(kFaThreads), FaSmem<DH>::bytes(KG), s, q, k, v, pos, o, n,
-                       Hq, Hkv, scale_log2, p.causal, n_qtiles, mp, clear_words, n_clear, row0);
+                       Hq, Hkv, scale_log2, p.causal, n_qtiles, mp, clear_words, n_clear, row0, clear_count);
     return launch_status();
 }
 
 dash_status launch_flash_fwd(const dash_layer_params& p, const void* q, const void* k, const void* v,
                              const int32_t* active_idx, int n, void* o, uint32_t* clear_words, int n_clear,
-                             hipStream_t s) {
+                             int32_t* clear_count, hipStream_t s) {
     if (n == 0) return DASH_OK;
     const float scale = p.softmax_scale > 0.f ? p.softmax_scale : 1.0f / sqrtf((float)p.head_dim);
     if (p.dtype == DASH_F32) {
         const float *fq = (const float*)q, *fk = (const float*)k, *fv = (const float*)v;
-        return p.head_dim == 64 ? launch_f32<64>(p, fq, fk, fv, active_idx, n, (float*)o, scale, clear_words, n_clear, s)
-                                : launch_f32<128>(p, fq, fk, fv, active_idx, n, (float*)o, scale, clear_words, n_clear, s);
+        return p.head_dim == 64 ? launch_f32<64>(p, fq, fk, fv, active_idx, n, (float*)o, scale, clear_words, n_clear, clear_count, s)
+                                : launch_f32<128>(p, fq, fk, fv, active_idx, n, (float*)o, scale, clear_words, n_clear, clear_count, s);
     }
     // the MFMA kernel addresses K and V with 32-bit byte offsets
     if ((size_t)n * p.n_kv_heads * p.head_dim * 2 >= (size_t)1 << 31) return DASH_ERR_UNSUPPORTED;
@@ -894,12 +900,15 @@ dash_status launch_flash_fwd(const dash_layer_params& p, const void* q, const vo
     const int one_end = form == FA_TWO ? 0 : (form == FA_ONE ? n : n - n % kFaBM);  // rows of the one-group form
     dash_status st = DASH_OK;
     if (one_end > 0)
-        st = p.head_dim == 64 ? launch_mfma<64, 1>(p, bq, bk, bv, active_idx, n, 0, one_end, (__bf16*)o, scale_log2, clear_words, n_clear, s)
-                              : launch_mfma<128, 1>(p, bq, bk, bv, active_idx, n, 0, one_end, (__bf16*)o, scale_log2, clear_words, n_clear, s);
+        st = p.head_dim == 64 ? launch_mfma<64, 1>(p, bq, bk, bv, active_idx, n, 0, one_end, (__bf16*)o, scale_log2, clear_words, n_clear, clear_count, s)
+                              : launch_mfma<128, 1>(p, bq, bk, bv, active_idx, n, 0, one_end, (__bf16*)o, scale_log2, clear_words, n_clear, clear_count, s);
     if (st != DASH_OK || one_end == n) return st;
-    if (one_end > 0) n_clear = 0;  // cleared by the first launch
-    return p.head_dim == 64 ? launch_mfma<64, 2>(p, bq, bk, bv, active_idx, n, one_end, n, (__bf16*)o, scale_log2, clear_words, n_clear, s)
-                            : launch_mfma<128, 2>(p, bq, bk, bv, active_idx, n, one_end, n, (__bf16*)o, scale_log2, clear_words, n_clear, s);
+    if (one_end > 0) {  // cleared by the first launch
+        n_clear = 0;
+        clear_count = nullptr;
+    }
+    return p.head_dim == 64 ? launch_mfma<64, 2>(p, bq, bk, bv, active_idx, n, one_end, n, (__bf16*)o, scale_log2, clear_words, n_clear, clear_count, s)
+                            : launch_mfma<128, 2>(p, bq, bk, bv, active_idx, n, one_end, n, (__bf16*)o, scale_log2, clear_words, n_clear, clear_count, s);
 }
 
 }  // namespace dash

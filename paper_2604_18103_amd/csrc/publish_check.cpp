@@ -47,30 +47,29 @@ int dash_check_publish(int chunks, int splits, int late, int* gathered) {
     return call_failed ? -1 : n_out;
 }
 
-// A workgroup that gives up (sets the launch's FAILED word, then writes the count -1) beside the count's writer (writes
-// 0, looks at the word, then exchanges a 0 for the count, or writes -1 if it saw FAILED), in every order of their steps, after a
-// call that left any count. Returns the number of orders after which the count is not -1.
-int dash_check_publish_orders() {
+// A workgroup that gives up (sets the launch's FAILED word, then writes the count -1) beside the count's writer (the count being
+// 0: looks at the word, then exchanges the 0 for the count, or writes -1 if it saw FAILED), in every order of their steps.
+// Returns the number of orders after which the count is not -1, or, without_failure, not the writer's.
+int dash_check_publish_orders(int without_failure) {
     int wrong = 0;
-    for (int pick = 0; pick < 32; ++pick) {  // bit i: step i of the five is the failing workgroup's
+    for (int pick = 0; pick < 16; ++pick) {  // bit i: step i of the four is the failing workgroup's
         if (__builtin_popcount((unsigned)pick) != 2) continue;
-        for (int before : {-1, 0, 5}) {
-            unsigned long long word = 0;
-            int n_out = before, f = 0, w = 0;
-            bool seen = false;
-            for (int i = 0; i < 5; ++i) {
-                if ((pick >> i) & 1) {
-                    if (f++ == 0) word = kPubFailed;
+        unsigned long long word = 0, seen = 0;
+        int n_out = 0, f = 0, w = 0;
+        for (int i = 0; i < 4; ++i) {
+            if ((pick >> i) & 1) {
+                if (!without_failure) {
+                    if (f == 0) word = kPubFailed;
                     else n_out = -1;
-                    continue;
                 }
-                if (w == 0) n_out = 0;
-                if (w == 1) seen = word != 0;
-                if (w == 2 && (seen || n_out == 0)) n_out = seen ? -1 : 7;
-                ++w;
+                ++f;
+            } else if (w++ == 0) {
+                seen = word;
+            } else {
+                n_out = seen ? -1 : (n_out == 0 ? 7 : n_out);
             }
-            wrong += n_out != -1;
         }
+        wrong += n_out != (without_failure ? 7 : -1);
     }
     return wrong;
 }

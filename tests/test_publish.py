@@ -24,4 +24,5 @@ def test_a_late_publisher_fails_the_call(chunks):
 
 def test_giving_up_at_any_moment():
     """Whenever a workgroup gives up, before, between or after the steps of the count's writer, the count is -1."""
-    assert _load().dash_check_publish_orders() == 0
+    assert _load().dash_check_publish_orders(0) == 0
+    assert _load().dash_check_publish_orders(1) == 0  # and without one it is the count
