@@ -457,9 +457,9 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
     const int kv_end = causal ? min(n, tile_row0 + BM) : n;
     const int all_tiles = (kv_end + kFaBN - 1) / kFaBN;
     // tile t of this wave is key tile t, or, with two key groups, key tile 2 t + grp
-    const int n_tiles = KG == 1 ? all_tiles : (all_tiles - grp + 1) / 2;
+    const int n_tiles = KG == 1 ? all_tiles : fa_group_tiles(all_tiles, grp);
     const int n_rounds = KG == 1 ? all_tiles : (all_tiles + 1) / 2;
-    auto first_key = [&](int t) { return (KG == 1 ? t : 2 * t + grp) * kFaBN; };
+    auto first_key = [&](int t) { return fa_first_key(t, grp, KG); };
     // keys at or beyond this rank are masked for the whole wave; a wave whose rows all lie beyond the end does nothing
     const int wave_kend = q0 >= n ? 0 : (causal ? min(n, q0 + 32) : n);
 
@@ -740,11 +740,11 @@ __global__ __launch_bounds__(kFaThreads, 1) void flash_fwd_mfma(const __bf16* __
             if (grp == 1) {
                 dma_wait();
                 lds_barrier();
-                if (t + 2 < n_tiles) fetch_k(t + 2);
-                if (t + 1 < n_tiles) fetch_v(t + 1);
+                if (t + fa_k_lead(1) < n_tiles) fetch_k(t + fa_k_lead(1));
+                if (t + fa_v_lead(1) < n_tiles) fetch_v(t + fa_v_lead(1));
             } else {
-                if (t + 1 < n_tiles) fetch_k(t + 1);
-                if (t < n_tiles) fetch_v(t);
+                if (t + fa_k_lead(0) < n_tiles) fetch_k(t + fa_k_lead(0));
+                if (t + fa_v_lead(0) < n_tiles) fetch_v(t + fa_v_lead(0));
             }
             valu_phase(t);
             if (grp == 0) {

@@ -314,6 +314,14 @@ DASH_HD uint32_t fa_dma_voff_tail(uint32_t voff, int r, int rows_left, int Hkv, 
 }
 DASH_HD size_t fa_tile_bytes(int Hkv, int DH) { return (size_t)kFaBN * Hkv * DH * 2; }
 
+// Which key tiles a wave group works on: tile t of group grp is key tile t, or with two key groups (KG = 2) key tile 2 t + grp.
+DASH_HD constexpr int fa_first_key(int t, int grp, int KG) { return (KG == 1 ? t : 2 * t + grp) * kFaBN; }
+DASH_HD constexpr int fa_group_tiles(int all_tiles, int grp) { return (all_tiles - grp + 1) / 2; }  // KG = 2
+// Two key groups: how many tiles ahead of the round a group requests K and V. Group 0 requests K(t + lead) and V(t + lead) in
+// round t before its barrier t, group 1 after it; tiles below the lead are requested before the loop.
+DASH_HD constexpr int fa_k_lead(int grp) { return grp == 0 ? 1 : 2; }
+DASH_HD constexpr int fa_v_lead(int grp) { return grp == 0 ? 0 : 1; }
+
 // Two key groups (128 query rows and half of the serial key loop per workgroup) where the loop's length or the last round
 // of workgroups decides the time; one (256 rows) where the chip is full anyway, because either group of the split form
 // fetches its own K and V tiles and its rounds take 14 % longer.

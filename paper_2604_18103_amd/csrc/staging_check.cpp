@@ -272,4 +272,70 @@ int dash_check_flash_staging(int n, int Hkv, int DH, int causal, long long* n_lo
     return c.status;
 }
 
+// The same for the form with two key groups over the query rows [row0, row1) (128-row tiles; row0 > 0: the launch of the last
+// rows alone): every key tile is fetched once as K and once as V, by its group; every load is inside the operand and fetches the
+// clamped row; the positions that a causal mask reads lie in the workgroup's own 128; and a stage is written only after the
+// barrier that follows the last read of what it held, and read only after a barrier that follows the wait for it. (Reads:
+// round t reads K(t) and V(t - 1), after barrier t - 1. A request of round t lies before barrier t in group 0 and is waited
+// for before it, after barrier t in group 1 and waited for before barrier t + 1.)
+int dash_check_flash_groups(int n, int Hkv, int DH, int causal, int row0, int row1, long long* n_loads) {
+    Counter c;
+    if (n <= 0 || Hkv <= 0 || (DH != 64 && DH != 128) || row0 < 0 || row0 % kFaBM != 0 || row1 <= row0 || row1 > n) return -1;
+    constexpr int KG = 2, BM = kFaBM / KG;
+    const uint64_t kv_bytes = (uint64_t)n * Hkv * DH * 2;
+    const int n_qtiles = (row1 - row0 + BM - 1) / BM, dmas = fa_dmas(DH), cpr = fa_cpr(DH);
+    for (int qt = 0; qt < n_qtiles; ++qt) {
+        if (qt > 1 && qt < n_qtiles - 2) continue;
+        const int tile_row0 = row0 + qt * BM;
+        const int kv_end = causal ? sa_min(n, tile_row0 + BM) : n;
+        const int all_tiles = (kv_end + kFaBN - 1) / kFaBN, n_rounds = (all_tiles + 1) / 2;
+        std::vector<int> fetched((size_t)all_tiles * 2, 0);
+        for (int grp = 0; grp < 2; ++grp) {
+            const int n_tiles = fa_group_tiles(all_tiles, grp);
+            if (n_tiles > n_rounds) c.fail(6);
+            for (int is_k = 0; is_k < 2; ++is_k)
+                for (int t = 0; t < n_tiles; ++t) {
+                    const int key0 = fa_first_key(t, grp, KG), rows_left = n - key0;
+                    if (key0 / kFaBN >= all_tiles) {
+                        c.fail(7);
+                        continue;
+                    }
+                    ++fetched[(size_t)(key0 / kFaBN) * 2 + is_k];
+                    if (rows_left < 1) c.fail(3);
+                    const int lead = is_k ? fa_k_lead(grp) : fa_v_lead(grp);
+                    auto requested = [&](int u) { return u < lead ? -1 : u - lead + grp; };      // barriers passed by then
+                    const int readable = requested(t) < 0 ? (is_k && t == 0 ? 0 : 1) : requested(t) + 1;
+                    const int read = is_k ? t : t + 1;
+                    if (readable > read) c.fail(8);
+                    if (t + 2 < n_tiles && requested(t + 2) <= read) c.fail(9);
+                    if (t > 2 && t < n_tiles - 2) continue;  // the addresses are affine in the tile
+                    for (int g = 0; g < Hkv; ++g)
+                        for (int gw = 0; gw < 4; ++gw)
+                            for (int lane = 0; lane < 64; ++lane)
+                                for (int i = 0; i < dmas; ++i) {
+                                    const int r = fa_dma_row(gw, i, lane, DH);
+                                    const uint32_t voff = fa_dma_voff(r, lane, g, Hkv, DH, is_k != 0);
+                                    const int lchunk = (lane % cpr) ^ (is_k ? fa_k_swz(r, DH) : fa_v_swz(r, DH));
+                                    const uint32_t off = rows_left >= kFaBN ? voff : fa_dma_voff_tail(voff, r, rows_left, Hkv, DH);
+                                    const uint64_t addr = (uint64_t)(key0 / kFaBN) * fa_tile_bytes(Hkv, DH) + off;
+                                    const int grow = sa_min(key0 + r, n - 1);
+                                    if (addr != ((uint64_t)grow * Hkv + g) * DH * 2 + (uint64_t)lchunk * 16) c.fail(4);
+                                    if (addr + 16 > kv_bytes) c.fail(5);
+                                    ++c.loads;
+                                }
+                }
+            for (int w = 0; w < 4 && causal; ++w)  // a wave's masked tiles: those that reach beyond its first row
+                for (int t = 0; t < n_tiles; ++t) {
+                    const int q0 = tile_row0 + 32 * w, key0 = fa_first_key(t, grp, KG);
+                    const int wave_kend = q0 >= n ? 0 : sa_min(n, q0 + 32);
+                    if (key0 < wave_kend && key0 + kFaBN - 1 > q0 && (key0 < tile_row0 || key0 + kFaBN > tile_row0 + BM)) c.fail(10);
+                }
+        }
+        for (const int f : fetched)
+            if (f != 1) c.fail(11);
+    }
+    if (n_loads) *n_loads = c.loads;
+    return c.status;
+}
+
 }  // extern "C"
