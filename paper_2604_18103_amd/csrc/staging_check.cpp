@@ -229,6 +229,14 @@ void dash_small_plan(int M, int K, int N, int cu, int norms, unsigned long long 
     out[0] = p.form; out[1] = p.tiles; out[2] = p.parts; out[3] = p.ksteps_per_part;
 }
 
+// How a product whose columns have to lie in one tile by heads of `head` columns (0: none) is launched: out[0..4] = small form (-1:
+// large tiles) and its K parts; the large tiles' K parts, half tiles left over, and those tiles' K parts.
+void dash_product_plan(int M, int K, int N, int cu, int norms, int head, unsigned long long scratch, int* out) {
+    const GemmPlan g = gemm_plan(M, K, N, cu, scratch > 0, (size_t)scratch);
+    const SmallPlan p = small_plan(M, K, N, cu, norms != 0, head, scratch > 0, (size_t)scratch, large_tiles_us(g, M, N, cu));
+    out[0] = p.form; out[1] = p.parts; out[2] = g.parts; out[3] = g.rest; out[4] = rest_parts(g, cu, (size_t)scratch);
+}
+
 // The form attention takes: 0 one key group, 1 two, 2 one with the rows beyond the last whole tile as a launch of their own.
 int dash_fa_form(int n, int Hq, int head_dim, int causal, int cu) { return (int)fa_form(n, Hq, head_dim, causal != 0, cu); }
 

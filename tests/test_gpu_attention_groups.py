@@ -6,6 +6,8 @@ import torch
 
 from oracle import reference as ref
 from paper_2604_18103_amd import binding as B
+from test_attention_form import ONE, ONE_AND_TAIL, TWO
+from test_staging_addresses import _load
 
 pytestmark = pytest.mark.gpu
 
@@ -44,3 +46,30 @@ def test_one_key_group_with_a_nearly_empty_last_tile(n, hq, hkv, dh, causal):
     """Lengths just past the split form's range whose last 256-row tile holds 1, 129 and 129 rows: waves beyond the end
     do nothing. Without a causal mask also lengths whose last 1, 128 and 96 rows run as a launch of their own."""
     _run(n, hq, hkv, dh, causal, seed=n, rows=np.array([0, 1, 31, 32, 255, 256, n // 2, n - 130, n - 2, n - 1]))
+
+
+@pytest.mark.parametrize("n,hq,hkv,dh,causal,form", [
+    (64, 4, 2, 64, True, TWO), (128, 4, 2, 128, True, TWO), (130, 4, 2, 128, False, TWO), (193, 4, 2, 64, True, TWO),
+    (321, 28, 4, 128, True, TWO), (1000, 16, 4, 64, True, TWO), (1150, 28, 4, 128, False, TWO), (2433, 28, 4, 128, True, ONE),
+    (5377, 16, 4, 64, True, ONE), (4097, 16, 4, 64, False, ONE_AND_TAIL), (4224, 16, 4, 64, False, ONE_AND_TAIL),
+    (2400, 28, 4, 128, False, ONE_AND_TAIL), (2305, 28, 4, 128, False, ONE_AND_TAIL), (2432, 28, 4, 128, False, ONE_AND_TAIL)])
+def test_ordinary_rows_closely(n, hq, hkv, dh, causal, form):
+    """Normal q, k and v, every form by name. A bf16 number has 8 significant bits: its rounding is uniform in +-2^-8 of the
+    power of two below it, in the mean square 2^-8 / sqrt(3) * 0.72 = 1.6e-3 of the number. Scores have unit variance, so Q's
+    rounding moves a probability by that much, its own rounding again, and the result's a third time: 2.8e-3 of a row in the
+    2-norm, bound 3.5e-3 on the mean. A row that few keys carry has fewer independent roundings, each at most 3.9e-3: 8e-3 on
+    the largest. A weight between the two groups that is off by a hundredth moves a row by about 7e-3, so the mean shows it."""
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    assert _load().dash_fa_form(n, hq, dh, int(causal), units) == form
+    rng = np.random.default_rng(n)
+    q, k, v = (torch.from_numpy(rng.standard_normal((n, h, dh)).astype(np.float32)).bfloat16() for h in (hq, hkv, hkv))
+    pos = np.sort(rng.permutation(2 * n + 1)[:n]).astype(np.int32)
+    p = B.make_params(hq * dh, hq, hkv, dh, causal=causal)
+    o = torch.empty((n, hq * dh), dtype=torch.bfloat16, device="cuda")
+    B.dash_flash_fwd(p, q.cuda(), k.cuda(), v.cuda(), torch.from_numpy(pos).cuda(), n, o)
+    rows = np.unique(np.r_[0:min(n, 8), rng.integers(0, n, 40), max(n - 130, 0), max(n - 65, 0), n - 1])
+    want = ref.attention_rows(*(t.float().numpy() for t in (q, k, v)), pos, rows=rows, causal=causal).reshape(len(rows), hq, dh)
+    got = o.float().cpu().numpy()[rows].reshape(len(rows), hq, dh)
+    err = np.linalg.norm(got - want, axis=2) / np.linalg.norm(want, axis=2)
+    top, mean = float(err.max()), float(err.mean())
+    assert top <= 8e-3 and mean <= 3.5e-3

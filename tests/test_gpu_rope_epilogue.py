@@ -30,6 +30,33 @@ SHAPES = [(1, 64, 1, 1, 64), (65, 512, 6, 1, 64), (129, 512, 4, 2, 128), (70, 35
           (3612, 3584, 28, 4, 128), (4700, 512, 24, 8, 64), (5100, 512, 28, 4, 128)]
 
 
+# the form each of these takes with the scratch left after the table: small form and its K parts (-1: large tiles), the large
+# tiles' K parts, whether half tiles are left over, and those in K parts
+PLANNED = [((65, 512, 6, 1, 64), (0, 1)), ((300, 1024, 28, 4, 64), (0, 1)), ((70, 3584, 6, 1, 64), (0, 8)),
+           ((70, 3584, 4, 2, 128), (0, 8)), ((16, 8192, 28, 4, 128), (1, 7)), ((600, 1024, 28, 4, 64), (1, 1)),
+           ((333, 1024, 28, 4, 128), (1, 1)), ((804, 1024, 56, 8, 64), (2, 1)), ((804, 1024, 28, 4, 128), (2, 1)),
+           ((2000, 512, 28, 4, 64), (3, 1)), ((1300, 512, 28, 4, 128), (3, 1)), ((300, 14336, 56, 8, 64), (-1, 7, False, 1)),
+           ((300, 14336, 28, 4, 128), (-1, 7, False, 1)), ((2500, 3584, 56, 8, 64), (-1, 1, False, 1)),
+           ((3612, 1024, 56, 8, 64), (-1, 1, True, 1)), ((5100, 512, 28, 4, 128), (-1, 1, True, 1)),
+           ((3612, 3584, 56, 8, 64), (-1, 1, True, 6)), ((3612, 3584, 28, 4, 128), (-1, 1, True, 6))]
+
+
+@pytest.mark.parametrize("shape,form", PLANNED)
+def test_every_form_against_fp64(shape, form):
+    """Both head sizes in every form of the product: the partner column lies 32 or 64 columns away, in the same tile, the
+    neighbouring wave's, or another lane's of the second pass."""
+    n, d, hq, hkv, dh = shape
+    lib, out = _lib(), (ctypes.c_int * 5)()
+    lib.dash_product_plan.argtypes = [ctypes.c_int] * 6 + [ctypes.c_ulonglong, ctypes.POINTER(ctypes.c_int)]
+    p = B.make_params(d, hq, hkv, dh, rule=B.RULE_NONE)
+    scratch = B.qkv_workspace_bytes(p, n) - (n * (dh // 2) * 8 + 255) // 256 * 256
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    lib.dash_product_plan(n, d, (hq + 2 * hkv) * dh, units, 0, dh, max(scratch, 1), out)
+    got = tuple(out)[:2] if form[0] >= 0 else (out[0], out[2], out[3] > 0, out[4])
+    assert got == form
+    test_against_fp64(n, d, hq, hkv, dh)
+
+
 @pytest.mark.parametrize("n,d,hq,hkv,dh", SHAPES)
 def test_against_fp64(n, d, hq, hkv, dh):
     """One bf16 rounding of the rotated fp32 sums (2-norm of a row below 2^-8; measured 1.7e-3), h rounded to bf16 on the way
