@@ -1,8 +1,10 @@
 """Chain of attention-only layers with halting after every layer (a multi-shot schedule).
 
 Host driver only: every step runs in the HIP kernels behind the C ABI. Per layer l:
-    q, k, v = RMSNorm(x_l) W_q, W_k, W_v          dash_rmsnorm_qkv   (LN of Eq. 1 and the projections)
-    q, k    = RoPE(q, k; original positions S_l)  dash_rope_qk       (optional: rope_theta)
+    q, k, v = RMSNorm(x_l) W_q, W_k, W_v          (LN of Eq. 1 and the projections)
+    q, k    = RoPE(q, k; original positions S_l)  (optional: rope_theta)
+              one call with a concatenated weight (dash_rmsnorm_qkv_rope, without rope_theta dash_rmsnorm_qkv_fused),
+              with separate ones dash_rmsnorm_qkv and dash_rope_qk
     x_next, scores, halt, x_{l+1}, S_{l+1}, n_{l+1} = dash_attn_layer(..., rule = TOPK, k_keep = n_l - floor(f n_l))
 The compacted output of one layer is the input of the next (Alg. 1 step 4); the survivor count is read back
 once per layer (4 bytes) to size the next launch.

@@ -374,7 +374,8 @@ size_t published_bytes(int n, bool topk) {
     return ((size_t)((n + kChunkRows - 1) / kChunkRows) * 2 + 1) * sizeof(unsigned long long) + (topk ? (size_t)((n + 1) / 2) * 2 * sizeof(uint32_t) : 0);
 }
 
-// Scores, decision and compaction in one launch (TOPK: n <= kFusedTopkRows). `published` (published_bytes, 8-byte aligned) and the count must have been cleared on this stream before (launch_flash_fwd does it for the layer call).
+// Scores, decision and compaction in one launch (TOPK: n <= kFusedTopkRows). `published` (published_bytes, 8-byte aligned) and
+// the count must have been cleared on this stream before (launch_flash_fwd does it for the layer call).
 dash_status launch_score_decide_compact(const dash_layer_params& p, const NormSums& sums, int n, float* scores, uint8_t* halt, void* published, const int32_t* active_idx,
                                         const void* x_next, int row_bytes, void* x_compact, int32_t* new_active_idx,
                                         int32_t* n_active_out, hipStream_t s) {

@@ -174,10 +174,9 @@ DASH_HD bool small_work_of(int b, int tiles, int parts, int& tile, int& part) {
 // measured beyond that line, small tiles were up to 1.3 times as slow where they had been chosen, and never more than 8 %
 // faster. Otherwise the form expected to be fastest is taken. (With few rows of a wide product the large form may also
 // cut its left-over half tiles along K, which large_tiles_us leaves out: at 257 to 384 rows of 3584 x 37888 that estimate would
-// turn to the large tiles, which measured 3 to 4 % slower.) The
-// expectation is a count of rounds over the compute units times the K steps times what one step was measured to take, plus
-// what a launch costs (us, 256 compute units at their usual clock under matrix work; the forms differ by 10 to 300 %, so
-// the figures only have to be roughly right):
+// turn to the large tiles, which measured 2 to 4 % slower.) The expectation is a count of rounds over the compute units times
+// the K steps times what one step was measured to take, plus what a launch costs (us, 256 compute units at their usual clock
+// under matrix work; the forms differ by 10 to 300 %, so the figures only have to be roughly right):
 //   small form       KW NS  per unit  step alone, step of a full unit   (weight from memory, not from the last-level cache)
 //   64 x  64          2  3     1        0.205                             0.23
 //   64 x 128          2  3     1        0.31                              0.35
@@ -190,9 +189,9 @@ DASH_HD bool small_work_of(int b, int tiles, int parts, int& tile, int& part) {
 // Measured over 916 products (17 to 12001 rows, K 512 to 4096, N 512 to 6144; each repeated on one weight, and the shorter ones
 // on weights from memory): below the line 0.62 and 0.64 times the large tiles' time on average; at worst 1.09 times on cached
 // weights and, at K = 4096 on weights from memory, 1.18. (Beyond those ranges: five K steps, 2201 x 320 x 3584, 14 / 18; a column
-// tile for 8 columns, 6600 x 3584 x 520, 50 / 66.) Feed-forward of 17 and 63 rows, 3584 x 18944: 133 / 103, 133 / 113. Large tiles / this choice, us, K = N = 3584 (with a row norm's launch,
-// about 5), cached and from memory: 63 rows 24.6 / 14.9 and 25.1 / 17.7, 511 40 / 28 and 41 / 35, 901 48 / 38 and 48 / 46, 1401
-// 58 / 49.5 and 58 / 58.6, 2201 75 / 60 and 75 / 65; from 2305 on large.
+// tile for 8 columns, 6600 x 3584 x 520, 50 / 66.) Large tiles / this choice, us, K = N = 3584 with a row norm's launch of about
+// 5, cached and from memory: 63 rows 24.6 / 14.9 and 25.1 / 17.7, 511 40 / 28 and 41 / 35, 901 48 / 38 and 48 / 46, 1401 58 / 49.5
+// and 58 / 58.6, 2201 75 / 60 and 75 / 65; from 2305 on large. Feed-forward 3584 x 18944: 17 rows 133 / 103, 63 133 / 113.
 struct SmallForm {
     int BM, BN, KW, NS, per_cu;
     double step_us, full_us;

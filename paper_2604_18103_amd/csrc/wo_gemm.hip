@@ -546,11 +546,12 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
 }
 
 // ------------------------------------------------------------------------------------------------
-// The same product on small tiles: BM x BN (64 or 128 each), 4 waves in 2 x 2, several workgroups per compute unit.
+// The same product on small tiles: BM x BN (64 or 128 each), KW groups of 4 waves in 2 x 2. One workgroup per compute unit (96 to
+// 144 KB of LDS), of the 128 x 128 form with one K group two.
 // Few rows leave the 256 x 256 tiles with a handful of workgroups, which then have to be cut along K and summed in a
 // second pass: with 177 rows the fp32 sums written and read back were more bytes than the weight. Small tiles fill the
 // chip without that: 177 rows of K = N = 3584 take 15.5 us instead of 26, 333 rows of 512 4.8 instead of 15 (small_plan).
-// KW groups of 4 waves share a workgroup's tile and split its K steps (group kg: steps kg, kg + KW, ...), each with NS
+// The KW groups share a workgroup's tile and split its K steps (group kg: steps kg, kg + KW, ...), each with NS
 // operand stages of its own; their sums meet in the epilogue, in the order of kg. One barrier per round: a step is
 // multiplied from registers while the next one's fragments are read and the step NS ahead is requested. What bounds it: per
 // 64 x 64 step 48 KB through LDS (16 written, 32 read), 384 cycles of it, of the 500 that a step takes; more stages or K
@@ -561,7 +562,7 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
 constexpr size_t small_smem_bytes(int BM, int BN, int KW, int NS) { return (size_t)KW * NS * (BM + BN) * kGK * sizeof(__bf16); }
 
 template <int EPI, int BM, int BN, int KW, int NS>
-__global__ __launch_bounds__(KW * kSWaves * kWave, KW == 4 ? 4 : 2) void gemm_small_kernel(const __bf16* __restrict__ A, const __bf16* __restrict__ B,
+__global__ __launch_bounds__(KW * kSWaves * kWave, 2) void gemm_small_kernel(const __bf16* __restrict__ A, const __bf16* __restrict__ B,
                                                                   int M, int K, int N, const __bf16* __restrict__ x,
                                                                   __bf16* __restrict__ out, float* __restrict__ partials,
                                                                   float* __restrict__ split_sums, int mt, int tiles, int parts,

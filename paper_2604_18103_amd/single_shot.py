@@ -2,7 +2,8 @@
 start layer l_s) and multi-shot schedules (decisions at several blocks, App. D).
 
 Every step of a block runs in the HIP library:
-    q, k, v      = RMSNorm(H) W_q, W_k, W_v ; RoPE at the original positions        dash_rmsnorm_qkv, dash_rope_qk
+    q, k, v      = RMSNorm(H) W_q, W_k, W_v ; RoPE at the original positions        dash_rmsnorm_qkv_rope, or with separate
+                                                                                     weights dash_rmsnorm_qkv + dash_rope_qk
     U, H~        = Attn(.) W_o, H + U                                                dash_flash_fwd + dash_wo_residual_rownorm,
                                                                                      or dash_attn_layer at l = l_s
     H_next       = H~ + FFN(LN(H~))                                                  dash_ffn_swiglu
