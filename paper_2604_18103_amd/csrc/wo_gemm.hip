@@ -35,7 +35,9 @@ __global__ __launch_bounds__(kF32Split * kWave) void wo_f32_kernel(const float* 
     __shared__ float part[kF32Split][16][kF32TileN + 4];
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const int i = lane % 16, g = lane / 16;
-    const int m0 = blockIdx.y * kF32TileM, n0 = blockIdx.x * kF32TileN;
+    const int64_t tile_m = (int64_t)blockIdx.z * gridDim.y + blockIdx.y;  // the last slice of row tiles may be padded
+    if (tile_m * kF32TileM >= M) return;                                  // the whole workgroup
+    const int m0 = (int)tile_m * kF32TileM, n0 = blockIdx.x * kF32TileN;
     f32x4 acc[2][4];
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb)
@@ -1280,7 +1282,11 @@ dash_status launch_wo_residual_rownorm(const dash_layer_params& p, const void* o
     if (n == 0) return DASH_OK;
     const int K = p.n_q_heads * p.head_dim, N = p.d;
     if (p.dtype == DASH_F32) {
-        dim3 grid((N + kF32TileN - 1) / kF32TileN, (n + kF32TileM - 1) / kF32TileM);
+        // a launch has at most 65535 workgroups along y: more row tiles go along z in slices
+        constexpr int64_t kSlice = 32768;
+        const int64_t row_tiles = ((int64_t)n + kF32TileM - 1) / kF32TileM;
+        const dim3 grid((N + kF32TileN - 1) / kF32TileN, (unsigned)(row_tiles < kSlice ? row_tiles : kSlice),
+                        (unsigned)((row_tiles + kSlice - 1) / kSlice));
         hipLaunchKernelGGL(wo_f32_kernel, grid, dim3(kF32Split * kWave), 0, s, (const float*)o, (const float*)w_o,
                            (const float*)x, n, K, N, (float*)x_next, partials, delta_dbg);
         if (sums) *sums = NormSums{partials, norm_partials_per_row(N, p.dtype), 1};

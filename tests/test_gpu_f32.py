@@ -69,3 +69,17 @@ def test_f32_projection_tile_edges(n, hq, dh, d):
     sums = part.cpu().numpy().astype(np.float64).sum(axis=0)
     np.testing.assert_allclose(sums[:, 0], (want ** 2).sum(axis=1), rtol=1e-5)
     np.testing.assert_allclose(sums[:, 1], (x.astype(np.float64) ** 2).sum(axis=1), rtol=1e-5)
+
+
+def test_f32_projection_of_more_rows_than_a_grid_dimension_holds_tiles():
+    """2.1 million rows are 65628 row tiles of 32, beyond the 65535 workgroups that a launch has along y."""
+    n, K, d = 2_100_077, 64, 4
+    g = torch.Generator(device="cuda").manual_seed(2)
+    a, w, x = (torch.randn(s, generator=g, device="cuda") for s in ((n, K), (K, d), (n, d)))
+    p = B.make_params(d, 1, 1, 64, dtype=B.DASH_F32)
+    xn, part = torch.zeros_like(x), torch.zeros((1, n, 2), device="cuda")
+    B.dash_wo_residual_rownorm(p, a, w, x, n, xn, part)
+    want = a.double() @ w.double()
+    assert float((xn.double() - x.double() - want).abs().max()) <= 1e-5 * float(want.abs().max())
+    assert float((part[0, :, 0].double() - want.pow(2).sum(dim=1)).abs().max()) <= 1e-5 * float(want.pow(2).sum(dim=1).max())
+    assert float((part[0, :, 1].double() - x.double().pow(2).sum(dim=1)).abs().max()) <= 1e-5 * float(x.pow(2).sum(dim=1).max())
