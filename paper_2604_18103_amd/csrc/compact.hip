@@ -5,7 +5,6 @@
 // the kept counts of all earlier chunks (written by the decision kernel, one wave ballot each), so no
 // cross-workgroup waiting is needed; ranks inside the chunk come from ballot + popcount.
 #include "common.h"
-#include "lds_ops.h"
 #include "publish.h"
 #include "score_rows.h"
 
@@ -115,11 +114,9 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(
 //    kFusedTopkRows / 64 = 24 workgroups, a fraction of what the chip holds, but nothing reserves that room: beside
 //    kernels on other streams that fill the chip, the last of them may come late.
 // Every wait is bounded (kPubSpinLimit), and one that ends without its word fails the call: a publisher that gave up
-// publishes FAILED instead of a mask; whoever reads FAILED, or gives up itself, gathers nothing, sets the launch's own FAILED
-// word and then writes the survivor count -1. The count is 0 when the kernel starts (cleared with the words), and its writer,
-// one thread of the last chunk's publisher, looks at that word early and at the end exchanges the 0 for the count. So a
-// workgroup that failed before the look is seen, and one that fails after it leaves a -1 that the exchange does not replace,
-// or replaces the count. (Nothing waits for the early look; one after the count took 0.4 us of the call.)
+// publishes FAILED instead of a mask; whoever reads FAILED, or gives up itself, gathers nothing and writes the survivor count -1.
+// The count is 0 when the kernel starts (cleared with the words), and its writer, one thread of the last chunk's publisher,
+// exchanges the 0 for the count: a -1 that is there already stays, and one that comes later replaces the count.
 // ------------------------------------------------------------------------------------------------
 constexpr int kPubSpinLimit = 1 << 20;
 constexpr int kKeyMissing = 1 << 20;  // in place of a count of keys
@@ -151,21 +148,16 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
     const int row = chunk * kChunkRows + lane;
     bool bad = false;
     unsigned long long mask;
-    unsigned long long* call_failed = published + 2 * gridDim.x;
-    // the thread that writes the survivor count, in a wave that publishes nothing
-    const bool counts = chunk == (int)gridDim.x - 1 && blockIdx.y == 0 && tid == kWave;
-    unsigned long long seen = 0;
     if (blockIdx.y == 0) {
         // publisher: scores, flags, the chunk's kept mask
         const float2 t = row_sums_256(partials, cols, fold, n, chunk * kChunkRows, red);
-        if (counts) seen = __hip_atomic_load(call_failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         bool keep = false;
         if (TOPK) {
             __shared__ __attribute__((aligned(16))) uint32_t keys[kFusedTopkRows];
             __shared__ int before[kCompactWaves][kChunkRows];
             const float sc = score_from_sums(t, score_kind);
             const uint32_t mine = order_key(sc);
-            uint32_t* words = reinterpret_cast<uint32_t*>(call_failed + 1);
+            uint32_t* words = reinterpret_cast<uint32_t*>(published + 2 * gridDim.x);
             if (wave == 0 && row < n) {
                 __hip_atomic_store(words + row, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 scores[row] = sc;
@@ -268,7 +260,6 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
     int part = 0;
     for (int c = tid; c < chunk; c += kCompactThreads)
         part += pub_count(wait_published(published + 2 * c, bad));
-    if (seen != 0) bad = true;
     part = wave_sum_int(part);
     const unsigned long long any_bad = __ballot(bad);
     if (lane == 0) {
@@ -287,14 +278,10 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
         failed |= wave_bad[w];
     }
     if (failed) {  // uniform: every thread read the same LDS words
-        if (tid == kWave) {
-            __hip_atomic_store(call_failed, kPubFailed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            dma_wait();
-            __hip_atomic_store(n_out, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        if (tid == 0) __hip_atomic_store(n_out, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
-    if (counts) {
+    if (chunk == (int)gridDim.x - 1 && blockIdx.y == 0 && tid == 0) {
         int cleared = 0;
         (void)__hip_atomic_compare_exchange_strong(n_out, &cleared, base + cnt, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                    __HIP_MEMORY_SCOPE_AGENT);
@@ -369,9 +356,9 @@ dash_status launch_compact(const uint8_t* halt, const int32_t* chunk_counts, con
     return launch_status();
 }
 
-// words of the one-launch kernel: two per chunk, FAILED of the launch, and for TOPK a key per row
+// words of the one-launch kernel: two per chunk, and for TOPK a key per row
 size_t published_bytes(int n, bool topk) {
-    return ((size_t)((n + kChunkRows - 1) / kChunkRows) * 2 + 1) * sizeof(unsigned long long) + (topk ? (size_t)((n + 1) / 2) * 2 * sizeof(uint32_t) : 0);
+    return (size_t)((n + kChunkRows - 1) / kChunkRows) * 2 * sizeof(unsigned long long) + (topk ? (size_t)((n + 1) / 2) * 2 * sizeof(uint32_t) : 0);
 }
 
 // Scores, decision and compaction in one launch (TOPK: n <= kFusedTopkRows). `published` (published_bytes, 8-byte aligned) and

@@ -4,8 +4,7 @@
 //
 // Two 64-bit words per chunk of 64 rows, zero at the start, each valid on its own (one relaxed device-scope access each):
 //   word 0 = kept mask bits 0..31 | kept count << 32 | FAILED | READY      word 1 = kept mask bits 32..63 | FAILED | READY
-// FAILED: the publisher gave up waiting and its mask means nothing. One more word after them says FAILED as soon as any
-// workgroup of the launch has given up.
+// FAILED: the publisher gave up waiting and its mask means nothing.
 #pragma once
 
 #include "staging_addr.h"

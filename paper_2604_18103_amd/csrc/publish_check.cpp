@@ -23,7 +23,6 @@ int dash_check_publish(int chunks, int splits, int late, int* gathered) {
             words[2 * c + 1] |= pub_word1(mask_of(c), missing);
         }
     int n_out = 0;
-    bool call_failed = false;
     for (int c = 0; c < chunks; ++c) {
         gathered[c] = 0;
         for (int y = 0; y < splits; ++y) {
@@ -36,42 +35,15 @@ int dash_check_publish(int chunks, int splits, int late, int* gathered) {
                 base += pub_count(words[2 * e]);
             }
             if (failed) {
-                call_failed = true;
+                n_out = -1;
             } else {
                 if (y > 0 && pub_mask(words[2 * c], words[2 * c + 1]) != mask_of(c)) return -100;
                 ++gathered[c];
             }
-            if (c == chunks - 1 && y == 0) n_out = failed ? -1 : base + c % 65;
+            if (c == chunks - 1 && y == 0 && !failed && n_out == 0) n_out = base + c % 65;  // exchanges the 0
         }
     }
-    return call_failed ? -1 : n_out;
-}
-
-// A workgroup that gives up (sets the launch's FAILED word, then writes the count -1) beside the count's writer (the count being
-// 0: looks at the word, then exchanges the 0 for the count, or writes -1 if it saw FAILED), in every order of their steps.
-// Returns the number of orders after which the count is not -1, or, without_failure, not the writer's.
-int dash_check_publish_orders(int without_failure) {
-    int wrong = 0;
-    for (int pick = 0; pick < 16; ++pick) {  // bit i: step i of the four is the failing workgroup's
-        if (__builtin_popcount((unsigned)pick) != 2) continue;
-        unsigned long long word = 0, seen = 0;
-        int n_out = 0, f = 0, w = 0;
-        for (int i = 0; i < 4; ++i) {
-            if ((pick >> i) & 1) {
-                if (!without_failure) {
-                    if (f == 0) word = kPubFailed;
-                    else n_out = -1;
-                }
-                ++f;
-            } else if (w++ == 0) {
-                seen = word;
-            } else {
-                n_out = seen ? -1 : (n_out == 0 ? 7 : n_out);
-            }
-        }
-        wrong += n_out != (without_failure ? 7 : -1);
-    }
-    return wrong;
+    return n_out;
 }
 
 }  // extern "C"
