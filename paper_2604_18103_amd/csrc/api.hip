@@ -177,6 +177,8 @@ size_t dash_workspace_bytes(const dash_layer_params* p, int32_t n_capacity) {
 dash_status dash_init(void) {
     dash_status st = init_flash_kernels();
     if (st != DASH_OK) return st;
+    st = init_few_kernels();
+    if (st != DASH_OK) return st;
     st = init_gemm_kernels();
     if (st != DASH_OK) return st;
     void* scratch = nullptr;

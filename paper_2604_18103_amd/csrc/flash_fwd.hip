@@ -6,10 +6,11 @@
 // "position of key <= position of query" equals "rank of key <= rank of query"; whole tiles are
 // skipped by rank and the elements of diagonal tiles are masked by comparing positions.
 //
-// Two kernels:
-//   flash_fwd_mfma<DH, KG> bf16, MFMA 32x32x16, fp32 softmax and accumulation (the hot kernel)
+// Kernels:
+//   flash_fwd_mfma<DH, KG> bf16, MFMA 32x32x16, fp32 softmax and accumulation (the hot kernel); few rows: flash_few.hip
 //   flash_fwd_f32<DH> fp32, MFMA 16x16x4 fp32, keys split over the waves of a workgroup
 #include "common.h"
+#include "flash_map.h"
 #include "lds_ops.h"
 #include "staging_addr.h"
 
@@ -260,40 +261,6 @@ constexpr int kFaThreads = 512;
 constexpr float kMaskedScore = -1.0e30f;
 // 2^20 as a float: a lane's 32-key partial row sum above this moves the softmax reference
 constexpr int kRowSumLimitBits = 0x49800000;
-
-// Work-item -> (query tile, head) map. Workgroups are handed to the 8 XCDs round-robin
-// (workgroup b runs on XCD b % 8) and each XCD has its own L2, so all workgroups of one XCD are given
-// the same KV head (or as few as possible): its K/V tiles are then fetched into that L2 once and shared
-// by the query heads of the group and by neighbouring query tiles. Heaviest (latest) query tiles first.
-struct FaMap {
-    int xcd_mode;      // 1: XCD-aware, 0: plain
-    int xcds_per_g;    // XCDs serving one KV head (Hkv <= 8)
-    int g_per_xcd;     // KV heads per XCD (Hkv >= 8)
-    int items_per_g;   // n_qtiles * group size
-};
-
-__device__ __forceinline__ bool fa_map_block(const FaMap& mp, int bid, int n_qtiles, int Hq, int Hkv,
-                                             int& qt, int& head) {
-    const int group = Hq / Hkv;
-    if (!mp.xcd_mode) {
-        qt = n_qtiles - 1 - bid / Hq;
-        head = bid % Hq;
-        return true;
-    }
-    const int xcd = bid % 8, slot = bid / 8;
-    int g, idx;
-    if (mp.g_per_xcd == 1) {
-        g = xcd / mp.xcds_per_g;
-        idx = slot * mp.xcds_per_g + xcd % mp.xcds_per_g;
-    } else {
-        g = xcd * mp.g_per_xcd + slot % mp.g_per_xcd;
-        idx = slot / mp.g_per_xcd;
-    }
-    if (idx >= mp.items_per_g) return false;
-    qt = n_qtiles - 1 - idx / group;
-    head = g * group + idx % group;
-    return true;
-}
 
 // LDS layout of one K or V stage: 64 rows of DH bf16, unpadded (the direct global->LDS loads write 1 KB of
 // consecutive LDS per wave instruction, so rows cannot be padded). Bank conflicts are avoided by an XOR
@@ -864,18 +831,9 @@ static dash_status launch_mfma(const dash_layer_params& p, const __bf16* q, cons
                                const int32_t* pos, int n, int row0, int row1, __bf16* o, float scale_log2,
                                uint32_t* clear_words, int n_clear, int32_t* clear_count, hipStream_t s) {
     const int n_qtiles = (row1 - row0 + kFaBM / KG - 1) / (kFaBM / KG);
-    const int Hq = p.n_q_heads, Hkv = p.n_kv_heads, group = Hq / Hkv;
-    FaMap mp{0, 1, 1, n_qtiles * group};
-    unsigned blocks = (unsigned)n_qtiles * Hq;
-    if (Hkv <= 8 && 8 % Hkv == 0) {
-        mp.xcd_mode = 1;
-        mp.xcds_per_g = 8 / Hkv;
-        blocks = 8u * (unsigned)((mp.items_per_g + mp.xcds_per_g - 1) / mp.xcds_per_g);
-    } else if (Hkv % 8 == 0) {
-        mp.xcd_mode = 1;
-        mp.g_per_xcd = Hkv / 8;
-        blocks = 8u * (unsigned)(mp.items_per_g * mp.g_per_xcd);
-    }
+    const int Hq = p.n_q_heads, Hkv = p.n_kv_heads;
+    unsigned blocks = 0;
+    const FaMap mp = fa_map(n_qtiles, Hq, Hkv, blocks);
     hipLaunchKernelGGL((flash_fwd_mfma<DH, KG>), dim3(blocks), dim3(kFaThreads), FaSmem<DH>::bytes(KG), s, q, k, v, pos, o, n,
                        Hq, Hkv, scale_log2, p.causal, n_qtiles, mp, clear_words, n_clear, row0, clear_count);
     return launch_status();
@@ -896,6 +854,9 @@ dash_status launch_flash_fwd(const dash_layer_params& p, const void* q, const vo
     if (init_flash_kernels() != DASH_OK || compute_units() <= 0) return DASH_ERR_HIP;
     const float scale_log2 = scale * 1.4426950408889634f;
     const __bf16 *bq = (const __bf16*)q, *bk = (const __bf16*)k, *bv = (const __bf16*)v;
+    const int waves = few_waves(n, p.n_q_heads, p.head_dim, p.causal != 0, compute_units());
+    if (waves > 0)
+        return launch_flash_few(p, bq, bk, bv, active_idx, n, (__bf16*)o, scale_log2, waves, clear_words, n_clear, clear_count, s);
     const FaForm form = fa_form(n, p.n_q_heads, p.head_dim, p.causal != 0, compute_units());  // staging_addr.h
     const int one_end = form == FA_TWO ? 0 : (form == FA_ONE ? n : n - n % kFaBM);  // rows of the one-group form
     dash_status st = DASH_OK;

@@ -351,4 +351,29 @@ inline FaForm fa_form(int n, int Hq, int head_dim, bool causal, int cu) {
     return t_two < (head_dim == 64 ? 0.96 : 0.94) * t_one ? FA_TWO : FA_ONE;
 }
 
+// ------------------------------------------------------------------------------------------------
+// Attention over few rows: workgroups of 32 query rows whose waves take 32-key blocks of their own. A wave fetches whole
+// blocks (few_loads instructions of fa_rows_per_dma rows each); lane offsets and clamping as above.
+// ------------------------------------------------------------------------------------------------
+constexpr int kFewKeys = 32;
+DASH_HD constexpr int few_loads(int DH) { return kFewKeys / fa_rows_per_dma(DH); }
+DASH_HD int few_row(int i, int lane, int DH) { return i * fa_rows_per_dma(DH) + lane / fa_cpr(DH); }
+DASH_HD size_t few_block_bytes(int Hkv, int DH) { return (size_t)kFewKeys * Hkv * DH * 2; }
+// Waves per workgroup of that form, 0: the tiled kernels (fa_form). Its workgroups fetch a key block for 32 rows where those fetch
+// it for 128 or 256, so it pays while latencies and not the L2 decide: counted in its workgroups per compute unit, with a
+// causal mask (half of the blocks, long rows first) up to 3, at head size 64 (half the bytes) 5; without one, where a third
+// workgroup per unit is a whole round, 2. Measured, us, this form / the tiled ones; causal, 28 heads of 128: n = 64 5.7 / 8.4, 192
+// 7.3 / 10.6, 512 10.8 / 15.2, 832 (2.8 per unit) 18.1 / 18.8, 960 (3.3) 20.8 / 20.2; 14 heads 2048 (3.5) 31.9 / 33.1, 8 heads 3072
+// (3) 35.3 / 44.1, 4096 (4) 58 / 57; 16 heads of 64: 64 4.7 / 6.8, 1024 9.8 / 15.2, 2560 (5) 27.2 / 27.8, 2816 34.1 / 29.8; 32 heads
+// of 64: 1280 (5) 18.8 / 18.9. Without a mask, 28 heads of 128: 576 (2) 12.9 / 14.5, 640 (2.2) 20.6 / 15.4; 16 heads of 64: 1024 (2)
+// 12.0 / 13.9, 1152 16.1 / 15.1.
+// Eight waves, which halve the serial loop, while all workgroups are resident at once (one per unit, at head size 64 two): 4 heads of
+// 128, causal, four waves / eight: 512 9.0 / 8.8, 2048 21.3 / 17.7; beyond that the smaller workgroups overlap better: 28 heads
+// of 128 320 (1.1 per unit) 8.6 / 9.7.
+inline int few_waves(int n, int Hq, int head_dim, bool causal, int cu) {
+    const long long wgs = (long long)((n + 31) / 32) * Hq;
+    if (wgs > (long long)cu * (causal ? (head_dim == 64 ? 5 : 3) : 2)) return 0;
+    return wgs <= (long long)cu * (head_dim == 64 ? 2 : 1) ? 8 : 4;
+}
+
 }  // namespace dash

@@ -237,7 +237,7 @@ void dash_product_plan(int M, int K, int N, int cu, int norms, int head, unsigne
     out[0] = p.form; out[1] = p.parts; out[2] = g.parts; out[3] = g.rest; out[4] = rest_parts(g, cu, (size_t)scratch);
 }
 
-// The form attention takes: 0 one key group, 1 two, 2 one with the rows beyond the last whole tile as a launch of their own.
+// The form attention takes among the tiled kernels (dash_few_waves = 0): 0 one key group, 1 two, 2 one with the rows beyond the last whole tile as a launch of their own.
 int dash_fa_form(int n, int Hq, int head_dim, int causal, int cu) { return (int)fa_form(n, Hq, head_dim, causal != 0, cu); }
 
 // Checks every K and V staging load of the attention launch over n rows (K, V: [n][Hkv][DH] bf16): for each
@@ -345,5 +345,54 @@ int dash_check_flash_groups(int n, int Hkv, int DH, int causal, int row0, int ro
     if (n_loads) *n_loads = c.loads;
     return c.status;
 }
+
+// Attention over few rows (workgroups of 32 query rows, `waves` waves): over all query tiles every 32-key block that a tile can see
+// is fetched by exactly one wave, once as K and once as V; every load is inside the operand, fetches the clamped row, and
+// together they fill a stage; the positions that a causal mask reads are those of the tile's own rows.
+int dash_check_flash_few(int n, int Hkv, int DH, int causal, int waves, long long* n_loads) {
+    Counter c;
+    if (n <= 0 || Hkv <= 0 || (DH != 64 && DH != 128) || waves <= 0) return -1;
+    const uint64_t kv_bytes = (uint64_t)n * Hkv * DH * 2;
+    const int cpr = fa_cpr(DH);
+    for (int qt = 0; qt < (n + 31) / 32; ++qt) {
+        const int row0 = 32 * qt, kend = causal ? sa_min(n, row0 + 32) : n, n_blocks = (kend + kFewKeys - 1) / kFewKeys;
+        std::vector<int> taken((size_t)n_blocks, 0);
+        for (int w = 0; w < waves; ++w)
+            for (int b = w; b < n_blocks; b += waves) {
+                ++taken[(size_t)b];
+                const int rows_left = n - b * kFewKeys;
+                if (rows_left < 1) c.fail(3);
+                if (causal && b * kFewKeys + kFewKeys - 1 > row0 && b * kFewKeys != row0) c.fail(10);
+                for (int g = 0; g < Hkv; ++g)
+                    for (int is_k = 0; is_k < 2; ++is_k) {
+                        std::vector<char> filled((size_t)kFewKeys * cpr, 0);
+                        for (int lane = 0; lane < 64; ++lane)
+                            for (int i = 0; i < few_loads(DH); ++i) {
+                                const int r = few_row(i, lane, DH);
+                                if (r < 0 || r >= kFewKeys || r * cpr + lane % cpr != i * 64 + lane) { c.fail(1); continue; }
+                                filled[(size_t)r * cpr + lane % cpr] = 1;
+                                const int lchunk = (lane % cpr) ^ (is_k ? fa_k_swz(r, DH) : fa_v_swz(r, DH));
+                                if (lchunk < 0 || lchunk >= cpr) c.fail(2);
+                                const uint32_t voff = fa_dma_voff(r, lane, g, Hkv, DH, is_k != 0);
+                                const uint32_t off = rows_left >= kFewKeys ? voff : fa_dma_voff_tail(voff, r, rows_left, Hkv, DH);
+                                const uint64_t addr = (uint64_t)b * few_block_bytes(Hkv, DH) + off;
+                                const int grow = sa_min(b * kFewKeys + r, n - 1);
+                                if (addr != ((uint64_t)grow * Hkv + g) * DH * 2 + (uint64_t)lchunk * 16) c.fail(4);
+                                if (addr + 16 > kv_bytes) c.fail(5);
+                                ++c.loads;
+                            }
+                        for (const char f : filled)
+                            if (!f) c.fail(6);
+                    }
+            }
+        for (const int t : taken)
+            if (t != 1) c.fail(11);
+    }
+    if (n_loads) *n_loads = c.loads;
+    return c.status;
+}
+
+// Waves of the few-row form, 0 where the tiled kernels run.
+int dash_few_waves(int n, int Hq, int head_dim, int causal, int cu) { return few_waves(n, Hq, head_dim, causal != 0, cu); }
 
 }  // extern "C"
