@@ -489,12 +489,13 @@ dash_status dash_attn_layer(const dash_layer_params* p, const void* x, const voi
 
     // NONE / THRESHOLD, and TOPK of few rows: scores, decision and compaction run as one launch whose workgroups hand
     // each other keys and the chunks' kept masks through words that have to start cleared: the attention kernel clears
-    // them on its way
+    // them on its way (TOPK of few rows hands nothing over)
     const bool topk = p->rule == DASH_RULE_TOPK, one_launch = !topk || n <= kFusedTopkRows;
     uint32_t* published = reinterpret_cast<uint32_t*>(ws + w.published_off);
-    const int n_clear = one_launch ? (int)(published_bytes(n, topk) / sizeof(uint32_t)) : 0;
+    const bool handed = one_launch && !(topk && n <= kFewTopkRows);
+    const int n_clear = handed ? (int)(published_bytes(n, topk) / sizeof(uint32_t)) : 0;
     if (profile) DASH_HIP_CHECK(hipEventRecord(profile->ev[0], s));
-    st = launch_flash_fwd(*p, q, k, v, active_idx, n, o, published, n_clear, one_launch ? n_active_out : nullptr, s);
+    st = launch_flash_fwd(*p, q, k, v, active_idx, n, o, published, n_clear, handed ? n_active_out : nullptr, s);
     if (st != DASH_OK) return st;
     if (profile) DASH_HIP_CHECK(hipEventRecord(profile->ev[1], s));
     NormSums sums{};

@@ -101,6 +101,11 @@ dash_status launch_score_rows(const float* delta, const void* x, int n, int d, i
 // and compaction one after the other, us: 64 rows of 28 x 128 heads 29.1 / 34.4, 512 51.3 / 54.9, 1500 93.5 / 94.6, 2120
 // 120.4 / 119.5; of 4 x 128 heads: 64 20.4 / 26.1, 1500 45.1 / 47.2, 2120 56.7 / 56.4.
 constexpr int kFusedTopkRows = 1536;
+// ... of these, up to this many without an exchange, every workgroup deciding about all rows itself (topk_compact_few_kernel). Layer
+// call in a graph, with the exchange / without, us: width 512 64 rows 16.8 / 14.6, 256 20.7 / 18.0, 512 23.3 / 21.7, 650 25.3 /
+// 26.1; width 3584 64 rows 26.0 / 22.7, 256 35.6 / 32.7, 512 46.7 / 46.0, 650 59.2 / 63.8 (the norm pairs of all rows, read
+// by each workgroup, grow with the width). THRESHOLD, whose workgroups wait for one word, gains nothing by it.
+constexpr int kFewTopkRows = 512;
 size_t published_bytes(int n, bool topk);  // words the fused score + decision + compaction kernel publishes its chunks through
 dash_status launch_score_decide_compact(const dash_layer_params& p, const NormSums& sums, int n, float* scores, uint8_t* halt, void* published, const int32_t* active_idx,
                                         const void* x_next, int row_bytes, void* x_compact, int32_t* new_active_idx,

@@ -110,7 +110,7 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(
 // the grid.
 //  - NONE, THRESHOLD: a workgroup (c, y) waits for publishers (c', 0) with c' <= c only. They have a smaller linear index,
 //    are therefore resident or done, and publish without having waited.
-//  - TOPK: the publishers wait for one another, so they have to be resident together. They are at most
+//  - TOPK (more than kFewTopkRows rows): the publishers wait for one another, so they have to be resident together. They are at most
 //    kFusedTopkRows / 64 = 24 workgroups, a fraction of what the chip holds, but nothing reserves that room: beside
 //    kernels on other streams that fill the chip, the last of them may come late.
 // Every wait is bounded (kPubSpinLimit), and one that ends without its word fails the call: a publisher that gave up
@@ -309,6 +309,110 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// TOPK of few rows: scores, decision and compaction in one launch without any exchange. Each workgroup (c, y) finishes the
+// scores of ALL rows, one of its waves selects, and the workgroup gathers its columns of its chunk's kept rows. Repeated is little
+// (at width 3584 the pairs of 256 rows are 115 KB, through the L2); saved are two round trips between workgroups (keys, masks), and no word has to be cleared. Thread (r, q)
+// of 256 x 4 adds a quarter of the pairs of rows r, r + 256, ...
+// The selection, 4 RPT keys per lane of one wave: the k_cand-th greatest key bit by bit (the greatest T that k_cand keys reach),
+// counted by ballots, without a barrier; where exactly k_cand keys reach a T the set is found, so only rows that tie with the
+// last one kept take all 32 steps.
+// Bound by latency: norms, selection (about a microsecond), gather. (Counting, for each row, the candidates before it was as fast
+// up to 128 rows and 1 us slower at 256.) Figures: kFewTopkRows.
+// ------------------------------------------------------------------------------------------------
+constexpr int kFewThreads = 1024;
+
+template <int RPT>
+__global__ __launch_bounds__(kFewThreads) void topk_compact_few_kernel(
+    const float* __restrict__ partials, int cols, int fold, int n, int score_kind, int k_keep, int n_first, int n_last,
+    float* __restrict__ scores, uint8_t* __restrict__ halt, const int32_t* __restrict__ active_idx,
+    const uint4* __restrict__ x_next, int row_vecs, int vecs_per_split, uint4* __restrict__ x_compact,
+    int32_t* __restrict__ new_idx, int32_t* __restrict__ n_out) {
+    static_assert(RPT <= 2, "rows of a launch");
+    constexpr int kRows = 256 * RPT, kChunks = kRows / kChunkRows;
+    __shared__ float2 red[4][kRows];
+    __shared__ uint32_t keys[kRows];
+    __shared__ unsigned long long masks[kChunks];
+    __shared__ int kept_rows[kChunkRows];
+    const int chunk = blockIdx.x, tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+#pragma unroll
+    for (int u = 0; u < RPT; ++u) {
+        const int r = u * 256 + tid % 256;
+        red[tid / 256][r] = row_quarter(partials, cols, fold, n, r, tid / 256);
+    }
+    __syncthreads();
+    const int lo = min(n_first, n), hi = max(lo, n - n_last);  // candidates are rows [lo, hi)
+    if (tid < kRows) {
+        const float sc = score_from_sums(add_quarters(red[0][tid], red[1][tid], red[2][tid], red[3][tid]), score_kind);
+        keys[tid] = tid >= lo && tid < hi ? order_key(sc) : 0u;  // 0, which no score's key is: no candidate
+        if (blockIdx.y == 0 && wave == chunk && tid < n) scores[tid] = sc;
+    }
+    __syncthreads();
+    if (wave == 0) {
+        const int k_cand = max(0, min(k_keep - (n - (hi - lo)), hi - lo));
+        uint32_t k[kChunks], T = 0u;
+#pragma unroll
+        for (int c = 0; c < kChunks; ++c) k[c] = keys[c * kChunkRows + lane];
+        int reach = k_cand == 0 ? 0 : hi - lo;  // keys that reach T
+#pragma unroll 1
+        for (uint32_t bit = 0x80000000u; bit != 0u && reach != k_cand; bit >>= 1) {
+            int cnt = 0;
+#pragma unroll
+            for (int c = 0; c < kChunks; ++c) cnt += __popcll(__ballot(k[c] >= (T | bit)));
+            if (cnt >= k_cand) {
+                T |= bit;
+                reach = cnt;
+            }
+        }
+        int over = reach - k_cand;  // of the rows at T itself the last ones go, this many
+#pragma unroll
+        for (int c = kChunks - 1; c >= 0; --c) {
+            const int r = c * kChunkRows + lane;
+            unsigned long long kept = k_cand == 0 ? 0ull : __ballot(k[c] != 0u && k[c] >= T);
+            if (over > 0) {
+                const unsigned long long tie = __ballot(k[c] == T);
+                kept &= ~__ballot(k[c] == T && __popcll(tie >> lane) <= over);  // this row and the ties behind it in the chunk
+                over -= min(over, (int)__popcll(tie));
+            }
+            kept |= __ballot(r < n && row_protected(r, n, n_first, n_last));
+            if (lane == 0) masks[c] = kept;
+            if (c == chunk) {
+                const bool keep = (kept >> lane) & 1ull;
+                if (keep) kept_rows[__popcll(kept & ((1ull << lane) - 1ull))] = r;
+                if (blockIdx.y == 0 && r < n) halt[r] = keep ? 0 : 1;
+            }
+        }
+    }
+    __syncthreads();
+    int base = 0;
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c) base += c < chunk ? __popcll(masks[c]) : 0;
+    const int cnt = __popcll(masks[chunk]);
+    if (blockIdx.y == 0) {
+        if (tid < cnt) new_idx[base + tid] = active_idx[kept_rows[tid]];
+        if (chunk == (int)gridDim.x - 1 && tid == 0) *n_out = base + cnt;
+    }
+    const int v0 = (int)blockIdx.y * vecs_per_split, v1 = min(row_vecs, v0 + vecs_per_split);
+    constexpr int R = 4;
+    for (int r0 = wave * R; r0 < cnt; r0 += kFewThreads / kWave * R) {
+        const uint4* from[R];
+        uint4* to[R];
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const int r = min(r0 + i, cnt - 1);  // a clamped duplicate rewrites the same bytes
+            from[i] = x_next + (size_t)kept_rows[r] * row_vecs;
+            to[i] = x_compact + (size_t)(base + r) * row_vecs;
+        }
+        for (int c = v0 + lane; c < v1; c += kWave) {
+            uint4 val[R];
+#pragma unroll
+            for (int i = 0; i < R; ++i) val[i] = from[i][c];
+#pragma unroll
+            for (int i = 0; i < R; ++i) to[i][c] = val[i];
+        }
+    }
+}
+
 __global__ void write_zero_kernel(int32_t* p) { *p = 0; }
 
 __global__ __launch_bounds__(256) void validate_idx_kernel(const int32_t* __restrict__ idx, int n, int N,
@@ -362,7 +466,8 @@ size_t published_bytes(int n, bool topk) {
 }
 
 // Scores, decision and compaction in one launch (TOPK: n <= kFusedTopkRows). `published` (published_bytes, 8-byte aligned) and
-// the count must have been cleared on this stream before (launch_flash_fwd does it for the layer call).
+// the count must have been cleared on this stream before (launch_flash_fwd does it for the layer call), except for
+// TOPK up to kFewTopkRows rows, which hands nothing over.
 dash_status launch_score_decide_compact(const dash_layer_params& p, const NormSums& sums, int n, float* scores, uint8_t* halt, void* published, const int32_t* active_idx,
                                         const void* x_next, int row_bytes, void* x_compact, int32_t* new_active_idx,
                                         int32_t* n_active_out, hipStream_t s) {
@@ -371,6 +476,13 @@ dash_status launch_score_decide_compact(const dash_layer_params& p, const NormSu
     int splits, vecs_per_split;
     gather_splits(n_chunks, row_vecs, splits, vecs_per_split);
     const bool topk = p.rule == DASH_RULE_TOPK;
+    if (topk && n <= kFewTopkRows) {
+        hipLaunchKernelGGL(n <= 256 ? topk_compact_few_kernel<1> : topk_compact_few_kernel<2>,
+                           dim3(n_chunks, splits), dim3(kFewThreads), 0, s, sums.pairs, sums.cols, sums.fold, n, p.score_kind,
+                           topk_keep(p, n), p.keep_first_n, p.keep_last_n, scores, halt, active_idx, (const uint4*)x_next,
+                           row_vecs, vecs_per_split, (uint4*)x_compact, new_active_idx, n_active_out);
+        return launch_status();
+    }
     hipLaunchKernelGGL(topk ? score_decide_compact_kernel<true> : score_decide_compact_kernel<false>, dim3(n_chunks, splits),
                        dim3(kCompactThreads), 0, s, sums.pairs, sums.cols, sums.fold, n, p.score_kind, p.rule, p.tau,
                        topk ? topk_keep(p, n) : 0, p.keep_first_n, p.keep_last_n, scores, halt, (unsigned long long*)published,

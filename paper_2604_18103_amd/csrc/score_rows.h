@@ -7,13 +7,9 @@
 
 namespace dash {
 
-// Sum of the partial pairs of one row, taken by the four threads (row, q = 0..3) of a 256-thread
-// workgroup that covers 64 rows: thread q adds partials q, q+4, ... in order, then the four sums are
-// added in order q = 0..3 through LDS. Fixed order, so the score is bit-reproducible.
-__device__ __forceinline__ float2 row_sums_256(const float* __restrict__ partials, int cols, int fold, int n, int row_base,
-                                               float2 (*red)[kChunkRows]) {
-    const int r = threadIdx.x % kChunkRows, qd = threadIdx.x / kChunkRows;
-    const int row = row_base + r;
+// Quarter qd (0..3) of the sum of a row's partial pairs: pairs qd, qd + 4, ... in order. The four quarters are added in order
+// qd = 0..3, so a score has the same bits whoever finishes it.
+__device__ __forceinline__ float2 row_quarter(const float* __restrict__ partials, int cols, int fold, int n, int row, int qd) {
     float sd = 0.f, sx = 0.f;
     if (row < n) {
         const float2* src = reinterpret_cast<const float2*>(partials) + row;
@@ -43,15 +39,20 @@ __device__ __forceinline__ float2 row_sums_256(const float* __restrict__ partial
             }
         }
     }
-    red[qd][r] = make_float2(sd, sx);
+    return make_float2(sd, sx);
+}
+__device__ __forceinline__ float2 add_quarters(float2 a, float2 b, float2 c, float2 d) {
+    return make_float2(a.x + b.x + c.x + d.x, a.y + b.y + c.y + d.y);
+}
+
+// Sum of the partial pairs of one row, taken by the four threads (row, q = 0..3) of a 256-thread workgroup that covers 64 rows.
+__device__ __forceinline__ float2 row_sums_256(const float* __restrict__ partials, int cols, int fold, int n, int row_base,
+                                               float2 (*red)[kChunkRows]) {
+    const int r = threadIdx.x % kChunkRows, qd = threadIdx.x / kChunkRows;
+    red[qd][r] = row_quarter(partials, cols, fold, n, row_base + r, qd);
     __syncthreads();
-    float2 t = red[0][r];
-#pragma unroll
-    for (int k = 1; k < 4; ++k) {
-        t.x += red[k][r].x;
-        t.y += red[k][r].y;
-    }
-    return t;  // valid in every thread; callers use the copy of wave 0
+    // valid in every thread; callers use the copy of wave 0
+    return add_quarters(red[0][r], red[1][r], red[2][r], red[3][r]);
 }
 
 __device__ __forceinline__ float score_from_sums(float2 t, int score_kind) {
