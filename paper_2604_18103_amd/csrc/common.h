@@ -59,8 +59,8 @@ dash_status launch_flash_fwd(const dash_layer_params& p, const void* q, const vo
 // flash_few.hip
 dash_status init_few_kernels();
 dash_status launch_flash_few(const dash_layer_params& p, const __bf16* q, const __bf16* k, const __bf16* v,
-                             const int32_t* pos, int n, __bf16* o, float scale_log2, int waves, uint32_t* clear_words, int n_clear,
-                             int32_t* clear_count, hipStream_t s);
+                             const int32_t* pos, int n, int row0, __bf16* o, float scale_log2, int waves, uint32_t* clear_words,
+                             int n_clear, int32_t* clear_count, hipStream_t s);
 // wo_gemm.hip
 int norm_partials_per_row(int d, int dtype);
 // Row norms as a product left them: `cols` pairs per row, of which `fold` (1 or kNormFold) neighbours make up one of the

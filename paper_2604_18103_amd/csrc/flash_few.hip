@@ -39,7 +39,7 @@ __global__ __launch_bounds__(KW * kWave, 2) void flash_few(const __bf16* __restr
                                                             const __bf16* __restrict__ v, const int32_t* __restrict__ pos,
                                                             __bf16* __restrict__ o, int n, int Hq, int Hkv, float scale_log2,
                                                             int causal, int n_qtiles, FaMap mp, uint32_t* __restrict__ clear_words,
-                                                            int n_clear, int32_t* __restrict__ clear_count) {
+                                                            int n_clear, int row_base, int32_t* __restrict__ clear_count) {
     using SM = FewSmem<DH>;
     constexpr int KC = DH / 16, DB = DH / 32;
     constexpr int LOADS = few_loads(DH);
@@ -57,7 +57,7 @@ __global__ __launch_bounds__(KW * kWave, 2) void flash_few(const __bf16* __restr
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int j = lane % 32, h = lane / 32;
     const int tg = lane / 16, ti = lane % 16;
-    const int row0 = qt * 32, row = min(row0 + j, n - 1);
+    const int row0 = row_base + qt * 32, row = min(row0 + j, n - 1);
     __bf16* Qs = reinterpret_cast<__bf16*>(few_smem_raw);
     __bf16* Ks = Qs + SM::kStage + wave * 2 * SM::kStage;
     __bf16* Vs = Ks + SM::kStage;
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(KW * kWave, 2) void flash_few(const __bf16* __restr
         const int i = wave * QL + u;
         if (LOADS % KW != 0 && i >= LOADS) continue;
         const int r = few_row(i, lane, DH);
-        dma_load16(reinterpret_cast<const char*>(q) + (size_t)qt * few_block_bytes(Hq, DH),
+        dma_load16(reinterpret_cast<const char*>(q) + (size_t)(row0 / kFewKeys) * few_block_bytes(Hq, DH),
                    fa_dma_voff_tail(fa_dma_voff(r, lane, head, Hq, DH, true), r, min(n - row0, 32), Hq, DH),
                    lds_addr(Qs) + (uint32_t)(i * 1024));
     }
@@ -266,23 +266,23 @@ dash_status init_few_kernels() {
 
 template <int DH, int KW>
 static void launch_few(const dash_layer_params& p, const __bf16* q, const __bf16* k, const __bf16* v, const int32_t* pos, int n,
-                       __bf16* o, float scale_log2, uint32_t* clear_words, int n_clear, int32_t* clear_count, hipStream_t s) {
-    const int n_qtiles = (n + 31) / 32;
+                       int row0, __bf16* o, float scale_log2, uint32_t* clear_words, int n_clear, int32_t* clear_count, hipStream_t s) {
+    const int n_qtiles = (n - row0 + 31) / 32;
     unsigned blocks = 0;
     const FaMap mp = fa_map(n_qtiles, p.n_q_heads, p.n_kv_heads, blocks);
     hipLaunchKernelGGL((flash_few<DH, KW>), dim3(blocks), dim3(KW * kWave), FewSmem<DH>::bytes(KW), s, q, k, v, pos, o, n,
-                       p.n_q_heads, p.n_kv_heads, scale_log2, p.causal, n_qtiles, mp, clear_words, n_clear, clear_count);
+                       p.n_q_heads, p.n_kv_heads, scale_log2, p.causal, n_qtiles, mp, clear_words, n_clear, row0, clear_count);
 }
 
-// waves: few_waves (staging_addr.h), 4 or 8
+// Query rows [row0, n), row0 a multiple of 32, against all keys. waves: 4 or 8 (few_waves, staging_addr.h)
 dash_status launch_flash_few(const dash_layer_params& p, const __bf16* q, const __bf16* k, const __bf16* v,
-                             const int32_t* pos, int n, __bf16* o, float scale_log2, int waves, uint32_t* clear_words, int n_clear,
-                             int32_t* clear_count, hipStream_t s) {
+                             const int32_t* pos, int n, int row0, __bf16* o, float scale_log2, int waves, uint32_t* clear_words,
+                             int n_clear, int32_t* clear_count, hipStream_t s) {
     if (init_few_kernels() != DASH_OK) return DASH_ERR_HIP;
     if (p.head_dim == 64)
-        (waves == 8 ? launch_few<64, 8> : launch_few<64, 4>)(p, q, k, v, pos, n, o, scale_log2, clear_words, n_clear, clear_count, s);
+        (waves == 8 ? launch_few<64, 8> : launch_few<64, 4>)(p, q, k, v, pos, n, row0, o, scale_log2, clear_words, n_clear, clear_count, s);
     else
-        (waves == 8 ? launch_few<128, 8> : launch_few<128, 4>)(p, q, k, v, pos, n, o, scale_log2, clear_words, n_clear, clear_count, s);
+        (waves == 8 ? launch_few<128, 8> : launch_few<128, 4>)(p, q, k, v, pos, n, row0, o, scale_log2, clear_words, n_clear, clear_count, s);
     return launch_status();
 }
 

@@ -856,7 +856,7 @@ dash_status launch_flash_fwd(const dash_layer_params& p, const void* q, const vo
     const __bf16 *bq = (const __bf16*)q, *bk = (const __bf16*)k, *bv = (const __bf16*)v;
     const int waves = few_waves(n, p.n_q_heads, p.head_dim, p.causal != 0, compute_units());
     if (waves > 0)
-        return launch_flash_few(p, bq, bk, bv, active_idx, n, (__bf16*)o, scale_log2, waves, clear_words, n_clear, clear_count, s);
+        return launch_flash_few(p, bq, bk, bv, active_idx, n, 0, (__bf16*)o, scale_log2, waves, clear_words, n_clear, clear_count, s);
     const FaForm form = fa_form(n, p.n_q_heads, p.head_dim, p.causal != 0, compute_units());  // staging_addr.h
     const int one_end = form == FA_TWO ? 0 : (form == FA_ONE ? n : n - n % kFaBM);  // rows of the one-group form
     dash_status st = DASH_OK;
@@ -868,6 +868,8 @@ dash_status launch_flash_fwd(const dash_layer_params& p, const void* q, const vo
         n_clear = 0;
         clear_count = nullptr;
     }
+    if (form == FA_ONE_AND_TAIL && fa_few_tail(n, p.n_q_heads, p.head_dim, compute_units()))
+        return launch_flash_few(p, bq, bk, bv, active_idx, n, one_end, (__bf16*)o, scale_log2, 8, clear_words, n_clear, clear_count, s);
     return p.head_dim == 64 ? launch_mfma<64, 2>(p, bq, bk, bv, active_idx, n, one_end, n, (__bf16*)o, scale_log2, clear_words, n_clear, clear_count, s)
                             : launch_mfma<128, 2>(p, bq, bk, bv, active_idx, n, one_end, n, (__bf16*)o, scale_log2, clear_words, n_clear, clear_count, s);
 }

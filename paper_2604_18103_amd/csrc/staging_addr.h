@@ -336,7 +336,13 @@ DASH_HD constexpr int fa_v_lead(int grp) { return grp == 0 ? 0 : 1; }
 //    last whole 256-row tile may also run as a launch of their own in the split form, so that a few of them do not cost a
 //    round of all (4 % lower will do: the whole tiles keep their form): 28 heads of 128: 2400 111 / 101, 14001 7 / 6.67
 //    rounds, 0.967 times; 32 of 128: 4100 298 / 270; 16 of 64: 4097 112 / 107, 8200 354 / 341.
+//    Where the workgroups of those rows are all resident at once, the last rows run in the few-row form (32 rows and 8
+//    key-splitting waves per workgroup, flash_few.hip): a quarter of a round and less. In the split form / so, us: 28 heads of
+//    128 2305 102 / 88, 2559 111 / 95, 4700 317 / 288; 32 of 128 4100 284 / 260; 16 of 64 4097 108 / 91, 4351 114 / 94, 8200 336 / 303.
 enum FaForm { FA_ONE = 0, FA_TWO = 1, FA_ONE_AND_TAIL = 2 };
+inline bool fa_few_tail(int n, int Hq, int head_dim, int cu) {
+    return (long long)((n % kFaBM + 31) / 32) * Hq <= (long long)cu * (head_dim == 64 ? 2 : 1);
+}
 inline FaForm fa_form(int n, int Hq, int head_dim, bool causal, int cu) {
     auto rounds = [&](long long wgs) { return (double)((wgs + cu - 1) / cu); };
     const long long one = (long long)((n + kFaBM - 1) / kFaBM) * Hq, two = (long long)((n + kFaBM / 2 - 1) / (kFaBM / 2)) * Hq;
@@ -344,8 +350,7 @@ inline FaForm fa_form(int n, int Hq, int head_dim, bool causal, int cu) {
     const double t_one = rounds(one), t_two = 0.57 * rounds(two);
     const int tail = n % kFaBM;
     if (tail > 0 && n > kFaBM) {
-        // one active wave per key group (32 rows) takes about two thirds of a full workgroup's time
-        const double t_tail = rounds(one - Hq) + (tail <= 32 ? 0.4 : 0.57 * rounds(tail <= kFaBM / 2 ? Hq : 2 * Hq)) + 0.1;
+        const double t_tail = rounds(one - Hq) + (fa_few_tail(n, Hq, head_dim, cu) ? 0.25 : 0.57 * rounds(tail <= kFaBM / 2 ? Hq : 2 * Hq)) + 0.1;
         if (t_tail < 0.96 * t_one && t_tail < t_two) return FA_ONE_AND_TAIL;
     }
     return t_two < (head_dim == 64 ? 0.96 : 0.94) * t_one ? FA_TWO : FA_ONE;

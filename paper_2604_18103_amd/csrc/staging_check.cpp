@@ -392,6 +392,9 @@ int dash_check_flash_few(int n, int Hkv, int DH, int causal, int waves, long lon
     return c.status;
 }
 
+// Whether the rows beyond the last whole tile take the few-row form (where dash_fa_form is 2).
+int dash_fa_few_tail(int n, int Hq, int head_dim, int cu) { return fa_few_tail(n, Hq, head_dim, cu); }
+
 // Waves of the few-row form, 0 where the tiled kernels run.
 int dash_few_waves(int n, int Hq, int head_dim, int causal, int cu) { return few_waves(n, Hq, head_dim, causal != 0, cu); }
 

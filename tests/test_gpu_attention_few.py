@@ -6,7 +6,7 @@ import torch
 
 from oracle import reference as ref
 from paper_2604_18103_amd import binding as B
-from test_attention_form import TWO
+from test_attention_form import ONE_AND_TAIL, TWO
 from test_gpu_attention_groups import _run
 from test_gpu_infinite_keys import _attention
 from test_staging_addresses import _load
@@ -71,3 +71,12 @@ def test_two_key_groups_beyond_it(n, hq, hkv, dh, causal):
     _run(n, hq, hkv, dh, causal, seed=n, rows=rows)
     for infinite in (slice(64, 128), slice(0, 64)):
         _attention(n, hq, hkv, dh, causal, infinite, n % 2 == 1, rows)
+
+
+@pytest.mark.parametrize("n,hq,hkv,dh,few", [(4129, 16, 4, 64, 1), (4351, 16, 4, 64, 1), (2336, 28, 4, 128, 1), (2559, 28, 4, 128, 1), (1279, 64, 8, 128, 0)])
+def test_the_rows_beyond_the_last_whole_tile(n, hq, hkv, dh, few):
+    """Without a causal mask, 32, 33 and 255 of them, in the few-row form and, where its workgroups would not all be resident, in the split one."""
+    lib = _load()
+    assert lib.dash_fa_form(n, hq, dh, 0, _units()) == ONE_AND_TAIL and lib.dash_fa_few_tail(n, hq, dh, _units()) == few
+    end = n - n % 256
+    _run(n, hq, hkv, dh, False, seed=n, rows=np.unique(np.r_[0, end - 1, end, end + 1, min(end + 31, n - 1), min(end + 32, n - 1), n - 2, n - 1]))
