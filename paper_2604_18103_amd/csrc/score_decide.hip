@@ -63,8 +63,11 @@ constexpr int kSelectBatch = 16;    // scores a thread has in flight per load ba
 // cost the widely spread case 5 % and take a third off the crowded ones; four cost more than they return.
 constexpr int kHistCopies = 2;
 
+constexpr int kListMax = 64;  // so many keys left in a bin are ranked by counting (one wave); more take another pass
 struct SelectShared {
     int hist[kSelectBins][kHistCopies];  // the copies of a bin side by side: in different LDS banks
+    uint32_t list[kListMax], wave_min[kSelectThreads / kWave], wave_max[kSelectThreads / kWave];
+    int n_list;
     int wave_tot[kSelectThreads / kWave];
     uint32_t prefix;
     int remaining, ties;
@@ -120,6 +123,27 @@ __device__ __forceinline__ void select_bin(SelectShared& sh, int shift, uint32_t
     __syncthreads();
     prefix = sh.prefix;
     remaining = sh.remaining;
+}
+
+// Smallest and largest of the threads' values, uniform; ends with a barrier.
+__device__ __forceinline__ void range_of_keys(SelectShared& sh, uint32_t& kmin, uint32_t& kmax) {
+    constexpr int kWaves = kSelectThreads / kWave;
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o));
+        kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o));
+    }
+    if (lane == 0) {
+        sh.wave_min[wave] = kmin;
+        sh.wave_max[wave] = kmax;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        kmin = min(kmin, sh.wave_min[w]);
+        kmax = max(kmax, sh.wave_max[w]);
+    }
 }
 
 __device__ __forceinline__ int pass_shift(int pass) { return pass == 0 ? 21 : (pass == 1 ? 10 : 0); }
@@ -256,13 +280,19 @@ __global__ __launch_bounds__(256) void topk_flag_kernel(const float* __restrict_
 }
 
 // TopK decision (Eq. 3) of up to 1024 * B rows in ONE launch of one workgroup: selection and flags together.
-// Thread t holds the keys of rows u * 1024 + t (u < B) in registers, so the scores are read once: the three radix
-// passes, the flags and the kept counts per 64-row chunk (chunk u * 16 + w is what wave w holds at step u) all work
+// Thread t holds the keys of rows u * 1024 + t (u < B) in registers, so the scores are read once: the passes, the flags and the
+// kept counts per 64-row chunk (chunk u * 16 + w is what wave w holds at step u) all work
 // from those registers. Same total order, same tie rule (earliest rows first) and same outputs as the
-// topk_select_kernel + topk_flag_kernel pair, which serves longer inputs. One compute unit does all of it, so the
-// time is that unit's instruction throughput (about 20 vector instructions per row over the three passes and the
-// flags), not memory: 16-byte loads with four flags per store, and the keys in LDS under short rolled loops,
-// measured slower than this plain form.
+// topk_select_kernel + topk_flag_kernel pair, which serves longer inputs.
+// The bins of the first pass are 2048 equal steps over the keys' own range, not their top digits: the scores of a layer span a few
+// octaves, so top digits put them into a few dozen bins, whose adds LDS does one after the other, and leave two more passes. Over
+// their range the wanted bin is left with a handful of keys, of which the wanted one is found by counting. A bin that keeps more
+// (an outlier stretched the range, or ties) takes another pass of 2048 steps inside it, three in all at most.
+// One compute unit does all of it, so the time is latencies (launch, loads, range, pass, search, flags: 7 us for any few rows) and
+// from 8192 rows on that unit's instruction throughput. Heavy-tailed scores, us, top digits in three passes / this: 64 rows 8.9 /
+// 6.9, 2120 9.0 / 7.4, 8192 9.6 / 8.1, 16384 13.4 / 12.0; all within a few percent of each other 11.2 / 8.1 at 8192, 16.6 / 11.9 at
+// 16384; all equal 19.8 / 11.0 and 33 / 18; one zero among them (a range of its own, two passes) 9.7 / 9.4.
+// 16-byte loads with four flags per store, and the keys in LDS under short rolled loops, measured slower than this plain form.
 template <int B>
 __global__ __launch_bounds__(kSelectThreads) void topk_decide_small_kernel(
     const float* __restrict__ scores, int n, int n_first, int n_last, int k_keep, int keep_low,
@@ -289,22 +319,63 @@ __global__ __launch_bounds__(kSelectThreads) void topk_decide_small_kernel(
     int quota = 0;
     bool rank_ties = false;
     if (k_cand > 0) {
-        uint32_t prefix = 0u;
-        int remaining = k_cand;
+        // The bins cover the candidates' own range: 2048 equal steps of the keys from the smallest to the largest.
+        uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+            if ((cand >> u) & 1u) {
+                kmin = min(kmin, key[u]);
+                kmax = max(kmax, key[u]);
+            }
+        clear_hist(sh);
+        if (tid == 0) sh.n_list = 0;
+        range_of_keys(sh, kmin, kmax);  // ends with a barrier
+        uint32_t base = kmin;           // keys of interest: (key - base) >> width is 0
+        int width = 32;
+        int shift = max(0, 32 - __clz((int)(kmax - kmin)) - 11);
+        int remaining = k_cand, in_bin = n_cand;
 #pragma unroll 1
-        for (int pass = 0; pass < 3; ++pass) {
-            const int shift = pass_shift(pass);
-            const uint32_t digit_mask = pass_digit_mask(pass), hi_mask = pass_high_mask(pass);
-            clear_hist(sh);
-            __syncthreads();
+        for (;;) {
+            const uint32_t span = width >= 32 ? 0xFFFFFFFFu : (1u << width) - 1u;
 #pragma unroll
             for (int u = 0; u < B; ++u)
-                if (((cand >> u) & 1u) && (key[u] & hi_mask) == prefix)
-                    hist_add(sh, (key[u] >> shift) & digit_mask);
+                if (((cand >> u) & 1u) && key[u] - base <= span) hist_add(sh, (key[u] - base) >> shift);
             __syncthreads();
-            select_bin(sh, shift, prefix, remaining);
+            uint32_t bin = 0u;
+            select_bin(sh, 0, bin, remaining);
+            base += bin << shift;
+            width = shift;
+            in_bin = sh.ties;
+            if (shift == 0 || in_bin <= kListMax) break;
+            clear_hist(sh);
+            shift = max(0, shift - 11);
+            __syncthreads();
         }
-        T = prefix;
+        if (width > 0) {
+            // few keys are left in the bin: the wanted one by counting
+            const uint32_t span = (1u << width) - 1u;
+#pragma unroll
+            for (int u = 0; u < B; ++u)
+                if (((cand >> u) & 1u) && key[u] - base <= span) sh.list[atomicAdd(&sh.n_list, 1)] = key[u];
+            __syncthreads();
+            if (tid < in_bin) {
+                const uint32_t mine = sh.list[tid];
+                int greater = 0, same = 0;
+                for (int i = 0; i < in_bin; ++i) {
+                    greater += sh.list[i] > mine;
+                    same += sh.list[i] == mine;
+                }
+                if (greater < remaining && remaining <= greater + same) {  // every holder of that key writes the same
+                    sh.prefix = mine;
+                    sh.remaining = remaining - greater;
+                    sh.ties = same;
+                }
+            }
+            __syncthreads();
+            base = sh.prefix;
+            remaining = sh.remaining;
+        }
+        T = base;
         quota = remaining;               // >= 1: ties (key == T) still to be kept
         rank_ties = sh.ties > remaining; // more rows tie with the K-th key than may be kept
     }
@@ -418,7 +489,7 @@ dash_status topk_static_scratch_ptr(void** out) {
 }
 
 // The TopK decision on n > 0 scores: up to 16384 rows in one launch that keeps the keys in registers (when the
-// caller allows it: 9 us at 8192 rows, 12.6 at 16384, where the two launches take 14; at 32768 rows it would take 23
+// caller allows it: 8 us at 8192 rows, 12 at 16384, where the two launches take 14; at 32768 rows it would take 23
 // against their 20, the flags of the longer input being spread over many workgroups), longer inputs by the selection
 // kernel, which leaves its state and tie counts in ws, and the flag kernel.
 static void launch_topk(const float* scores, int n, int n_first, int n_last, int k_keep, int keep_low, uint8_t* halt,
