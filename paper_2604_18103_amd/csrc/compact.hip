@@ -28,6 +28,21 @@ __device__ __forceinline__ int wave_sum_int(int v) {
     return v;
 }
 
+// Rows that compact_kernel gathers go by the caches (non-temporal loads and stores): each is read and written once, and what they
+// displaced, the rows that are still to be gathered or scattered and the next launches' operands, is worth more there. Measured
+// with inputs that change from pass to pass, plain / loads and stores by the caches, us: block-level signal path (scores, TopK, gather, scatter) of
+// 16384 rows of 3584 109 / 88, with a reader of the gathered rows behind it 149 / 142, 60000 rows 365 / 304 and 531 / 493, 1000 rows
+// 24 / 22 and 27 / 25.5; the chain of eight layers from 32768 rows the same (23.13 ms). The one-launch kernel below keeps plain ones: its rows were written
+// by the projection right before (8192 rows 0.3 % faster without, 16384 0.15 % slower).
+__device__ __forceinline__ uint4 load_once(const uint4* p) {
+    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+    return make_uint4(v[0], v[1], v[2], v[3]);
+}
+__device__ __forceinline__ void store_once(uint4* p, uint4 v) {
+    const u32x4 w = {v.x, v.y, v.z, v.w};
+    __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(p));
+}
+
 constexpr int kCompactThreads = 256;
 constexpr int kCompactWaves = kCompactThreads / kWave;
 
@@ -80,9 +95,9 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(
         for (int c = v0 + lane; c < v1; c += kWave) {
             uint4 val[R];
 #pragma unroll
-            for (int i = 0; i < R; ++i) val[i] = src[i][c];
+            for (int i = 0; i < R; ++i) val[i] = load_once(src[i] + c);
 #pragma unroll
-            for (int i = 0; i < R; ++i) dst[i][c] = val[i];
+            for (int i = 0; i < R; ++i) store_once(dst[i] + c, val[i]);
         }
     }
 }
@@ -501,7 +516,8 @@ dash_status launch_validate_idx(const int32_t* idx, int n, int N, int32_t* viola
 
 // Halted tokens keep the state they had when they halted (Sec. 3.4): selected rows are written to a
 // full-length buffer at their original positions. One wave per row, 16-byte vectors; rows whose position
-// lies outside [0, N) are skipped.
+// lies outside [0, N) are skipped. The buffer is read when the prompt is done: its rows are stored by the caches (with the signal's
+// x_old loaded so, the signal path of 16384 rows 118 -> 107.5 us).
 template <typename T>
 __global__ __launch_bounds__(256) void scatter_rows_kernel(const T* __restrict__ rows, const int32_t* __restrict__ idx,
                                                            const uint8_t* __restrict__ sel, int sel_value, int n,
@@ -515,7 +531,7 @@ __global__ __launch_bounds__(256) void scatter_rows_kernel(const T* __restrict__
     if (p < 0 || p >= N) return;
     const u32x4* src = reinterpret_cast<const u32x4*>(rows + (size_t)row * d);
     u32x4* dst = reinterpret_cast<u32x4*>(full + (size_t)p * d);
-    for (int c = lane; c < d / VEC; c += kWave) dst[c] = src[c];
+    for (int c = lane; c < d / VEC; c += kWave) __builtin_nontemporal_store(src[c], dst + c);
 }
 
 dash_status launch_scatter_rows(const void* rows, const int32_t* idx, const uint8_t* sel, int sel_value, int n,

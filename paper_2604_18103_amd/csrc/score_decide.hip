@@ -544,7 +544,10 @@ dash_status launch_decide_topk(const dash_layer_params& p, const float* scores, 
 }
 
 // Block-level signal of the ablation (Sec. 5.4): Eq. 2 on the change of a row across a whole block,
-// ||x_new - x_old||_2, optionally relative to ||x_old||_2. One wave per row, 16-byte loads, two reads per element.
+// ||x_new - x_old||_2, optionally relative to ||x_old||_2. One wave per row, 16-byte loads, two reads per element. HBM-bound:
+// 235 MB at 16384 rows of 3584 in 51 us. x_old is not needed after this and is loaded by the caches, so that x_new, whose rows are
+// gathered and scattered next, stays in the last-level cache (whole path 118 -> 113.5 us). Four pieces of either row in flight per
+// lane instead of the compiler's order: no change.
 template <typename T>
 __global__ __launch_bounds__(256) void score_diff_rows_kernel(const T* __restrict__ x_new, const T* __restrict__ x_old,
                                                               int n, int d, int kind, float* __restrict__ scores) {
@@ -558,7 +561,7 @@ __global__ __launch_bounds__(256) void score_diff_rows_kernel(const T* __restric
     for (int c = lane * VEC; c < d; c += kWave * VEC) {  // d % VEC == 0 is checked by the caller
         T va[VEC], vb[VEC];
         *reinterpret_cast<u32x4*>(va) = *reinterpret_cast<const u32x4*>(a + c);
-        *reinterpret_cast<u32x4*>(vb) = *reinterpret_cast<const u32x4*>(b + c);
+        *reinterpret_cast<u32x4*>(vb) = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(b + c));
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
             const float o = to_float(vb[e]), df = to_float(va[e]) - o;
