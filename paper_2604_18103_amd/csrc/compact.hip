@@ -28,12 +28,12 @@ __device__ __forceinline__ int wave_sum_int(int v) {
     return v;
 }
 
-// Rows that compact_kernel gathers go by the caches (non-temporal loads and stores): each is read and written once, and what they
+// Gathered rows go by the caches (non-temporal loads and stores): each is read and written once, and what they
 // displaced, the rows that are still to be gathered or scattered and the next launches' operands, is worth more there. Measured
 // with inputs that change from pass to pass, plain / loads and stores by the caches, us: block-level signal path (scores, TopK, gather, scatter) of
 // 16384 rows of 3584 109 / 88, with a reader of the gathered rows behind it 149 / 142, 60000 rows 365 / 304 and 531 / 493, 1000 rows
-// 24 / 22 and 27 / 25.5; the chain of eight layers from 32768 rows the same (23.13 ms). The one-launch kernel below keeps plain ones: its rows were written
-// by the projection right before (8192 rows 0.3 % faster without, 16384 0.15 % slower).
+// 24 / 22 and 27 / 25.5; the chain of eight layers from 32768 rows the same (23.13 ms). In the layer call's one launch (THRESHOLD, 28 heads, width
+// 3584): 1000 rows 70 / 64.7, 1500 96.6 / 90.5, 3000 167.6 / 162.5, 12000 1093 / 1086, 16384 the same.
 __device__ __forceinline__ uint4 load_once(const uint4* p) {
     const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
     return make_uint4(v[0], v[1], v[2], v[3]);
@@ -317,9 +317,9 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
         for (int c = v0 + lane; c < v1; c += kWave) {
             uint4 val[R];
 #pragma unroll
-            for (int i = 0; i < R; ++i) val[i] = src[i][c];
+            for (int i = 0; i < R; ++i) val[i] = load_once(src[i] + c);
 #pragma unroll
-            for (int i = 0; i < R; ++i) dst[i][c] = val[i];
+            for (int i = 0; i < R; ++i) store_once(dst[i] + c, val[i]);
         }
     }
 }
@@ -421,9 +421,9 @@ __global__ __launch_bounds__(kFewThreads) void topk_compact_few_kernel(
         for (int c = v0 + lane; c < v1; c += kWave) {
             uint4 val[R];
 #pragma unroll
-            for (int i = 0; i < R; ++i) val[i] = from[i][c];
+            for (int i = 0; i < R; ++i) val[i] = load_once(from[i] + c);
 #pragma unroll
-            for (int i = 0; i < R; ++i) to[i][c] = val[i];
+            for (int i = 0; i < R; ++i) store_once(to[i] + c, val[i]);
         }
     }
 }
