@@ -110,6 +110,91 @@ __global__ __launch_bounds__(kF32Split * kWave) void wo_f32_kernel(const float* 
 }
 
 // ------------------------------------------------------------------------------------------------
+// The same on tiles of 16 rows x 64 columns, where those are no more than the compute units: with 32-row tiles 512 rows of 256
+// occupied 64 units with twice the serial work. The same split of K, so the same sums. A wave has four chunks in flight (in the
+// kernel above the compiler moves the next chunk's loads to their use; where many workgroups share a unit, that and the fewer
+// registers are the faster way: four chunks in flight there cost 10 to 35 %), and x is asked for before the product. Measured, 32-row
+// tiles / these, us, K = N: 512 rows of 256 6.2 / 4.9, of 512 8.9 / 6.8, 177 of 1024 13.7 / 10.4, 63 of 3584 42 / 27.6; with more tiles
+// than units 257 rows of 1024 13.8 / 16.1, 1100 of 256 6.4 / 7.2.
+// ------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(kF32Split * kWave) void wo_f32_few_kernel(const float* __restrict__ A, const float* __restrict__ B,
+                                                                       const float* __restrict__ x, int M, int K, int N,
+                                                                       float* __restrict__ x_next, float* __restrict__ partials,
+                                                                       float* __restrict__ delta_dbg) {
+    __shared__ float part[kF32Split][16][kF32TileN + 4];
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int i = lane % 16, g = lane / 16;
+    const int m0 = (int)blockIdx.y * 16, n0 = blockIdx.x * kF32TileN;
+    // the epilogue's thread: 16 per row, four columns each; x is asked for before the product
+    const int lr = tid / 16, gm = m0 + lr, gn = n0 + 4 * (tid % 16);
+    const bool has_row = tid < 256, ok = has_row && gm < M && gn < N;
+    f32x4 xv = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (ok) xv = *reinterpret_cast<const f32x4*>(x + (size_t)gm * N + gn);
+    f32x4 acc[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // rows beyond M and columns beyond N are computed on clamped addresses and never stored (K % 16 == 0, N % 4 == 0)
+    const float* ap = A + (size_t)min(m0 + i, M - 1) * K + 4 * g;
+    const float* bp = B + (size_t)(4 * g) * N + min(n0 + 4 * i, N - 4);
+    struct Chunk {
+        f32x4 a, b[4];
+    };
+    auto load = [&](int k0, Chunk& c) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) c.b[s] = *reinterpret_cast<const f32x4*>(bp + (size_t)(k0 + s) * N);
+        c.a = *reinterpret_cast<const f32x4*>(ap + k0);
+    };
+    auto multiply = [&](const Chunk& c) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(c.a[s], c.b[s][e], acc[e], 0, 0, 0);
+    };
+    // The chunks of a wave in order, kAhead of them in flight; the conditions are scalar, so each is a load of its own kind and not
+    // moved to its use.
+    constexpr int kAhead = 4, kStep = 16 * kF32Split;
+    Chunk c[kAhead];
+    int k0 = 16 * wave;
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+        if (k0 + u * kStep < K) load(k0 + u * kStep, c[u]);
+    for (; k0 < K; k0 += kAhead * kStep) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            if (k0 + u * kStep < K) {
+                multiply(c[u]);
+                if (k0 + (u + kAhead) * kStep < K) load(k0 + (u + kAhead) * kStep, c[u]);
+            }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        *reinterpret_cast<f32x4*>(&part[wave][4 * g + r][4 * i]) = f32x4{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+    __syncthreads();
+    if (!has_row) return;  // whole waves
+    f32x4 d = *reinterpret_cast<const f32x4*>(&part[0][lr][4 * (tid % 16)]);
+#pragma unroll
+    for (int w = 1; w < kF32Split; ++w) d += *reinterpret_cast<const f32x4*>(&part[w][lr][4 * (tid % 16)]);
+    float sd = 0.f, sx = 0.f;
+    if (ok) {
+        *reinterpret_cast<f32x4*>(x_next + (size_t)gm * N + gn) = xv + d;
+        if (delta_dbg) *reinterpret_cast<f32x4*>(delta_dbg + (size_t)gm * N + gn) = d;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            sd = fmaf(d[e], d[e], sd);
+            sx = fmaf(xv[e], xv[e], sx);
+        }
+    }
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) {
+        sd += __shfl_xor(sd, off);
+        sx += __shfl_xor(sx, off);
+    }
+    if (tid % 16 == 0 && gm < M)
+        *reinterpret_cast<float2*>(partials + ((size_t)blockIdx.x * M + gm) * 2) = make_float2(sd, sx);
+}
+
+// ------------------------------------------------------------------------------------------------
 // MFMA kernel (bf16): C[M,N] = A[M,K] B[K,N], A and B row-major.
 // Workgroup tile 256x256, K step 64; 8 waves in 2 (M) x 4 (N), two per SIMD, each wave 128x64 = 8x4 blocks of
 // v_mfma_f32_16x16x32_bf16 (128 fp32 accumulator registers per lane). On normally distributed operands the part
@@ -1282,6 +1367,13 @@ dash_status launch_wo_residual_rownorm(const dash_layer_params& p, const void* o
     if (n == 0) return DASH_OK;
     const int K = p.n_q_heads * p.head_dim, N = p.d;
     if (p.dtype == DASH_F32) {
+        const int64_t col_tiles = (N + kF32TileN - 1) / kF32TileN;
+        if (((int64_t)n + 15) / 16 * col_tiles <= compute_units()) {
+            hipLaunchKernelGGL(wo_f32_few_kernel, dim3((unsigned)col_tiles, (n + 15) / 16), dim3(kF32Split * kWave), 0, s, (const float*)o,
+                               (const float*)w_o, (const float*)x, n, K, N, (float*)x_next, partials, delta_dbg);
+            if (sums) *sums = NormSums{partials, norm_partials_per_row(N, p.dtype), 1};
+            return launch_status();
+        }
         // a launch has at most 65535 workgroups along y: more row tiles go along z in slices
         constexpr int64_t kSlice = 32768;
         const int64_t row_tiles = ((int64_t)n + kF32TileM - 1) / kF32TileM;
