@@ -27,7 +27,7 @@ DASH_HD int sa_max(int a, int b) { return a > b ? a : b; }
 constexpr int kGM = 256, kGN = 256, kGK = 64;
 constexpr int kGWaves = 8;
 
-DASH_HD constexpr int gemm_adma(int BM) { return BM / 8 / 8; }   // A load instructions per wave and K step
+DASH_HD constexpr int gemm_adma(int BM) { return (BM / 8 + kGWaves - 1) / kGWaves; }  // A load instructions per wave and K step
 DASH_HD constexpr int gemm_bdma() { return kGK / 2 / 8; }         // B load instructions per wave and K step
 
 DASH_HD int gemm_a_row(int wave, int i, int lane, int adma) { return (wave * adma + i) * 8 + lane / 8; }
@@ -130,6 +130,31 @@ inline GemmPlan gemm_plan(int M, int K, int N, int cu, bool may_split, size_t sp
     g.seg = (g.full + 7) / 8;
     g.grid = g.plain ? g.full : 8 * g.seg;
     return g;
+}
+
+// Lower tiles for a round that 256-row tiles would fill by more than half but not quite: its workgroups then take 32 rb / 256 of the
+// time, on more units. On the workload's data the part is power-limited and runs faster while units idle, so half of that is
+// what is gained, less a launch where whole rounds go before it.
+//  - products of one round: the lowest tile that still fits it. Measured, 256-row tiles / these, us, K = N = 3584: 2400 rows 82 / 67,
+//    3000 78 / 71, 3400 80 / 76 (192 rows), 3700 84 / 82.5 (224); K = 18944 2400 330 / 281, 3700 410 / 400; 3584 x 4608 with the row
+//    norm's launch 1800 74 / 64; 1024 x 1024 9000 30.5 / 26.7. Not 224 rows where the row tiles are a multiple of 8 and the columns
+//    few: the plain tile order, which lets an XCD share row panels, is worth more (8192 x 1024 x 1536 34.6 / 36.0).
+//  - the last of several rounds, for long contractions: K = 18944, N = 3584: 7500 rows 853 / 792, 8192 860 / 845, 11885 1312 / 1239,
+//    13000 1339 / 1300; at K = 3584 it is within the noise (11885 260 / 253, 8192 169 / 175).
+// All rounds on lower tiles is slower: 10000 rows of K = 18944 1046 / 1169.
+struct RowPlan {
+    int rb, whole;  // 16-row blocks per wave of the lower tiles (0: none), 256-row row tiles before them
+};
+inline RowPlan row_plan(const GemmPlan& g, int M, int cu) {
+    if (cu <= 0 || g.parts >= 2 || g.rest > 0) return RowPlan{0, 0};
+    const int rounds = (g.tiles + cu - 1) / cu, whole = (int)((long long)(rounds - 1) * cu / g.nt);
+    for (int rb = 6; rb <= 7; ++rb) {
+        const long long t = (long long)((M - whole * kGM + 32 * rb - 1) / (32 * rb)) * g.nt;
+        const double gain_us = 0.5 * (1.0 - rb / 8.0) * g.ksteps * 1.66;
+        if (rb == 7 && g.plain && g.nt < 8) continue;
+        if (t <= cu && (whole == 0 || gain_us > 20.0)) return RowPlan{rb, whole};
+    }
+    return RowPlan{0, 0};
 }
 
 // Tile index that workgroup b of the whole-tile launch takes, or -1 (padding of the last stretch: the workgroup leaves).

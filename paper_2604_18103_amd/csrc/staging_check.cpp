@@ -153,6 +153,53 @@ void dash_gemm_launch_plan(int M, int K, int N, int cu, unsigned long long split
     out[5] = g.rest; out[6] = g.plain; out[7] = g.grid;
 }
 
+// The lower tiles of a round (row_plan): out[0..1] = 16-row blocks per wave (0: none), 256-row row tiles before them.
+void dash_row_plan(int M, int K, int N, int cu, unsigned long long split_bytes, int* out) {
+    const RowPlan r = row_plan(gemm_plan(M, K, N, cu, split_bytes > 0, (size_t)split_bytes), M, cu);
+    out[0] = r.rb; out[1] = r.whole;
+}
+
+// Checks the launch of rows [row0, row1) on tiles of 32 rb rows: every tile is taken once, every row lies in one tile, the lower
+// tiles' launch fits one round, every load of the A tile fetches the clamped row and fills the tile's rows.
+int dash_check_rows(int M, int K, int N, int row0, int row1, int rb) {
+    Counter c;
+    const int BM = 32 * rb, mt = (row1 - row0 + BM - 1) / BM, nt = (N + kGN - 1) / kGN, full = mt * nt, seg = (full + 7) / 8;
+    const bool plain = mt % 8 == 0;
+    if (row0 % kGM != 0 || row1 > M || (row1 < M && (row1 - row0) % BM != 0)) c.fail(1);
+    std::vector<int> taken((size_t)full, 0);
+    for (int b = 0; b < (plain ? full : 8 * seg); ++b) {
+        const int idx = gemm_index_of(b, full, plain, seg);
+        if (idx < 0) continue;
+        if (idx >= full) { c.fail(2); continue; }
+        int tm = -1, tn = -1;
+        gemm_tile_of(idx, mt, nt, plain, tm, tn);
+        if (tm < 0 || tm >= mt || tn < 0 || tn >= nt) { c.fail(3); continue; }
+        ++taken[(size_t)tn * mt + tm];
+    }
+    for (const int t : taken)
+        if (t != 1) c.fail(4);
+    const int adma = gemm_adma(BM), rows = 8 * kGWaves * adma;  // fetched rows: at least the tile's
+    for (int tm = 0; tm < mt; ++tm) {
+        const int m0 = row0 + tm * BM;
+        if (m0 >= M) c.fail(5);
+        std::vector<char> seen((size_t)rows * 8, 0);
+        for (int wave = 0; wave < kGWaves; ++wave)
+            for (int lane = 0; lane < 64; ++lane)
+                for (int i = 0; i < adma; ++i) {
+                    const int row = gemm_a_row(wave, i, lane, adma), lchunk = gemm_a_lchunk(row, lane);
+                    if (row < 0 || row >= rows || lchunk < 0 || lchunk >= 8) { c.fail(6); continue; }
+                    seen[(size_t)row * 8 + lchunk] = 1;
+                    const uint64_t addr = (uint64_t)gemm_a_base_elem(m0, M, K, 0) * 2 + gemm_a_off(m0, M, K, row, lchunk);
+                    if (addr != ((uint64_t)sa_min(m0 + row, M - 1) * K + lchunk * 8) * 2) c.fail(7);
+                    if (addr + (uint64_t)(K / kGK - 1) * gemm_a_step_bytes() + 16 > (uint64_t)M * K * 2) c.fail(8);
+                }
+        for (const char s : seen)
+            if (!s) c.fail(9);
+    }
+    if (rows < BM || (rb == 8 && rows != BM)) c.fail(10);
+    return c.status;
+}
+
 // The workgroups of a small-tile launch of `tiles` tiles in `parts` K parts: the most that one XCD gets, or -1 if some tile of
 // some part is not taken exactly once.
 int dash_small_deal(int tiles, int parts) {

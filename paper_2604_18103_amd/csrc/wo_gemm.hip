@@ -210,16 +210,17 @@ __global__ __launch_bounds__(kF32Split * kWave) void wo_f32_few_kernel(const flo
 // ------------------------------------------------------------------------------------------------
 constexpr int kGThreads = kGWaves * kWave;  // tile constants kGM, kGN, kGK: staging_addr.h
 constexpr int kGBElems = kGK * kGN;
-// Operand stages in LDS: a stage holds the A tile (64 MB rows) and the B tile of one K step. The 256-row tile has
+// Operand stages in LDS: a stage holds the A tile (32 RB rows, whole load instructions of every wave: the 224-row tile fetches 256)
+// and the B tile of one K step. The 256-row tile has
 // two stages (128 KB): the tiles of step k + 2 are requested once every wave is done with step k. The 128-row half
 // tile has three (144 KB) and requests three steps ahead: its steps are half as long, and with only one step of
 // lead it waited for memory latency at every step.
-constexpr int gemm_stages(int MB) { return MB == 2 ? 3 : 2; }
-constexpr int gemm_stage_elems(int MB) { return 64 * MB * kGK + kGBElems; }
-constexpr size_t gemm_smem_bytes(int MB) { return (size_t)gemm_stages(MB) * gemm_stage_elems(MB) * sizeof(__bf16); }
+constexpr int gemm_stages(int RB) { return RB == 4 ? 3 : 2; }
+constexpr int gemm_stage_elems(int RB) { return 8 * kGWaves * gemm_adma(32 * RB) * kGK + kGBElems; }
+constexpr size_t gemm_smem_bytes(int RB) { return (size_t)gemm_stages(RB) * gemm_stage_elems(RB) * sizeof(__bf16); }
 constexpr int kEpiStr = 64 + 4;  // fp32 words per staged epilogue row (conflict-free 16-byte reads of two rows by 16 lanes)
-static_assert(gemm_smem_bytes(4) >= 8 * 32 * kEpiStr * sizeof(float) + 4 * kGM * 2 * sizeof(float) &&
-                  gemm_smem_bytes(2) >= 8 * 32 * kEpiStr * sizeof(float) + 4 * kGM * 2 * sizeof(float),
+static_assert(gemm_smem_bytes(6) >= 8 * 32 * kEpiStr * sizeof(float) + 4 * kGM * 2 * sizeof(float) &&
+                  gemm_smem_bytes(4) >= 8 * 32 * kEpiStr * sizeof(float) + 4 * kGM * 2 * sizeof(float),
               "epilogue staging and the row-sum exchange must fit");
 
 
@@ -268,16 +269,17 @@ __device__ __forceinline__ __bf16* qkv_dst(__bf16* q, const QkvOut& o, int row, 
 // How the workgroups of a launch map to tiles (staging_addr.h: GemmPlan, gemm_index_of, gemm_tile_of).
 struct GemmLaunch {
     int mt, nt, ksteps;
-    int full, plain, seg;   // the launch of 256-row tiles (MB = 4): tile order and indices per XCD
-    int first_tile;         // MB = 2: half tiles start at this tile index
+    int full, plain, seg;   // the launch of whole tiles: tile order and indices per XCD
+    int first_tile;         // half tiles start at this tile index
+    int row0;               // first row of the tiles (not half tiles)
     int ksteps_per_split;   // EPI_SPLITK: K steps per part (part = blockIdx.y)
 };
 
-// MB = 32-row blocks per wave: 4 gives the 256-row tile, 2 a 128-row half tile. Half tiles finish the
-// grid: when the 256-row tiles do not fill a whole number of rounds over the compute units, the tiles of
+// RB = 16-row blocks per wave: 8 gives the 256-row tile, 7 and 6 tiles of 224 and 192 rows (RowPlan), 4 a 128-row half tile. Half
+// tiles finish the grid: when the 256-row tiles do not fill a whole number of rounds over the compute units, the tiles of
 // the last, partly filled round are cut in two so that twice as many units share them: workgroup b of that
 // second launch handles half b % 2 of tile first_tile + b / 2.
-template <int EPI, int MB>
+template <int EPI, int RB>
 __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* __restrict__ A,
                                                                  const __bf16* __restrict__ B, int M, int K,
                                                                  int N, const __bf16* __restrict__ x,
@@ -285,9 +287,10 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
                                                                  float* __restrict__ partials,
                                                                  float* __restrict__ f32_out,  // delta (debug) or split sums
                                                                  GemmLaunch L, QkvOut qkv) {
-    constexpr int BM = 64 * MB;   // rows of this workgroup's tile
-    constexpr int WM = 32 * MB;   // rows of a wave's tile
-    constexpr int NS = gemm_stages(MB), kAElems = BM * kGK, kStageElems = gemm_stage_elems(MB);
+    constexpr int BM = 32 * RB;   // rows of this workgroup's tile
+    constexpr int WM = 16 * RB;   // rows of a wave's tile
+    constexpr bool HALF = RB == 4;
+    constexpr int NS = gemm_stages(RB), kStageElems = gemm_stage_elems(RB), kAElems = kStageElems - kGBElems;
     extern __shared__ __attribute__((aligned(16))) unsigned char gemm_smem_raw[];
     __bf16* smem = reinterpret_cast<__bf16*>(gemm_smem_raw);
     const int tid = threadIdx.x, lane = tid % kWave;
@@ -296,10 +299,10 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
     // this workgroup's tile and K steps
     int tile_idx, ks0 = 0, n_ksteps = L.ksteps;
     if (EPI == EPI_SPLITK) {
-        tile_idx = MB == 2 ? L.first_tile + (int)blockIdx.x / 2 : (int)blockIdx.x;
+        tile_idx = HALF ? L.first_tile + (int)blockIdx.x / 2 : (int)blockIdx.x;
         ks0 = (int)blockIdx.y * L.ksteps_per_split;
         n_ksteps = min(L.ksteps_per_split, L.ksteps - ks0);
-    } else if (MB == 2) {
+    } else if (HALF) {
         tile_idx = L.first_tile + (int)blockIdx.x / 2;
     } else {
         tile_idx = gemm_index_of((int)blockIdx.x, L.full, L.plain != 0, L.seg);
@@ -307,9 +310,8 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
     }
     int tile_m, tile_n;
     gemm_tile_of(tile_idx, L.mt, L.nt, L.plain != 0, tile_m, tile_n);
-    const int m0 = tile_m * kGM + (MB == 4 ? 0 : ((int)blockIdx.x % 2) * BM), n0 = tile_n * kGN;
+    const int m0 = HALF ? tile_m * kGM + ((int)blockIdx.x % 2) * BM : L.row0 + tile_m * BM, n0 = tile_n * kGN;
 
-    constexpr int RB = 2 * MB;  // 16-row blocks of the wave's tile; 4 column blocks of 16
     f32x4 acc[RB][4];
 #pragma unroll
     for (int a = 0; a < RB; ++a)
@@ -446,6 +448,7 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
         const int row = wm * WM + 16 * a + fi;
         af[a] = *reinterpret_cast<const bf16x8*>(&sa[row * kGK + ((4 * ks + fg) ^ ((row / 2) % 8)) * 8]);
     };
+    constexpr int kGroup = MF % 8 == 0 ? MF / 8 : 4;
     constexpr int kRequestEvery = 3;  // MFMAs from one tile request to the next
     static_assert((kStepLoads - 1) * kRequestEvery < MF, "the requests of a step fit into its second half");
     auto second_half = [&](int st_next, bool request, int st_free) {
@@ -466,7 +469,7 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
                     else read_a_frag(st_next, 0, u - 4, Af[0]);
                 }
             acc[m / 4][m % 4] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Af[1][m / 4], Bf[1][m % 4], acc[m / 4][m % 4], 0, 0, 0);
-            if (m % (MF / 8) == MF / 8 - 1) __builtin_amdgcn_sched_barrier(0);
+            if (m % kGroup == kGroup - 1) __builtin_amdgcn_sched_barrier(0);
         }
         if (request) {
             a_base += gemm_a_step_bytes();
@@ -516,17 +519,18 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
             dst[step] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(x + (size_t)gm * N + min(gn_e, N - 8)));
         }
     };
+    constexpr int EB = (RB + 1) / 2;  // 32-row blocks, the last one of 16 rows where RB is odd
     if (EPI == EPI_RESIDUAL_NORM) fetch_x(0, xv[0]);
 #pragma unroll
-    for (int a = 0; a < MB; ++a) {
-        if (EPI == EPI_RESIDUAL_NORM && a + 1 < MB) fetch_x(a + 1, xv[(a + 1) & 1]);
+    for (int a = 0; a < EB; ++a) {
+        if (EPI == EPI_RESIDUAL_NORM && a + 1 < EB) fetch_x(a + 1, xv[(a + 1) & 1]);
 #pragma unroll
         for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
             for (int b = 0; b < 4; ++b)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)  // accumulator register r of a 16x16 block: row 4 g + r, column i
-                    stage[(16 * sb + 4 * fg + r) * kEpiStr + 16 * b + fi] = acc[2 * a + sb][b][r];
+                    if (2 * a + sb < RB) stage[(16 * sb + 4 * fg + r) * kEpiStr + 16 * b + fi] = acc[2 * a + sb < RB ? 2 * a + sb : 0][b][r];
         __syncthreads();  // every wave runs the same epilogue schedule, so the barrier is uniform
         if (EPI == EPI_SWIGLU) {
             // 4 lanes per row: lane c takes gate columns 8c..8c+7 and the up columns 32 + 8c..
@@ -535,6 +539,7 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
 #pragma unroll
             for (int step = 0; step < 2; ++step) {
                 const int lr = 16 * step + s_row;
+                if (32 * a + 16 * step >= WM) break;
                 const int gm = m0 + wm * WM + 32 * a + lr;
                 const f32x4 g0 = *reinterpret_cast<const f32x4*>(&stage[lr * kEpiStr + 8 * s_c]);
                 const f32x4 g1 = *reinterpret_cast<const f32x4*>(&stage[lr * kEpiStr + 8 * s_c + 4]);
@@ -555,6 +560,7 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
 #pragma unroll
         for (int step = 0; step < 4; ++step) {
             const int lr = 8 * step + e_row;
+            if (32 * a + 8 * step >= WM) break;
             const int gm = m0 + wm * WM + 32 * a + lr;
             const f32x4 d0 = *reinterpret_cast<const f32x4*>(&stage[lr * kEpiStr + 8 * e_c8]);
             const f32x4 d1 = *reinterpret_cast<const f32x4*>(&stage[lr * kEpiStr + 8 * e_c8 + 4]);
@@ -588,7 +594,7 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
             } else if (EPI == EPI_SPLITK) {
                 if (ok) {
                     // whole products: [part][M][N]; left-over half tiles: [part][half tile][128][256]
-                    float* dst = MB == 2 ? f32_out + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * rest_sum_elems() +
+                    float* dst = HALF ? f32_out + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * rest_sum_elems() +
                                                (size_t)(gm - m0) * kGN + (gn_e - n0)
                                          : f32_out + ((size_t)blockIdx.y * M + gm) * N + gn_e;
                     *reinterpret_cast<f32x4*>(dst) = d0;
@@ -1168,14 +1174,17 @@ int compute_units() {
     return n;
 }
 
-// One-time launch attribute of every instantiation of the MFMA kernel: its dynamic LDS (128 KB, half tiles 144 KB).
+// One-time launch attribute of every instantiation of the MFMA kernel: its dynamic LDS (112 to 144 KB).
+template <int EPI, int RB>
+static hipError_t set_gemm_lds_size(hipError_t e) {
+    return e != hipSuccess ? e : hipFuncSetAttribute((const void*)gemm_mfma_kernel<EPI, RB>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                     (int)gemm_smem_bytes(RB));
+}
 template <int EPI>
-static hipError_t set_gemm_lds_size() {
-    hipError_t e = hipFuncSetAttribute((const void*)gemm_mfma_kernel<EPI, 4>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_smem_bytes(4));
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute((const void*)gemm_mfma_kernel<EPI, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)gemm_smem_bytes(2));
+static hipError_t set_gemm_lds_sizes() {
+    hipError_t e = set_gemm_lds_size<EPI, 4>(set_gemm_lds_size<EPI, 8>(hipSuccess));
+    if constexpr (EPI != EPI_SPLITK) e = set_gemm_lds_size<EPI, 6>(set_gemm_lds_size<EPI, 7>(e));
+    return e;
 }
 
 template <int EPI, int F>
@@ -1195,12 +1204,12 @@ static hipError_t set_small_lds_sizes() {
 
 dash_status init_gemm_kernels() {
     static const hipError_t err = [] {
-        hipError_t e = set_gemm_lds_size<EPI_RESIDUAL_NORM>();
-        if (e == hipSuccess) e = set_gemm_lds_size<EPI_STORE>();
-        if (e == hipSuccess) e = set_gemm_lds_size<EPI_SWIGLU>();
-        if (e == hipSuccess) e = set_gemm_lds_size<EPI_SPLITK>();
-        if (e == hipSuccess) e = set_gemm_lds_size<EPI_QKV>();
-        if (e == hipSuccess) e = set_gemm_lds_size<EPI_QKV_ROPE>();
+        hipError_t e = set_gemm_lds_sizes<EPI_RESIDUAL_NORM>();
+        if (e == hipSuccess) e = set_gemm_lds_sizes<EPI_STORE>();
+        if (e == hipSuccess) e = set_gemm_lds_sizes<EPI_SWIGLU>();
+        if (e == hipSuccess) e = set_gemm_lds_sizes<EPI_SPLITK>();
+        if (e == hipSuccess) e = set_gemm_lds_sizes<EPI_QKV>();
+        if (e == hipSuccess) e = set_gemm_lds_sizes<EPI_QKV_ROPE>();
         if (e == hipSuccess) e = set_small_lds_sizes<EPI_QKV_ROPE>();
         if (e == hipSuccess) e = set_small_lds_sizes<EPI_RESIDUAL_NORM>();
         if (e == hipSuccess) e = set_small_lds_sizes<EPI_STORE>();
@@ -1290,10 +1299,25 @@ static dash_status launch_small(const SmallPlan& g, GemmArgs a, void* scratch, N
     return launch_status();
 }
 
+// Rows [row0, row1) of a product on tiles of 32 RB rows.
+template <int EPI, int RB>
+static void launch_rows(const GemmArgs& a, int row0, int row1, float* delta_dbg, hipStream_t s) {
+    GemmLaunch L{};
+    L.mt = (row1 - row0 + 32 * RB - 1) / (32 * RB);
+    L.nt = (a.N + kGN - 1) / kGN;
+    L.ksteps = a.K / kGK;
+    L.plain = L.mt % 8 == 0;
+    L.full = L.mt * L.nt;
+    L.seg = (L.full + 7) / 8;
+    L.row0 = row0;
+    hipLaunchKernelGGL((gemm_mfma_kernel<EPI, RB>), dim3(L.plain ? L.full : 8 * L.seg), dim3(kGThreads), gemm_smem_bytes(RB), s, a.A,
+                       a.B, a.M, a.K, a.N, a.x, a.out, a.partials, delta_dbg, L, a.qkv);
+}
+
 // Products of few rows: the small tiles (small_plan). Otherwise
 // 256x256 tiles for every whole round over the compute units, in an order that keeps the tiles an XCD runs at one
 // time close together (GemmPlan); if the tiles left over would occupy at most half of the units, they are run as
-// 128-row half tiles by a second launch (same kernel, MB = 2). Products with few tiles are split along K when
+// 128-row half tiles by a second launch (same kernel, RB = 4). Products with few tiles are split along K when
 // `split_ws` (device scratch of `split_bytes`) allows.
 template <int EPI>
 static dash_status launch_gemm(const __bf16* A, const __bf16* B, int M, int K, int N, const __bf16* x,
@@ -1323,15 +1347,21 @@ static dash_status launch_gemm(const __bf16* A, const __bf16* B, int M, int K, i
     if (g.parts >= 2) {
         float* sums = reinterpret_cast<float*>(split_ws);
         L.ksteps_per_split = g.ksteps_per_part;
-        hipLaunchKernelGGL((gemm_mfma_kernel<EPI_SPLITK, 4>), dim3(g.tiles, g.parts), dim3(kGThreads), gemm_smem_bytes(4), s,
+        hipLaunchKernelGGL((gemm_mfma_kernel<EPI_SPLITK, 8>), dim3(g.tiles, g.parts), dim3(kGThreads), gemm_smem_bytes(8), s,
                            A, B, M, K, N, nullptr, nullptr, nullptr, sums, L, qkv);
         launch_splitk_reduce<EPI>(sums, g.parts, args, s);
+        return launch_status();
+    }
+    const RowPlan rows = row_plan(g, M, compute_units());
+    if (rows.rb > 0) {
+        if (rows.whole > 0) launch_rows<EPI, 8>(args, 0, rows.whole * kGM, delta_dbg, s);
+        (rows.rb == 6 ? launch_rows<EPI, 6> : launch_rows<EPI, 7>)(args, rows.whole * kGM, M, delta_dbg, s);
         return launch_status();
     }
     L.full = g.full;
     L.seg = g.seg;
     if (g.full > 0)
-        hipLaunchKernelGGL((gemm_mfma_kernel<EPI, 4>), dim3(g.grid), dim3(kGThreads), gemm_smem_bytes(4), s, A, B, M, K, N, x,
+        hipLaunchKernelGGL((gemm_mfma_kernel<EPI, 8>), dim3(g.grid), dim3(kGThreads), gemm_smem_bytes(8), s, A, B, M, K, N, x,
                            out, partials, delta_dbg, L, qkv);
     if (g.rest > 0) {
         L.first_tile = g.full;
@@ -1339,14 +1369,14 @@ static dash_status launch_gemm(const __bf16* A, const __bf16* B, int M, int K, i
         if (parts >= 2) {
             float* sums = reinterpret_cast<float*>(split_ws);
             L.ksteps_per_split = (g.ksteps + parts - 1) / parts;
-            hipLaunchKernelGGL((gemm_mfma_kernel<EPI_SPLITK, 2>), dim3(2 * g.rest, parts), dim3(kGThreads), gemm_smem_bytes(2), s,
+            hipLaunchKernelGGL((gemm_mfma_kernel<EPI_SPLITK, 4>), dim3(2 * g.rest, parts), dim3(kGThreads), gemm_smem_bytes(4), s,
                                A, B, M, K, N, nullptr, nullptr, nullptr, sums, L, qkv);
             constexpr int kRows = 256 / (EPI == EPI_SWIGLU ? 16 : 32);
             hipLaunchKernelGGL((rest_reduce_kernel<EPI>), dim3(2 * g.rest, kGM / 2 / kRows), dim3(256), 0, s, sums, parts, M, N,
                                x, out, partials, L, qkv);
             return launch_status();
         }
-        hipLaunchKernelGGL((gemm_mfma_kernel<EPI, 2>), dim3(2 * g.rest), dim3(kGThreads), gemm_smem_bytes(2), s, A, B, M, K, N,
+        hipLaunchKernelGGL((gemm_mfma_kernel<EPI, 4>), dim3(2 * g.rest), dim3(kGThreads), gemm_smem_bytes(4), s, A, B, M, K, N,
                            x, out, partials, delta_dbg, L, qkv);
     }
     return launch_status();
