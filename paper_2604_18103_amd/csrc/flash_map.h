@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.h"
+#include "staging_addr.h"
 
 namespace dash {
 
@@ -14,17 +15,19 @@ struct FaMap {
     int xcds_per_g;    // XCDs serving one KV head (Hkv <= 8)
     int g_per_xcd;     // KV heads per XCD (Hkv >= 8)
     int items_per_g;   // n_qtiles * group size
+    int units, later;  // fa_item_of; with the XCD map of one XCD
 };
 
 __device__ __forceinline__ bool fa_map_block(const FaMap& mp, int bid, int n_qtiles, int Hq, int Hkv,
                                              int& qt, int& head) {
     const int group = Hq / Hkv;
     if (!mp.xcd_mode) {
-        qt = n_qtiles - 1 - bid / Hq;
-        head = bid % Hq;
+        const int item = fa_item_of(bid, mp.later, mp.units);
+        qt = n_qtiles - 1 - item / Hq;
+        head = item % Hq;
         return true;
     }
-    const int xcd = bid % 8, slot = bid / 8;
+    const int xcd = bid % 8, slot = fa_item_of(bid / 8, mp.later, mp.units);
     int g, idx;
     if (mp.g_per_xcd == 1) {
         g = xcd / mp.xcds_per_g;
@@ -39,9 +42,10 @@ __device__ __forceinline__ bool fa_map_block(const FaMap& mp, int bid, int n_qti
     return true;
 }
 
-// The map of a launch over n_qtiles query tiles, and its workgroups.
-inline FaMap fa_map(int n_qtiles, int Hq, int Hkv, unsigned& blocks) {
-    FaMap mp{0, 1, 1, n_qtiles * (Hq / Hkv)};
+// The map of a launch over n_qtiles query tiles, and its workgroups. `units`: compute units, where the launch's workgroups run one
+// at a time on each and rows get longer from tile to tile; else 0, and they start heaviest first.
+inline FaMap fa_map(int n_qtiles, int Hq, int Hkv, unsigned& blocks, int units = 0) {
+    FaMap mp{0, 1, 1, n_qtiles * (Hq / Hkv), 0, 0};
     blocks = (unsigned)n_qtiles * Hq;
     if (Hkv <= 8 && 8 % Hkv == 0) {
         mp.xcd_mode = 1;
@@ -52,6 +56,8 @@ inline FaMap fa_map(int n_qtiles, int Hq, int Hkv, unsigned& blocks) {
         mp.g_per_xcd = Hkv / 8;
         blocks = 8u * (unsigned)(mp.items_per_g * mp.g_per_xcd);
     }
+    mp.units = mp.xcd_mode ? units / 8 : units;
+    mp.later = units > 0 ? fa_later((int)(mp.xcd_mode ? blocks / 8 : blocks), mp.units) : 0;
     return mp;
 }
 

@@ -284,6 +284,11 @@ void dash_product_plan(int M, int K, int N, int cu, int norms, int head, unsigne
     out[0] = p.form; out[1] = p.parts; out[2] = g.parts; out[3] = g.rest; out[4] = rest_parts(g, cu, (size_t)scratch);
 }
 
+// The item that each of `slots` workgroups takes on `units` units.
+void dash_fa_order(int slots, int units, int* out) {
+    for (int s = 0; s < slots; ++s) out[s] = fa_item_of(s, fa_later(slots, units), units);
+}
+
 // The form attention takes among the tiled kernels (dash_few_waves = 0): 0 one key group, 1 two, 2 one with the rows beyond the last whole tile as a launch of their own.
 int dash_fa_form(int n, int Hq, int head_dim, int causal, int cu) { return (int)fa_form(n, Hq, head_dim, causal != 0, cu); }
 
