@@ -838,7 +838,7 @@ static dash_status launch_mfma(const dash_layer_params& p, const __bf16* q, cons
     const int n_qtiles = (row1 - row0 + kFaBM / KG - 1) / (kFaBM / KG);
     const int Hq = p.n_q_heads, Hkv = p.n_kv_heads;
     unsigned blocks = 0;
-    const FaMap mp = fa_map(n_qtiles, Hq, Hkv, blocks, p.causal ? compute_units() : 0);
+    const FaMap mp = p.causal ? fa_map_later(n_qtiles, Hq, Hkv, DH, KG, compute_units(), blocks) : fa_map(n_qtiles, Hq, Hkv, blocks);
     hipLaunchKernelGGL((flash_fwd_mfma<DH, KG>), dim3(blocks), dim3(kFaThreads), FaSmem<DH>::bytes(KG), s, q, k, v, pos, o, n,
                        Hq, Hkv, scale_log2, p.causal, n_qtiles, mp, clear_words, n_clear, row0, clear_count);
     return launch_status();

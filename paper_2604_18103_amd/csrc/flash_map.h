@@ -42,22 +42,23 @@ __device__ __forceinline__ bool fa_map_block(const FaMap& mp, int bid, int n_qti
     return true;
 }
 
-// The map of a launch over n_qtiles query tiles, and its workgroups. `units`: compute units, where the launch's workgroups run one
-// at a time on each and rows get longer from tile to tile; else 0, and they start heaviest first.
-inline FaMap fa_map(int n_qtiles, int Hq, int Hkv, unsigned& blocks, int units = 0) {
+// The map of a launch over n_qtiles query tiles, and its workgroups, which start heaviest first (fa_map_later: but for the few
+// that fa_launch_later has wait).
+inline FaMap fa_map(int n_qtiles, int Hq, int Hkv, unsigned& blocks) {
     FaMap mp{0, 1, 1, n_qtiles * (Hq / Hkv), 0, 0};
-    blocks = (unsigned)n_qtiles * Hq;
-    if (Hkv <= 8 && 8 % Hkv == 0) {
-        mp.xcd_mode = 1;
-        mp.xcds_per_g = 8 / Hkv;
-        blocks = 8u * (unsigned)((mp.items_per_g + mp.xcds_per_g - 1) / mp.xcds_per_g);
-    } else if (Hkv % 8 == 0) {
-        mp.xcd_mode = 1;
-        mp.g_per_xcd = Hkv / 8;
-        blocks = 8u * (unsigned)(mp.items_per_g * mp.g_per_xcd);
-    }
-    mp.units = mp.xcd_mode ? units / 8 : units;
-    mp.later = units > 0 ? fa_later((int)(mp.xcd_mode ? blocks / 8 : blocks), mp.units) : 0;
+    const int slots = fa_slots(n_qtiles, Hq, Hkv);
+    mp.xcd_mode = fa_xcd_map(Hkv);
+    if (mp.xcd_mode && Hkv <= 8) mp.xcds_per_g = 8 / Hkv;
+    else if (mp.xcd_mode) mp.g_per_xcd = Hkv / 8;
+    blocks = mp.xcd_mode ? 8u * (unsigned)slots : (unsigned)slots;
+    return mp;
+}
+
+// The same where a launch's workgroups run one at a time on each of `cu` units and rows get longer from tile to tile.
+inline FaMap fa_map_later(int n_qtiles, int Hq, int Hkv, int head_dim, int groups, int cu, unsigned& blocks) {
+    FaMap mp = fa_map(n_qtiles, Hq, Hkv, blocks);
+    mp.units = mp.xcd_mode ? cu / 8 : cu;
+    mp.later = fa_launch_later(n_qtiles, Hq, Hkv, head_dim, groups, cu);
     return mp;
 }
 

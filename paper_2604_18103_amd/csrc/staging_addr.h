@@ -382,18 +382,45 @@ inline FaForm fa_form(int n, int Hq, int head_dim, bool causal, int cu) {
 }
 
 // Order in which the tiled kernels' workgroups start under a causal mask (their lengths fall linearly): heaviest first, but with 2.25
-// to 3.5 workgroups per unit the `later` heaviest start in the second round and not in the first. Heaviest first, a unit that began
+// to 3.5 workgroups per unit the `later` heaviest may start in the second round and not in the first. Heaviest first, a unit that began
 // with one of the longest gets no third workgroup and the others one too many: the last end 5 to 10 % after an even deal would.
 // Started second, behind the middle ones, the longest fill up to a common end. By list scheduling that ends up to 8 % earlier
-// and nowhere later (1 to 16 heads, 8 to 160 row tiles, a workgroup's fixed cost 0.5 or 0.8 of a tile). From 3.5 per unit on there are
-// short ones enough to fill up with, and with few more than 2 it is the longest that end last. Measured, us, heaviest first / this:
-// 28 heads of 128 (4 KV) 5600 rows 215 / 213, 6144 252 / 245, 6874 308 / 301, 7424 351 / 347, 8000 400 / 399; 32 heads (8 KV) 4700
-// 177 / 169, 5120 205 / 193, 6144 280 / 275; 16 heads of 64 10000 233 / 221, 11000 277 / 259; at 2.1 and 2.2 per unit 226 / 229 (12
-// heads of 64, 11500) and 181 / 183 (28 of 128, 5120).
+// and nowhere later (1 to 16 heads, 8 to 160 row tiles, a workgroup's fixed cost 0.5 or 0.8 of a tile); from 3.5 per unit on there are
+// short ones enough to fill up with, and with few more than 2 it is the longest that end last. On the card it gains less, and only (fa_deal_pays)
+//  - with 13 row tiles or more (two key groups: 24 of 128 rows), so that the lengths are graded finely enough to fill up with: 64
+//    heads of 64 2779 rows (11) 83.8 / 86.5, 64 of 128 3035 rows (12) 142 / 145, 32 of 64 2445 rows (20 of 128) 45.5 / 46.1;
+//  - up to 3.1 per unit, of head size 128 with 24 tiles or more up to 3.5: 40 heads of 128 5339 rows (3.3) 247 / 252, 24 of 64
+//    9435 (3.5) 279 / 283; 16 of 128 13531 (3.3) 598 / 590;
+//  - at head size 64, one key group, from 2.45 on and with the XCD map: 16 heads 9435 rows (2.3) 196 / 199, 12 heads of 3 groups,
+//    without that map, 13019 rows 273 / 277.
+// Measured, us, repeated for some milliseconds, heaviest first / this: head size 128, 8 heads 20443 rows 700 / 668, 16 heads 10203 361 / 340,
+// 28 heads (4 KV) 5851 218 / 212, 6107 235 / 226, 6875 287 / 284, 32 heads 5083 191 / 180, 5339 208 / 196, 6107 261 / 255, 48 heads 3291
+// 130 / 125, 12 of 3 groups 14811 560 / 547; head size 64, one key group, 16 heads 12251 316 / 312, 24 heads 7387 185 / 181, 40 heads
+// 4059 105 / 102; two key groups, single calls, 16 heads 4935 72.9 / 68.1, 12 heads 6595 92.5 / 85.0, 8 heads 10081 135 / 122.
 // slots: workgroups in that order on `units` units, one at a time each.
 inline int fa_later(int slots, int units) {
     if (4 * slots <= 9 * units || 2 * slots >= 7 * units) return 0;
     return sa_min((int)((3.5 * units - slots) / 1.4 + 0.5), units);
+}
+// groups: key groups of the form; xcd_map: the workgroups of a KV head share XCDs
+inline bool fa_deal_pays(int slots, int units, int n_qtiles, int head_dim, int groups, bool xcd_map) {
+    const double per_unit = (double)slots / units;
+    if (n_qtiles < (groups == 2 ? 24 : 13)) return false;
+    if (head_dim == 64 && groups == 1 && (per_unit < 2.45 || !xcd_map)) return false;
+    return per_unit < (head_dim == 128 && n_qtiles >= 24 ? 3.5 : 3.1);
+}
+// A launch's workgroups in one order: those of an XCD with the XCD map, else all.
+DASH_HD bool fa_xcd_map(int Hkv) { return (Hkv <= 8 && 8 % Hkv == 0) || Hkv % 8 == 0; }
+inline int fa_slots(int n_qtiles, int Hq, int Hkv) {
+    if (!fa_xcd_map(Hkv)) return n_qtiles * Hq;
+    const int items = n_qtiles * (Hq / Hkv);  // per KV head
+    return Hkv <= 8 ? (items * Hkv + 7) / 8 : items * (Hkv / 8);
+}
+// How many of the heaviest start later in a causal launch of n_qtiles row tiles on cu units.
+inline int fa_launch_later(int n_qtiles, int Hq, int Hkv, int head_dim, int groups, int cu) {
+    const bool xcds = fa_xcd_map(Hkv);
+    const int slots = fa_slots(n_qtiles, Hq, Hkv), units = xcds ? cu / 8 : cu;
+    return units > 0 && fa_deal_pays(slots, units, n_qtiles, head_dim, groups, xcds) ? fa_later(slots, units) : 0;
 }
 DASH_HD int fa_item_of(int slot, int later, int units) {
     return slot < units ? slot + later : (slot < units + later ? slot - units : slot);

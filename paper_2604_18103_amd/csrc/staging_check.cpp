@@ -289,6 +289,12 @@ void dash_fa_order(int slots, int units, int* out) {
     for (int s = 0; s < slots; ++s) out[s] = fa_item_of(s, fa_later(slots, units), units);
 }
 
+// The workgroups of a causal launch in one order, and how many of them start later.
+int dash_fa_launch_later(int n_qtiles, int Hq, int Hkv, int head_dim, int groups, int cu, int* slots) {
+    *slots = fa_slots(n_qtiles, Hq, Hkv);
+    return fa_launch_later(n_qtiles, Hq, Hkv, head_dim, groups, cu);
+}
+
 // The form attention takes among the tiled kernels (dash_few_waves = 0): 0 one key group, 1 two, 2 one with the rows beyond the last whole tile as a launch of their own.
 int dash_fa_form(int n, int Hq, int head_dim, int causal, int cu) { return (int)fa_form(n, Hq, head_dim, causal != 0, cu); }
 
