@@ -164,7 +164,7 @@ void dash_row_plan(int M, int K, int N, int cu, unsigned long long split_bytes, 
 int dash_check_rows(int M, int K, int N, int row0, int row1, int rb) {
     Counter c;
     const int BM = 32 * rb, mt = (row1 - row0 + BM - 1) / BM, nt = (N + kGN - 1) / kGN, full = mt * nt, seg = (full + 7) / 8;
-    const bool plain = mt % 8 == 0;
+    const bool plain = rows_plain(mt, rb);
     if (row0 % kGM != 0 || row1 > M || (row1 < M && (row1 - row0) % BM != 0)) c.fail(1);
     std::vector<int> taken((size_t)full, 0);
     for (int b = 0; b < (plain ? full : 8 * seg); ++b) {
@@ -198,6 +198,28 @@ int dash_check_rows(int M, int K, int N, int row0, int row1, int rb) {
     }
     if (rows < BM || (rb == 8 && rows != BM)) c.fail(10);
     return c.status;
+}
+
+// Column tiles that one XCD reads in the launch of rows [row0, row1) on tiles of 32 rb rows: the most.
+int dash_rows_columns(int N, int row0, int row1, int rb) {
+    const int mt = (row1 - row0 + 32 * rb - 1) / (32 * rb), nt = (N + kGN - 1) / kGN, full = mt * nt, seg = (full + 7) / 8;
+    const bool plain = rows_plain(mt, rb);
+    int most = 0;
+    for (int xcd = 0; xcd < 8; ++xcd) {
+        std::vector<char> seen((size_t)nt, 0);
+        for (int b = xcd; b < (plain ? full : 8 * seg); b += 8) {
+            const int idx = gemm_index_of(b, full, plain, seg);
+            int tm = 0, tn = 0;
+            if (idx >= 0) {
+                gemm_tile_of(idx, mt, nt, plain, tm, tn);
+                seen[(size_t)tn] = 1;
+            }
+        }
+        int columns = 0;
+        for (const char c : seen) columns += c;
+        most = sa_max(most, columns);
+    }
+    return most;
 }
 
 // The workgroups of a small-tile launch of `tiles` tiles in `parts` K parts: the most that one XCD gets, or -1 if some tile of

@@ -1309,7 +1309,7 @@ static void launch_rows(const GemmArgs& a, int row0, int row1, float* delta_dbg,
     L.mt = (row1 - row0 + 32 * RB - 1) / (32 * RB);
     L.nt = (a.N + kGN - 1) / kGN;
     L.ksteps = a.K / kGK;
-    L.plain = L.mt % 8 == 0;
+    L.plain = rows_plain(L.mt, RB);
     L.full = L.mt * L.nt;
     L.seg = (L.full + 7) / 8;
     L.row0 = row0;

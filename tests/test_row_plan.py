@@ -38,3 +38,10 @@ def test_every_row_once_and_in_range():
                 assert lib.dash_check_rows(M, K, N, 0, whole * 256, 8) == 0, (M, K, N)
             assert lib.dash_check_rows(M, K, N, whole * 256, M, rb) == 0, (M, K, N)
     assert taken > 100
+
+
+@pytest.mark.parametrize("M,K,N,rb", [(1486, 8192, 8192, 6), (1486, 4096, 6144, 6), (3022, 3584, 3584, 6), (4430, 4096, 2048, 6), (2400, 3584, 3584, 6)])
+def test_an_xcd_reads_few_columns(M, K, N, rb):
+    """32 consecutive tiles of panels of four columns and at least seven rows: parts of at most three panels."""
+    assert _plan(M, K, N) == (rb, 0) and -(-M // (32 * rb)) >= 7
+    assert _load().dash_rows_columns(N, 0, M, rb) <= 12
