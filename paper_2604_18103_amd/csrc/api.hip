@@ -492,7 +492,8 @@ dash_status dash_attn_layer(const dash_layer_params* p, const void* x, const voi
     // them on its way (TOPK of few rows hands nothing over)
     const bool topk = p->rule == DASH_RULE_TOPK, one_launch = !topk || n <= kFusedTopkRows;
     uint32_t* published = reinterpret_cast<uint32_t*>(ws + w.published_off);
-    const bool handed = one_launch && !(topk && n <= kFewTopkRows);
+    // how many norm pairs a row gets is known with the product's form: at most one per 64 columns
+    const bool handed = one_launch && !(topk && few_topk(n, (p->d + 63) / 64));
     const int n_clear = handed ? (int)(published_bytes(n, topk) / sizeof(uint32_t)) : 0;
     if (profile) DASH_HIP_CHECK(hipEventRecord(profile->ev[0], s));
     st = launch_flash_fwd(*p, q, k, v, active_idx, n, o, published, n_clear, handed ? n_active_out : nullptr, s);

@@ -101,11 +101,15 @@ dash_status launch_score_rows(const float* delta, const void* x, int n, int d, i
 // and compaction one after the other, us: 64 rows of 28 x 128 heads 29.1 / 34.4, 512 51.3 / 54.9, 1500 93.5 / 94.6, 2120
 // 120.4 / 119.5; of 4 x 128 heads: 64 20.4 / 26.1, 1500 45.1 / 47.2, 2120 56.7 / 56.4.
 constexpr int kFusedTopkRows = 1536;
-// ... of these, up to this many without an exchange, every workgroup deciding about all rows itself (topk_compact_few_kernel). Layer
-// call in a graph, with the exchange / without, us: width 512 64 rows 16.8 / 14.6, 256 20.7 / 18.0, 512 23.3 / 21.7, 650 25.3 /
-// 26.1; width 3584 64 rows 26.0 / 22.7, 256 35.6 / 32.7, 512 46.7 / 46.0, 650 59.2 / 63.8 (the norm pairs of all rows, read
-// by each workgroup, grow with the width). THRESHOLD, whose workgroups wait for one word, gains nothing by it.
-constexpr int kFewTopkRows = 512;
+// ... of these, up to this many without an exchange, every workgroup deciding about all rows itself (topk_compact_few_kernel): always up
+// to 256 rows (a row per thread and quarter), beyond that while a row has at most 64 norm pairs (NormSums::cols), since every
+// workgroup reads the pairs of all rows. Layer call in a graph, with the exchange / without, us: width 512 64 rows 17.0 / 14.5, 256
+// 20.4 / 17.2, 512 22.7 / 21.2, 650 25.3 / 26.1; width 3584 (56 pairs) 64 rows 26.1 / 22.8, 256 34.7 / 31.9, 512 44.7 / 44.9; fp32 of
+// width 4096 (64 pairs) 512 219.6 / 217.9; width 6144 (96 pairs) 320 rows 54.6 / 55.6; width 8192 (128) 200 rows 61.1 / 59.2, 512
+// 95.5 / 98.1, of 2 heads 512 31.9 / 35.5; width 16384 (256) 200 rows 95.4 / 91.4, 384 143 / 150. THRESHOLD, whose workgroups wait for one
+// word, gains nothing by it.
+constexpr int kFewTopkRows = 512, kFewTopkPairs = 64;
+inline bool few_topk(int n, int cols) { return n <= 256 || (n <= kFewTopkRows && cols <= kFewTopkPairs); }
 size_t published_bytes(int n, bool topk);  // words the fused score + decision + compaction kernel publishes its chunks through
 dash_status launch_score_decide_compact(const dash_layer_params& p, const NormSums& sums, int n, float* scores, uint8_t* halt, void* published, const int32_t* active_idx,
                                         const void* x_next, int row_bytes, void* x_compact, int32_t* new_active_idx,

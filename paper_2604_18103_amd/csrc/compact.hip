@@ -125,7 +125,7 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(
 // the grid.
 //  - NONE, THRESHOLD: a workgroup (c, y) waits for publishers (c', 0) with c' <= c only. They have a smaller linear index,
 //    are therefore resident or done, and publish without having waited.
-//  - TOPK (more than kFewTopkRows rows): the publishers wait for one another, so they have to be resident together. They are at most
+//  - TOPK (where few_topk does not hold): the publishers wait for one another, so they have to be resident together. They are at most
 //    kFusedTopkRows / 64 = 24 workgroups, a fraction of what the chip holds, but nothing reserves that room: beside
 //    kernels on other streams that fill the chip, the last of them may come late.
 // Every wait is bounded (kPubSpinLimit), and one that ends without its word fails the call: a publisher that gave up
@@ -333,7 +333,7 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
 // counted by ballots, without a barrier; where exactly k_cand keys reach a T the set is found, so only rows that tie with the
 // last one kept take all 32 steps.
 // Bound by latency: norms, selection (about a microsecond), gather. (Counting, for each row, the candidates before it was as fast
-// up to 128 rows and 1 us slower at 256.) Figures: kFewTopkRows.
+// up to 128 rows and 1 us slower at 256.) Figures: few_topk.
 // ------------------------------------------------------------------------------------------------
 constexpr int kFewThreads = 1024;
 
@@ -482,7 +482,7 @@ size_t published_bytes(int n, bool topk) {
 
 // Scores, decision and compaction in one launch (TOPK: n <= kFusedTopkRows). `published` (published_bytes, 8-byte aligned) and
 // the count must have been cleared on this stream before (launch_flash_fwd does it for the layer call), except for
-// TOPK up to kFewTopkRows rows, which hands nothing over.
+// TOPK where few_topk holds, which hands nothing over.
 dash_status launch_score_decide_compact(const dash_layer_params& p, const NormSums& sums, int n, float* scores, uint8_t* halt, void* published, const int32_t* active_idx,
                                         const void* x_next, int row_bytes, void* x_compact, int32_t* new_active_idx,
                                         int32_t* n_active_out, hipStream_t s) {
@@ -491,7 +491,7 @@ dash_status launch_score_decide_compact(const dash_layer_params& p, const NormSu
     int splits, vecs_per_split;
     gather_splits(n_chunks, row_vecs, splits, vecs_per_split);
     const bool topk = p.rule == DASH_RULE_TOPK;
-    if (topk && n <= kFewTopkRows) {
+    if (topk && few_topk(n, sums.cols)) {
         hipLaunchKernelGGL(n <= 256 ? topk_compact_few_kernel<1> : topk_compact_few_kernel<2>,
                            dim3(n_chunks, splits), dim3(kFewThreads), 0, s, sums.pairs, sums.cols, sums.fold, n, p.score_kind,
                            topk_keep(p, n), p.keep_first_n, p.keep_last_n, scores, halt, active_idx, (const uint4*)x_next,
