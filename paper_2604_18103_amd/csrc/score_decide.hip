@@ -66,7 +66,8 @@ constexpr int kHistCopies = 2;
 constexpr int kListMax = 64;  // so many keys left in a bin are ranked by counting (one wave); more take another pass
 struct SelectShared {
     int hist[kSelectBins][kHistCopies];  // the copies of a bin side by side: in different LDS banks
-    uint32_t list[kListMax], wave_min[kSelectThreads / kWave], wave_max[kSelectThreads / kWave];
+    uint32_t list[kListMax];
+    uint2 least[kSelectThreads / kWave];
     int n_list;
     int wave_tot[kSelectThreads / kWave];
     uint32_t prefix;
@@ -125,25 +126,33 @@ __device__ __forceinline__ void select_bin(SelectShared& sh, int shift, uint32_t
     remaining = sh.remaining;
 }
 
-// Smallest and largest of the threads' values, uniform; ends with a barrier.
-__device__ __forceinline__ void range_of_keys(SelectShared& sh, uint32_t& kmin, uint32_t& kmax) {
-    constexpr int kWaves = kSelectThreads / kWave;
+// The least of the threads' values, of either of two, uniform; ends with a barrier. By row shifts and broadcasts inside a wave, over the
+// waves by one LDS read per lane: with shuffles, and every thread reading all waves' values, it took half a microsecond longer.
+template <int CTRL>
+__device__ __forceinline__ void fold_lanes(uint32_t& a, uint32_t& b) {  // lanes without a source keep their own
+    a = min(a, (uint32_t)__builtin_amdgcn_update_dpp((int)a, (int)a, CTRL, 0xF, 0xF, false));
+    b = min(b, (uint32_t)__builtin_amdgcn_update_dpp((int)b, (int)b, CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ void fold_row(uint32_t& a, uint32_t& b) {  // of 16 lanes, into its last
+    fold_lanes<0x111>(a, b);  // row_shr:1, 2, 4, 8
+    fold_lanes<0x112>(a, b);
+    fold_lanes<0x114>(a, b);
+    fold_lanes<0x118>(a, b);
+}
+__device__ __forceinline__ void least_of_all(SelectShared& sh, uint32_t& a, uint32_t& b) {
+    static_assert(kSelectThreads / kWave == 16, "a row of lanes per wave's values");
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o));
-        kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o));
-    }
-    if (lane == 0) {
-        sh.wave_min[wave] = kmin;
-        sh.wave_max[wave] = kmax;
-    }
+    fold_row(a, b);
+    fold_lanes<0x142>(a, b);  // row_bcast:15, 31: a row's last lane to the next row, the second row's to the last two
+    fold_lanes<0x143>(a, b);
+    if (lane == kWave - 1) sh.least[wave] = make_uint2(a, b);
     __syncthreads();
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        kmin = min(kmin, sh.wave_min[w]);
-        kmax = max(kmax, sh.wave_max[w]);
-    }
+    const uint2 w = sh.least[lane % 16];
+    a = w.x;
+    b = w.y;
+    fold_row(a, b);
+    a = (uint32_t)__builtin_amdgcn_readlane((int)a, 15);
+    b = (uint32_t)__builtin_amdgcn_readlane((int)b, 15);
 }
 
 __device__ __forceinline__ int pass_shift(int pass) { return pass == 0 ? 21 : (pass == 1 ? 10 : 0); }
@@ -284,14 +293,17 @@ __global__ __launch_bounds__(256) void topk_flag_kernel(const float* __restrict_
 // kept counts per 64-row chunk (chunk u * 16 + w is what wave w holds at step u) all work
 // from those registers. Same total order, same tie rule (earliest rows first) and same outputs as the
 // topk_select_kernel + topk_flag_kernel pair, which serves longer inputs.
-// The bins of the first pass are 2048 equal steps over the keys' own range, not their top digits: the scores of a layer span a few
+// The bins of a pass are 2048 equal steps over the keys' own range, not their top digits: the scores of a layer span a few
 // octaves, so top digits put them into a few dozen bins, whose adds LDS does one after the other, and leave two more passes. Over
 // their range the wanted bin is left with a handful of keys, of which the wanted one is found by counting. A bin that keeps more
-// (an outlier stretched the range, or ties) takes another pass of 2048 steps inside it, three in all at most.
-// One compute unit does all of it, so the time is latencies (launch, loads, range, pass, search, flags: 7 us for any few rows) and
-// from 8192 rows on that unit's instruction throughput. Heavy-tailed scores, us, top digits in three passes / this: 64 rows 8.9 /
-// 6.9, 2120 9.0 / 7.4, 8192 9.6 / 8.1, 16384 13.4 / 12.0; all within a few percent of each other 11.2 / 8.1 at 8192, 16.6 / 11.9 at
-// 16384; all equal 19.8 / 11.0 and 33 / 18; one zero among them (a range of its own, two passes) 9.7 / 9.4.
+// (an outlier stretched the range, or ties) is taken over its own keys' range in turn: bins of 2^21, 2^10 keys and one at most, so
+// three passes, and none for a bin whose keys are all equal. (Taken in fixed steps instead, ties and neighbours go through all passes
+// behind a range that was not worth finding: 16384 rows of tied scores 16.2 us, of neighbours behind an outlier 26.7.)
+// One compute unit does all of it, so the time is latencies (launch, loads, range, pass, search, flags: 6 us for any few rows) and
+// from 8192 rows on that unit's instruction throughput. Heavy-tailed scores, us, top digits in three passes / this:
+// 64 rows 8.2 / 5.4, 2120 8.4 / 5.9, 8192 8.9 / 7.5, 16384 12.6 / 11.1; all within a few percent of each other 10.5 / 6.9 at 8192, 15.9 / 10.7
+// at 16384; all equal 19.0 / 6.0 and 32.5 / 9.6; steps of an eighth 10.1 / 8.3 and 14.7 / 12.7; of both signs 8.9 / 8.7 and 12.6 / 12.8;
+// neighbours behind an outlier 15.6 / 11.9 and 25.6 / 18.9; one zero among nearly equal ones, 10.4 / 10.6 and 15.8 / 16.3.
 // 16-byte loads with four flags per store, and the keys in LDS under short rolled loops, measured slower than this plain form.
 template <int B>
 __global__ __launch_bounds__(kSelectThreads) void topk_decide_small_kernel(
@@ -307,77 +319,77 @@ __global__ __launch_bounds__(kSelectThreads) void topk_decide_small_kernel(
     const int n_cand = hi - lo;
     const int k_cand = max(0, min(k_keep - (n - n_cand), n_cand));
     uint32_t key[B];
-    uint32_t cand = 0u;  // bit u: row u * 1024 + tid is a candidate
+    const uint32_t no_key = keep_low ? 0xFFFFFFFFu : 0u;  // which no score has (order_key is at least 0x007FFFFF): no candidate
+    uint32_t cand = 0u;                                   // bit u: row u * 1024 + tid is a candidate
 #pragma unroll
     for (int u = 0; u < B; ++u) {
         const int r = u * kSelectThreads + tid;
-        key[u] = rank_key(r < n ? scores[r] : 0.f, keep_low);
         if (r >= lo && r < hi) cand |= 1u << u;
+        key[u] = (cand >> u) & 1u ? rank_key(scores[r], keep_low) : no_key;
     }
     // nothing unprotected survives: no key exceeds the threshold and no tie is kept
     uint32_t T = 0xFFFFFFFFu;
     int quota = 0;
     bool rank_ties = false;
     if (k_cand > 0) {
-        // The bins cover the candidates' own range: 2048 equal steps of the keys from the smallest to the largest.
-        uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
-#pragma unroll
-        for (int u = 0; u < B; ++u)
-            if ((cand >> u) & 1u) {
-                kmin = min(kmin, key[u]);
-                kmax = max(kmax, key[u]);
-            }
-        clear_hist(sh);
+        // Keys of interest are those with key - base <= span, `same` of them: at first every score's.
+        uint32_t base = keep_low ? 0u : 1u, span = 0xFFFFFFFEu;
+        int remaining = k_cand, same = n_cand;
         if (tid == 0) sh.n_list = 0;
-        range_of_keys(sh, kmin, kmax);  // ends with a barrier
-        uint32_t base = kmin;           // keys of interest: (key - base) >> width is 0
-        int width = 32;
-        int shift = max(0, 32 - __clz((int)(kmax - kmin)) - 11);
-        int remaining = k_cand, in_bin = n_cand;
 #pragma unroll 1
         for (;;) {
-            const uint32_t span = width >= 32 ? 0xFFFFFFFFu : (1u << width) - 1u;
+            // The bins cover their own range: 2048 equal steps from the smallest to the largest. (Unsigned distances from either
+            // end are beyond span for all other keys.)
+            uint32_t lead = 0xFFFFFFFFu, trail = 0xFFFFFFFFu;
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                lead = min(lead, key[u] - base);
+                trail = min(trail, base + span - key[u]);
+            }
+            clear_hist(sh);
+            least_of_all(sh, lead, trail);  // ends with a barrier
+            base += lead;
+            span -= lead + trail;
+            if (span == 0u) break;  // one value
+            const int shift = max(0, 21 - __clz((int)span));
 #pragma unroll
             for (int u = 0; u < B; ++u)
-                if (((cand >> u) & 1u) && key[u] - base <= span) hist_add(sh, (key[u] - base) >> shift);
+                if (key[u] - base <= span) hist_add(sh, (key[u] - base) >> shift);
             __syncthreads();
             uint32_t bin = 0u;
             select_bin(sh, 0, bin, remaining);
             base += bin << shift;
-            width = shift;
-            in_bin = sh.ties;
-            if (shift == 0 || in_bin <= kListMax) break;
-            clear_hist(sh);
-            shift = max(0, shift - 11);
-            __syncthreads();
+            span = min((1u << shift) - 1u, span - (bin << shift));  // never beyond the largest key, so never at no_key
+            same = sh.ties;
+            if (span == 0u || same <= kListMax) break;
         }
-        if (width > 0) {
-            // few keys are left in the bin: the wanted one by counting
-            const uint32_t span = (1u << width) - 1u;
+        if (span > 0u) {
+            // few keys are left: the wanted one by counting
 #pragma unroll
             for (int u = 0; u < B; ++u)
-                if (((cand >> u) & 1u) && key[u] - base <= span) sh.list[atomicAdd(&sh.n_list, 1)] = key[u];
+                if (key[u] - base <= span) sh.list[atomicAdd(&sh.n_list, 1)] = key[u];
             __syncthreads();
-            if (tid < in_bin) {
+            if (tid < same) {
                 const uint32_t mine = sh.list[tid];
-                int greater = 0, same = 0;
-                for (int i = 0; i < in_bin; ++i) {
+                int greater = 0, equal = 0;
+                for (int i = 0; i < same; ++i) {
                     greater += sh.list[i] > mine;
-                    same += sh.list[i] == mine;
+                    equal += sh.list[i] == mine;
                 }
-                if (greater < remaining && remaining <= greater + same) {  // every holder of that key writes the same
+                if (greater < remaining && remaining <= greater + equal) {  // every holder of that key writes the same
                     sh.prefix = mine;
                     sh.remaining = remaining - greater;
-                    sh.ties = same;
+                    sh.ties = equal;
                 }
             }
             __syncthreads();
             base = sh.prefix;
             remaining = sh.remaining;
+            same = sh.ties;
         }
         T = base;
-        quota = remaining;               // >= 1: ties (key == T) still to be kept
-        rank_ties = sh.ties > remaining; // more rows tie with the K-th key than may be kept
+        quota = remaining;           // >= 1: ties (key == T) still to be kept
+        rank_ties = same > remaining;  // more rows tie with the K-th key than may be kept
     }
     if (rank_ties) {
 #pragma unroll
@@ -489,7 +501,7 @@ dash_status topk_static_scratch_ptr(void** out) {
 }
 
 // The TopK decision on n > 0 scores: up to 16384 rows in one launch that keeps the keys in registers (when the
-// caller allows it: 8 us at 8192 rows, 12 at 16384, where the two launches take 14; at 32768 rows it would take 23
+// caller allows it: 7.5 us at 8192 rows, 11 at 16384, where the two launches take 14; at 32768 rows it would take 23
 // against their 20, the flags of the longer input being spread over many workgroups), longer inputs by the selection
 // kernel, which leaves its state and tie counts in ws, and the flag kernel.
 static void launch_topk(const float* scores, int n, int n_first, int n_last, int k_keep, int keep_low, uint8_t* halt,

@@ -26,18 +26,24 @@ def _scores(kind, n, rng):
         s[: min(n, 600)] = np.repeat(_steps(3.0, 200), 3)[: min(n, 600)]
     elif kind == "edge":           # 64 and 65 keys in a bin (steps of 2^-3 of a range of 2^8)
         s = np.r_[0.0, 256.0, 8.0 + _steps(1.0, 64) * 0.01, 16.0 + _steps(1.0, 65) * 0.01, rng.uniform(64, 200, max(n - 131, 0))][:n]
+    elif kind == "outliers":       # a crowd of few values behind an outlier on either side: its own range is one value or few
+        s = np.round(rng.normal(size=n) * 8) / 8
+        s[: min(n, 2)] = (np.inf, -np.inf)[: min(n, 2)]
+    elif kind == "top":            # the last bin of the whole range is crowded and ends with the largest key that there is
+        s = rng.choice(_steps(3.0e38, 40), n)
+        s[: n // 3], s[n // 3: n // 3 + 1] = np.nan, -np.inf
     else:                          # signed zeros, infinities, NaN, the smallest and largest numbers
         s = rng.choice(np.array([0.0, -0.0, np.inf, -np.inf, np.nan, 1e-45, -1e-45, 3.4e38, -3.4e38, 1.0, 1.0000001]), n)
     rng.shuffle(s)
     return s.astype(np.float32)
 
 
-@pytest.mark.parametrize("kind", ["dense", "crowd", "tied crowd", "edge", "odd"])
+@pytest.mark.parametrize("kind", ["dense", "crowd", "tied crowd", "edge", "outliers", "top", "odd"])
 @pytest.mark.parametrize("n", [1, 2, 64, 1025, 8192, 8193, 16384])
 def test_every_end(n, kind):
     rng = np.random.default_rng(n)
     s = _scores(kind, n, rng)
-    rank = int((s > 3.0).sum()) if kind != "odd" else n // 2
+    rank = int((s > 3.0).sum()) if kind not in ("odd", "outliers", "top") else n // 2
     cuts = sorted({min(n, max(0, k)) for k in (0, 1, n // 3, n - 1, n, rank, rank - 1, rank - 64, rank - 65, rank - 499, rank - 500, rank - 501)})
     dev = torch.from_numpy(s).cuda()
     halt, counts = torch.empty((n,), dtype=torch.uint8, device="cuda"), torch.empty(((n + 63) // 64,), dtype=torch.int32, device="cuda")
