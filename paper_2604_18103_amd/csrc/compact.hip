@@ -33,7 +33,11 @@ __device__ __forceinline__ int wave_sum_int(int v) {
 // with inputs that change from pass to pass, plain / loads and stores by the caches, us: block-level signal path (scores, TopK, gather, scatter) of
 // 16384 rows of 3584 109 / 88, with a reader of the gathered rows behind it 149 / 142, 60000 rows 365 / 304 and 531 / 493, 1000 rows
 // 24 / 22 and 27 / 25.5; the chain of eight layers from 32768 rows the same (23.13 ms). In the layer call's one launch (THRESHOLD, 28 heads, width
-// 3584): 1000 rows 70 / 64.7, 1500 96.6 / 90.5, 3000 167.6 / 162.5, 12000 1093 / 1086, 16384 the same.
+// 3584) it depends on what comes next. Three calls in turn on inputs and weights of their own, which the caches hold between them: 333
+// rows the same, 1000 65.1 / 63.7, 2120 120 / 113, 3000 167 / 153, 6000 394 / 393. Layers one behind the other, 16 with weights of
+// their own and the next one's norm reading the gathered rows, us a layer: 64 rows 45.3 / 46.1, 333 75.4 / 75.5, 1000 134.4 / 134.2,
+// 2120 200 / 201, 3000 260 / 259, 6000 587 / 582; of width 512 (60 layers) 333 rows 29.9 / 30.0, 3000 61.3 / 61.6, 6000 105.1 / 105.1: within
+// a percent either way but for the fewest rows. (Both in one kernel, plain up to 4 MB of rows: 64 rows 45.5, but 0.3 us more in a call by itself.)
 __device__ __forceinline__ uint4 load_once(const uint4* p) {
     const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
     return make_uint4(v[0], v[1], v[2], v[3]);
