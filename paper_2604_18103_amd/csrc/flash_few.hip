@@ -68,15 +68,12 @@ __global__ __launch_bounds__(KW * kWave, 2) void flash_few(const __bf16* __restr
     const int kend = causal ? min(n, row0 + 32) : n, n_blocks = (kend + kFewKeys - 1) / kFewKeys;
     // the query rows, once for all waves (a wave's own fragments from memory are 32-byte pieces of 32 rows per instruction: four
     // waves kept the address unit busy with them for most of the prologue)
-    constexpr int QL = (LOADS + KW - 1) / KW;
 #pragma unroll
-    for (int u = 0; u < QL; ++u) {
-        const int i = wave * QL + u;
+    for (int u = 0; u < few_q_loads(DH, KW); ++u) {
+        const int i = few_q_index(wave, u, DH, KW);
         if (LOADS % KW != 0 && i >= LOADS) continue;
-        const int r = few_row(i, lane, DH);
-        dma_load16(reinterpret_cast<const char*>(q) + (size_t)(row0 / kFewKeys) * few_block_bytes(Hq, DH),
-                   fa_dma_voff_tail(fa_dma_voff(r, lane, head, Hq, DH, true), r, min(n - row0, 32), Hq, DH),
-                   lds_addr(Qs) + (uint32_t)(i * 1024));
+        dma_load16(reinterpret_cast<const char*>(q) + few_q_base(row0, Hq, DH),
+                   few_q_voff(row0, n, few_row(i, lane, DH), lane, head, Hq, DH), lds_addr(Qs) + (uint32_t)(i * 1024));
     }
     uint32_t k_off[LOADS], v_off[LOADS];
 #pragma unroll

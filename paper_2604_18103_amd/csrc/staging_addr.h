@@ -440,6 +440,13 @@ constexpr int kFewKeys = 32;
 DASH_HD constexpr int few_loads(int DH) { return kFewKeys / fa_rows_per_dma(DH); }
 DASH_HD int few_row(int i, int lane, int DH) { return i * fa_rows_per_dma(DH) + lane / fa_cpr(DH); }
 DASH_HD size_t few_block_bytes(int Hkv, int DH) { return (size_t)kFewKeys * Hkv * DH * 2; }
+// The 32 query rows come the same way, dealt to the KW waves: instruction u (< few_q_loads) of a wave is the i-th of the few_loads, or none.
+DASH_HD constexpr int few_q_loads(int DH, int KW) { return (few_loads(DH) + KW - 1) / KW; }
+DASH_HD int few_q_index(int wave, int u, int DH, int KW) { return wave * few_q_loads(DH, KW) + u; }
+DASH_HD size_t few_q_base(int row0, int Hq, int DH) { return (size_t)(row0 / kFewKeys) * few_block_bytes(Hq, DH); }
+DASH_HD uint32_t few_q_voff(int row0, int n, int r, int lane, int head, int Hq, int DH) {
+    return fa_dma_voff_tail(fa_dma_voff(r, lane, head, Hq, DH, true), r, sa_min(n - row0, kFewKeys), Hq, DH);
+}
 // Waves per workgroup of that form, 0: the tiled kernels (fa_form). Its workgroups fetch a key block for 32 rows where those fetch
 // it for 128 or 256, so it pays while latencies and not the L2 decide: counted in its workgroups per compute unit, with a
 // causal mask (half of the blocks, long rows first) up to 3, at head size 64 (half the bytes) 5; without one, where a third

@@ -472,6 +472,38 @@ int dash_check_flash_few(int n, int Hkv, int DH, int causal, int waves, long lon
     return c.status;
 }
 
+// ... and the query rows of its launch over rows [row_base, n): in every workgroup each of the 32 rows' pieces is fetched once by one
+// wave, clamped, in range, to its place.
+int dash_check_few_queries(int n, int Hq, int DH, int waves, int row_base, long long* n_loads) {
+    Counter c;
+    if (n <= row_base || row_base % 32 != 0 || Hq <= 0 || (DH != 64 && DH != 128) || waves <= 0) return -1;
+    const int cpr = fa_cpr(DH), loads = few_loads(DH);
+    for (int qt = 0; qt < (n - row_base + 31) / 32; ++qt)
+        for (int head = 0; head < Hq; ++head) {
+            const int row0 = row_base + 32 * qt;
+            std::vector<int> filled((size_t)32 * cpr, 0);
+            for (int wave = 0; wave < waves; ++wave)
+                for (int u = 0; u < few_q_loads(DH, waves); ++u) {
+                    const int i = few_q_index(wave, u, DH, waves);
+                    if (loads % waves != 0 && i >= loads) continue;  // as the kernel
+                    for (int lane = 0; lane < 64; ++lane) {
+                        const int r = few_row(i, lane, DH), place = i * 64 + lane;  // 16-byte pieces of the stage
+                        if (i >= loads || r < 0 || r >= 32 || place / cpr != r) { c.fail(1); continue; }
+                        ++filled[(size_t)place];
+                        const int lchunk = (place % cpr) ^ fa_k_swz(r, DH);
+                        const uint64_t addr = (uint64_t)few_q_base(row0, Hq, DH) + few_q_voff(row0, n, r, lane, head, Hq, DH);
+                        if (addr != ((uint64_t)sa_min(row0 + r, n - 1) * Hq + head) * DH * 2 + (uint64_t)lchunk * 16) c.fail(4);
+                        if (addr + 16 > (uint64_t)n * Hq * DH * 2) c.fail(5);
+                        ++c.loads;
+                    }
+                }
+            for (const int f : filled)
+                if (f != 1) c.fail(6);
+        }
+    if (n_loads) *n_loads = c.loads;
+    return c.status;
+}
+
 // Whether the rows beyond the last whole tile take the few-row form (where dash_fa_form is 2).
 int dash_fa_few_tail(int n, int Hq, int head_dim, int cu) { return fa_few_tail(n, Hq, head_dim, cu); }
 
