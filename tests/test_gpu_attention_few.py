@@ -29,7 +29,8 @@ def test_block_edges(n, hq, hkv, dh):
         _run(n, hq, hkv, dh, bool(causal), seed=n + dh)
 
 
-@pytest.mark.parametrize("n,hq,hkv,dh,causal", [(40, 4, 2, 64, True), (177, 28, 4, 128, True), (333, 4, 2, 128, False),
+@pytest.mark.parametrize("n,hq,hkv,dh,causal", [(40, 4, 2, 64, True), (64, 4, 2, 64, True), (128, 4, 2, 128, True), (130, 4, 2, 128, False),
+                                                (193, 4, 2, 64, True), (321, 28, 4, 128, True), (177, 28, 4, 128, True), (333, 4, 2, 128, False),
                                                 (800, 28, 4, 128, True), (1000, 16, 4, 64, True), (2500, 16, 4, 64, True), (500, 28, 4, 128, False)])
 def test_ordinary_rows_closely(n, hq, hkv, dh, causal):
     """P and the result are rounded to bf16 (each 1.6e-3 of a row in the 2-norm, test_gpu_attention_groups), Q is not rounded
@@ -64,12 +65,12 @@ def test_blocks_of_infinite_keys(dh, causal, low):
                                                 (641, 28, 4, 128, False), (703, 28, 4, 128, False), (1153, 16, 4, 64, False), (1217, 16, 4, 64, False)])
 def test_two_key_groups_beyond_it(n, hq, hkv, dh, causal):
     """128-row workgroups of the tiled kernel whose last tile holds 1 to 128 rows, with an odd and an even number of key tiles;
-    and a first key tile of either group without a finite score."""
+    and without a finite score a first key tile of either group, and the first two of group 1."""
     lib = _load()
     assert lib.dash_few_waves(n, hq, dh, int(causal), _units()) == 0 and lib.dash_fa_form(n, hq, dh, int(causal), _units()) == TWO
     rows = np.unique(np.r_[0, 1, 63, 64, 127, 128, n // 2, n - 66, n - 65, n - 2, n - 1])
     _run(n, hq, hkv, dh, causal, seed=n, rows=rows)
-    for infinite in (slice(64, 128), slice(0, 64)):
+    for infinite in (slice(64, 128), slice(0, 64), slice(64, 256)):
         _attention(n, hq, hkv, dh, causal, infinite, n % 2 == 1, rows)
 
 

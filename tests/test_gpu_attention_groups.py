@@ -1,5 +1,5 @@
-"""The bf16 attention kernel's two forms (one key group per workgroup, two for short sequences) at the edges of their
-tiles, against the fp64 oracle."""
+"""The tiled bf16 attention kernel's two forms (one key group per workgroup, two for shorter sequences) at the edges of their
+tiles, against the fp64 oracle; the shortest lengths, at the same edges, take the few-row form (test_gpu_attention_few)."""
 import numpy as np
 import pytest
 import torch
@@ -35,8 +35,11 @@ def _run(n, hq, hkv, dh, causal, seed, rows=None):
 @pytest.mark.parametrize("dh", [64, 128])
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 96, 127, 128, 129, 192, 193, 257, 320])
 def test_two_key_groups_at_tile_edges(n, dh):
-    """128-row workgroups; group 1 has no tile up to 64 keys, one tile less than group 0 at odd tile counts."""
+    """Lengths at the edges of the two key groups' tiles that are so short that the few-row form takes them; the two groups themselves
+    run in test_gpu_attention_few.test_two_key_groups_beyond_it."""
+    units = torch.cuda.get_device_properties(0).multi_processor_count
     for causal in (True, False):
+        assert _load().dash_few_waves(n, 4, dh, int(causal), units) > 0
         _run(n, 4, 2, dh, causal, seed=n + dh)
 
 
@@ -49,18 +52,22 @@ def test_one_key_group_with_a_nearly_empty_last_tile(n, hq, hkv, dh, causal):
 
 
 @pytest.mark.parametrize("n,hq,hkv,dh,causal,form", [
-    (64, 4, 2, 64, True, TWO), (128, 4, 2, 128, True, TWO), (130, 4, 2, 128, False, TWO), (193, 4, 2, 64, True, TWO),
-    (321, 28, 4, 128, True, TWO), (1000, 16, 4, 64, True, TWO), (1150, 28, 4, 128, False, TWO), (2433, 28, 4, 128, True, ONE),
+    (1000, 28, 4, 128, True, TWO), (2303, 28, 4, 128, True, TWO), (2561, 16, 4, 64, True, TWO), (5000, 16, 4, 64, True, TWO),
+    (1153, 16, 4, 64, False, TWO), (4480, 16, 4, 64, False, TWO), (1150, 28, 4, 128, False, TWO), (2433, 28, 4, 128, True, ONE),
     (5377, 16, 4, 64, True, ONE), (4097, 16, 4, 64, False, ONE_AND_TAIL), (4224, 16, 4, 64, False, ONE_AND_TAIL),
-    (2400, 28, 4, 128, False, ONE_AND_TAIL), (2305, 28, 4, 128, False, ONE_AND_TAIL), (2432, 28, 4, 128, False, ONE_AND_TAIL)])
+    (2400, 28, 4, 128, False, ONE_AND_TAIL), (2305, 28, 4, 128, False, ONE_AND_TAIL), (2432, 28, 4, 128, False, ONE_AND_TAIL),
+    (1279, 64, 8, 128, False, ONE_AND_TAIL)])
 def test_ordinary_rows_closely(n, hq, hkv, dh, causal, form):
-    """Normal q, k and v, every form by name. A bf16 number has 8 significant bits: its rounding is uniform in +-2^-8 of the
-    power of two below it, in the mean square 2^-8 / sqrt(3) * 0.72 = 1.6e-3 of the number. Scores have unit variance, so Q's
-    rounding moves a probability by that much, its own rounding again, and the result's a third time: 2.8e-3 of a row in the
-    2-norm, bound 3.5e-3 on the mean. A row that few keys carry has fewer independent roundings, each at most 3.9e-3: 8e-3 on
-    the largest. A weight between the two groups that is off by a hundredth moves a row by about 7e-3, so the mean shows it."""
+    """Normal q, k and v, every tiled form by name; ONE_AND_TAIL's last rows in the few-row form, with 64 heads in the split one.
+    A bf16 number has 8 significant bits: its rounding is uniform in +-2^-8 of the power of two below it, in the mean square
+    2^-8 / sqrt(3) * 0.72 = 1.6e-3 of the number. Scores have unit variance, so Q's rounding moves a probability by that much, its
+    own rounding again, and the result's a third time: 2.8e-3 of a row in the 2-norm, bound 3.5e-3 on the mean. A row that few
+    keys carry has fewer independent roundings, each at most 3.9e-3: 8e-3 on the largest. A weight between the two groups that is
+    off by a hundredth moves a row by about 7e-3, so the mean shows it."""
     units = torch.cuda.get_device_properties(0).multi_processor_count
-    assert _load().dash_fa_form(n, hq, dh, int(causal), units) == form
+    lib = _load()
+    assert lib.dash_few_waves(n, hq, dh, int(causal), units) == 0 and lib.dash_fa_form(n, hq, dh, int(causal), units) == form
+    assert form != ONE_AND_TAIL or lib.dash_fa_few_tail(n, hq, dh, units) == (hq != 64)
     rng = np.random.default_rng(n)
     q, k, v = (torch.from_numpy(rng.standard_normal((n, h, dh)).astype(np.float32)).bfloat16() for h in (hq, hkv, hkv))
     pos = np.sort(rng.permutation(2 * n + 1)[:n]).astype(np.int32)

@@ -6,6 +6,7 @@ import torch
 
 from oracle import reference as ref
 from paper_2604_18103_amd import binding as B
+from test_staging_addresses import _load
 
 pytestmark = pytest.mark.gpu
 
@@ -37,8 +38,10 @@ def _attention(n, hq, hkv, dh, causal, infinite, low, rows):
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("dh", [64, 128])
 def test_a_tile_of_infinite_keys(dh, causal, low):
-    """Two key groups: keys 64-127 are group 1's first tile, keys 0-63 group 0's, 64-255 the first two tiles of group 1."""
+    """So few rows that the few-row form takes them: whole key blocks of one to all of its waves. (The tiles of two key groups:
+    test_gpu_attention_few.test_two_key_groups_beyond_it.)"""
     n = 330
+    assert _load().dash_few_waves(n, 4, dh, int(causal), torch.cuda.get_device_properties(0).multi_processor_count) > 0
     for infinite in (slice(64, 128), slice(0, 64), slice(64, 256)):
         _attention(n, 4, 2, dh, causal, infinite, low, np.arange(n))
 
@@ -46,6 +49,7 @@ def test_a_tile_of_infinite_keys(dh, causal, low):
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("hq,hkv,dh,n", [(16, 4, 64, 5377), (28, 4, 128, 2433)])
 def test_one_key_group(hq, hkv, dh, n, causal):
-    """The same with 256-row workgroups: the first tile, and the first three."""
+    """The first tile, and the first three, of 256-row workgroups; without a causal mask of 16 heads of 64 the first of group 0, and
+    the first of group 1 beside the first two of group 0."""
     for infinite in (slice(0, 64), slice(0, 192)):
         _attention(n, hq, hkv, dh, causal, infinite, True, np.array([0, 63, 64, 191, 192, 200, 255, 256, 300, n // 2, n - 1]))
