@@ -24,8 +24,9 @@ def _scores(kind, n, rng):
     elif kind == "tied crowd":     # the same with every value three times
         s = np.exp(rng.normal(0.0, 8.0, n))
         s[: min(n, 600)] = np.repeat(_steps(3.0, 200), 3)[: min(n, 600)]
-    elif kind == "edge":           # 64 and 65 keys in a bin (steps of 2^-3 of a range of 2^8)
-        s = np.r_[0.0, 256.0, 8.0 + _steps(1.0, 64) * 0.01, 16.0 + _steps(1.0, 65) * 0.01, rng.uniform(64, 200, max(n - 131, 0))][:n]
+    elif kind == "edge":           # scores from 0 to 256: bins of 2^20 keys, an eighth of an octave; 64 and 65 different keys in one each
+        s = np.r_[0.0, 256.0, _steps(8.01, 64), _steps(16.01, 65), rng.uniform(64, 200, max(n - 131, 0))][:n]
+        assert n < 131 or (len(np.unique(_steps(8.01, 64))), len(np.unique(_steps(16.01, 65)))) == (64, 65)
     elif kind == "outliers":       # a crowd of few values behind an outlier on either side: its own range is one value or few
         s = np.round(rng.normal(size=n) * 8) / 8
         s[: min(n, 2)] = (np.inf, -np.inf)[: min(n, 2)]
@@ -45,6 +46,8 @@ def test_every_end(n, kind):
     s = _scores(kind, n, rng)
     rank = int((s > 3.0).sum()) if kind not in ("odd", "outliers", "top") else n // 2
     cuts = sorted({min(n, max(0, k)) for k in (0, 1, n // 3, n - 1, n, rank, rank - 1, rank - 64, rank - 65, rank - 499, rank - 500, rank - 501)})
+    if kind == "edge":             # inside either block, from both ends
+        cuts = sorted({*cuts, *(k for i in (1, 17, 32, 63, 64, 65, 66, 97, 128, 129) for k in (i + 1, n - 1 - i) if 0 <= k <= n)})
     dev = torch.from_numpy(s).cuda()
     halt, counts = torch.empty((n,), dtype=torch.uint8, device="cuda"), torch.empty(((n + 63) // 64,), dtype=torch.int32, device="cuda")
     ws = torch.empty((256 + 4 * counts.numel(),), dtype=torch.uint8, device="cuda")
