@@ -97,10 +97,12 @@ dash_status launch_score_decide(const dash_layer_params& p, const NormSums& sums
 dash_status launch_score_rows(const float* delta, const void* x, int n, int d, int dtype, int kind,
                               float* scores, hipStream_t s);
 // compact.hip
-// TOPK in one launch with score and compaction up to this many rows. Layer call in a graph, one launch / score, selection
-// and compaction one after the other, us: 64 rows of 28 x 128 heads 29.1 / 34.4, 512 51.3 / 54.9, 1500 93.5 / 94.6, 2120
-// 120.4 / 119.5; of 4 x 128 heads: 64 20.4 / 26.1, 1500 45.1 / 47.2, 2120 56.7 / 56.4.
-constexpr int kFusedTopkRows = 1536;
+// TOPK in one launch with score and compaction up to this many rows. Layer call in a graph, one launch whose workgroups exchange
+// keys / score, selection and compaction one after the other, us: width 3584 513 rows 45.5 / 46.1, 640 57.0 / 57.7, 1000 68.2 / 67.7, 1200
+// 80.3 / 79.8, 1536 90.4 / 88.9; width 512 513 23.6 / 25.0, 1000 27.8 / 28.6, 1200 30.2 / 29.9, 1536 33.0 / 32.4; width 1024 513 24.8 / 25.9, 1000
+// 30.0 / 29.8, 1536 41.0 / 39.6; width 8192 300 30.0 / 31.7, 1000 44.5 / 44.4, 1536 53.5 / 52.0: the exchange is a fixed cost and grows
+// with the rows that every chunk counts through, the selection's launch is about 6 us whatever the rows.
+constexpr int kFusedTopkRows = 1024;
 // ... of these, up to this many without an exchange, every workgroup deciding about all rows itself (topk_compact_few_kernel): always up
 // to 256 rows (a row per thread and quarter), beyond that while a row has at most 64 norm pairs (NormSums::cols), since every
 // workgroup reads the pairs of all rows. Layer call in a graph, with the exchange / without, us: width 512 64 rows 17.0 / 14.5, 256
