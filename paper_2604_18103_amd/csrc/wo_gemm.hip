@@ -21,9 +21,9 @@ namespace dash {
 // and few columns, so a larger tile would leave the chip idle and a wave with all of K a long serial chain. Step s of
 // chunk c contracts 16 c + 4 g + s (lane = 16 g + i) and column block e holds columns 4 i + e, so that every operand is a
 // 16-byte global load; no LDS and no barrier in the loop. Latency-bound at a few hundred rows, then bound by the L2
-// reads (96 words per 32 x 64 products and step). Measured, with K = N: 512 rows of 256 under 8 us
-// (the host's rate of calls; 38 with 64 x 64 tiles staged through LDS), 2048 of 512 15 us (97), 8192 of 512 48 us (127); the
-// error against 64 bits fell from 2.9e-7 to 1.2e-7, the chains of adds being shorter.
+// reads (96 words per 32 x 64 products and step). Measured, with K = N (in parentheses with 64 x 64 tiles staged through LDS): 2048 rows
+// of 512 15 us (97), 8192 of 512 46 us (127); the error against 64 bits fell from 2.9e-7 to 1.2e-7, the chains of adds being shorter.
+// Fewer rows: wo_f32_few_kernel.
 // ------------------------------------------------------------------------------------------------
 constexpr int kF32TileM = 32, kF32TileN = 64;
 constexpr int kF32Split = 8;
@@ -396,7 +396,7 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
                 acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a], bfr[b], acc[a][b], 0, 0, 0);
     };
     // issue order of one slice: the fragment reads of the slice after it spread between its MFMAs
-    constexpr int RD = RB + 8, MF = 4 * RB;  // LDS reads and MFMAs per slice: 16 and 32, or 12 and 16
+    constexpr int RD = RB + 8, MF = 4 * RB;  // LDS reads and MFMAs per slice: 16 and 32 (256 rows), 15 and 28, 14 and 24, 12 and 16
     auto pin_slice = [] {
 #pragma unroll
         for (int i = 0; i < 2 * RD - MF; ++i) {
@@ -433,7 +433,7 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
     // wave queues behind it and issues no MFMA meanwhile (a burst after the barrier: 5 % slower; one request per
     // MFMA, per 2, per 4: 3, 1.5 and 0.5 % slower than per 3). The requests are opaque to the compiler's scheduler
     // and fence its LDS reads, so this half is placed by hand: requests, the fragment reads of the next slice (B
-    // first) at even distances, MFMAs, pinned in eight groups.
+    // first) at even distances, MFMAs, pinned in eight groups (224 rows: seven of four, 28 having no eighth).
     auto read_b_frag = [&](int st, int ks, int b, bf16x8* bfr) {
         const __bf16* sb = smem + st * kStageElems + kAElems;
         const int krow = 32 * ks + 8 * fg + fi / 4;
