@@ -288,7 +288,8 @@ __global__ __launch_bounds__(256) void topk_flag_kernel(const float* __restrict_
     if (lane == 0) chunk_counts[chunk] = __popcll(m);
 }
 
-// TopK decision (Eq. 3) of up to 1024 * B rows in ONE launch of one workgroup: selection and flags together.
+// TopK decision (Eq. 3) of up to 1024 * B rows (B 4, 8 or 16: every step of every loop costs, also beyond the last row) in ONE launch
+// of one workgroup: selection and flags together.
 // Thread t holds the keys of rows u * 1024 + t (u < B) in registers, so the scores are read once: the passes, the flags and the
 // kept counts per 64-row chunk (chunk u * 16 + w is what wave w holds at step u) all work
 // from those registers. Same total order, same tie rule (earliest rows first) and same outputs as the
@@ -299,11 +300,12 @@ __global__ __launch_bounds__(256) void topk_flag_kernel(const float* __restrict_
 // (an outlier stretched the range, or ties) is taken over its own keys' range in turn: bins of 2^21, 2^10 keys and one at most, so
 // three passes, and none for a bin whose keys are all equal. (Taken in fixed steps instead, ties and neighbours go through all passes
 // behind a range that was not worth finding: 16384 rows of tied scores 16.2 us, of neighbours behind an outlier 26.7.)
-// One compute unit does all of it, so the time is latencies (launch, loads, range, pass, search, flags: 6 us for any few rows) and
+// One compute unit does all of it, so the time is latencies (launch, loads, range, pass, search, flags: 4.6 us for any few rows) and
 // from 8192 rows on that unit's instruction throughput. Heavy-tailed scores, us, top digits in three passes / this:
-// 64 rows 8.2 / 5.4, 2120 8.4 / 5.9, 8192 8.9 / 7.5, 16384 12.6 / 11.1; all within a few percent of each other 10.5 / 6.9 at 8192, 15.9 / 10.7
-// at 16384; all equal 19.0 / 6.0 and 32.5 / 9.6; steps of an eighth 10.1 / 8.3 and 14.7 / 12.7; of both signs 8.9 / 8.7 and 12.6 / 12.8;
-// neighbours behind an outlier 15.6 / 11.9 and 25.6 / 18.9; one zero among nearly equal ones, 10.4 / 10.6 and 15.8 / 16.3.
+// 64 rows 8.2 / 4.6, 2120 8.4 / 4.8, 8192 8.9 / 7.2, 16384 12.6 / 10.4; all within a few percent of each other 10.5 / 6.8 at 8192, 15.9 / 10.1
+// at 16384; all equal 19.0 / 5.7 and 32.5 / 9.1; steps of an eighth 10.1 / 8.0 and 14.7 / 12.4; of both signs 8.9 / 8.4 and 12.6 / 12.4;
+// neighbours behind an outlier 15.6 / 11.4 and 25.6 / 18.4; one zero among nearly equal ones 10.4 / 10.1 and 15.8 / 15.7. Scalar branches
+// round the steps beyond the last row, instead of a form for 4096, took their schedule from the 16 steps (16384 rows 13.2).
 // 16-byte loads with four flags per store, and the keys in LDS under short rolled loops, measured slower than this plain form.
 template <int B>
 __global__ __launch_bounds__(kSelectThreads) void topk_decide_small_kernel(
@@ -318,14 +320,22 @@ __global__ __launch_bounds__(kSelectThreads) void topk_decide_small_kernel(
     const int lo = min(n_first, n), hi = max(lo, n - n_last);  // candidates are rows [lo, hi)
     const int n_cand = hi - lo;
     const int k_cand = max(0, min(k_keep - (n - n_cand), n_cand));
+    // All loads in flight together: unconditional, on clamped rows, and used by an empty asm before any key is formed (left to their use,
+    // they went out one behind the other, 16 trips to memory: 1.7 us of the signal path of 16384 rows).
+    float score[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) score[u] = scores[min(u * kSelectThreads + tid, n - 1)];
+#pragma unroll
+    for (int u = 0; u < B; ++u) asm volatile("" : "+v"(score[u]));
     uint32_t key[B];
     const uint32_t no_key = keep_low ? 0xFFFFFFFFu : 0u;  // which no score has (order_key is at least 0x007FFFFF): no candidate
     uint32_t cand = 0u;                                   // bit u: row u * 1024 + tid is a candidate
 #pragma unroll
     for (int u = 0; u < B; ++u) {
         const int r = u * kSelectThreads + tid;
-        if (r >= lo && r < hi) cand |= 1u << u;
-        key[u] = (cand >> u) & 1u ? rank_key(scores[r], keep_low) : no_key;
+        const bool is_cand = r >= lo && r < hi;
+        if (is_cand) cand |= 1u << u;
+        key[u] = is_cand ? rank_key(score[u], keep_low) : no_key;
     }
     // nothing unprotected survives: no key exceeds the threshold and no tie is kept
     uint32_t T = 0xFFFFFFFFu;
@@ -501,17 +511,15 @@ dash_status topk_static_scratch_ptr(void** out) {
 }
 
 // The TopK decision on n > 0 scores: up to 16384 rows in one launch that keeps the keys in registers (when the
-// caller allows it: 7.5 us at 8192 rows, 11 at 16384, where the two launches take 14; at 32768 rows it would take 23
+// caller allows it: 7.2 us at 8192 rows, 10.4 at 16384, where the two launches take 14; at 32768 rows it would take 23
 // against their 20, the flags of the longer input being spread over many workgroups), longer inputs by the selection
 // kernel, which leaves its state and tie counts in ws, and the flag kernel.
 static void launch_topk(const float* scores, int n, int n_first, int n_last, int k_keep, int keep_low, uint8_t* halt,
                         int32_t* chunk_counts, void* ws, bool one_launch_allowed, hipStream_t s) {
-    if (one_launch_allowed && n <= 8 * kSelectThreads) {
-        hipLaunchKernelGGL(topk_decide_small_kernel<8>, dim3(1), dim3(kSelectThreads), 0, s, scores, n, n_first,
-                           n_last, k_keep, keep_low, halt, chunk_counts);
-    } else if (one_launch_allowed && n <= 16 * kSelectThreads) {
-        hipLaunchKernelGGL(topk_decide_small_kernel<16>, dim3(1), dim3(kSelectThreads), 0, s, scores, n, n_first,
-                           n_last, k_keep, keep_low, halt, chunk_counts);
+    if (one_launch_allowed && n <= 16 * kSelectThreads) {
+        hipLaunchKernelGGL(n <= 4 * kSelectThreads ? topk_decide_small_kernel<4>
+                                                   : (n <= 8 * kSelectThreads ? topk_decide_small_kernel<8> : topk_decide_small_kernel<16>),
+                           dim3(1), dim3(kSelectThreads), 0, s, scores, n, n_first, n_last, k_keep, keep_low, halt, chunk_counts);
     } else {
         TopkState* st = reinterpret_cast<TopkState*>(ws);
         int32_t* tie_counts = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(ws) + 256);

@@ -40,7 +40,7 @@ def _scores(kind, n, rng):
 
 
 @pytest.mark.parametrize("kind", ["dense", "crowd", "tied crowd", "edge", "outliers", "top", "odd"])
-@pytest.mark.parametrize("n", [1, 2, 64, 1025, 8192, 8193, 16384])
+@pytest.mark.parametrize("n", [1, 2, 64, 1025, 4096, 4097, 8192, 8193, 16384])
 def test_every_end(n, kind):
     rng = np.random.default_rng(n)
     s = _scores(kind, n, rng)
