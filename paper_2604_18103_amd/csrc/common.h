@@ -98,11 +98,11 @@ dash_status launch_score_rows(const float* delta, const void* x, int n, int d, i
                               float* scores, hipStream_t s);
 // compact.hip
 // TOPK in one launch with score and compaction up to this many rows. Layer call in a graph, one launch whose workgroups exchange
-// keys / score, selection and compaction one after the other, us: width 3584 513 rows 45.5 / 46.1, 640 57.0 / 57.7, 1000 68.2 / 67.7, 1200
-// 80.3 / 79.8, 1536 90.4 / 88.9; width 512 513 23.6 / 25.0, 1000 27.8 / 28.6, 1200 30.2 / 29.9, 1536 33.0 / 32.4; width 1024 513 24.8 / 25.9, 1000
-// 30.0 / 29.8, 1536 41.0 / 39.6; width 8192 300 30.0 / 31.7, 1000 44.5 / 44.4, 1536 53.5 / 52.0: the exchange is a fixed cost and grows
-// with the rows that every chunk counts through, the selection's launch is about 6 us whatever the rows.
-constexpr int kFusedTopkRows = 1024;
+// keys / score, selection and compaction one after the other, us: width 3584 513 rows 45.4 / 45.5, 640 57.2 / 57.1, 800 62.2 / 61.9, 1000
+// 68.0 / 66.9; width 512 513 23.6 / 24.6, 720 25.5 / 26.0, 800 26.3 / 26.4, 1000 27.9 / 27.6; width 1024 513 25.0 / 25.3, 720 26.95 / 27.0, 800 28.2 /
+// 27.8, 1536 41.0 / 39.6; width 8192 300 29.9 / 31.0, 576 39.0 / 39.6, 720 40.0 / 39.9, 1000 44.5 / 43.3: the exchange is a fixed cost and
+// grows with the rows that every chunk counts through, the selection's launch is 4.6 us whatever the rows.
+constexpr int kFusedTopkRows = 768;
 // ... of these, up to this many without an exchange, every workgroup deciding about all rows itself (topk_compact_few_kernel): always up
 // to 256 rows (a row per thread and quarter), beyond that while a row has at most 64 norm pairs (NormSums::cols), since every
 // workgroup reads the pairs of all rows. Layer call in a graph, with the exchange / without, us: width 512 64 rows 17.0 / 14.5, 256

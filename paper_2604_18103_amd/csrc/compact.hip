@@ -130,7 +130,7 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(
 //  - NONE, THRESHOLD: a workgroup (c, y) waits for publishers (c', 0) with c' <= c only. They have a smaller linear index,
 //    are therefore resident or done, and publish without having waited.
 //  - TOPK (where few_topk does not hold): the publishers wait for one another, so they have to be resident together. They are at most
-//    kFusedTopkRows / 64 = 16 workgroups, a fraction of what the chip holds, but nothing reserves that room: beside
+//    kFusedTopkRows / 64 = 12 workgroups, a fraction of what the chip holds, but nothing reserves that room: beside
 //    kernels on other streams that fill the chip, the last of them may come late.
 // Every wait is bounded (kPubSpinLimit), and one that ends without its word fails the call: a publisher that gave up
 // publishes FAILED instead of a mask; whoever reads FAILED, or gives up itself, gathers nothing and writes the survivor count -1.
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
             const int k_cand = max(0, min(k_keep - (n - (hi - lo)), hi - lo));
             // everybody's keys, two per load, all of a thread's loads in flight at once; what has not arrived is asked for
             // again together
-            constexpr int kLoads = kFusedTopkRows / 2 / kCompactThreads;
+            constexpr int kLoads = (kFusedTopkRows / 2 + kCompactThreads - 1) / kCompactThreads;
             const int n_pairs = (n + 1) / 2;  // the last may reach one word beyond the n-th: padding, 0
             const unsigned long long* pairs = reinterpret_cast<const unsigned long long*>(words);
             uint2 kv[kLoads];

@@ -341,7 +341,7 @@ def test_layer_call_in_one_launch_equals_the_staged_calls(n, d, prot):
             assert k == min(n, prot[0] + prot[1])
 
 
-@pytest.mark.parametrize("rule,n", [("threshold", 1500), ("topk", 1500), ("none", 1500), ("topk", 900), ("topk", 300)])
+@pytest.mark.parametrize("rule,n", [("threshold", 1500), ("topk", 1500), ("none", 1500), ("topk", 700), ("topk", 300)])
 def test_layer_call_in_a_hip_graph_replays_like_eager_calls(rule, n):
     """The layer call records only kernels (the words its one-launch score/decision/compaction hands chunks over
     with are cleared by the attention kernel of the same call, not by a memset), so it can be captured in a HIP

@@ -1,4 +1,4 @@
-"""The layer call's TOPK rule up to 1024 rows, where scores, decision and compaction are one launch: against the oracle's
+"""The layer call's TOPK rule up to 768 rows, where scores, decision and compaction are one launch: against the oracle's
 TopK on the GPU's own scores, bit for bit."""
 import numpy as np
 import pytest
@@ -47,14 +47,14 @@ def _layer(n, d, hq, k_keep, prot, kind, seed):
     assert torch.equal(halt, buf.halt_mask[:n])
 
 
-@pytest.mark.parametrize("n", [1, 63, 64, 65, 255, 257, 513, 960, 961, 1000, 1023, 1024, 1025, 1472, 1473, 1535, 1536, 1537])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 255, 257, 513, 704, 705, 767, 768, 769, 1000, 1472, 1473, 1535, 1536, 1537])
 def test_against_the_oracle(n):
     for i, (k_keep, prot) in enumerate(((n // 3, (0, 0)), (n, (0, 0)), (0, (0, 0)), (max(1, n // 2), (min(n, 5), min(n, 3))),
                                         (2, (min(n, 64), min(n, 32))))):
-        _layer(n, 64 if n > 1500 or n == 1024 else 264, 1, k_keep, prot, "spread", seed=n + i)
+        _layer(n, 64 if n > 1500 or n == 768 else 264, 1, k_keep, prot, "spread", seed=n + i)
 
 
 @pytest.mark.parametrize("kind", ["tied", "nan", "few"])
 def test_ties_and_nans(kind):
-    for n, k_keep, prot in ((200, 77, (0, 0)), (333, 150, (10, 7)), (1000, 930, (64, 32)), (1500, 1400, (64, 32)), (130, 1, (0, 0))):
+    for n, k_keep, prot in ((200, 77, (0, 0)), (333, 150, (10, 7)), (700, 650, (64, 32)), (1500, 1400, (64, 32)), (130, 1, (0, 0))):
         _layer(n, 128, 2, k_keep, prot, kind, seed=n)
