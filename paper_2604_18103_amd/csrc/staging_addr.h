@@ -452,7 +452,8 @@ DASH_HD uint32_t few_q_voff(int row0, int n, int r, int lane, int head, int Hq, 
 // causal mask (half of the blocks, long rows first) up to 3, at head size 64 (half the bytes) 5; without one, where a third
 // workgroup per unit is a whole round, 2. Measured, us, this form / the tiled ones; causal, 28 heads of 128: n = 64 5.7 / 8.4, 192
 // 7.3 / 10.6, 512 10.8 / 15.2, 832 (2.8 per unit) 18.1 / 18.8, 960 (3.3) 20.8 / 20.2; 14 heads 2048 (3.5) 31.9 / 33.1, 8 heads 3072
-// (3) 35.3 / 44.1, 4096 (4) 58 / 57; 16 heads of 64: 64 4.7 / 6.8, 1024 9.8 / 15.2, 2560 (5) 27.2 / 27.8, 2816 34.1 / 29.8; 32 heads
+// (3) 35.3 / 44.1, 4096 (4) 58 / 57; the longest that take it, 4 heads 6144 (3) 65 / 79, 2 heads 11000 (2.7) 110 / 134, one head 16385 (2)
+// 151 / 191, one of 64 24577 (3) 162 / 188; 16 heads of 64: 64 4.7 / 6.8, 1024 9.8 / 15.2, 2560 (5) 27.2 / 27.8, 2816 34.1 / 29.8; 32 heads
 // of 64: 1280 (5) 18.8 / 18.9. Without a mask, 28 heads of 128: 576 (2) 12.9 / 14.5, 640 (2.2) 20.6 / 15.4; 16 heads of 64: 1024 (2)
 // 12.0 / 13.9, 1152 16.1 / 15.1.
 // Eight waves, which halve the serial loop, while all workgroups are resident at once (one per unit, at head size 64 two): 4 heads of
