@@ -147,10 +147,13 @@ struct RowPlan {
     int rb, whole;  // 16-row blocks per wave of the lower tiles (0: none), 256-row row tiles before them
 };
 // Tile order of a launch over whole rows of tiles. Lower tiles are one round, so each XCD holds all of its tiles at once: in the plain
-// order those are one row tile in 8 and every column, and the whole weight passes through every L2, where a block of 8 x 4 tiles
-// reads four columns of it. Row tiles a multiple of 8, plain / in column panels, us: 1486 rows of 8192 x 8192 175 / 150,
-// 1486 of 2048 x 8192 53 / 48, of 4096 x 6144 79 / 69, 3022 of 3584 x 3584 71.5 / 70.0, 4430 of 4096 x 2048 69.8 / 67.5.
-DASH_HD bool rows_plain(int mt, int rb) { return rb == 8 && mt % 8 == 0; }
+// order mt / 8 row tiles and every column, in column panels blocks of 8 x 4 tiles. With 8 row tiles the plain order gives an XCD one of them
+// and the whole weight, and panels are faster whatever the weight; from 16 on an operand that has just been written is read through one L2
+// and not two, which is worth more. 256-row tiles / lower ones plain / in panels, us, operand written before each call: 1491 rows of 256 x
+// 8192 21.5 / 19.9 / 19.4, of 1024 x 6144 34.2 / 32.1 / 30.3, of 4096 x 6144 97.7 / 94.2 / 89.9, of 8192 x 8192 177 / 185 / 165; 6099 of 512 x 1536
+// 26.5 / 23.6 / 26.4, 4563 of 1024 x 2048 37.4 / 31.1 / 32.9, 3027 of 2048 x 4096 56.1 / 52.5 / 53.7, of 18944 x 3584 431 / 401 / 410, 3027 of 14336 x
+// 4096 and 4563 of 4096 x 2048 the same. (Repeated on operands that stay in the L2s panels are up to 4 % faster there too.)
+DASH_HD bool rows_plain(int mt, int rb) { return mt % 8 == 0 && (rb == 8 || mt > 8); }
 inline RowPlan row_plan(const GemmPlan& g, int M, int cu) {
     if (cu <= 0 || g.parts >= 2 || g.rest > 0) return RowPlan{0, 0};
     const int rounds = (g.tiles + cu - 1) / cu, whole = (int)((long long)(rounds - 1) * cu / g.nt);

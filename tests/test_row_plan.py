@@ -40,8 +40,15 @@ def test_every_row_once_and_in_range():
     assert taken > 100
 
 
-@pytest.mark.parametrize("M,K,N,rb", [(1486, 8192, 8192, 6), (1486, 4096, 6144, 6), (3022, 3584, 3584, 6), (4430, 4096, 2048, 6), (2400, 3584, 3584, 6)])
+@pytest.mark.parametrize("M,K,N,rb", [(1486, 8192, 8192, 6), (1486, 256, 8192, 6), (1486, 4096, 6144, 6), (2400, 3584, 3584, 6)])
 def test_an_xcd_reads_few_columns(M, K, N, rb):
-    """32 consecutive tiles of panels of four columns and at least seven rows: parts of at most three panels."""
+    """Up to 8 row tiles, and where they are no multiple of 8: 32 consecutive tiles of panels of four columns and at least seven rows,
+    which are parts of at most three panels."""
     assert _plan(M, K, N) == (rb, 0) and -(-M // (32 * rb)) >= 7
     assert _load().dash_rows_columns(N, 0, M, rb) <= 12
+
+
+@pytest.mark.parametrize("M,K,N", [(3027, 2048, 4096), (6099, 512, 1536), (4563, 1024, 2048)])
+def test_an_xcd_reads_whole_rows(M, K, N):
+    """16 row tiles and more in eights: the plain order, every column of an eighth of the rows."""
+    assert _plan(M, K, N) == (6, 0) and _load().dash_rows_columns(N, 0, M, 6) == N // 256
