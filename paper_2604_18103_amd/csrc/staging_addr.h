@@ -139,9 +139,10 @@ inline GemmPlan gemm_plan(int M, int K, int N, int cu, bool may_split, size_t sp
 //    3000 78 / 71, 3400 80 / 76 (192 rows), 3700 84 / 82.5 (224); K = 18944 2400 330 / 281, 3700 410 / 400; 3584 x 4608 with the row
 //    norm's launch 1800 74 / 64; 1024 x 1024 9000 30.5 / 26.7. Not 224 rows where the row tiles are a multiple of 8 and the columns
 //    few: the plain tile order, which lets an XCD share row panels, is worth more (8192 x 1024 x 1536 34.6 / 36.0).
-//    And not 224 rows where they fill every unit: none idles then (1742 of 2048 x 8192 54.6 / 55.3, 7630 of 14336 x 4096 650 / 659, 3534 300 / 301).
 //  - the last of several rounds, for long contractions: K = 18944, N = 3584: 7500 rows 853 / 792, 8192 860 / 845, 11885 1312 / 1239,
 //    13000 1339 / 1300; at K = 3584 it is within the noise (11885 260 / 253, 8192 169 / 175).
+//    Not 224 rows where they fill every unit, so that none idles: 14336 x 4096 7635 rows 648 / 658, 11731 978 / 1009, 15827 1310 / 1371.
+//    (As the only round they gain there too: 3539 rows of 4096 x 4096 100.9 / 95.7, 7123 of 1024 x 2048 38.9 / 34.6.)
 // All rounds on lower tiles is slower: 10000 rows of K = 18944 1046 / 1169.
 struct RowPlan {
     int rb, whole;  // 16-row blocks per wave of the lower tiles (0: none), 256-row row tiles before them
@@ -160,7 +161,7 @@ inline RowPlan row_plan(const GemmPlan& g, int M, int cu) {
     for (int rb = 6; rb <= 7; ++rb) {
         const long long t = (long long)((M - whole * kGM + 32 * rb - 1) / (32 * rb)) * g.nt;
         const double gain_us = 0.5 * (1.0 - rb / 8.0) * g.ksteps * 1.66;
-        if (rb == 7 && ((g.plain && g.nt < 8) || t == cu)) continue;
+        if (rb == 7 && ((g.plain && g.nt < 8) || (whole > 0 && t == cu))) continue;
         if (t <= cu && (whole == 0 || gain_us > 20.0)) return RowPlan{rb, whole};
     }
     return RowPlan{0, 0};

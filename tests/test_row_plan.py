@@ -18,7 +18,7 @@ def _plan(M, K, N):
 @pytest.mark.parametrize("M,K,N,rb,whole", [
     (2400, 3584, 3584, 6, 0), (3456, 3584, 3584, 6, 0), (3457, 3584, 3584, 7, 0), (4032, 3584, 3584, 7, 0), (4033, 3584, 3584, 0, 0),
     (2305, 3584, 4608, 6, 0), (2688, 3584, 4608, 6, 0), (7500, 18944, 3584, 6, 18), (8192, 18944, 3584, 7, 18), (11885, 18944, 3584, 6, 36),
-    (11885, 3584, 3584, 0, 0), (8192, 3584, 3584, 0, 0), (9216, 18944, 3584, 0, 0), (16384, 3584, 3584, 0, 0), (8192, 1024, 1536, 0, 0), (1742, 2048, 8192, 0, 0), (7630, 14336, 4096, 0, 0), (7000, 14336, 4096, 6, 16), (6874, 18944, 3584, 0, 0)])
+    (11885, 3584, 3584, 0, 0), (8192, 3584, 3584, 0, 0), (9216, 18944, 3584, 0, 0), (16384, 3584, 3584, 0, 0), (8192, 1024, 1536, 0, 0), (1742, 2048, 8192, 7, 0), (3539, 4096, 4096, 7, 0), (7630, 14336, 4096, 0, 0), (11731, 14336, 4096, 0, 0), (7000, 14336, 4096, 6, 16), (6874, 18944, 3584, 0, 0)])
 def test_where(M, K, N, rb, whole):
     assert _plan(M, K, N) == (rb, whole)
 
