@@ -215,7 +215,7 @@ DASH_HD bool small_work_of(int b, int tiles, int parts, int& tile, int& part) {
 //   small form       KW NS  per unit  step alone, step of a full unit   (weight from memory, not from the last-level cache)
 //   64 x  64          2  3     1        0.205                             0.23
 //   64 x 128          2  3     1        0.31                              0.35
-//  128 x 128          2  2     1        0.50                              0.70
+//  128 x 128          1  3     1        0.45                              0.61
 //  128 x 128          1  2     2        0.64,  0.875 (two workgroups)     0.80, 0.95
 //   large tile 1.35 (units two thirds busy or less) to 1.66 (all busy), half tile 0.65 to 0.98
 //   a second pass over K parts: 4 + 8 bytes per partial sum at 8 TB/s; several rounds of small tiles: a factor 1.3 (the L2)
@@ -225,7 +225,7 @@ DASH_HD bool small_work_of(int b, int tiles, int parts, int& tile, int& part) {
 // on weights from memory): below the line 0.62 and 0.64 times the large tiles' time on average; at worst 1.09 times on cached
 // weights and, at K = 4096 on weights from memory, 1.18. (Beyond those ranges: five K steps, 2201 x 320 x 3584, 14 / 18; a column
 // tile for 8 columns, 6600 x 3584 x 520, 50 / 66.) Large tiles / this choice, us, K = N = 3584 with a row norm's launch of about
-// 5, cached and from memory: 63 rows 24.6 / 14.9 and 25.1 / 17.7, 511 40 / 28 and 41 / 35, 901 48 / 38 and 48 / 46, 1401 58 / 49.5
+// 5, cached and from memory: 63 rows 24.6 / 14.9 and 25.1 / 17.7, 511 40 / 28 and 41 / 35, 901 48 / 37 and 48 / 43, 1401 58 / 49.5
 // and 58 / 58.6, 2201 75 / 60 and 75 / 65; from 2305 on large. Feed-forward 3584 x 18944: 17 rows 133 / 103, 63 133 / 113.
 struct SmallForm {
     int BM, BN, KW, NS, per_cu;
@@ -233,7 +233,7 @@ struct SmallForm {
 };
 constexpr SmallForm kSmallForms[4] = {{64, 64, 2, 3, 1, 0.205, 0.205},
                                       {64, 128, 2, 3, 1, 0.31, 0.31},
-                                      {128, 128, 2, 2, 1, 0.50, 0.50},
+                                      {128, 128, 1, 3, 1, 0.45, 0.45},
                                       {128, 128, 1, 2, 2, 0.64, 0.875}};
 constexpr int kSmallSplitMinSteps = 6;  // K steps of a part, at least
 

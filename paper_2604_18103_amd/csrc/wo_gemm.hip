@@ -640,7 +640,7 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
 
 // ------------------------------------------------------------------------------------------------
 // The same product on small tiles: BM x BN (64 or 128 each), KW groups of 4 waves in 2 x 2. One workgroup per compute unit (96 to
-// 144 KB of LDS), of the 128 x 128 form with one K group two.
+// 144 KB of LDS), of the second 128 x 128 form two.
 // Few rows leave the 256 x 256 tiles with a handful of workgroups, which then have to be cut along K and summed in a
 // second pass: with 177 rows the fp32 sums written and read back were more bytes than the weight. Small tiles fill the
 // chip without that: 177 rows of K = N = 3584 take 15.5 us instead of 26, 333 rows of 512 4.8 instead of 15 (small_plan).
@@ -649,9 +649,15 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
 // multiplied from registers while the next one's fragments are read and the step NS ahead is requested. What bounds it: per
 // 64 x 64 step 48 KB through LDS (16 written, 32 read), 384 cycles of it, of the 500 that a step takes; more stages or K
 // groups do not shorten it.
-// 128 x 128 tiles wait for their operands' way from the L2: 910 rows of K = N = 3584 take 34.7 us with the weight cached and 43.4
-// with it from memory; half K steps in four stages 36.6 and 38.2, but 2120 rows 66 and 79 instead of 55 and 62 (half lines of A);
-// requests dealt out among the MFMAs, as the large tiles do, 38.1 and 47.1: a step has one round to land, so it is requested first.
+// 128 x 128 tiles, one workgroup per unit (KW 1, NS 3): four waves, one per SIMD, so what a wave does one after the other is not covered
+// by another: requests, fragment reads and MFMAs are dealt out among one another as the large tiles do it, with two steps of lead for
+// the requests to land in. Per step 96 KB through LDS and 512 cycles each of requests and MFMAs, 0.45 us. As two K groups of two
+// stages, each requesting a step at once and ahead of its fragment reads, a step took 0.50 us on cached weights and 0.70 on weights from memory,
+// which then had one round to land: K = N = 3584 with a row norm's launch, weights from memory, 640 rows 48.5 -> 44.0 us, 995 48.8 -> 44.7, 1150
+// 50.6 -> 46.5; 4096 700 rows 52.9 -> 44.9; cached 640 34.5 -> 32.9, 995 the same. Four or five stages are no faster. (Four waves
+// that request and read in turn, without the interleaving: 0.66 us a step whatever the stages.)
+// Two workgroups per unit (NS 2) cover each other's gaps and keep the plain order: a step has one round to land, so it is requested
+// first (interleaved: 1400 rows 47.5 -> 46.1 us, 2120 57.0 -> 57.8).
 // Row norms (EPI_RESIDUAL_NORM) come as one pair per 64 columns, as a wave column of the large tiles sums them;
 // fold_partials_kernel adds them up to 256 columns for callers that see them.
 // ------------------------------------------------------------------------------------------------
@@ -718,26 +724,28 @@ __global__ __launch_bounds__(KW * kSWaves * kWave, 2) void gemm_small_kernel(con
     struct Frags {  // operands of one K step
         bf16x8 a[2][RB], b[2][CB];
     };
+    auto read_a = [&](int st, int ks, int a) {
+        const int row = wm * (BM / 2) + 16 * a + fi;
+        return *reinterpret_cast<const bf16x8*>(&smem[st * kStageElems + row * kGK + ((4 * ks + fg) ^ ((row / 2) % 8)) * 8]);
+    };
+    auto read_b = [&](int st, int ks, int b) {
+        const __bf16* sb = smem + st * kStageElems + kAElems;
+        const int krow = 32 * ks + 8 * fg + fi / 4;  // and krow + 4: the same swizzle
+        const int col = wn * (BN / 2) + 16 * b + 4 * (fi % 4);
+        const int scol = ((col / 8) ^ small_b_swz(krow, BN)) * 8 + col % 8;
+        const s16x4 lo = lds_read_tr16(&sb[krow * BN + scol]);
+        const s16x4 hi = lds_read_tr16(&sb[(krow + 4) * BN + scol]);
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    auto read_slice = [&](int st, int ks, bf16x8* af, bf16x8* bfr) {
+#pragma unroll
+        for (int b = 0; b < CB; ++b) bfr[b] = read_b(st, ks, b);
+#pragma unroll
+        for (int a = 0; a < RB; ++a) af[a] = read_a(st, ks, a);
+    };
     auto read_frags = [&](int st, Frags& f) {
-        const __bf16* sa = smem + st * kStageElems;
-        const __bf16* sb = sa + kAElems;
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-#pragma unroll
-            for (int b = 0; b < CB; ++b) {
-                const int krow = 32 * ks + 8 * fg + fi / 4;  // and krow + 4: the same swizzle
-                const int col = wn * (BN / 2) + 16 * b + 4 * (fi % 4);
-                const int scol = ((col / 8) ^ small_b_swz(krow, BN)) * 8 + col % 8;
-                const s16x4 lo = lds_read_tr16(&sb[krow * BN + scol]);
-                const s16x4 hi = lds_read_tr16(&sb[(krow + 4) * BN + scol]);
-                f.b[ks][b] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-            }
-#pragma unroll
-            for (int a = 0; a < RB; ++a) {
-                const int row = wm * (BM / 2) + 16 * a + fi;
-                f.a[ks][a] = *reinterpret_cast<const bf16x8*>(&sa[row * kGK + ((4 * ks + fg) ^ ((row / 2) % 8)) * 8]);
-            }
-        }
+        for (int ks = 0; ks < 2; ++ks) read_slice(st, ks, f.a[ks], f.b[ks]);
     };
     auto mfmas = [&](const Frags& f) {
 #pragma unroll
@@ -762,27 +770,89 @@ __global__ __launch_bounds__(KW * kSWaves * kWave, 2) void gemm_small_kernel(con
     else
         dma_wait();
     lds_barrier();
-    // Round t multiplies its step from registers while the next step's fragments are read. Before barrier t this wave's
-    // part of step t + 1 has landed (the NS - 2 steps after it may be in flight) and its fragments of step t are in
-    // registers; so after it every wave's part of step t + 1 is there, and the stage of step t takes step t + NS.
-    // Every group passes the same number of barriers.
     Frags f[2];
-    if (n_mine > 0) read_frags(0, f[0]);
     int st = 0;  // t % NS
-    auto round = [&](int t, const Frags& cur, Frags& next) {
-        if (t + NS <= n_mine)
-            dma_wait_keep<(NS - 2) * kStepLoads>();
-        else
-            dma_wait();
-        lds_barrier();
-        if (t + NS < n_mine) request(st);
-        st = st + 1 == NS ? 0 : st + 1;
-        if (t + 1 < n_mine) read_frags(st, next);
-        if (t < n_mine) mfmas(cur);
-    };
-    for (int t = 0; t < n_rounds; t += 2) {
-        round(t, f[0], f[1]);
-        if (t + 1 < n_rounds) round(t + 1, f[1], f[0]);
+    if constexpr (NS > 2 && KW == 1) {
+        // The large tiles' round (gemm_mfma_kernel): two 32-wide slices a step, the fragments of a slice read while the MFMAs of the one
+        // before it run; the wait for the next step and the barrier sit before the second slice's MFMAs, among which the step
+        // NS ahead is requested into the stage that every wave has read by then. The last NS steps request nothing.
+        constexpr int RD = RB + 2 * CB, MF = RB * CB, UNITS = RB + CB;
+        constexpr int kRequestEvery = MF / kStepLoads;
+        static_assert(kRequestEvery >= 1 && RD <= MF && MF <= 2 * RD, "reads and requests of a half step fit between its MFMAs");
+        auto second_half = [&](int st_next, bool ask) {
+            const uint32_t so = (uint32_t)(st * kStageElems * 2);
+#pragma unroll
+            for (int m = 0; m < MF; ++m) {
+#pragma unroll
+                for (int l = 0; l < kStepLoads; ++l)
+                    if (m == l * kRequestEvery && ask) {
+                        if (l < ADMA) dma_load16(a_base, a_off[l], lds_a + so + l * 1024);
+                        else dma_load16(b_base, b_off[l - ADMA], lds_b + so + (l - ADMA) * 1024);
+                    }
+#pragma unroll
+                for (int u = 0; u < UNITS; ++u)  // fragment u before the first MFMA m with u * MF <= m * UNITS
+                    if (u * MF <= m * UNITS && (m == 0 || u * MF > (m - 1) * UNITS)) {
+                        if (u < CB) f[0].b[0][u] = read_b(st_next, 0, u);
+                        else f[0].a[0][u - CB] = read_a(st_next, 0, u - CB);
+                    }
+                acc[m / CB][m % CB] =
+                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[0].a[1][m / CB], f[0].b[1][m % CB], acc[m / CB][m % CB], 0, 0, 0);
+                if (m % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+            }
+            if (ask) {
+                a_base += gemm_a_step_bytes();
+                b_base += b_step;
+            }
+        };
+        auto step = [&](bool ask) {
+            const int st_next = st + 1 == NS ? 0 : st + 1;
+            read_slice(st, 1, f[0].a[1], f[0].b[1]);
+#pragma unroll
+            for (int a = 0; a < RB; ++a)
+#pragma unroll
+                for (int b = 0; b < CB; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[0].a[0][a], f[0].b[0][b], acc[a][b], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 2 * RD - MF; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < MF - RD; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            }
+            if (ask) dma_wait_keep<(NS - 2) * kStepLoads>();
+            else dma_wait();
+            lds_barrier();
+            second_half(st_next, ask);
+            st = st_next;
+        };
+        if (n_ksteps > 0) read_slice(0, 0, f[0].a[0], f[0].b[0]);
+        int kt = 0;
+        for (; kt + NS < n_ksteps; ++kt) step(true);
+        for (; kt < n_ksteps; ++kt) step(false);
+    } else {
+        // Round t multiplies its step from registers while the next step's fragments are read. Before barrier t this wave's
+        // part of step t + 1 has landed (the NS - 2 steps after it may be in flight) and its fragments of step t are in
+        // registers; so after it every wave's part of step t + 1 is there, and the stage of step t takes step t + NS.
+        // Every group passes the same number of barriers.
+        if (n_mine > 0) read_frags(0, f[0]);
+        auto round = [&](int t, const Frags& cur, Frags& next) {
+            if (t + NS <= n_mine)
+                dma_wait_keep<(NS - 2) * kStepLoads>();
+            else
+                dma_wait();
+            lds_barrier();
+            if (t + NS < n_mine) request(st);
+            st = st + 1 == NS ? 0 : st + 1;
+            if (t + 1 < n_mine) read_frags(st, next);
+            if (t < n_mine) mfmas(cur);
+        };
+        for (int t = 0; t < n_rounds; t += 2) {
+            round(t, f[0], f[1]);
+            if (t + 1 < n_rounds) round(t + 1, f[1], f[0]);
+        }
     }
     __syncthreads();  // the operand stages are free and are reused
 
