@@ -97,22 +97,21 @@ dash_status launch_score_decide(const dash_layer_params& p, const NormSums& sums
 dash_status launch_score_rows(const float* delta, const void* x, int n, int d, int dtype, int kind,
                               float* scores, hipStream_t s);
 // compact.hip
-// TOPK in one launch with score and compaction up to this many rows. Layer call in a graph, one launch whose workgroups exchange
-// keys / score, selection and compaction one after the other, us: width 3584 513 rows 45.4 / 45.5, 640 57.2 / 57.1, 800 62.2 / 61.9, 1000
-// 68.0 / 66.9; width 512 513 23.6 / 24.6, 720 25.5 / 26.0, 800 26.3 / 26.4, 1000 27.9 / 27.6; width 1024 513 25.0 / 25.3, 720 26.95 / 27.0, 800 28.2 /
-// 27.8, 1536 41.0 / 39.6; width 8192 300 29.9 / 31.0, 576 39.0 / 39.6, 720 40.0 / 39.9, 1000 44.5 / 43.3: the exchange is a fixed cost and
-// grows with the rows that every chunk counts through, the selection's launch is 4.6 us whatever the rows.
-constexpr int kFusedTopkRows = 768;
+// TOPK in one launch with score and compaction up to this many rows (topk_compact_kernel), four keys per thread. Layer call in a graph,
+// score, selection and compaction one after the other (up to 768 rows: in one launch that ranked by counting) / this, us: width 512
+// 640 rows 24.9 / 23.1, 1000 28.0 / 26.0, 2000 34.6 / 32.8; 1024 600 25.1 / 22.9, 1500 36.0 / 34.2, 4000 76.9 / 76.4; 3584 700 58.0 / 52.5 (of which
+// 1.5 are the projection's), 2120 116.1 / 114.2, 4096 213.1 / 211.9. With eight keys per thread 6874 rows 465.6 / 465.0 and a chain's layer of
+// them 685.7 / 687.2: there every workgroup's selection takes what the launches do.
+constexpr int kFusedTopkRows = 4096;
 // ... of these, up to this many without an exchange, every workgroup deciding about all rows itself (topk_compact_few_kernel): always up
-// to 256 rows (a row per thread and quarter), beyond that while a row has at most 64 norm pairs (NormSums::cols), since every
-// workgroup reads the pairs of all rows. Layer call in a graph, with the exchange / without, us: width 512 64 rows 17.0 / 14.5, 256
-// 20.4 / 17.2, 512 22.7 / 21.2, 650 25.3 / 26.1; width 3584 (56 pairs) 64 rows 26.1 / 22.8, 256 34.7 / 31.9, 512 44.7 / 44.9; fp32 of
-// width 4096 (64 pairs) 512 219.6 / 217.9; width 6144 (96 pairs) 320 rows 54.6 / 55.6; width 8192 (128) 200 rows 61.1 / 59.2, 512
-// 95.5 / 98.1, of 2 heads 512 31.9 / 35.5; width 16384 (256) 200 rows 95.4 / 91.4, 384 143 / 150. THRESHOLD, whose workgroups wait for one
-// word, gains nothing by it.
-constexpr int kFewTopkRows = 512, kFewTopkPairs = 64;
+// to 256 rows (a row per thread and quarter), beyond that while a row has at most 32 norm pairs (NormSums::cols), since every
+// workgroup reads the pairs of all rows. Layer call in a graph, topk_compact_kernel / without exchange, us: width 512 64 rows 17.3 / 14.3, 256
+// 19.8 / 16.7, 512 22.0 / 20.9; width 3584 (56 pairs) 64 rows 24.9 / 22.1, 256 32.2 / 30.4, 333 38.8 / 39.5, 512 41.3 / 42.7; fp32 of width
+// 256 (4 pairs) 512 24.4 / 23.2; width 16384 (256 pairs), with an exchange that ranked by counting, 200 rows 95.4 / 91.4, 384 143 / 150.
+// THRESHOLD, whose workgroups wait for one word, gains nothing by it.
+constexpr int kFewTopkRows = 512, kFewTopkPairs = 32;
 inline bool few_topk(int n, int cols) { return n <= 256 || (n <= kFewTopkRows && cols <= kFewTopkPairs); }
-size_t published_bytes(int n, bool topk);  // words the fused score + decision + compaction kernel publishes its chunks through
+size_t published_bytes(int n, bool topk);  // words through which the one-launch kernels hand over masks and counts, or keys
 dash_status launch_score_decide_compact(const dash_layer_params& p, const NormSums& sums, int n, float* scores, uint8_t* halt, void* published, const int32_t* active_idx,
                                         const void* x_next, int row_bytes, void* x_compact, int32_t* new_active_idx,
                                         int32_t* n_active_out, hipStream_t s);

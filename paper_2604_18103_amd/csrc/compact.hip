@@ -7,6 +7,7 @@
 #include "common.h"
 #include "publish.h"
 #include "score_rows.h"
+#include "topk_select.h"
 
 namespace dash {
 
@@ -107,8 +108,7 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(
 }
 
 // ------------------------------------------------------------------------------------------------
-// Score, decision and compaction in ONE launch (rules NONE and THRESHOLD of the layer call, TOPK up to
-// kFusedTopkRows rows).
+// Score, decision and compaction in ONE launch (rules NONE and THRESHOLD of the layer call).
 //
 // Grid (chunks of 64 rows, column splits), 256 threads. Workgroup (c, 0) finishes the scores of chunk c from the
 // norm partials, writes scores and halt flags and PUBLISHES the chunk's kept mask and count; every workgroup
@@ -118,27 +118,15 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(
 // Published words: publish.h. They must be zero when the kernel starts (the attention kernel of the same layer call clears
 // them).
 //
-// TOPK: a publisher first shares its rows' scores as order-preserving keys (one 32-bit word per row; no key is 0, so a
-// word is its own READY flag), takes everybody's, and ranks its 64 rows by counting: row r is kept when fewer than K
-// candidates come before it (a greater key, or the same key in an earlier row - the order of the selection kernels). That
-// is n^2 comparisons spread over the publishers, n / 4 per thread, in place of a radix selection that one workgroup does
-// behind a launch of its own. Bound by latency: the norms, one exchange through the last-level cache, the count, the
-// gather. (Figures: kFusedTopkRows.)
-//
 // Waiting. Workgroups are dispatched in the order of their linear index (x fastest), and the publishers (c, 0) are the first of
-// the grid.
-//  - NONE, THRESHOLD: a workgroup (c, y) waits for publishers (c', 0) with c' <= c only. They have a smaller linear index,
-//    are therefore resident or done, and publish without having waited.
-//  - TOPK (where few_topk does not hold): the publishers wait for one another, so they have to be resident together. They are at most
-//    kFusedTopkRows / 64 = 12 workgroups, a fraction of what the chip holds, but nothing reserves that room: beside
-//    kernels on other streams that fill the chip, the last of them may come late.
-// Every wait is bounded (kPubSpinLimit), and one that ends without its word fails the call: a publisher that gave up
-// publishes FAILED instead of a mask; whoever reads FAILED, or gives up itself, gathers nothing and writes the survivor count -1.
+// the grid: a workgroup (c, y) waits for publishers (c', 0) with c' <= c only, which have a smaller linear index, are therefore
+// resident or done, and publish without having waited.
+// Every wait is bounded (kPubSpinLimit), and one that ends without its word fails the call: whoever gives up gathers nothing and writes
+// the survivor count -1.
 // The count is 0 when the kernel starts (cleared with the words), and its writer, one thread of the last chunk's publisher,
 // exchanges the 0 for the count: a -1 that is there already stays, and one that comes later replaces the count.
 // ------------------------------------------------------------------------------------------------
 constexpr int kPubSpinLimit = 1 << 20;
-constexpr int kKeyMissing = 1 << 20;  // in place of a count of keys
 
 __device__ __forceinline__ unsigned long long wait_published(const unsigned long long* word, bool& bad) {
     unsigned long long v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -152,9 +140,8 @@ __device__ __forceinline__ unsigned long long wait_published(const unsigned long
     return v;
 }
 
-template <bool TOPK>
 __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
-    const float* __restrict__ partials, int cols, int fold, int n, int score_kind, int rule, float tau, int k_keep, int n_first,
+    const float* __restrict__ partials, int cols, int fold, int n, int score_kind, int rule, float tau, int n_first,
     int n_last, float* __restrict__ scores, uint8_t* __restrict__ halt, unsigned long long* __restrict__ published,
     const int32_t* __restrict__ active_idx, const uint4* __restrict__ x_next, int row_vecs, int vecs_per_split,
     uint4* __restrict__ x_compact, int32_t* __restrict__ new_idx, int32_t* __restrict__ n_out) {
@@ -171,85 +158,7 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
         // publisher: scores, flags, the chunk's kept mask
         const float2 t = row_sums_256(partials, cols, fold, n, chunk * kChunkRows, red);
         bool keep = false;
-        if (TOPK) {
-            __shared__ __attribute__((aligned(16))) uint32_t keys[kFusedTopkRows];
-            __shared__ int before[kCompactWaves][kChunkRows];
-            const float sc = score_from_sums(t, score_kind);
-            const uint32_t mine = order_key(sc);
-            uint32_t* words = reinterpret_cast<uint32_t*>(published + 2 * gridDim.x);
-            if (wave == 0 && row < n) {
-                __hip_atomic_store(words + row, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                scores[row] = sc;
-            }
-            const int lo = min(n_first, n), hi = max(lo, n - n_last);  // candidates are rows [lo, hi)
-            const int k_cand = max(0, min(k_keep - (n - (hi - lo)), hi - lo));
-            // everybody's keys, two per load, all of a thread's loads in flight at once; what has not arrived is asked for
-            // again together
-            constexpr int kLoads = (kFusedTopkRows / 2 + kCompactThreads - 1) / kCompactThreads;
-            const int n_pairs = (n + 1) / 2;  // the last may reach one word beyond the n-th: padding, 0
-            const unsigned long long* pairs = reinterpret_cast<const unsigned long long*>(words);
-            uint2 kv[kLoads];
-            int spins = 0;
-            bool all = false;
-#pragma unroll
-            for (int u = 0; u < kLoads; ++u) kv[u] = make_uint2(0u, 0u);
-            while (!all) {
-#pragma unroll
-                for (int u = 0; u < kLoads; ++u) {
-                    const int i = u * kCompactThreads + tid;
-                    if (i < n_pairs && (kv[u].x == 0u || (kv[u].y == 0u && 2 * i + 1 < n))) {
-                        const unsigned long long w = __hip_atomic_load(pairs + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        kv[u] = make_uint2((uint32_t)w, (uint32_t)(w >> 32));
-                    }
-                }
-                all = true;
-#pragma unroll
-                for (int u = 0; u < kLoads; ++u) {
-                    const int i = u * kCompactThreads + tid;
-                    if (i < n_pairs && (kv[u].x == 0u || (kv[u].y == 0u && 2 * i + 1 < n))) all = false;
-                }
-                if (!all && ++spins > kPubSpinLimit) {
-                    bad = true;
-                    all = true;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kLoads; ++u) {
-                const int i = u * kCompactThreads + tid, r = 2 * i;
-                if (i >= (int)gridDim.x * (kChunkRows / 2)) continue;
-                uint2 c = kv[u];  // 0 comes before nothing: padding and protected rows
-                if (r < lo || r >= hi) c.x = 0u;
-                if (r + 1 < lo || r + 1 >= hi) c.y = 0u;
-                *reinterpret_cast<uint2*>(&keys[r]) = c;
-            }
-            __syncthreads();
-            int cnt_before = 0;
-            const uint32_t tie = mine - 1u;  // > tie: greater or the same
-            for (int c = wave; c < (int)gridDim.x; c += kCompactWaves) {
-                const uint4* src = reinterpret_cast<const uint4*>(keys + c * kChunkRows);
-                const uint32_t than = c < chunk ? tie : mine;
-                uint4 kv[kChunkRows / 4];
-#pragma unroll
-                for (int e = 0; e < kChunkRows / 4; ++e) kv[e] = src[e];
-#pragma unroll
-                for (int e = 0; e < kChunkRows / 4; ++e)
-                    cnt_before += (int)(kv[e].x > than) + (int)(kv[e].y > than) + (int)(kv[e].z > than) + (int)(kv[e].w > than);
-                if (c == chunk) {  // a row of the own chunk before this one counts on a tie too
-#pragma unroll
-                    for (int e = 0; e < kChunkRows / 4; ++e)
-                        cnt_before += (int)(kv[e].x == mine && 4 * e < lane) + (int)(kv[e].y == mine && 4 * e + 1 < lane) +
-                                      (int)(kv[e].z == mine && 4 * e + 2 < lane) + (int)(kv[e].w == mine && 4 * e + 3 < lane);
-                }
-            }
-            before[wave][lane] = bad ? kKeyMissing : cnt_before;
-            __syncthreads();
-            int rank = 0;
-#pragma unroll
-            for (int w = 0; w < kCompactWaves; ++w) rank += before[w][lane];
-            bad = __any(rank >= kKeyMissing);  // some thread's key never came: the ranks mean nothing
-            keep = row < n && (row_protected(row, n, n_first, n_last) || rank < k_cand);
-            if (wave == 0 && row < n) halt[row] = keep ? 0 : 1;
-        } else if (row < n) {  // every wave holds the sums of the chunk's rows (row = lane): every wave gets the same mask
+        if (row < n) {  // every wave holds the sums of the chunk's rows (row = lane): every wave gets the same mask
             const float sc = score_from_sums(t, score_kind);
             const bool h = rule == DASH_RULE_THRESHOLD && !row_protected(row, n, n_first, n_last) && sc < tau;
             keep = !h;
@@ -265,12 +174,7 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
             __hip_atomic_store(published + 2 * chunk + 1, pub_word1(mask, bad), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     } else {
-        // the chunk's mask from its publisher (every lane reads the same two words: one request per wave; one wave asks
-        // until it is there, or the waiters' requests hold up the publishers' exchange)
-        if (TOPK) {
-            if (wave == 0) (void)wait_published(published + 2 * (gridDim.x - 1), bad);
-            __syncthreads();
-        }
+        // the chunk's mask from its publisher (every lane reads the same two words: one request per wave)
         const unsigned long long w0 = wait_published(published + 2 * chunk, bad);
         const unsigned long long w1 = wait_published(published + 2 * chunk + 1, bad);
         mask = pub_mask(w0, w1);
@@ -432,6 +336,123 @@ __global__ __launch_bounds__(kFewThreads) void topk_compact_few_kernel(
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// TOPK of more rows in one launch. The first workgroups, one per 64 rows, finish scores and share them as order-preserving keys
+// (one 32-bit word per row, cleared by the attention kernel of the same call; no key is 0, so a word is its own READY flag);
+// they wait for nothing and are done. Each of the others (chunk, column split) takes the keys of ALL rows, finds the cut with all of its
+// 1024 threads (select_cut, keys in registers), and gathers its columns of its chunk's kept rows. The cut is found in as many
+// places as there are workgroups, all resident at once, so it costs its time once; saved are the launches of score, decision and
+// compaction and two trips of flags and counts through memory.
+// Waiting: publishers have the smallest linear indexes, so whoever waits for one waits for a workgroup that was dispatched before it. Every
+// wait is bounded (kPubSpinLimit), and one that ends without its key fails the call: the workgroup gathers nothing and writes the survivor
+// count -1, as score_decide_compact_kernel does. All threads ask for their keys at once and again while one is missing: with one wave
+// asking for the last row first, a trip to memory more, 640 rows of width 512 took 23.9 us and not 23.1.
+// Bound by latency: pairs, key out and back, cut, gather. Figures: kFusedTopkRows.
+// ------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(kSelectThreads, 8) void topk_compact_kernel(
+    const float* __restrict__ partials, int cols, int fold, int n, int n_chunks, int score_kind, int k_keep, int n_first, int n_last,
+    float* __restrict__ scores, uint8_t* __restrict__ halt, uint32_t* __restrict__ words, const int32_t* __restrict__ active_idx,
+    const uint4* __restrict__ x_next, int row_vecs, int vecs_per_split, uint4* __restrict__ x_compact,
+    int32_t* __restrict__ new_idx, int32_t* __restrict__ n_out) {
+    constexpr int B = kFusedTopkRows / kSelectThreads;  // keys of a thread
+    static_assert(kSelectThreads >= 4 * kChunkRows, "a thread per row of a chunk and quarter");
+    __shared__ SelectShared sh;
+    __shared__ float2 red[4][kChunkRows];
+    __shared__ int tie_base[topk_chunks(B)];
+    __shared__ unsigned long long masks[topk_chunks(B)];
+    __shared__ int kept_rows[kChunkRows];
+    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    if ((int)blockIdx.x < n_chunks) {  // publisher
+        const int row = (int)blockIdx.x * kChunkRows + lane;
+        if (wave < 4) red[wave][lane] = row_quarter(partials, cols, fold, n, row, wave);
+        __syncthreads();
+        if (wave == 0 && row < n) {
+            const float sc = score_from_sums(add_quarters(red[0][lane], red[1][lane], red[2][lane], red[3][lane]), score_kind);
+            __hip_atomic_store(words + row, order_key(sc), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            scores[row] = sc;
+        }
+        return;
+    }
+    const int chunk = ((int)blockIdx.x - n_chunks) % n_chunks, split = ((int)blockIdx.x - n_chunks) / n_chunks;
+    const int lo = min(n_first, n), hi = max(lo, n - n_last);  // candidates are rows [lo, hi)
+    const int k_cand = max(0, min(k_keep - (n - (hi - lo)), hi - lo));
+    int spins = 0;
+    uint32_t key[B];  // all of a thread's loads in flight at once; what has not arrived is asked for again together
+#pragma unroll
+    for (int u = 0; u < B; ++u) key[u] = 0u;
+    bool bad = false;
+    for (bool all = false; !all;) {
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+            if (u * kSelectThreads + tid < n && key[u] == 0u)
+                key[u] = __hip_atomic_load(words + u * kSelectThreads + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        all = true;
+#pragma unroll
+        for (int u = 0; u < B; ++u) all = all && (key[u] != 0u || u * kSelectThreads + tid >= n);
+        if (!all && ++spins > kPubSpinLimit) {
+            bad = true;
+            all = true;
+        }
+        if (!all) __builtin_amdgcn_s_sleep(2);
+    }
+    if (__syncthreads_or(bad)) {
+        if (tid == 0) __hip_atomic_store(n_out, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    }
+    uint32_t cand = 0u;  // bit u: row u * 1024 + tid is a candidate; 0, which no score's key is, for others
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+        const int r = u * kSelectThreads + tid;
+        if (r >= lo && r < hi) cand |= 1u << u;
+        else key[u] = 0u;
+    }
+    const TopkCut cut = select_cut<B>(sh, tie_base, key, cand, hi - lo, k_cand, 0);
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+        const unsigned long long m = __ballot(cut_keeps<B>(cut, tie_base, key, cand, u, u * kSelectThreads + tid < n));
+        if (lane == 0) masks[u * (kSelectThreads / kWave) + wave] = m;
+    }
+    __syncthreads();
+    int base = 0;
+    for (int c = lane; c < chunk; c += kWave) base += __popcll(masks[c]);
+    base = wave_sum_int(base);
+    const unsigned long long mask = masks[chunk];
+    const int cnt = __popcll(mask), rank = __popcll(mask & ((1ull << lane) - 1ull)), row = chunk * kChunkRows + lane;
+    const bool keep = (mask >> lane) & 1ull;
+    if (wave == 0) {
+        if (keep) kept_rows[rank] = row;
+        if (split == 0) {
+            if (row < n) halt[row] = keep ? 0 : 1;
+            if (keep) new_idx[base + rank] = active_idx[row];
+            if (chunk == n_chunks - 1 && lane == 0) {
+                int cleared = 0;
+                (void)__hip_atomic_compare_exchange_strong(n_out, &cleared, base + cnt, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                           __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    }
+    __syncthreads();
+    const int v0 = split * vecs_per_split, v1 = min(row_vecs, v0 + vecs_per_split);
+    constexpr int R = 4;
+    for (int r0 = wave * R; r0 < cnt; r0 += kSelectThreads / kWave * R) {
+        const uint4* from[R];
+        uint4* to[R];
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const int r = min(r0 + i, cnt - 1);  // a clamped duplicate rewrites the same bytes
+            from[i] = x_next + (size_t)kept_rows[r] * row_vecs;
+            to[i] = x_compact + (size_t)(base + r) * row_vecs;
+        }
+        for (int c = v0 + lane; c < v1; c += kWave) {
+            uint4 val[R];
+#pragma unroll
+            for (int i = 0; i < R; ++i) val[i] = load_once(from[i] + c);
+#pragma unroll
+            for (int i = 0; i < R; ++i) store_once(to[i] + c, val[i]);
+        }
+    }
+}
+
 __global__ void write_zero_kernel(int32_t* p) { *p = 0; }
 
 __global__ __launch_bounds__(256) void validate_idx_kernel(const int32_t* __restrict__ idx, int n, int N,
@@ -444,10 +465,12 @@ __global__ __launch_bounds__(256) void validate_idx_kernel(const int32_t* __rest
     if (bad) atomicAdd(violations, 1);
 }
 
-// Column splits of the gather: whole wave-widths (64 vectors), enough workgroups to fill 256 CUs several times over.
-static void gather_splits(int n_chunks, int row_vecs, int& splits, int& vecs_per_split) {
+constexpr int kGatherGroups = 2048;  // of 256 threads
+constexpr int kTopkGatherGroups = 384;  // of 1024 threads, of which the chip holds 512
+// Column splits of the gather: whole wave-widths (64 vectors), enough workgroups to fill 256 CUs several times over (`wanted`).
+static void gather_splits(int n_chunks, int row_vecs, int wanted, int& splits, int& vecs_per_split) {
     const int wave_cols = (row_vecs + kWave - 1) / kWave;
-    splits = (2048 + n_chunks - 1) / n_chunks;
+    splits = (wanted + n_chunks - 1) / n_chunks;
     if (splits > wave_cols) splits = wave_cols;
     if (splits < 1) splits = 1;
     vecs_per_split = ((wave_cols + splits - 1) / splits) * kWave;
@@ -472,16 +495,16 @@ dash_status launch_compact(const uint8_t* halt, const int32_t* chunk_counts, con
     const int n_chunks = (n + kChunkRows - 1) / kChunkRows;
     const int row_vecs = row_bytes / 16;
     int splits, vecs_per_split;
-    gather_splits(n_chunks, row_vecs, splits, vecs_per_split);
+    gather_splits(n_chunks, row_vecs, kGatherGroups, splits, vecs_per_split);
     hipLaunchKernelGGL(compact_kernel, dim3(n_chunks, splits), dim3(kCompactThreads), 0, s, halt,
                        chunk_counts, active_idx, (const uint4*)x_next, n, row_vecs, vecs_per_split,
                        (uint4*)x_compact, new_active_idx, n_active_out);
     return launch_status();
 }
 
-// words of the one-launch kernel: two per chunk, and for TOPK a key per row
+// words of the one-launch kernels: two per chunk, for TOPK a key per row
 size_t published_bytes(int n, bool topk) {
-    return (size_t)((n + kChunkRows - 1) / kChunkRows) * 2 * sizeof(unsigned long long) + (topk ? (size_t)((n + 1) / 2) * 2 * sizeof(uint32_t) : 0);
+    return topk ? (size_t)n * sizeof(uint32_t) : (size_t)((n + kChunkRows - 1) / kChunkRows) * 2 * sizeof(unsigned long long);
 }
 
 // Scores, decision and compaction in one launch (TOPK: n <= kFusedTopkRows). `published` (published_bytes, 8-byte aligned) and
@@ -493,20 +516,25 @@ dash_status launch_score_decide_compact(const dash_layer_params& p, const NormSu
     const int n_chunks = (n + kChunkRows - 1) / kChunkRows;
     const int row_vecs = row_bytes / 16;
     int splits, vecs_per_split;
-    gather_splits(n_chunks, row_vecs, splits, vecs_per_split);
-    const bool topk = p.rule == DASH_RULE_TOPK;
-    if (topk && few_topk(n, sums.cols)) {
+    const bool topk = p.rule == DASH_RULE_TOPK, few = topk && few_topk(n, sums.cols);
+    gather_splits(n_chunks, row_vecs, topk && !few ? kTopkGatherGroups : kGatherGroups, splits, vecs_per_split);
+    if (few) {
         hipLaunchKernelGGL(n <= 256 ? topk_compact_few_kernel<1> : topk_compact_few_kernel<2>,
                            dim3(n_chunks, splits), dim3(kFewThreads), 0, s, sums.pairs, sums.cols, sums.fold, n, p.score_kind,
                            topk_keep(p, n), p.keep_first_n, p.keep_last_n, scores, halt, active_idx, (const uint4*)x_next,
                            row_vecs, vecs_per_split, (uint4*)x_compact, new_active_idx, n_active_out);
         return launch_status();
     }
-    hipLaunchKernelGGL(topk ? score_decide_compact_kernel<true> : score_decide_compact_kernel<false>, dim3(n_chunks, splits),
-                       dim3(kCompactThreads), 0, s, sums.pairs, sums.cols, sums.fold, n, p.score_kind, p.rule, p.tau,
-                       topk ? topk_keep(p, n) : 0, p.keep_first_n, p.keep_last_n, scores, halt, (unsigned long long*)published,
-                       active_idx, (const uint4*)x_next, row_vecs, vecs_per_split, (uint4*)x_compact, new_active_idx,
-                       n_active_out);
+    if (topk) {
+        hipLaunchKernelGGL(topk_compact_kernel, dim3(n_chunks * (1 + splits)), dim3(kSelectThreads), 0, s, sums.pairs, sums.cols, sums.fold, n, n_chunks, p.score_kind, topk_keep(p, n),
+                           p.keep_first_n, p.keep_last_n, scores, halt, (uint32_t*)published, active_idx, (const uint4*)x_next,
+                           row_vecs, vecs_per_split, (uint4*)x_compact, new_active_idx, n_active_out);
+        return launch_status();
+    }
+    hipLaunchKernelGGL(score_decide_compact_kernel, dim3(n_chunks, splits), dim3(kCompactThreads), 0, s, sums.pairs, sums.cols,
+                       sums.fold, n, p.score_kind, p.rule, p.tau, p.keep_first_n, p.keep_last_n, scores, halt,
+                       (unsigned long long*)published, active_idx, (const uint4*)x_next, row_vecs, vecs_per_split,
+                       (uint4*)x_compact, new_active_idx, n_active_out);
     return launch_status();
 }
 

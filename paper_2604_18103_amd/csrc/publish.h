@@ -1,10 +1,10 @@
-// The words through which the workgroups of the one-launch score + decision + compaction kernel hand each other the chunks'
-// decisions, and what a reader takes from them. Plain C++ for the host and the device: the kernel uses these functions, and
+// The words through which the workgroups of the one-launch score + decision + compaction kernel (rules NONE and THRESHOLD) hand each other
+// the chunks' decisions, and what a reader takes from them. Plain C++ for the host and the device: the kernel uses these functions, and
 // a host program (staging_check.cpp) steps the same exchange with a key missing.
 //
 // Two 64-bit words per chunk of 64 rows, zero at the start, each valid on its own (one relaxed device-scope access each):
 //   word 0 = kept mask bits 0..31 | kept count << 32 | FAILED | READY      word 1 = kept mask bits 32..63 | FAILED | READY
-// FAILED: the publisher gave up waiting and its mask means nothing.
+// FAILED: the publisher gave up and its mask means nothing (those of NONE and THRESHOLD wait for nothing and never do).
 #pragma once
 
 #include "staging_addr.h"
