@@ -241,6 +241,8 @@ struct SmallPlan {
     int form;                              // index into kSmallForms, -1: the large tiles
     int mt, nt, tiles, grid;               // grid = workgroups of all parts, padded to a multiple of 8
     int parts, ksteps_per_part;            // parts >= 2: fp32 sums and a second pass
+    int few_rows;                          // few_tile_plan: rows of its tiles, 0: the form above
+    double us;                             // estimate
 };
 inline double sa_busy(int wgs, int cu) {  // 0 up to two thirds of the units busy, 1 from all of them on
     const double b = ((double)wgs / cu - 0.65) / 0.35;
@@ -285,6 +287,7 @@ inline int rest_parts(const GemmPlan& g, int cu, size_t scratch_bytes) {
 inline SmallPlan small_plan(int M, int K, int N, int cu, bool norms, int head, bool scratch, size_t scratch_bytes, double large_us) {
     SmallPlan best{};
     best.form = -1;
+    best.us = large_us;
     const long long large_tiles = (long long)((M + kGM - 1) / kGM) * ((N + kGN - 1) / kGN);
     if (cu <= 0 || !scratch || (M > 2 * kGM && 2 * large_tiles > cu)) return best;
     double best_us = 0.95 * large_us - 0.5;  // so close, the large tiles were the faster ones (few K steps)
@@ -307,8 +310,55 @@ inline SmallPlan small_plan(int M, int K, int N, int cu, bool norms, int head, b
             if (parts > 1) t += second_pass_us(parts, M, N);
             if (t < best_us) {
                 best_us = t;
-                best = SmallPlan{f, mt, nt, (int)tiles, 8 * (((int)tiles * parts + 7) / 8), parts, per};
+                best = SmallPlan{f, mt, nt, (int)tiles, 8 * (((int)tiles * parts + 7) / 8), parts, per, 0, t};
             }
+        }
+    }
+    return best;
+}
+
+// ------------------------------------------------------------------------------------------------
+// Tiles for the fewest rows: 16, 32 or 48 rows x 64 columns, 8 waves that take K steps of their own (wave w: w, w + 8, ...). A load
+// instruction is 8 rows of 128 bytes of either operand; swizzles, bases and lane offsets are those of the tiles above.
+// ------------------------------------------------------------------------------------------------
+constexpr int kFewTileN = 64, kFewTileWaves = 8;
+DASH_HD int few_tile_row(int i, int lane) { return 8 * i + lane / 8; }
+DASH_HD constexpr size_t few_tile_smem_bytes(int bm) {  // the waves' stages; in the end their sums, rows of 64 + 4 words
+    const size_t stages = (size_t)kFewTileWaves * (bm + kFewTileN) * kGK * 2, sums = (size_t)kFewTileWaves * bm * (kFewTileN + 4) * 4;
+    return stages > sums ? stages : sums;
+}
+// These tiles for products of up to kFewTileRows rows, where they are expected to be faster than `other`, the form chosen so far. One round
+// of workgroups; in K parts where the tiles leave units idle, every wave with a step at least. The expectation (us): a launch with one
+// step per wave, 2.6 + 0.035 per row; every step more 1.05 + 0.01 per row, 0.2 more where a quarter of the units or less share the
+// weight's way from the last-level cache; K parts (of either) 2.4 beside the second pass. Where the other form is in K parts and this one is
+// not, 4.8 against it: the parts' sums leave fewer norm pairs to read, and a weight from memory goes through more units at a time.
+// No more than eight steps per wave: a longer contraction's weight comes from memory, and more slowly so (18944 x 3584 in four parts, 16 rows,
+// with the gate and up product 96.9 / 99.5).
+// Measured, the other forms / these: layer calls, weights in the last-level cache, width 3584 16 rows 21.9 / 20.3, 48 23.9 / 22.8, 177 28.6 /
+// 27.1; 4096 177 29.5 / 28.5; 512 16 12.2 / 11.35, 333 17.6 / 16.5, 700 21.5 / 20.6; 1024 16 14.0 / 12.4, 177 16.7 / 15.0, 511 20.4 / 19.8; weights from
+// memory 3584 16 23.3 / 22.3, 177 37.1 / 33.7. Front end of width 1024 with heads of 64, 150 rows 9.55 / 8.05; feed-forward 512 x 1408 64 rows 14.2 /
+// 11.4, 600 19.05 / 18.3. Left out, being no faster: 64 rows a tile (256 rows of 3584 30.3 / 30.5), more than 1024 rows (1500 of 512 x 512 6.8 / 7.0),
+// one pass over 64 rows of 3584 where the others take four parts (22.7 / 22.75, from memory 26.4 / 27.6).
+constexpr int kFewTileRows = 1024, kFewTileMostRows = 48, kFewTileMostSteps = 8;
+inline SmallPlan few_tile_plan(int M, int K, int N, int cu, bool norms, int head, bool scratch, size_t scratch_bytes, const SmallPlan& other) {
+    SmallPlan best = other;
+    if (cu <= 0 || !scratch || M > kFewTileRows) return best;
+    const int nt = (N + kFewTileN - 1) / kFewTileN, ksteps = K / kGK;
+    best.us += other.parts > 1 ? 2.4 : 0.0;
+    for (int bm = 16; bm <= kFewTileMostRows; bm += 16) {
+        const int mt = (M + bm - 1) / bm;
+        const long long tiles = (long long)mt * nt;
+        if (tiles > cu) continue;
+        const int most = sa_min(cu / (int)tiles, ksteps / kFewTileWaves);
+        for (int parts = 1; parts <= sa_max(most, 1); ++parts) {
+            const int per = (ksteps + parts - 1) / parts;
+            if ((parts == 1 && head > kFewTileN) || (ksteps + per - 1) / per != parts || per > kFewTileMostSteps * kFewTileWaves) continue;
+            const size_t need = parts > 1 ? (size_t)parts * M * N * sizeof(float) : (norms ? (size_t)((N + 63) / 64) * M * 2 * sizeof(float) : 0);
+            if (need > scratch_bytes) continue;
+            const double step = 1.05 + 0.01 * bm + (4 * tiles * parts <= cu ? 0.2 : 0.0);
+            double t = 2.6 + 0.035 * bm + ((per + kFewTileWaves - 1) / kFewTileWaves - 1) * step;
+            t += parts > 1 ? 2.4 + second_pass_us(parts, M, N) : (other.parts > 1 ? 4.8 : 0.0);
+            if (t < best.us) best = SmallPlan{-1, mt, nt, (int)tiles, 8 * (((int)tiles * parts + 7) / 8), parts, per, bm, t};
         }
     }
     return best;

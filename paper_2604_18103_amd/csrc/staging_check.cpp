@@ -286,6 +286,68 @@ int dash_check_small_staging(int M, int K, int N, int form, long long* n_loads) 
     return c.status;
 }
 
+// Checks the tiles of `bm` rows and 64 columns whose waves take K steps of their own: every load fetches the clamped row and column of its
+// wave's step, a step's loads fill the stage, and the waves' steps are all steps of all `parts`.
+int dash_check_few_tiles(int M, int K, int N, int bm, int parts, long long* n_loads) {
+    Counter c;
+    if (M <= 0 || K <= 0 || K % kGK != 0 || N <= 0 || N % 8 != 0 || bm % 16 != 0 || bm > 64 || parts < 1) return -1;
+    const int mt = (M + bm - 1) / bm, nt = (N + kFewTileN - 1) / kFewTileN, ksteps = K / kGK, per = (ksteps + parts - 1) / parts;
+    const uint64_t a_bytes = (uint64_t)M * K * 2, b_bytes = (uint64_t)K * N * 2;
+    if (dash_small_deal(mt * nt, parts) < 0) c.fail(2);
+    if (few_tile_smem_bytes(bm) > 160 * 1024) c.fail(3);
+    std::vector<char> a_seen((size_t)bm * 8, 0), b_seen((size_t)kGK * (kFewTileN / 8), 0), step_seen((size_t)ksteps, 0);
+    for (int tm = 0; tm < mt; ++tm)
+        for (int tn = 0; tn < nt; ++tn) {
+            if (tm != 0 && tm != mt - 1 && tn != 0 && tn != nt - 1) continue;
+            const int m0 = tm * bm, n0 = tn * kFewTileN;
+            for (int part = 0; part < parts; ++part)
+                for (int wave = 0; wave < kFewTileWaves; ++wave) {
+                    const int ks0 = part * per, steps = sa_min(per, ksteps - ks0), mine = (steps - wave + kFewTileWaves - 1) / kFewTileWaves;
+                    uint64_t a_base = gemm_a_base_elem(m0, M, K, ks0 + wave) * 2, b_base = gemm_b_base_elem(n0, N, ks0 + wave) * 2;
+                    for (int t = 0; t < mine; ++t) {
+                        const int ks = ks0 + wave + t * kFewTileWaves;
+                        if (ks >= ksteps || ks >= ks0 + per) { c.fail(4); continue; }
+                        step_seen[(size_t)ks] = 1;
+                        for (int lane = 0; lane < 64; ++lane) {
+                            for (int i = 0; i < bm / 8; ++i) {
+                                const int row = few_tile_row(i, lane), lchunk = gemm_a_lchunk(row, lane);
+                                if (row < 0 || row >= bm || lchunk < 0 || lchunk >= 8) { c.fail(5); continue; }
+                                a_seen[(size_t)row * 8 + lchunk] = 1;
+                                const uint64_t addr = a_base + gemm_a_off(m0, M, K, row, lchunk);
+                                if (addr != ((uint64_t)sa_min(m0 + row, M - 1) * K + (uint64_t)ks * kGK + lchunk * 8) * 2) c.fail(6);
+                                if (addr + 16 > a_bytes) c.fail(7);
+                                ++c.loads;
+                            }
+                            for (int i = 0; i < kGK / 8; ++i) {
+                                const int row = few_tile_row(i, lane), lchunk = small_b_lchunk(row, lane, kFewTileN);
+                                if (row < 0 || row >= kGK || lchunk < 0 || lchunk >= kFewTileN / 8) { c.fail(8); continue; }
+                                b_seen[(size_t)row * (kFewTileN / 8) + lchunk] = 1;
+                                const uint64_t addr = b_base + gemm_b_off(n0, N, row, lchunk);
+                                if (addr != ((uint64_t)(ks * kGK + row) * N + sa_min(n0 + lchunk * 8, N - 8)) * 2) c.fail(9);
+                                if (addr + 16 > b_bytes) c.fail(10);
+                                ++c.loads;
+                            }
+                        }
+                        a_base += kFewTileWaves * gemm_a_step_bytes();
+                        b_base += kFewTileWaves * gemm_b_step_bytes(N);
+                    }
+                }
+        }
+    for (char v : a_seen) if (!v) c.fail(11);
+    for (char v : b_seen) if (!v) c.fail(12);
+    for (char v : step_seen) if (!v) c.fail(13);
+    if (n_loads) *n_loads = c.loads;
+    return c.status;
+}
+
+// Those tiles' choice: out[0..3] = rows of a tile (0: another form), tiles, parts, K steps per part.
+void dash_few_tile_plan(int M, int K, int N, int cu, int norms, int head, unsigned long long scratch, int* out) {
+    const GemmPlan g = gemm_plan(M, K, N, cu, scratch > 0, (size_t)scratch);
+    const SmallPlan s = small_plan(M, K, N, cu, norms != 0, head, scratch > 0, (size_t)scratch, large_tiles_us(g, M, N, cu));
+    const SmallPlan p = few_tile_plan(M, K, N, cu, norms != 0, head, scratch > 0, (size_t)scratch, s);
+    out[0] = p.few_rows; out[1] = p.tiles; out[2] = p.parts; out[3] = p.ksteps_per_part;
+}
+
 // K parts of the left-over half tiles, 1: one pass.
 int dash_rest_parts(int M, int K, int N, int cu, unsigned long long scratch) {
     return rest_parts(gemm_plan(M, K, N, cu, scratch > 0, (size_t)scratch), cu, (size_t)scratch);

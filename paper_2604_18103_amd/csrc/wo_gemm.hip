@@ -638,6 +638,95 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
     }
 }
 
+// Epilogue of STAGED rows of a small tile's BN columns, whose KW groups' sums lie in LDS one behind the other (rows of BN + 4 words): a
+// thread has 8 consecutive columns of one row (16-byte loads of x, 16-byte stores). row_of: the product's row of a staged one.
+template <int EPI, int BN, int STAGED, int KW, int THREADS, class RowOf>
+__device__ __forceinline__ void small_epilogue(const float* stage, int tid, RowOf row_of, int n0, int part, int M, int N,
+                                               const __bf16* __restrict__ x, __bf16* __restrict__ out, float* __restrict__ partials,
+                                               float* __restrict__ split_sums, const QkvOut& qkv) {
+    constexpr int STR = BN + 4;
+    auto sum8 = [&](const float* src, float* v) {  // eight columns, the K groups' parts in their order
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = src[e];
+#pragma unroll
+        for (int g = 1; g < KW; ++g)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] += src[g * STAGED * STR + e];
+    };
+            if (EPI == EPI_SWIGLU) {
+                // lane group of 4 per row and 64 columns: lane c takes gate columns 8c..8c+7 and the up columns 32 + 8c..
+                constexpr int LPR = BN / 16, ROWS = THREADS / LPR;
+#pragma unroll
+                for (int p = 0; p < (STAGED + ROWS - 1) / ROWS; ++p) {
+                    const int sr = p * ROWS + tid / LPR, l = tid % LPR;
+                    if (sr >= STAGED) break;
+                    const int gm = row_of(sr);
+                    const int gcol = (n0 + 64 * (l / 4)) / 2 + 8 * (l % 4);
+                    float gv[8], uv[8];
+                    sum8(&stage[sr * STR + 64 * (l / 4) + 8 * (l % 4)], gv);
+                    sum8(&stage[sr * STR + 64 * (l / 4) + 8 * (l % 4) + 32], uv);
+                    if (gm < M && gcol < N / 2) {
+                        bf16x8 ov;
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) ov[e] = (__bf16)(gv[e] / (1.0f + __expf(-gv[e])) * uv[e]);
+                        *reinterpret_cast<bf16x8*>(out + (size_t)gm * (N / 2) + gcol) = ov;
+                    }
+                }
+            } else {
+                constexpr int LPR = BN / 8, ROWS = THREADS / LPR;
+#pragma unroll
+                for (int p = 0; p < (STAGED + ROWS - 1) / ROWS; ++p) {
+                    const int sr = p * ROWS + tid / LPR, l = tid % LPR;
+                    if (sr >= STAGED) break;
+                    const int gm = row_of(sr), gn = n0 + 8 * l;
+                    float dv[8];
+                    sum8(&stage[sr * STR + 8 * l], dv);
+                    const bool ok = gm < M && gn < N;
+                    if (EPI == EPI_RESIDUAL_NORM) {
+                        float sd = 0.f, sx = 0.f;
+                        if (ok) {
+                            const bf16x8 xr = *reinterpret_cast<const bf16x8*>(x + (size_t)gm * N + gn);
+                            bf16x8 ov;
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) {
+                                const float xf = (float)xr[e];
+                                ov[e] = (__bf16)(xf + dv[e]);
+                                sd = fmaf(dv[e], dv[e], sd);
+                                sx = fmaf(xf, xf, sx);
+                            }
+                            *reinterpret_cast<bf16x8*>(out + (size_t)gm * N + gn) = ov;
+                        }
+                        if (partials) {
+#pragma unroll
+                            for (int off = 4; off > 0; off >>= 1) {
+                                sd += __shfl_xor(sd, off);
+                                sx += __shfl_xor(sx, off);
+                            }
+                            if (l % 8 == 0 && ok)
+                                *reinterpret_cast<float2*>(partials + ((size_t)(gn / 64) * M + gm) * 2) = make_float2(sd, sx);
+                        }
+                    } else if (EPI == EPI_SPLITK) {
+                        if (ok) {
+                            float* dst = split_sums + ((size_t)part * M + gm) * N + gn;
+                            *reinterpret_cast<f32x4*>(dst) = f32x4{dv[0], dv[1], dv[2], dv[3]};
+                            *reinterpret_cast<f32x4*>(dst + 4) = f32x4{dv[4], dv[5], dv[6], dv[7]};
+                        }
+                    } else if (ok) {
+                        if (EPI == EPI_QKV_ROPE && gn < qkv.Dq + qkv.Dkv) {  // a head lies in one tile (the launcher's choice)
+                            float partner[8];
+                            sum8(&stage[sr * STR + ((8 * l) ^ qkv.half)], partner);
+                            rope8(qkv, gm, gn, partner, dv);
+                        }
+                        bf16x8 ov;
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) ov[e] = (__bf16)dv[e];
+                        __bf16* dst = epi_qkv(EPI) ? qkv_dst(out, qkv, gm, gn) : out + (size_t)gm * N + gn;
+                        *reinterpret_cast<bf16x8*>(dst) = ov;
+                    }
+                }
+            }
+}
+
 // ------------------------------------------------------------------------------------------------
 // The same product on small tiles: BM x BN (64 or 128 each), KW groups of 4 waves in 2 x 2. One workgroup per compute unit (96 to
 // 144 KB of LDS), of the second 128 x 128 form two.
@@ -856,17 +945,8 @@ __global__ __launch_bounds__(KW * kSWaves * kWave, 2) void gemm_small_kernel(con
     }
     __syncthreads();  // the operand stages are free and are reused
 
-    // Epilogue, 32 rows of either wave row at a time: the accumulators go to LDS, then a thread has 8 consecutive columns
-    // of one row (16-byte loads of x, 16-byte stores).
+    // Epilogue, 32 rows of either wave row at a time: the accumulators go to LDS first.
     float* stage = reinterpret_cast<float*>(small_smem_raw);
-    auto sum8 = [&](const float* src, float* v) {  // eight columns, the K groups' parts in their order
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = src[e];
-#pragma unroll
-        for (int g = 1; g < KW; ++g)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] += src[g * 64 * STR + e];
-    };
 #pragma unroll
     for (int a = 0; a < BM / 64; ++a) {
 #pragma unroll
@@ -877,80 +957,107 @@ __global__ __launch_bounds__(KW * kSWaves * kWave, 2) void gemm_small_kernel(con
                 for (int r = 0; r < 4; ++r)  // accumulator register r of a 16x16 block: row 4 g + r, column i
                     stage[(64 * kg + 32 * wm + 16 * sb + 4 * fg + r) * STR + wn * (BN / 2) + 16 * b + fi] = acc[2 * a + sb][b][r];
         __syncthreads();
-        if (EPI == EPI_SWIGLU) {
-            // lane group of 4 per row and 64 columns: lane c takes gate columns 8c..8c+7 and the up columns 32 + 8c..
-            constexpr int LPR = BN / 16, ROWS = kThreads / LPR;
-#pragma unroll
-            for (int p = 0; p < (64 + ROWS - 1) / ROWS; ++p) {
-                const int sr = p * ROWS + tid / LPR, l = tid % LPR;
-                if (sr >= 64) break;  // whole waves
-                const int gm = m0 + (sr / 32) * (BM / 2) + 32 * a + sr % 32;
-                const int gcol = (n0 + 64 * (l / 4)) / 2 + 8 * (l % 4);
-                float gv[8], uv[8];
-                sum8(&stage[sr * STR + 64 * (l / 4) + 8 * (l % 4)], gv);
-                sum8(&stage[sr * STR + 64 * (l / 4) + 8 * (l % 4) + 32], uv);
-                if (gm < M && gcol < N / 2) {
-                    bf16x8 ov;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) ov[e] = (__bf16)(gv[e] / (1.0f + __expf(-gv[e])) * uv[e]);
-                    *reinterpret_cast<bf16x8*>(out + (size_t)gm * (N / 2) + gcol) = ov;
-                }
-            }
-        } else {
-            constexpr int LPR = BN / 8, ROWS = kThreads / LPR;
-#pragma unroll
-            for (int p = 0; p < (64 + ROWS - 1) / ROWS; ++p) {
-                const int sr = p * ROWS + tid / LPR, l = tid % LPR;
-                if (sr >= 64) break;  // whole waves
-                const int gm = m0 + (sr / 32) * (BM / 2) + 32 * a + sr % 32, gn = n0 + 8 * l;
-                float dv[8];
-                sum8(&stage[sr * STR + 8 * l], dv);
-                const bool ok = gm < M && gn < N;
-                if (EPI == EPI_RESIDUAL_NORM) {
-                    float sd = 0.f, sx = 0.f;
-                    if (ok) {
-                        const bf16x8 xr = *reinterpret_cast<const bf16x8*>(x + (size_t)gm * N + gn);
-                        bf16x8 ov;
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            const float xf = (float)xr[e];
-                            ov[e] = (__bf16)(xf + dv[e]);
-                            sd = fmaf(dv[e], dv[e], sd);
-                            sx = fmaf(xf, xf, sx);
-                        }
-                        *reinterpret_cast<bf16x8*>(out + (size_t)gm * N + gn) = ov;
-                    }
-                    if (partials) {
-#pragma unroll
-                        for (int off = 4; off > 0; off >>= 1) {
-                            sd += __shfl_xor(sd, off);
-                            sx += __shfl_xor(sx, off);
-                        }
-                        if (l % 8 == 0 && ok)
-                            *reinterpret_cast<float2*>(partials + ((size_t)(gn / 64) * M + gm) * 2) = make_float2(sd, sx);
-                    }
-                } else if (EPI == EPI_SPLITK) {
-                    if (ok) {
-                        float* dst = split_sums + ((size_t)part * M + gm) * N + gn;
-                        *reinterpret_cast<f32x4*>(dst) = f32x4{dv[0], dv[1], dv[2], dv[3]};
-                        *reinterpret_cast<f32x4*>(dst + 4) = f32x4{dv[4], dv[5], dv[6], dv[7]};
-                    }
-                } else if (ok) {
-                    if (EPI == EPI_QKV_ROPE && gn < qkv.Dq + qkv.Dkv) {  // a head lies in one tile (the launcher's choice)
-                        float partner[8];
-                        sum8(&stage[sr * STR + ((8 * l) ^ qkv.half)], partner);
-                        rope8(qkv, gm, gn, partner, dv);
-                    }
-                    bf16x8 ov;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) ov[e] = (__bf16)dv[e];
-                    __bf16* dst = epi_qkv(EPI) ? qkv_dst(out, qkv, gm, gn) : out + (size_t)gm * N + gn;
-                    *reinterpret_cast<bf16x8*>(dst) = ov;
-                }
-            }
-        }
+        small_epilogue<EPI, BN, 64, KW, kThreads>(
+            stage, tid, [&](int sr) { return m0 + (sr / 32) * (BM / 2) + 32 * a + sr % 32; }, n0, part, M, N, x, out, partials, split_sums, qkv);
         __syncthreads();
     }
+}
+
+// ------------------------------------------------------------------------------------------------
+// The same product for the fewest rows: 16 RB x 64 tiles whose 8 waves split the K steps and share nothing until the end: wave w takes
+// the steps w, w + 8, ... of the whole tile, fetches their operands into LDS of its own (one stage, A and B) and asks for the next
+// step as soon as this one's fragments are in registers. No barrier in the loop, every byte of a stage is read once, and the
+// lowest tile that a launch's workgroups take in one round is used (few_tile_plan).
+// A compute unit has at most 64 KB in flight, and a step's first bytes come from the last-level cache or memory, so a step takes 1.0 to 1.7 us
+// whatever the tile, of a launch of 2.5 to 4.5 us. K = N = 3584, weight in the last-level cache, us, the forms above / this: 177 rows
+// 15.1 / 13.0, 16 in four K parts with their second pass 12.6 / 10.8; 333 rows of 512 x 512 4.0 / 3.2, of 1024 x 1024 5.4 / 4.5. Two stages, 5 or 10
+// waves, and fragments straight from memory (22 us; 8-byte loads have half the rate) are no faster; all 177 rows on one 192-row tile in four K parts
+// took 16.7 without the second pass.
+// ------------------------------------------------------------------------------------------------
+template <int EPI, int RB>
+__global__ __launch_bounds__(kFewTileWaves * kWave, 2) void gemm_few_kernel(const __bf16* __restrict__ A, const __bf16* __restrict__ B, int M, int K,
+                                                                  int N, const __bf16* __restrict__ x, __bf16* __restrict__ out,
+                                                                  float* __restrict__ partials, float* __restrict__ split_sums, int mt,
+                                                                  int tiles, int parts, int ksteps, int ksteps_per_split, QkvOut qkv) {
+    constexpr int BM = 16 * RB, BN = kFewTileN, CB = BN / 16, W = kFewTileWaves;
+    constexpr int kAElems = BM * kGK, kStageElems = (BM + BN) * kGK, STR = BN + 4;
+    extern __shared__ __attribute__((aligned(16))) unsigned char few_tile_smem_raw[];
+    const int tid = threadIdx.x, lane = tid % kWave, fi = lane % 16, fg = lane / 16;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    int idx, part;
+    if (!small_work_of((int)blockIdx.x, tiles, EPI == EPI_SPLITK ? parts : 1, idx, part)) return;  // padding: the whole workgroup
+    const int m0 = (idx % mt) * BM, n0 = (idx / mt) * BN;
+    const int ks0 = EPI == EPI_SPLITK ? part * ksteps_per_split : 0;
+    const int n_ksteps = EPI == EPI_SPLITK ? min(ksteps_per_split, ksteps - ks0) : ksteps, n_mine = (n_ksteps - wave + W - 1) / W;
+    __bf16* sa = reinterpret_cast<__bf16*>(few_tile_smem_raw) + wave * kStageElems;  // this wave's stage
+    __bf16* sb = sa + kAElems;
+
+    f32x4 acc[RB][CB];
+#pragma unroll
+    for (int a = 0; a < RB; ++a)
+#pragma unroll
+        for (int b = 0; b < CB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    constexpr int ADMA = BM / 8, BDMA = kGK / 8;  // load instructions of a step, 8 rows each
+    uint32_t a_off[ADMA], b_off[BDMA];
+#pragma unroll
+    for (int i = 0; i < ADMA; ++i) a_off[i] = gemm_a_off(m0, M, K, few_tile_row(i, lane), gemm_a_lchunk(few_tile_row(i, lane), lane));
+#pragma unroll
+    for (int i = 0; i < BDMA; ++i) b_off[i] = gemm_b_off(n0, N, few_tile_row(i, lane), small_b_lchunk(few_tile_row(i, lane), lane, BN));
+    const char* a_base = reinterpret_cast<const char*>(A + gemm_a_base_elem(m0, M, K, ks0 + wave));
+    const char* b_base = reinterpret_cast<const char*>(B + gemm_b_base_elem(n0, N, ks0 + wave));
+    const size_t b_step = W * gemm_b_step_bytes(N);
+    const uint32_t lds_a = lds_addr(sa), lds_b = lds_addr(sb);
+    auto request = [&] {  // the wave's steps strictly in order
+#pragma unroll
+        for (int i = 0; i < BDMA; ++i) dma_load16(b_base, b_off[i], lds_b + i * 1024);
+#pragma unroll
+        for (int i = 0; i < ADMA; ++i) dma_load16(a_base, a_off[i], lds_a + i * 1024);
+        a_base += W * gemm_a_step_bytes();
+        b_base += b_step;
+    };
+    if (n_mine > 0) request();
+    for (int t = 0; t < n_mine; ++t) {
+        dma_wait();
+        wave_sync_lds();
+        bf16x8 af[2][RB], bfr[2][CB];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+            for (int b = 0; b < CB; ++b) {
+                const int krow = 32 * ks + 8 * fg + fi / 4;  // and krow + 4: the same swizzle
+                const int col = 16 * b + 4 * (fi % 4), scol = ((col / 8) ^ small_b_swz(krow, BN)) * 8 + col % 8;
+                const s16x4 lo = lds_read_tr16(&sb[krow * BN + scol]);
+                const s16x4 hi = lds_read_tr16(&sb[(krow + 4) * BN + scol]);
+                bfr[ks][b] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            }
+#pragma unroll
+            for (int a = 0; a < RB; ++a) {
+                const int row = 16 * a + fi;
+                af[ks][a] = *reinterpret_cast<const bf16x8*>(&sa[row * kGK + ((4 * ks + fg) ^ ((row / 2) % 8)) * 8]);
+            }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");  // the stage is in registers
+        __builtin_amdgcn_sched_barrier(0);
+        if (t + 1 < n_mine) request();
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int a = 0; a < RB; ++a)
+#pragma unroll
+                for (int b = 0; b < CB; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[ks][a], bfr[ks][b], acc[a][b], 0, 0, 0);
+    }
+    __syncthreads();  // every wave's stage is read and nothing is in flight
+    float* stage = reinterpret_cast<float*>(few_tile_smem_raw);
+#pragma unroll
+    for (int a = 0; a < RB; ++a)
+#pragma unroll
+        for (int b = 0; b < CB; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)  // accumulator register r of a 16x16 block: row 4 g + r, column i
+                stage[(BM * wave + 16 * a + 4 * fg + r) * STR + 16 * b + fi] = acc[a][b][r];
+    __syncthreads();
+    small_epilogue<EPI, BN, BM, W, W * kWave>(stage, tid, [&](int sr) { return m0 + sr; }, n0, part, M, N, x, out, partials, split_sums, qkv);
 }
 
 // Row norms of a small-tile product, kNormFold neighbouring columns of pairs to one: fine[cols][M] -> partials[P][M].
@@ -1266,9 +1373,19 @@ static hipError_t set_small_lds_size() {
     return hipFuncSetAttribute((const void*)gemm_small_kernel<EPI, f.BM, f.BN, f.KW, f.NS>,
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)small_smem_bytes(f.BM, f.BN, f.KW, f.NS));
 }
+template <int EPI, int RB>
+static hipError_t set_few_tile_lds_size(hipError_t e) {
+    return e != hipSuccess ? e : hipFuncSetAttribute((const void*)gemm_few_kernel<EPI, RB>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                     (int)few_tile_smem_bytes(16 * RB));
+}
+template <int EPI>
+static hipError_t set_few_tile_lds_sizes() {
+    return set_few_tile_lds_size<EPI, 3>(set_few_tile_lds_size<EPI, 2>(set_few_tile_lds_size<EPI, 1>(hipSuccess)));
+}
 template <int EPI>
 static hipError_t set_small_lds_sizes() {
-    hipError_t e = set_small_lds_size<EPI, 0>();
+    hipError_t e = set_few_tile_lds_sizes<EPI>();
+    if (e == hipSuccess) e = set_small_lds_size<EPI, 0>();
     if (e == hipSuccess) e = set_small_lds_size<EPI, 1>();
     if (e == hipSuccess) e = set_small_lds_size<EPI, 2>();
     if (e == hipSuccess) e = set_small_lds_size<EPI, 3>();
@@ -1288,6 +1405,7 @@ dash_status init_gemm_kernels() {
         if (e == hipSuccess) e = set_small_lds_sizes<EPI_STORE>();
         if (e == hipSuccess) e = set_small_lds_sizes<EPI_SWIGLU>();
         if (e == hipSuccess) e = set_small_lds_sizes<EPI_QKV>();
+        if (e == hipSuccess) e = set_few_tile_lds_sizes<EPI_SPLITK>();
         if (e == hipSuccess) e = set_small_lds_size<EPI_SPLITK, 0>();
         if (e == hipSuccess) e = set_small_lds_size<EPI_SPLITK, 1>();
         return e;
@@ -1329,6 +1447,20 @@ static void launch_small_form(const SmallPlan& g, const GemmArgs& a, hipStream_t
                        a.split_sums, g.mt, g.tiles, g.parts, a.K / kGK, g.ksteps_per_part, a.qkv);
 }
 
+template <int EPI, int RB>
+static void launch_few_tile_rows(const SmallPlan& g, const GemmArgs& a, hipStream_t s) {
+    hipLaunchKernelGGL((gemm_few_kernel<EPI, RB>), dim3(g.grid), dim3(kFewTileWaves * kWave), few_tile_smem_bytes(16 * RB), s, a.A, a.B, a.M,
+                       a.K, a.N, a.x, a.out, a.partials, a.split_sums, g.mt, g.tiles, g.parts, a.K / kGK, g.ksteps_per_part, a.qkv);
+}
+template <int EPI>
+static void launch_few_tiles(const SmallPlan& g, const GemmArgs& a, hipStream_t s) {
+    switch (g.few_rows) {
+        case 16: launch_few_tile_rows<EPI, 1>(g, a, s); break;
+        case 32: launch_few_tile_rows<EPI, 2>(g, a, s); break;
+        default: launch_few_tile_rows<EPI, kFewTileMostRows / 16>(g, a, s); break;
+    }
+}
+
 // Adds the K parts and applies the epilogue.
 template <int EPI>
 static void launch_splitk_reduce(const float* sums, int parts, const GemmArgs& a, hipStream_t s) {
@@ -1338,14 +1470,16 @@ static void launch_splitk_reduce(const float* sums, int parts, const GemmArgs& a
                        parts, a.M, a.N, a.x, a.out, a.partials, a.qkv);
 }
 
-// A small-tile product (g.form >= 0). scratch: the K parts' sums, or the fine row norms, which `sums` then describes or,
+// A small-tile product (g.form >= 0, or g.few_rows > 0). scratch: the K parts' sums, or the fine row norms, which `sums` then describes or,
 // without it, are folded into a.partials; a.partials = nullptr: the caller has no use for row norms.
 template <int EPI>
 static dash_status launch_small(const SmallPlan& g, GemmArgs a, void* scratch, NormSums* sums, hipStream_t s) {
     if (g.parts >= 2) {
         GemmArgs part = a;
         part.split_sums = reinterpret_cast<float*>(scratch);
-        if (g.form == 0)
+        if (g.few_rows > 0)
+            launch_few_tiles<EPI_SPLITK>(g, part, s);
+        else if (g.form == 0)
             launch_small_form<EPI_SPLITK, 0>(g, part, s);
         else
             launch_small_form<EPI_SPLITK, 1>(g, part, s);
@@ -1354,7 +1488,9 @@ static dash_status launch_small(const SmallPlan& g, GemmArgs a, void* scratch, N
     }
     float* coarse = a.partials;
     if (EPI == EPI_RESIDUAL_NORM && coarse) a.partials = reinterpret_cast<float*>(scratch);
-    switch (g.form) {
+    if (g.few_rows > 0)
+        launch_few_tiles<EPI>(g, a, s);
+    else switch (g.form) {
         case 0: launch_small_form<EPI, 0>(g, a, s); break;
         case 1: launch_small_form<EPI, 1>(g, a, s); break;
         case 2: launch_small_form<EPI, 2>(g, a, s); break;
@@ -1405,9 +1541,11 @@ static dash_status launch_gemm(const __bf16* A, const __bf16* B, int M, int K, i
     const bool norms = EPI == EPI_RESIDUAL_NORM && want_norms;
     if (sums_out) *sums_out = NormSums{partials, (N + kGN - 1) / kGN, 1};
     // the debug output keeps the product off K parts and small tiles: with and without scratch it has the same bits
-    const SmallPlan small = small_plan(M, K, N, compute_units(), norms, EPI == EPI_QKV_ROPE ? 2 * qkv.half : 0, split_ws != nullptr, split_ws ? split_bytes : 0,
-                                       large_tiles_us(g, M, N, compute_units()));
-    if (small.form >= 0 && !delta_dbg) {
+    const int head = EPI == EPI_QKV_ROPE ? 2 * qkv.half : 0;
+    const size_t scratch_bytes = split_ws ? split_bytes : 0;
+    SmallPlan small = small_plan(M, K, N, compute_units(), norms, head, split_ws != nullptr, scratch_bytes, large_tiles_us(g, M, N, compute_units()));
+    small = few_tile_plan(M, K, N, compute_units(), norms, head, split_ws != nullptr, scratch_bytes, small);
+    if ((small.form >= 0 || small.few_rows > 0) && !delta_dbg) {
         GemmArgs a = args;
         if (!norms && small.parts < 2) a.partials = nullptr;
         return launch_small<EPI>(small, a, split_ws, sums_out, s);
