@@ -639,10 +639,11 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
 }
 
 // Epilogue of STAGED rows of a small tile's BN columns, whose KW groups' sums lie in LDS one behind the other (rows of BN + 4 words): a
-// thread has 8 consecutive columns of one row (16-byte loads of x, 16-byte stores). row_of: the product's row of a staged one.
-template <int EPI, int BN, int STAGED, int KW, int THREADS, class RowOf>
+// thread has 8 consecutive columns of one row (16-byte stores). row_of: the product's row of a staged one; x_of: a thread's p-th piece of x,
+// row gm from column gn on.
+template <int EPI, int BN, int STAGED, int KW, int THREADS, class RowOf, class XOf>
 __device__ __forceinline__ void small_epilogue(const float* stage, int tid, RowOf row_of, int n0, int part, int M, int N,
-                                               const __bf16* __restrict__ x, __bf16* __restrict__ out, float* __restrict__ partials,
+                                               XOf x_of, __bf16* __restrict__ out, float* __restrict__ partials,
                                                float* __restrict__ split_sums, const QkvOut& qkv) {
     constexpr int STR = BN + 4;
     auto sum8 = [&](const float* src, float* v) {  // eight columns, the K groups' parts in their order
@@ -685,7 +686,7 @@ __device__ __forceinline__ void small_epilogue(const float* stage, int tid, RowO
                     if (EPI == EPI_RESIDUAL_NORM) {
                         float sd = 0.f, sx = 0.f;
                         if (ok) {
-                            const bf16x8 xr = *reinterpret_cast<const bf16x8*>(x + (size_t)gm * N + gn);
+                            const bf16x8 xr = x_of(p, gm, gn);
                             bf16x8 ov;
 #pragma unroll
                             for (int e = 0; e < 8; ++e) {
@@ -853,6 +854,23 @@ __global__ __launch_bounds__(KW * kSWaves * kWave, 2) void gemm_small_kernel(con
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
     };
     constexpr int kStepLoads = ADMA + BDMA;
+    // One workgroup per unit: the epilogue's x is asked for during the K loop, all of it at once. In the epilogue nothing covers its way from
+    // memory, once per 64 rows (K = N = 3584 with attention and score, 640 rows 51.1 -> 50.4 us, with x and weights from memory 60.6 -> 57.5,
+    // 1000 70.6 -> 67.0). The waits of the steps count the tiles' requests alone: with x in flight they wait for more than they need, never
+    // for less. Two workgroups per unit cover it, and asking early costs them 2 to 3 % (2120 rows 112.7 -> 116.1).
+    constexpr bool kEarlyX = EPI == EPI_RESIDUAL_NORM && NS > 2 && KW == 1;
+    constexpr int kXRows = kThreads / (BN / 8), XP = 64 / kXRows;  // small_epilogue's rows at a time
+    auto epi_row = [&](int a, int sr) { return m0 + (sr / 32) * (BM / 2) + 32 * a + sr % 32; };
+    bf16x8 xr[kEarlyX ? BM / 64 : 1][kEarlyX ? XP : 1];
+    auto load_x = [&] {  // rows and columns beyond the end: the last ones, never used
+        if constexpr (kEarlyX)
+#pragma unroll
+            for (int a = 0; a < BM / 64; ++a)
+#pragma unroll
+                for (int p = 0; p < XP; ++p)
+                    xr[a][p] = *reinterpret_cast<const bf16x8*>(x + (size_t)min(epi_row(a, p * kXRows + tid / (BN / 8)), M - 1) * N +
+                                                                min(n0 + 8 * (tid % (BN / 8)), N - 8));
+    };
     for (int j = 0; j < min(NS, n_mine); ++j) request(j);
     if (n_mine >= NS)
         dma_wait_keep<(NS - 1) * kStepLoads>();  // the first step has landed
@@ -919,7 +937,12 @@ __global__ __launch_bounds__(KW * kSWaves * kWave, 2) void gemm_small_kernel(con
         };
         if (n_ksteps > 0) read_slice(0, 0, f[0].a[0], f[0].b[0]);
         int kt = 0;
-        for (; kt + NS < n_ksteps; ++kt) step(true);
+        const int x_step = max(0, n_ksteps - NS - 2);  // as the last steps are requested
+        if (n_ksteps <= NS) load_x();
+        for (; kt + NS < n_ksteps; ++kt) {
+            if (kt == x_step) load_x();
+            step(true);
+        }
         for (; kt < n_ksteps; ++kt) step(false);
     } else {
         // Round t multiplies its step from registers while the next step's fragments are read. Before barrier t this wave's
@@ -958,7 +981,12 @@ __global__ __launch_bounds__(KW * kSWaves * kWave, 2) void gemm_small_kernel(con
                     stage[(64 * kg + 32 * wm + 16 * sb + 4 * fg + r) * STR + wn * (BN / 2) + 16 * b + fi] = acc[2 * a + sb][b][r];
         __syncthreads();
         small_epilogue<EPI, BN, 64, KW, kThreads>(
-            stage, tid, [&](int sr) { return m0 + (sr / 32) * (BM / 2) + 32 * a + sr % 32; }, n0, part, M, N, x, out, partials, split_sums, qkv);
+            stage, tid, [&](int sr) { return epi_row(a, sr); }, n0, part, M, N,
+            [&](int p, int gm, int gn) {
+                if constexpr (kEarlyX) return xr[a][p];
+                else return *reinterpret_cast<const bf16x8*>(x + (size_t)gm * N + gn);
+            },
+            out, partials, split_sums, qkv);
         __syncthreads();
     }
 }
@@ -1057,7 +1085,8 @@ __global__ __launch_bounds__(kFewTileWaves * kWave, 2) void gemm_few_kernel(cons
             for (int r = 0; r < 4; ++r)  // accumulator register r of a 16x16 block: row 4 g + r, column i
                 stage[(BM * wave + 16 * a + 4 * fg + r) * STR + 16 * b + fi] = acc[a][b][r];
     __syncthreads();
-    small_epilogue<EPI, BN, BM, W, W * kWave>(stage, tid, [&](int sr) { return m0 + sr; }, n0, part, M, N, x, out, partials, split_sums, qkv);
+    small_epilogue<EPI, BN, BM, W, W * kWave>(stage, tid, [&](int sr) { return m0 + sr; }, n0, part, M, N,
+        [&](int, int gm, int gn) { return *reinterpret_cast<const bf16x8*>(x + (size_t)gm * N + gn); }, out, partials, split_sums, qkv);
 }
 
 // Row norms of a small-tile product, kNormFold neighbouring columns of pairs to one: fine[cols][M] -> partials[P][M].
