@@ -489,12 +489,25 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
         second_half(st_next, true, st);
         st = st_next;
     }
+    const int e_row = lane / 8, e_c8 = lane % 8;
+    const int gn_e = n0 + wn * 64 + 8 * e_c8;
+    const bool col_ok = gn_e < N;
+    constexpr int EB = (RB + 1) / 2;  // the epilogue's 32-row blocks, the last one of 16 rows where RB is odd
+    bf16x8 xv[EB][4];
+    auto fetch_x = [&](int a) {
+#pragma unroll
+        for (int step = 0; step < 4; ++step) {
+            const int gm = min(m0 + wm * WM + 32 * a + 8 * step + e_row, M - 1);
+            xv[a][step] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(x + (size_t)gm * N + min(gn_e, N - 8)));
+        }
+    };
     for (; kt < n_ksteps; ++kt) {  // the last NS steps request nothing
         const int st_next = st + 1 == NS ? 0 : st + 1;
+        if (EPI == EPI_RESIDUAL_NORM && kt + 1 == n_ksteps) fetch_x(0);
         read_frags(st, 1, Af[1], Bf[1]);
         mfma_slice(Af[0], Bf[0]);
         pin_slice();
-        dma_wait();
+        if (kt + 1 < n_ksteps) dma_wait();  // no tiles are in flight in the last one
         asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
         lds_barrier();
         second_half(st_next, false, st);  // after the last step the fragments read are stale data, never used
@@ -505,25 +518,16 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
 
     // Epilogue, per 32-row block of the wave's tile: stage the fp32 accumulators in LDS, then every lane
     // handles 8 consecutive columns of one row - 16-byte x loads, 16-byte x_next stores, in-row sums over
-    // 8 lanes. The x vectors of the next block are fetched before the current one is processed.
+    // 8 lanes. The x vectors of the first block are asked for in the last K step, the others all at once ahead of the epilogue, in the
+    // operands' registers (a block ahead each: K = N = 3584 one round of tiles, 4096 rows 85.4 -> 83.2 us, 3000 67.5 -> 66.4; several rounds
+    // the same, inside the power limit).
     float* stage = reinterpret_cast<float*>(gemm_smem_raw) + wave * 32 * kEpiStr;
     float2* nrm = reinterpret_cast<float2*>(gemm_smem_raw + kGWaves * 32 * kEpiStr * sizeof(float));  // [4 wave columns][BM rows]
-    const int e_row = lane / 8, e_c8 = lane % 8;
-    const int gn_e = n0 + wn * 64 + 8 * e_c8;
-    const bool col_ok = gn_e < N;
-    bf16x8 xv[2][4];
-    auto fetch_x = [&](int a, bf16x8* dst) {
+    if (EPI == EPI_RESIDUAL_NORM)
 #pragma unroll
-        for (int step = 0; step < 4; ++step) {
-            const int gm = min(m0 + wm * WM + 32 * a + 8 * step + e_row, M - 1);
-            dst[step] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(x + (size_t)gm * N + min(gn_e, N - 8)));
-        }
-    };
-    constexpr int EB = (RB + 1) / 2;  // 32-row blocks, the last one of 16 rows where RB is odd
-    if (EPI == EPI_RESIDUAL_NORM) fetch_x(0, xv[0]);
+        for (int a = 1; a < EB; ++a) fetch_x(a);
 #pragma unroll
     for (int a = 0; a < EB; ++a) {
-        if (EPI == EPI_RESIDUAL_NORM && a + 1 < EB) fetch_x(a + 1, xv[(a + 1) & 1]);
 #pragma unroll
         for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
@@ -569,7 +573,7 @@ __global__ __launch_bounds__(kGThreads, 1) void gemm_mfma_kernel(const __bf16* _
             if (EPI == EPI_RESIDUAL_NORM) {
                 float sd = 0.f, sx = 0.f;
                 if (ok) {
-                    const bf16x8 xr = xv[a & 1][step];
+                    const bf16x8 xr = xv[a][step];
                     bf16x8 ov;
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
