@@ -227,7 +227,7 @@ dash_status dash_flash_fwd(const dash_layer_params* p, const void* q, const void
     if (n == 0) return DASH_OK;
     if (!q || !k || !v || !active_idx || !o) return DASH_ERR_INVALID_ARG;
     if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o)) return DASH_ERR_INVALID_ARG;
-    return launch_flash_fwd(*p, q, k, v, active_idx, n, o, nullptr, 0, nullptr, (hipStream_t)hip_stream);
+    return launch_flash_fwd(*p, q, k, v, active_idx, n, o, nullptr, 0, nullptr, nullptr, 0, (hipStream_t)hip_stream);
 }
 
 dash_status dash_wo_residual_rownorm(const dash_layer_params* p, const void* o, const void* w_o,
@@ -496,7 +496,7 @@ dash_status dash_attn_layer(const dash_layer_params* p, const void* x, const voi
     const bool handed = one_launch && !(topk && few_topk(n, (p->d + 63) / 64));
     const int n_clear = handed ? (int)(published_bytes(n, topk) / sizeof(uint32_t)) : 0;
     if (profile) DASH_HIP_CHECK(hipEventRecord(profile->ev[0], s));
-    st = launch_flash_fwd(*p, q, k, v, active_idx, n, o, published, n_clear, handed ? n_active_out : nullptr, s);
+    st = launch_flash_fwd(*p, q, k, v, active_idx, n, o, published, n_clear, handed ? n_active_out : nullptr, ws + w.split_off, w.split_bytes, s);
     if (st != DASH_OK) return st;
     if (profile) DASH_HIP_CHECK(hipEventRecord(profile->ev[1], s));
     NormSums sums{};

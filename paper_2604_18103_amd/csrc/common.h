@@ -51,16 +51,20 @@ dash_status init_gemm_kernels();
 int compute_units();  // of the current device, asked for once; 0 if that failed
 
 // flash_fwd.hip
+// scratch / scratch_bytes: optional, 16-byte aligned, for a few rows' attention over keys in parts
 // clear_words / n_clear, clear_count: optional device words the launch sets to zero (its first workgroup does it), for the
 // kernels that follow in the same layer call and need cleared scratch without a launch of their own
 dash_status launch_flash_fwd(const dash_layer_params& p, const void* q, const void* k, const void* v,
                              const int32_t* active_idx, int n, void* o, uint32_t* clear_words, int n_clear,
-                             int32_t* clear_count, hipStream_t s);
+                             int32_t* clear_count, void* scratch, size_t scratch_bytes, hipStream_t s);
 // flash_few.hip
 dash_status init_few_kernels();
 dash_status launch_flash_few(const dash_layer_params& p, const __bf16* q, const __bf16* k, const __bf16* v,
                              const int32_t* pos, int n, int row0, __bf16* o, float scale_log2, int waves, uint32_t* clear_words,
                              int n_clear, int32_t* clear_count, hipStream_t s);
+struct FewParts;
+dash_status launch_flash_few_parts(const dash_layer_params& p, const __bf16* q, const __bf16* k, const __bf16* v, const int32_t* pos, int n,
+                                   int row0, __bf16* o, float scale_log2, const FewParts& g, float* sums, hipStream_t s);
 // wo_gemm.hip
 int norm_partials_per_row(int d, int dtype);
 // Row norms as a product left them: `cols` pairs per row, of which `fold` (1 or kNormFold) neighbours make up one of the

@@ -34,12 +34,15 @@ struct FewSmem {
     static_assert(2 * kStage * sizeof(__bf16) == 32 * DH * sizeof(float), "a wave's sums take its stages' place");
 };
 
-template <int DH, int KW>
+// PARTS: the keys are cut over gridDim.y workgroups as well (few_tail_parts), `blocks_per_part` blocks each; a part leaves its rows' sums
+// [part][row - row_base][head][DH] in `sums` and their (reference, sum of weights) behind all of them, for few_parts_kernel to add.
+template <int DH, int KW, bool PARTS>
 __global__ __launch_bounds__(KW * kWave, 2) void flash_few(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
                                                             const __bf16* __restrict__ v, const int32_t* __restrict__ pos,
                                                             __bf16* __restrict__ o, int n, int Hq, int Hkv, float scale_log2,
                                                             int causal, int n_qtiles, FaMap mp, uint32_t* __restrict__ clear_words,
-                                                            int n_clear, int row_base, int32_t* __restrict__ clear_count) {
+                                                            int n_clear, int row_base, int32_t* __restrict__ clear_count,
+                                                            float* __restrict__ sums, int blocks_per_part) {
     using SM = FewSmem<DH>;
     constexpr int KC = DH / 16, DB = DH / 32;
     constexpr int LOADS = few_loads(DH);
@@ -66,6 +69,7 @@ __global__ __launch_bounds__(KW * kWave, 2) void flash_few(const __bf16* __restr
 
     // block b: rows 32 b .. 32 b + 31 of a sequence; the lane offsets are those of a whole block, rows beyond the end are clamped
     const int kend = causal ? min(n, row0 + 32) : n, n_blocks = (kend + kFewKeys - 1) / kFewKeys;
+    const int first = PARTS ? (int)blockIdx.y * blocks_per_part : 0, end = PARTS ? min(n_blocks, first + blocks_per_part) : n_blocks;
     // the query rows, once for all waves (a wave's own fragments from memory are 32-byte pieces of 32 rows per instruction: four
     // waves kept the address unit busy with them for most of the prologue)
 #pragma unroll
@@ -100,9 +104,9 @@ __global__ __launch_bounds__(KW * kWave, 2) void flash_few(const __bf16* __restr
     // without a causal mask, those beyond the last key. Key j of that block is masked for the rows below its limit.
     const int pos_q = causal ? pos[row] : 0;
     const bool masked = causal || n % kFewKeys != 0;
-    if (wave < n_blocks) {
-        request(k, k_off, Ks, wave);
-        request(v, v_off, Vs, wave);
+    if (first + wave < end) {
+        request(k, k_off, Ks, first + wave);
+        request(v, v_off, Vs, first + wave);
         dma_wait_keep<2 * LOADS>();
     } else {
         dma_wait();
@@ -123,8 +127,8 @@ __global__ __launch_bounds__(KW * kWave, 2) void flash_few(const __bf16* __restr
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) asm volatile("" : "+v"(Qf[kc]));
 
-    for (int b = wave; b < n_blocks; b += KW) {
-        const bool more = b + KW < n_blocks;  // wave-uniform
+    for (int b = first + wave; b < end; b += KW) {
+        const bool more = b + KW < end;  // wave-uniform
         dma_wait_keep<LOADS>();  // K(b); V(b), requested after it, may be in flight
         wave_sync_lds();
         f32x16 S;
@@ -200,7 +204,7 @@ __global__ __launch_bounds__(KW * kWave, 2) void flash_few(const __bf16* __restr
 
     // The results of the waves that had a block meet: 16-byte unit u = 4 db + rg of lane (j, h) is dims 8 u + 4 h .. + 3 of row j.
     constexpr int UNITS = 4 * DB, OWN = UNITS / KW;
-    const int n_waves = min(KW, n_blocks);
+    const int n_waves = min(KW, end - first);
     if (wave < n_waves) {
         l += __shfl_xor(l, 32);
         if (h == 0) stat[wave * 32 + j] = make_float2(m, l);
@@ -219,12 +223,13 @@ __global__ __launch_bounds__(KW * kWave, 2) void flash_few(const __bf16* __restr
 #pragma unroll
     for (int w = 0; w < KW; ++w)
         if (w < n_waves) M = fmaxf(M, stat[w * 32 + j].x);
+    const float ref = PARTS && M == -INFINITY ? 0.f : M;  // no finite score in this part: sums of 0
     const f32x4* all = reinterpret_cast<const f32x4*>(Qs + SM::kStage);
 #pragma unroll
     for (int w = 0; w < KW; ++w)
         if (w < n_waves) {
             const float2 s = stat[w * 32 + j];
-            a[w] = __builtin_amdgcn_exp2f(s.x - M);
+            a[w] = __builtin_amdgcn_exp2f(s.x - ref);
             L = fmaf(a[w], s.y, L);
 #pragma unroll
             for (int i = 0; i < OWN; ++i) {
@@ -233,8 +238,15 @@ __global__ __launch_bounds__(KW * kWave, 2) void flash_few(const __bf16* __restr
                 for (int e = 0; e < 4; ++e) t[i][e] = fmaf(a[w], x[e], t[i][e]);
             }
         }
-    const float inv = 1.0f / L;
     if (row0 + j >= n) return;
+    if constexpr (PARTS) {
+        const size_t rows = n - row_base, item = ((size_t)blockIdx.y * rows + (row - row_base)) * Hq + head;
+#pragma unroll
+        for (int i = 0; i < OWN; ++i) *reinterpret_cast<f32x4*>(sums + item * DH + 8 * (wave * OWN + i) + 4 * h) = t[i];
+        if (wave == 0 && h == 0) reinterpret_cast<float2*>(sums + (size_t)gridDim.y * rows * Hq * DH)[item] = make_float2(M, L);
+        return;
+    }
+    const float inv = 1.0f / L;
     __bf16* op = o + ((size_t)row * Hq + head) * DH + 4 * h;
 #pragma unroll
     for (int i = 0; i < OWN; ++i) {
@@ -245,9 +257,34 @@ __global__ __launch_bounds__(KW * kWave, 2) void flash_few(const __bf16* __restr
     }
 }
 
-template <int DH, int KW>
+// Adds the parts of each row and head, in their order; a thread has four dims.
+__global__ __launch_bounds__(256) void few_parts_kernel(const float* __restrict__ sums, int parts, int items, int DH, __bf16* __restrict__ o) {
+    const int u = blockIdx.x * 256 + threadIdx.x, item = u / (DH / 4);
+    if (item >= items) return;
+    const float2* stat = reinterpret_cast<const float2*>(sums + (size_t)parts * items * DH) + item;
+    const float* src = sums + (size_t)u * 4;
+    float M = -INFINITY, L = 0.f;
+    for (int p = 0; p < parts; ++p) M = fmaxf(M, stat[(size_t)p * items].x);
+    f32x4 t = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+    for (int p = 0; p < parts; ++p) {
+        const float2 s = stat[(size_t)p * items];
+        const f32x4 x = *reinterpret_cast<const f32x4*>(src + (size_t)p * items * DH);
+        const float a = __builtin_amdgcn_exp2f(s.x - M);
+        L = fmaf(a, s.y, L);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] = fmaf(a, x[e], t[e]);
+    }
+    const float inv = 1.0f / L;
+    bf16x4 ov;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ov[e] = (__bf16)(t[e] * inv);
+    *reinterpret_cast<bf16x4*>(o + (size_t)u * 4) = ov;
+}
+
+template <int DH, int KW, bool PARTS = false>
 static hipError_t set_few_lds_size() {
-    return hipFuncSetAttribute((const void*)flash_few<DH, KW>, hipFuncAttributeMaxDynamicSharedMemorySize, FewSmem<DH>::bytes(KW));
+    return hipFuncSetAttribute((const void*)flash_few<DH, KW, PARTS>, hipFuncAttributeMaxDynamicSharedMemorySize, FewSmem<DH>::bytes(KW));
 }
 
 dash_status init_few_kernels() {
@@ -256,6 +293,8 @@ dash_status init_few_kernels() {
         if (e == hipSuccess) e = set_few_lds_size<64, 8>();
         if (e == hipSuccess) e = set_few_lds_size<128, 4>();
         if (e == hipSuccess) e = set_few_lds_size<128, 8>();
+        if (e == hipSuccess) e = set_few_lds_size<64, 8, true>();
+        if (e == hipSuccess) e = set_few_lds_size<128, 8, true>();
         return e;
     }();
     return err == hipSuccess ? DASH_OK : DASH_ERR_HIP;
@@ -267,8 +306,27 @@ static void launch_few(const dash_layer_params& p, const __bf16* q, const __bf16
     const int n_qtiles = (n - row0 + 31) / 32;
     unsigned blocks = 0;
     const FaMap mp = fa_map(n_qtiles, p.n_q_heads, p.n_kv_heads, blocks);
-    hipLaunchKernelGGL((flash_few<DH, KW>), dim3(blocks), dim3(KW * kWave), FewSmem<DH>::bytes(KW), s, q, k, v, pos, o, n,
-                       p.n_q_heads, p.n_kv_heads, scale_log2, p.causal, n_qtiles, mp, clear_words, n_clear, row0, clear_count);
+    hipLaunchKernelGGL((flash_few<DH, KW, false>), dim3(blocks), dim3(KW * kWave), FewSmem<DH>::bytes(KW), s, q, k, v, pos, o, n,
+                       p.n_q_heads, p.n_kv_heads, scale_log2, p.causal, n_qtiles, mp, clear_words, n_clear, row0, clear_count, nullptr, 0);
+}
+template <int DH>
+static void launch_few_parts(const dash_layer_params& p, const __bf16* q, const __bf16* k, const __bf16* v, const int32_t* pos, int n,
+                             int row0, __bf16* o, float scale_log2, const FewParts& g, float* sums, hipStream_t s) {
+    constexpr int KW = kFewTailWaves;
+    const int n_qtiles = (n - row0 + 31) / 32, Hq = p.n_q_heads, items = (n - row0) * Hq;
+    unsigned blocks = 0;
+    const FaMap mp = fa_map(n_qtiles, Hq, p.n_kv_heads, blocks);
+    hipLaunchKernelGGL((flash_few<DH, KW, true>), dim3(blocks, g.parts), dim3(KW * kWave), FewSmem<DH>::bytes(KW), s, q, k, v, pos, o, n, Hq,
+                       p.n_kv_heads, scale_log2, p.causal, n_qtiles, mp, nullptr, 0, row0, nullptr, sums, g.blocks_per_part);
+    hipLaunchKernelGGL(few_parts_kernel, dim3((items * (DH / 4) + 255) / 256), dim3(256), 0, s, sums, g.parts, items, DH, o + (size_t)row0 * Hq * DH);
+}
+
+// The rows beyond the last whole tile, without a causal mask, their keys cut into parts (few_tail_parts).
+dash_status launch_flash_few_parts(const dash_layer_params& p, const __bf16* q, const __bf16* k, const __bf16* v, const int32_t* pos, int n,
+                                   int row0, __bf16* o, float scale_log2, const FewParts& g, float* sums, hipStream_t s) {
+    if (init_few_kernels() != DASH_OK) return DASH_ERR_HIP;
+    (p.head_dim == 64 ? launch_few_parts<64> : launch_few_parts<128>)(p, q, k, v, pos, n, row0, o, scale_log2, g, sums, s);
+    return launch_status();
 }
 
 // Query rows [row0, n), row0 a multiple of 32, against all keys. waves: 4 or 8 (few_waves, staging_addr.h)

@@ -846,7 +846,7 @@ static dash_status launch_mfma(const dash_layer_params& p, const __bf16* q, cons
 
 dash_status launch_flash_fwd(const dash_layer_params& p, const void* q, const void* k, const void* v,
                              const int32_t* active_idx, int n, void* o, uint32_t* clear_words, int n_clear,
-                             int32_t* clear_count, hipStream_t s) {
+                             int32_t* clear_count, void* scratch, size_t scratch_bytes, hipStream_t s) {
     if (n == 0) return DASH_OK;
     const float scale = p.softmax_scale > 0.f ? p.softmax_scale : 1.0f / sqrtf((float)p.head_dim);
     if (p.dtype == DASH_F32) {
@@ -873,8 +873,12 @@ dash_status launch_flash_fwd(const dash_layer_params& p, const void* q, const vo
         n_clear = 0;
         clear_count = nullptr;
     }
-    if (form == FA_ONE_AND_TAIL && fa_few_tail(n, p.n_q_heads, p.head_dim, compute_units()))
-        return launch_flash_few(p, bq, bk, bv, active_idx, n, one_end, (__bf16*)o, scale_log2, 8, clear_words, n_clear, clear_count, s);
+    if (form == FA_ONE_AND_TAIL && fa_few_tail(n, p.n_q_heads, p.head_dim, compute_units())) {
+        const FewParts parts = few_tail_parts(n, p.n_q_heads, p.head_dim, compute_units(), scratch ? scratch_bytes : 0);
+        if (parts.parts > 1)
+            return launch_flash_few_parts(p, bq, bk, bv, active_idx, n, one_end, (__bf16*)o, scale_log2, parts, (float*)scratch, s);
+        return launch_flash_few(p, bq, bk, bv, active_idx, n, one_end, (__bf16*)o, scale_log2, kFewTailWaves, clear_words, n_clear, clear_count, s);
+    }
     return p.head_dim == 64 ? launch_mfma<64, 2>(p, bq, bk, bv, active_idx, n, one_end, n, (__bf16*)o, scale_log2, clear_words, n_clear, clear_count, s)
                             : launch_mfma<128, 2>(p, bq, bk, bv, active_idx, n, one_end, n, (__bf16*)o, scale_log2, clear_words, n_clear, clear_count, s);
 }

@@ -519,4 +519,32 @@ inline int few_waves(int n, int Hq, int head_dim, bool causal, int cu) {
     return wgs <= (long long)cu * (head_dim == 64 ? 2 : 1) ? 8 : 4;
 }
 
+// The rows beyond the last whole tile (fa_few_tail), keys cut over several workgroups per 32 rows and head: a unit fetches a key block in
+// 0.9 us (head size 128: 1.7) per wave's turn whatever its waves, so a few workgroups that each go through all keys leave the chip idle.
+// Parts of at least a block per wave, one workgroup per unit in all, and another launch to add them, 4 us; where that is expected to
+// be shorter and the sums fit the scratch. 1: not cut. Layer calls without a causal mask, not cut / cut, us: 16 heads of 64 4097 rows 119.7 / 112.4,
+// 4129 120.4 / 114.5, 4319 125.7 / 122.4, 8193 337.6 / 317.8; 28 of 128 2305 156.9 / 149.9, 2400 159.8 / 157.2, 4609 410 / 392; 32 of 128 4100 398.4 / 384.7.
+// (Twice the waves per workgroup instead of twice the workgroups: 88.1 / 87.9 us of attention at 4097 rows.)
+constexpr int kFewTailWaves = 8;
+struct FewParts {
+    int parts, blocks_per_part;
+};
+DASH_HD size_t few_part_bytes(int rows, int Hq, int DH) { return (size_t)rows * Hq * (DH + 2) * sizeof(float); }
+inline FewParts few_tail_parts(int n, int Hq, int head_dim, int cu, size_t scratch_bytes) {
+    const int rows = n % kFaBM, wgs = (rows + 31) / 32 * Hq, blocks = (n + kFewKeys - 1) / kFewKeys;
+    FewParts best{1, blocks};
+    if (rows == 0) return best;
+    const double turn = head_dim == 64 ? 0.9 : 1.7;
+    auto turns = [](int b) { return (b + kFewTailWaves - 1) / kFewTailWaves; };
+    double best_us = turn * turns(blocks);
+    for (int parts = 2; parts * wgs <= cu; ++parts) {
+        const int per = kFewTailWaves * turns((blocks + parts - 1) / parts);
+        const double us = turn * turns(per) + 4.0;
+        if ((blocks + per - 1) / per != parts || parts * few_part_bytes(rows, Hq, head_dim) > scratch_bytes || us >= best_us) continue;
+        best = FewParts{parts, per};
+        best_us = us;
+    }
+    return best;
+}
+
 }  // namespace dash

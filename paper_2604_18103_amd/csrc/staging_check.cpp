@@ -566,6 +566,12 @@ int dash_check_few_queries(int n, int Hq, int DH, int waves, int row_base, long 
     return c.status;
 }
 
+// Parts of the keys of the rows beyond the last whole tile, and the key blocks of a part.
+int dash_few_tail_parts(int n, int Hq, int head_dim, int cu, size_t scratch_bytes, int* blocks_per_part) {
+    const FewParts g = few_tail_parts(n, Hq, head_dim, cu, scratch_bytes);
+    *blocks_per_part = g.blocks_per_part;
+    return g.parts;
+}
 // Whether the rows beyond the last whole tile take the few-row form (where dash_fa_form is 2).
 int dash_fa_few_tail(int n, int Hq, int head_dim, int cu) { return fa_few_tail(n, Hq, head_dim, cu); }
 
