@@ -658,78 +658,78 @@ __device__ __forceinline__ void small_epilogue(const float* stage, int tid, RowO
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[e] += src[g * STAGED * STR + e];
     };
-            if (EPI == EPI_SWIGLU) {
-                // lane group of 4 per row and 64 columns: lane c takes gate columns 8c..8c+7 and the up columns 32 + 8c..
-                constexpr int LPR = BN / 16, ROWS = THREADS / LPR;
+    if (EPI == EPI_SWIGLU) {
+        // lane group of 4 per row and 64 columns: lane c takes gate columns 8c..8c+7 and the up columns 32 + 8c..
+        constexpr int LPR = BN / 16, ROWS = THREADS / LPR;
 #pragma unroll
-                for (int p = 0; p < (STAGED + ROWS - 1) / ROWS; ++p) {
-                    const int sr = p * ROWS + tid / LPR, l = tid % LPR;
-                    if (sr >= STAGED) break;
-                    const int gm = row_of(sr);
-                    const int gcol = (n0 + 64 * (l / 4)) / 2 + 8 * (l % 4);
-                    float gv[8], uv[8];
-                    sum8(&stage[sr * STR + 64 * (l / 4) + 8 * (l % 4)], gv);
-                    sum8(&stage[sr * STR + 64 * (l / 4) + 8 * (l % 4) + 32], uv);
-                    if (gm < M && gcol < N / 2) {
-                        bf16x8 ov;
+        for (int p = 0; p < (STAGED + ROWS - 1) / ROWS; ++p) {
+            const int sr = p * ROWS + tid / LPR, l = tid % LPR;
+            if (sr >= STAGED) break;
+            const int gm = row_of(sr);
+            const int gcol = (n0 + 64 * (l / 4)) / 2 + 8 * (l % 4);
+            float gv[8], uv[8];
+            sum8(&stage[sr * STR + 64 * (l / 4) + 8 * (l % 4)], gv);
+            sum8(&stage[sr * STR + 64 * (l / 4) + 8 * (l % 4) + 32], uv);
+            if (gm < M && gcol < N / 2) {
+                bf16x8 ov;
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) ov[e] = (__bf16)(gv[e] / (1.0f + __expf(-gv[e])) * uv[e]);
-                        *reinterpret_cast<bf16x8*>(out + (size_t)gm * (N / 2) + gcol) = ov;
-                    }
-                }
-            } else {
-                constexpr int LPR = BN / 8, ROWS = THREADS / LPR;
-#pragma unroll
-                for (int p = 0; p < (STAGED + ROWS - 1) / ROWS; ++p) {
-                    const int sr = p * ROWS + tid / LPR, l = tid % LPR;
-                    if (sr >= STAGED) break;
-                    const int gm = row_of(sr), gn = n0 + 8 * l;
-                    float dv[8];
-                    sum8(&stage[sr * STR + 8 * l], dv);
-                    const bool ok = gm < M && gn < N;
-                    if (EPI == EPI_RESIDUAL_NORM) {
-                        float sd = 0.f, sx = 0.f;
-                        if (ok) {
-                            const bf16x8 xr = x_of(p, gm, gn);
-                            bf16x8 ov;
-#pragma unroll
-                            for (int e = 0; e < 8; ++e) {
-                                const float xf = (float)xr[e];
-                                ov[e] = (__bf16)(xf + dv[e]);
-                                sd = fmaf(dv[e], dv[e], sd);
-                                sx = fmaf(xf, xf, sx);
-                            }
-                            *reinterpret_cast<bf16x8*>(out + (size_t)gm * N + gn) = ov;
-                        }
-                        if (partials) {
-#pragma unroll
-                            for (int off = 4; off > 0; off >>= 1) {
-                                sd += __shfl_xor(sd, off);
-                                sx += __shfl_xor(sx, off);
-                            }
-                            if (l % 8 == 0 && ok)
-                                *reinterpret_cast<float2*>(partials + ((size_t)(gn / 64) * M + gm) * 2) = make_float2(sd, sx);
-                        }
-                    } else if (EPI == EPI_SPLITK) {
-                        if (ok) {
-                            float* dst = split_sums + ((size_t)part * M + gm) * N + gn;
-                            *reinterpret_cast<f32x4*>(dst) = f32x4{dv[0], dv[1], dv[2], dv[3]};
-                            *reinterpret_cast<f32x4*>(dst + 4) = f32x4{dv[4], dv[5], dv[6], dv[7]};
-                        }
-                    } else if (ok) {
-                        if (EPI == EPI_QKV_ROPE && gn < qkv.Dq + qkv.Dkv) {  // a head lies in one tile (the launcher's choice)
-                            float partner[8];
-                            sum8(&stage[sr * STR + ((8 * l) ^ qkv.half)], partner);
-                            rope8(qkv, gm, gn, partner, dv);
-                        }
-                        bf16x8 ov;
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) ov[e] = (__bf16)dv[e];
-                        __bf16* dst = epi_qkv(EPI) ? qkv_dst(out, qkv, gm, gn) : out + (size_t)gm * N + gn;
-                        *reinterpret_cast<bf16x8*>(dst) = ov;
-                    }
-                }
+                for (int e = 0; e < 8; ++e) ov[e] = (__bf16)(gv[e] / (1.0f + __expf(-gv[e])) * uv[e]);
+                *reinterpret_cast<bf16x8*>(out + (size_t)gm * (N / 2) + gcol) = ov;
             }
+        }
+    } else {
+        constexpr int LPR = BN / 8, ROWS = THREADS / LPR;
+#pragma unroll
+        for (int p = 0; p < (STAGED + ROWS - 1) / ROWS; ++p) {
+            const int sr = p * ROWS + tid / LPR, l = tid % LPR;
+            if (sr >= STAGED) break;
+            const int gm = row_of(sr), gn = n0 + 8 * l;
+            float dv[8];
+            sum8(&stage[sr * STR + 8 * l], dv);
+            const bool ok = gm < M && gn < N;
+            if (EPI == EPI_RESIDUAL_NORM) {
+                float sd = 0.f, sx = 0.f;
+                if (ok) {
+                    const bf16x8 xr = x_of(p, gm, gn);
+                    bf16x8 ov;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float xf = (float)xr[e];
+                        ov[e] = (__bf16)(xf + dv[e]);
+                        sd = fmaf(dv[e], dv[e], sd);
+                        sx = fmaf(xf, xf, sx);
+                    }
+                    *reinterpret_cast<bf16x8*>(out + (size_t)gm * N + gn) = ov;
+                }
+                if (partials) {
+#pragma unroll
+                    for (int off = 4; off > 0; off >>= 1) {
+                        sd += __shfl_xor(sd, off);
+                        sx += __shfl_xor(sx, off);
+                    }
+                    if (l % 8 == 0 && ok)
+                        *reinterpret_cast<float2*>(partials + ((size_t)(gn / 64) * M + gm) * 2) = make_float2(sd, sx);
+                }
+            } else if (EPI == EPI_SPLITK) {
+                if (ok) {
+                    float* dst = split_sums + ((size_t)part * M + gm) * N + gn;
+                    *reinterpret_cast<f32x4*>(dst) = f32x4{dv[0], dv[1], dv[2], dv[3]};
+                    *reinterpret_cast<f32x4*>(dst + 4) = f32x4{dv[4], dv[5], dv[6], dv[7]};
+                }
+            } else if (ok) {
+                if (EPI == EPI_QKV_ROPE && gn < qkv.Dq + qkv.Dkv) {  // a head lies in one tile (the launcher's choice)
+                    float partner[8];
+                    sum8(&stage[sr * STR + ((8 * l) ^ qkv.half)], partner);
+                    rope8(qkv, gm, gn, partner, dv);
+                }
+                bf16x8 ov;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) ov[e] = (__bf16)dv[e];
+                __bf16* dst = epi_qkv(EPI) ? qkv_dst(out, qkv, gm, gn) : out + (size_t)gm * N + gn;
+                *reinterpret_cast<bf16x8*>(dst) = ov;
+            }
+        }
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
