@@ -203,7 +203,7 @@ DASH_HD bool small_work_of(int b, int tiles, int parts, int& tile, int& part) {
     return b / 8 < seg && idx < work;
 }
 
-// Which form a product takes: the large tiles (gemm_plan) or one of four small-tile forms. Small tiles are for products of few
+// Which form a product takes: the large tiles (gemm_plan) or one of five small-tile forms (the fifth: tall_tile_plan). Small tiles are for products of few
 // rows (at most two large row tiles), and for others while the large tiles would occupy at most half of the units (their
 // alternative is then K parts and a second pass). From there on they save nothing worth a second rule: of 300 products
 // measured beyond that line, small tiles were up to 1.3 times as slow where they had been chosen, and never more than 8 %
@@ -231,10 +231,11 @@ struct SmallForm {
     int BM, BN, KW, NS, per_cu;
     double step_us, full_us;
 };
-constexpr SmallForm kSmallForms[4] = {{64, 64, 2, 3, 1, 0.205, 0.205},
+constexpr SmallForm kSmallForms[5] = {{64, 64, 2, 3, 1, 0.205, 0.205},
                                       {64, 128, 2, 3, 1, 0.31, 0.31},
                                       {128, 128, 1, 3, 1, 0.45, 0.45},
-                                      {128, 128, 1, 2, 2, 0.64, 0.875}};
+                                      {128, 128, 1, 2, 2, 0.64, 0.875},
+                                      {192, 128, 1, 3, 1, 0.65, 0.65}};  // tall_tile_plan
 constexpr int kSmallSplitMinSteps = 6;  // K steps of a part, at least
 
 struct SmallPlan {
@@ -315,6 +316,20 @@ inline SmallPlan small_plan(int M, int K, int N, int cu, bool norms, int head, b
         }
     }
     return best;
+}
+
+// 192 x 128 tiles, one workgroup per unit and all three stages' lead, in place of two 128 x 128 workgroups per unit (form 3), whose steps
+// have one round to land, where they fit one round. us, two workgroups / these; with a row norm's launch, weight cached: K = N = 3584 1153 rows
+// 46.4 / 44.0, 1400 48.0 / 46.0, 1728 50.6 / 48.9; 4096 1025 49.3 / 45.1, 1536 55.0 / 51.8; 1024 (16 steps) 4097 24.4 / 21.9, 5000 26.2 / 24.3, 6144 27.1 /
+// 27.2; front end of 3584 x 4608 1000 rows 46.3 / 42.4, 1344 50.9 / 47.1. Weights and x from memory: layer of 3584 1220 rows 86.8 / 72.2, 1700 100.8 / 91.2;
+// front end 1000 55.7 / 43.4. Fewer than 16 steps: 12000 rows of 512 x 512 19.7 / 20.4. 256 x 128 tiles: 2120 rows of 3584 the same from the caches and
+// from memory, 8192 of 1024 30.5 / 33.6.
+constexpr int kTallForm = 4, kTallMinSteps = 16;
+inline SmallPlan tall_tile_plan(int M, int N, int cu, const SmallPlan& other) {
+    const SmallForm& s = kSmallForms[kTallForm];
+    const int mt = (M + s.BM - 1) / s.BM, nt = (N + s.BN - 1) / s.BN, tiles = mt * nt, ksteps = other.ksteps_per_part;
+    if (other.form != 3 || (long long)mt * nt > cu || ksteps < kTallMinSteps) return other;
+    return SmallPlan{kTallForm, mt, nt, tiles, 8 * ((tiles + 7) / 8), 1, ksteps, 0, ksteps * s.step_us + 4.0};
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -242,7 +242,7 @@ int dash_small_deal(int tiles, int parts) {
 // every staging load of every K group fetches the clamped row and column its lane is meant to.
 int dash_check_small_staging(int M, int K, int N, int form, long long* n_loads) {
     Counter c;
-    if (M <= 0 || K <= 0 || K % kGK != 0 || N <= 0 || N % 8 != 0 || form < 0 || form >= 4) return -1;
+    if (M <= 0 || K <= 0 || K % kGK != 0 || N <= 0 || N % 8 != 0 || form < 0 || form > kTallForm) return -1;
     const SmallForm& f = kSmallForms[form];
     const int mt = (M + f.BM - 1) / f.BM, nt = (N + f.BN - 1) / f.BN, tiles = mt * nt;
     const uint64_t a_bytes = (uint64_t)M * K * 2, b_bytes = (uint64_t)K * N * 2;
@@ -346,6 +346,13 @@ void dash_few_tile_plan(int M, int K, int N, int cu, int norms, int head, unsign
     const SmallPlan s = small_plan(M, K, N, cu, norms != 0, head, scratch > 0, (size_t)scratch, large_tiles_us(g, M, N, cu));
     const SmallPlan p = few_tile_plan(M, K, N, cu, norms != 0, head, scratch > 0, (size_t)scratch, s);
     out[0] = p.few_rows; out[1] = p.tiles; out[2] = p.parts; out[3] = p.ksteps_per_part;
+}
+
+// The form a product takes with the taller tiles among them: out[0..1] = form, tiles.
+void dash_tall_tile_plan(int M, int K, int N, int cu, int norms, unsigned long long scratch, int* out) {
+    const GemmPlan g = gemm_plan(M, K, N, cu, scratch > 0, (size_t)scratch);
+    const SmallPlan p = tall_tile_plan(M, N, cu, small_plan(M, K, N, cu, norms != 0, 0, scratch > 0, (size_t)scratch, large_tiles_us(g, M, N, cu)));
+    out[0] = p.form; out[1] = p.tiles;
 }
 
 // K parts of the left-over half tiles, 1: one pass.

@@ -733,7 +733,7 @@ __device__ __forceinline__ void small_epilogue(const float* stage, int tid, RowO
 }
 
 // ------------------------------------------------------------------------------------------------
-// The same product on small tiles: BM x BN (64 or 128 each), KW groups of 4 waves in 2 x 2. One workgroup per compute unit (96 to
+// The same product on small tiles: BM x BN (64, 128 or 192 x 64 or 128), KW groups of 4 waves in 2 x 2. One workgroup per compute unit (96 to
 // 144 KB of LDS), of the second 128 x 128 form two.
 // Few rows leave the 256 x 256 tiles with a handful of workgroups, which then have to be cut along K and summed in a
 // second pass: with 177 rows the fp32 sums written and read back were more bytes than the weight. Small tiles fill the
@@ -757,8 +757,10 @@ __device__ __forceinline__ void small_epilogue(const float* stage, int tid, RowO
 // ------------------------------------------------------------------------------------------------
 constexpr size_t small_smem_bytes(int BM, int BN, int KW, int NS) { return (size_t)KW * NS * (BM + BN) * kGK * sizeof(__bf16); }
 
+// 192 rows: with x in flight as well the registers of two waves per SIMD are too few (1153 rows of 3584 48.0 us for 44.0), while the other
+// epilogues' loops are the faster ones with them (front end, 1000 rows, 42.4 us for 52.1).
 template <int EPI, int BM, int BN, int KW, int NS>
-__global__ __launch_bounds__(KW * kSWaves * kWave, 2) void gemm_small_kernel(const __bf16* __restrict__ A, const __bf16* __restrict__ B,
+__global__ __launch_bounds__(KW * kSWaves * kWave, BM > 128 && EPI == EPI_RESIDUAL_NORM ? 1 : 2) void gemm_small_kernel(const __bf16* __restrict__ A, const __bf16* __restrict__ B,
                                                                   int M, int K, int N, const __bf16* __restrict__ x,
                                                                   __bf16* __restrict__ out, float* __restrict__ partials,
                                                                   float* __restrict__ split_sums, int mt, int tiles, int parts,
@@ -1422,6 +1424,7 @@ static hipError_t set_small_lds_sizes() {
     if (e == hipSuccess) e = set_small_lds_size<EPI, 1>();
     if (e == hipSuccess) e = set_small_lds_size<EPI, 2>();
     if (e == hipSuccess) e = set_small_lds_size<EPI, 3>();
+    if (e == hipSuccess) e = set_small_lds_size<EPI, kTallForm>();
     return e;
 }
 
@@ -1527,7 +1530,8 @@ static dash_status launch_small(const SmallPlan& g, GemmArgs a, void* scratch, N
         case 0: launch_small_form<EPI, 0>(g, a, s); break;
         case 1: launch_small_form<EPI, 1>(g, a, s); break;
         case 2: launch_small_form<EPI, 2>(g, a, s); break;
-        default: launch_small_form<EPI, 3>(g, a, s); break;
+        case 3: launch_small_form<EPI, 3>(g, a, s); break;
+        default: launch_small_form<EPI, kTallForm>(g, a, s); break;
     }
     if (EPI == EPI_RESIDUAL_NORM && coarse) {
         static_assert(kGN == 64 * kNormFold, "a fine pair covers 64 columns");
@@ -1577,6 +1581,7 @@ static dash_status launch_gemm(const __bf16* A, const __bf16* B, int M, int K, i
     const int head = EPI == EPI_QKV_ROPE ? 2 * qkv.half : 0;
     const size_t scratch_bytes = split_ws ? split_bytes : 0;
     SmallPlan small = small_plan(M, K, N, compute_units(), norms, head, split_ws != nullptr, scratch_bytes, large_tiles_us(g, M, N, compute_units()));
+    small = tall_tile_plan(M, N, compute_units(), small);
     small = few_tile_plan(M, K, N, compute_units(), norms, head, split_ws != nullptr, scratch_bytes, small);
     if ((small.form >= 0 || small.few_rows > 0) && !delta_dbg) {
         GemmArgs a = args;
