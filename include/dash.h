@@ -123,8 +123,8 @@ int32_t dash_norm_partials_per_row(const dash_layer_params *params);
  * device outputs: x_next [n,d]; scores [n] fp32; halt_mask [n] uint8 (1 = halted);
  *                 x_compact [n,d] (first n_active_out rows valid, bitwise copies of kept
  *                 x_next rows); new_active_idx [n] (first n_active_out valid);
- *                 n_active_out: ONE device int32 (-1: a bounded wait between the call's workgroups ended without
- *                 its word, the other outputs are not valid)
+ *                 n_active_out: ONE device int32 (rules NONE and THRESHOLD, -1: a bounded wait between the call's workgroups ended
+ *                 without its word, the other outputs are not valid; TOPK waits for nothing without which it cannot end)
  *                 delta_dbg: NULL, or fp32 [n,d] that receives delta
  * workspace     : device, >= dash_workspace_bytes(params, n_active), 256-byte aligned
  * profile       : NULL or a dash_profile

@@ -496,7 +496,7 @@ dash_status dash_attn_layer(const dash_layer_params* p, const void* x, const voi
     const bool handed = one_launch && !(topk && few_topk(n, (p->d + 63) / 64));
     const int n_clear = handed ? (int)(published_bytes(n, topk) / sizeof(uint32_t)) : 0;
     if (profile) DASH_HIP_CHECK(hipEventRecord(profile->ev[0], s));
-    st = launch_flash_fwd(*p, q, k, v, active_idx, n, o, published, n_clear, handed ? n_active_out : nullptr, ws + w.split_off, w.split_bytes, s);
+    st = launch_flash_fwd(*p, q, k, v, active_idx, n, o, published, n_clear, handed && !topk ? n_active_out : nullptr, ws + w.split_off, w.split_bytes, s);
     if (st != DASH_OK) return st;
     if (profile) DASH_HIP_CHECK(hipEventRecord(profile->ev[1], s));
     NormSums sums{};

@@ -343,9 +343,9 @@ __global__ __launch_bounds__(kFewThreads) void topk_compact_few_kernel(
 // 1024 threads (select_cut, keys in registers), and gathers its columns of its chunk's kept rows. The cut is found in as many
 // places as there are workgroups, all resident at once, so it costs its time once; saved are the launches of score, decision and
 // compaction and two trips of flags and counts through memory.
-// Waiting: publishers have the smallest linear indexes, so whoever waits for one waits for a workgroup that was dispatched before it. Every
-// wait is bounded (kPubSpinLimit), and one that ends without its key fails the call: the workgroup gathers nothing and writes the survivor
-// count -1, as score_decide_compact_kernel does. All threads ask for their keys at once and again while one is missing: with one wave
+// Waiting: a key that does not come in time is computed where it is missing (take_keys, publish.h), so no workgroup depends on another
+// and the call cannot fail (a bounded wait that failed it, with the count exchanged for a -1, was no faster: 640 rows of width 512 23.0 -> 22.4 us
+// a layer, 2120 of 3584 107.2 -> 106.8). All threads ask for their keys at once and again while one is missing: with one wave
 // asking for the last row first, a trip to memory more, 640 rows of width 512 took 23.9 us and not 23.1.
 // Bound by latency: pairs, key out and back, cut, gather. Figures: kFusedTopkRows.
 // ------------------------------------------------------------------------------------------------
@@ -376,29 +376,12 @@ __global__ __launch_bounds__(kSelectThreads, 8) void topk_compact_kernel(
     const int chunk = ((int)blockIdx.x - n_chunks) % n_chunks, split = ((int)blockIdx.x - n_chunks) / n_chunks;
     const int lo = min(n_first, n), hi = max(lo, n - n_last);  // candidates are rows [lo, hi)
     const int k_cand = max(0, min(k_keep - (n - (hi - lo)), hi - lo));
-    int spins = 0;
-    uint32_t key[B];  // all of a thread's loads in flight at once; what has not arrived is asked for again together
-#pragma unroll
-    for (int u = 0; u < B; ++u) key[u] = 0u;
-    bool bad = false;
-    for (bool all = false; !all;) {
-#pragma unroll
-        for (int u = 0; u < B; ++u)
-            if (u * kSelectThreads + tid < n && key[u] == 0u)
-                key[u] = __hip_atomic_load(words + u * kSelectThreads + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        all = true;
-#pragma unroll
-        for (int u = 0; u < B; ++u) all = all && (key[u] != 0u || u * kSelectThreads + tid >= n);
-        if (!all && ++spins > kPubSpinLimit) {
-            bad = true;
-            all = true;
-        }
-        if (!all) __builtin_amdgcn_s_sleep(2);
-    }
-    if (__syncthreads_or(bad)) {
-        if (tid == 0) __hip_atomic_store(n_out, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return;
-    }
+    uint32_t key[B];
+    take_keys<B>(
+        key, tid, kSelectThreads, n,
+        [&](int r) { return __hip_atomic_load(words + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); },
+        [&](int r) { return order_key(score_from_sums(row_sums(partials, cols, fold, n, r), score_kind)); },
+        [] { __builtin_amdgcn_s_sleep(2); });
     uint32_t cand = 0u;  // bit u: row u * 1024 + tid is a candidate; 0, which no score's key is, for others
 #pragma unroll
     for (int u = 0; u < B; ++u) {
@@ -424,11 +407,7 @@ __global__ __launch_bounds__(kSelectThreads, 8) void topk_compact_kernel(
         if (split == 0) {
             if (row < n) halt[row] = keep ? 0 : 1;
             if (keep) new_idx[base + rank] = active_idx[row];
-            if (chunk == n_chunks - 1 && lane == 0) {
-                int cleared = 0;
-                (void)__hip_atomic_compare_exchange_strong(n_out, &cleared, base + cnt, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                           __HIP_MEMORY_SCOPE_AGENT);
-            }
+            if (chunk == n_chunks - 1 && lane == 0) *n_out = base + cnt;
         }
     }
     __syncthreads();

@@ -26,4 +26,36 @@ DASH_HD unsigned long long pub_mask(unsigned long long w0, unsigned long long w1
 }
 DASH_HD int pub_count(unsigned long long w0) { return (int)((w0 >> 32) & 0x7Full); }
 
+// Rule TOPK (topk_compact_kernel): one 32-bit word per row, its score's key, zero at the start. No key is 0, so a word is its own READY
+// flag. Keys u of a thread are rows u * stride + tid; a key whose word is still 0 when it has been asked for kKeyAsks times (a microsecond
+// or less each; they come after two to five) is made from its row's norm pairs, which the launch before has written. So nothing
+// depends on when, or whether, the word's writer gets onto the chip: the XCDs take their workgroups each at its own pace, and beside
+// calls on other streams a writer may start long after those that ask for its words.
+// ask(row): the row's word; own(row): its key from the pairs; rest(): between two rounds of asking.
+#if defined(__clang__)
+#define DASH_UNROLL _Pragma("unroll")
+#else
+#define DASH_UNROLL
+#endif
+constexpr int kKeyAsks = 64;
+template <int B, class Ask, class Own, class Rest>
+DASH_HD void take_keys(uint32_t (&key)[B], int tid, int stride, int n, Ask ask, Own own, Rest rest) {
+    DASH_UNROLL
+    for (int u = 0; u < B; ++u) key[u] = 0u;
+    for (int asks = 1;; ++asks) {  // all of a thread's words at once, and those that had not arrived again together
+        DASH_UNROLL
+        for (int u = 0; u < B; ++u)
+            if (u * stride + tid < n && key[u] == 0u) key[u] = ask(u * stride + tid);
+        bool all = true;
+        DASH_UNROLL
+        for (int u = 0; u < B; ++u) all = all && (key[u] != 0u || u * stride + tid >= n);
+        if (all) return;
+        if (asks == kKeyAsks) break;
+        rest();
+    }
+    DASH_UNROLL
+    for (int u = 0; u < B; ++u)
+        if (u * stride + tid < n && key[u] == 0u) key[u] = own(u * stride + tid);
+}
+
 }  // namespace dash

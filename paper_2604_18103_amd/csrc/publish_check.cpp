@@ -46,4 +46,25 @@ int dash_check_publish(int chunks, int splits, int late, int* gathered) {
     return n_out;
 }
 
+// Steps the keys' way into every thread of a one-launch TopK workgroup over n rows (take_keys); the words of rows [late0, late1) are still 0
+// the first late_asks times a thread asks for them (below 0: every time). *own: rows whose key was made from the pairs. Returns how
+// many rows ended with another key than their own.
+int dash_check_topk_keys(int n, int late0, int late1, int late_asks, int* own) {
+    constexpr int kStride = 1024, B = 4;
+    auto key_of = [](int r) { return 0x80000000u + 2654435761u * (uint32_t)r % 0x7FFFFFFFu; };
+    int wrong = 0;
+    *own = 0;
+    for (int tid = 0; tid < kStride; ++tid) {
+        std::vector<int> asked((size_t)n, 0);
+        uint32_t key[B];
+        take_keys<B>(
+            key, tid, kStride, n,
+            [&](int r) { return r >= late0 && r < late1 && (late_asks < 0 || asked[(size_t)r]++ < late_asks) ? 0u : key_of(r); },
+            [&](int r) { ++*own; return key_of(r); }, [] {});
+        for (int u = 0; u < B; ++u) wrong += key[u] != (u * kStride + tid < n ? key_of(u * kStride + tid) : 0u);
+    }
+    return wrong;
+}
+int dash_key_asks() { return kKeyAsks; }
+
 }  // extern "C"

@@ -9,19 +9,20 @@ namespace dash {
 
 // Quarter qd (0..3) of the sum of a row's partial pairs: pairs qd, qd + 4, ... in order. The four quarters are added in order
 // qd = 0..3, so a score has the same bits whoever finishes it.
+template <int UNROLL = 4>
 __device__ __forceinline__ float2 row_quarter(const float* __restrict__ partials, int cols, int fold, int n, int row, int qd) {
     float sd = 0.f, sx = 0.f;
     if (row < n) {
         const float2* src = reinterpret_cast<const float2*>(partials) + row;
         if (fold == 1) {
-#pragma unroll 4
+#pragma unroll UNROLL
             for (int p = qd; p < cols; p += 4) {
                 const float2 v = src[(size_t)p * n];
                 sd += v.x;
                 sx += v.y;
             }
         } else {  // kNormFold neighbouring columns make up a partial: added in order, all loads of a few partials in flight
-#pragma unroll 4
+#pragma unroll UNROLL
             for (int c0 = qd * kNormFold; c0 < cols; c0 += 4 * kNormFold) {
                 float2 v[kNormFold];
 #pragma unroll
@@ -43,6 +44,13 @@ __device__ __forceinline__ float2 row_quarter(const float* __restrict__ partials
 }
 __device__ __forceinline__ float2 add_quarters(float2 a, float2 b, float2 c, float2 d) {
     return make_float2(a.x + b.x + c.x + d.x, a.y + b.y + c.y + d.y);
+}
+// The same sum by one thread, in few registers.
+__device__ __forceinline__ float2 row_sums(const float* __restrict__ partials, int cols, int fold, int n, int row) {
+    float2 q[4];
+#pragma unroll
+    for (int qd = 0; qd < 4; ++qd) q[qd] = row_quarter<1>(partials, cols, fold, n, row, qd);
+    return add_quarters(q[0], q[1], q[2], q[3]);
 }
 
 // Sum of the partial pairs of one row, taken by the four threads (row, q = 0..3) of a 256-thread workgroup that covers 64 rows.
