@@ -125,7 +125,10 @@ int32_t dash_norm_partials_per_row(const dash_layer_params *params);
  *                 x_next rows); new_active_idx [n] (first n_active_out valid);
  *                 n_active_out: ONE device int32 (rules NONE and THRESHOLD, -1: a bounded wait between the call's workgroups ended
  *                 without its word, the other outputs are not valid; TOPK waits for nothing without which it cannot end)
- *                 delta_dbg: NULL, or fp32 [n,d] that receives delta
+ *                 delta_dbg: NULL, or fp32 [n,d] that receives delta. With it the outputs have the bits that the
+ *                 stage-level calls give (dash_wo_residual_rownorm with delta_dbg); without it the workspace lets
+ *                 the product, and without a causal mask the attention of the last n % 256 rows, add in another
+ *                 order, so results may differ in rounding
  * workspace     : device, >= dash_workspace_bytes(params, n_active), 256-byte aligned
  * profile       : NULL or a dash_profile
  *

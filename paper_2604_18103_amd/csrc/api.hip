@@ -496,7 +496,9 @@ dash_status dash_attn_layer(const dash_layer_params* p, const void* x, const voi
     const bool handed = one_launch && !(topk && few_topk(n, (p->d + 63) / 64));
     const int n_clear = handed ? (int)(published_bytes(n, topk) / sizeof(uint32_t)) : 0;
     if (profile) DASH_HIP_CHECK(hipEventRecord(profile->ev[0], s));
-    st = launch_flash_fwd(*p, q, k, v, active_idx, n, o, published, n_clear, handed && !topk ? n_active_out : nullptr, ws + w.split_off, w.split_bytes, s);
+    // the debug output keeps attention off key parts as it does the product: the bits of the stage-level calls
+    st = launch_flash_fwd(*p, q, k, v, active_idx, n, o, published, n_clear, handed && !topk ? n_active_out : nullptr,
+                          delta_dbg ? nullptr : ws + w.split_off, delta_dbg ? 0 : w.split_bytes, s);
     if (st != DASH_OK) return st;
     if (profile) DASH_HIP_CHECK(hipEventRecord(profile->ev[1], s));
     NormSums sums{};

@@ -39,3 +39,21 @@ def test_last_rows(n, hq, hkv, dh, cut, infinite):
         want[:, h] = torch.softmax(s, dim=1) @ vh
     err = (got - want).norm(dim=2) / want.norm(dim=2)
     assert float(err.max()) <= 8e-3 and float(err.mean()) <= 3e-3
+
+
+@pytest.mark.parametrize("n,hq,hkv,dh", [(4097, 16, 4, 64), (2305, 28, 4, 128)])
+def test_with_the_debug_output_the_stage_calls_bits(n, hq, hkv, dh):
+    """With delta_dbg the layer call adds in the order of the stage-level calls, attention included."""
+    d, bf = hq * dh, torch.bfloat16
+    p = B.make_params(d, hq, hkv, dh, causal=False, rule=B.RULE_NONE)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    rnd = lambda *shape: torch.randn(shape, generator=g, device="cuda").to(bf)
+    q, k, v, x, w = rnd(n, hq, dh), rnd(n, hkv, dh), rnd(n, hkv, dh), rnd(n, d), rnd(d, d)
+    idx = torch.arange(n, dtype=torch.int32, device="cuda")
+    buf = B.alloc_layer_buffers(p, n, with_delta=True)
+    B.dash_attn_layer(p, x, q, k, v, w, idx, n, buf)
+    o, x_next, delta = (torch.empty((n, d), dtype=t, device="cuda") for t in (bf, bf, torch.float32))
+    partials = torch.empty((B.norm_partials_per_row(p), n, 2), dtype=torch.float32, device="cuda")
+    B.dash_flash_fwd(p, q, k, v, idx, n, o)
+    B.dash_wo_residual_rownorm(p, o, w, x, n, x_next, partials, delta)
+    assert torch.equal(buf.x_next[:n], x_next) and torch.equal(buf.delta_dbg[:n], delta)
