@@ -379,6 +379,12 @@ inline SmallPlan few_tile_plan(int M, int K, int N, int cu, bool norms, int head
     return best;
 }
 
+// The form a product takes (form < 0 and no few_rows: the large tiles), for the launcher and for the checks.
+inline SmallPlan product_plan(const GemmPlan& g, int M, int K, int N, int cu, bool norms, int head, bool scratch, size_t scratch_bytes) {
+    const SmallPlan small = small_plan(M, K, N, cu, norms, head, scratch, scratch_bytes, large_tiles_us(g, M, N, cu));
+    return few_tile_plan(M, K, N, cu, norms, head, scratch, scratch_bytes, tall_tile_plan(M, N, cu, small));
+}
+
 // ------------------------------------------------------------------------------------------------
 // Attention: K/V tiles of 64 keys, rows of DH bf16, unpadded, 16-byte chunks XOR-swizzled inside a row. One
 // load instruction moves 1 KB = 64 / CPR rows; lane l lands in physical chunk l % CPR of row l / CPR. The four

@@ -340,39 +340,19 @@ int dash_check_few_tiles(int M, int K, int N, int bm, int parts, long long* n_lo
     return c.status;
 }
 
-// Those tiles' choice: out[0..3] = rows of a tile (0: another form), tiles, parts, K steps per part.
-void dash_few_tile_plan(int M, int K, int N, int cu, int norms, int head, unsigned long long scratch, int* out) {
-    const GemmPlan g = gemm_plan(M, K, N, cu, scratch > 0, (size_t)scratch);
-    const SmallPlan s = small_plan(M, K, N, cu, norms != 0, head, scratch > 0, (size_t)scratch, large_tiles_us(g, M, N, cu));
-    const SmallPlan p = few_tile_plan(M, K, N, cu, norms != 0, head, scratch > 0, (size_t)scratch, s);
-    out[0] = p.few_rows; out[1] = p.tiles; out[2] = p.parts; out[3] = p.ksteps_per_part;
-}
-
-// The form a product takes with the taller tiles among them: out[0..1] = form, tiles.
-void dash_tall_tile_plan(int M, int K, int N, int cu, int norms, unsigned long long scratch, int* out) {
-    const GemmPlan g = gemm_plan(M, K, N, cu, scratch > 0, (size_t)scratch);
-    const SmallPlan p = tall_tile_plan(M, N, cu, small_plan(M, K, N, cu, norms != 0, 0, scratch > 0, (size_t)scratch, large_tiles_us(g, M, N, cu)));
-    out[0] = p.form; out[1] = p.tiles;
-}
-
 // K parts of the left-over half tiles, 1: one pass.
 int dash_rest_parts(int M, int K, int N, int cu, unsigned long long scratch) {
     return rest_parts(gemm_plan(M, K, N, cu, scratch > 0, (size_t)scratch), cu, (size_t)scratch);
 }
 
-// The form a product takes: out[0..3] = form (-1: large tiles), tiles, parts, K steps per part.
-void dash_small_plan(int M, int K, int N, int cu, int norms, unsigned long long scratch, int* out) {
-    const GemmPlan g = gemm_plan(M, K, N, cu, scratch > 0, (size_t)scratch);
-    const SmallPlan p = small_plan(M, K, N, cu, norms != 0, 0, scratch > 0, (size_t)scratch, large_tiles_us(g, M, N, cu));
-    out[0] = p.form; out[1] = p.tiles; out[2] = p.parts; out[3] = p.ksteps_per_part;
-}
-
-// How a product whose columns have to lie in one tile by heads of `head` columns (0: none) is launched: out[0..4] = small form (-1:
-// large tiles) and its K parts; the large tiles' K parts, half tiles left over, and those tiles' K parts.
+// How a product whose columns have to lie in one tile by heads of `head` columns (0: none) is launched: out[0..4] = small form (-1: large
+// or few-row tiles), tiles, K parts, K steps per part, rows of the few-row tiles (0: not those); out[5..7] = if on large tiles, their K parts,
+// the half tiles left over, and those tiles' K parts.
 void dash_product_plan(int M, int K, int N, int cu, int norms, int head, unsigned long long scratch, int* out) {
     const GemmPlan g = gemm_plan(M, K, N, cu, scratch > 0, (size_t)scratch);
-    const SmallPlan p = small_plan(M, K, N, cu, norms != 0, head, scratch > 0, (size_t)scratch, large_tiles_us(g, M, N, cu));
-    out[0] = p.form; out[1] = p.parts; out[2] = g.parts; out[3] = g.rest; out[4] = rest_parts(g, cu, (size_t)scratch);
+    const SmallPlan p = product_plan(g, M, K, N, cu, norms != 0, head, scratch > 0, (size_t)scratch);
+    out[0] = p.form; out[1] = p.tiles; out[2] = p.parts; out[3] = p.ksteps_per_part; out[4] = p.few_rows;
+    out[5] = g.parts; out[6] = g.rest; out[7] = rest_parts(g, cu, (size_t)scratch);
 }
 
 // The item that each of `slots` workgroups takes on `units` units.

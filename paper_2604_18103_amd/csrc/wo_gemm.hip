@@ -1579,10 +1579,7 @@ static dash_status launch_gemm(const __bf16* A, const __bf16* B, int M, int K, i
     if (sums_out) *sums_out = NormSums{partials, (N + kGN - 1) / kGN, 1};
     // the debug output keeps the product off K parts and small tiles: with and without scratch it has the same bits
     const int head = EPI == EPI_QKV_ROPE ? 2 * qkv.half : 0;
-    const size_t scratch_bytes = split_ws ? split_bytes : 0;
-    SmallPlan small = small_plan(M, K, N, compute_units(), norms, head, split_ws != nullptr, scratch_bytes, large_tiles_us(g, M, N, compute_units()));
-    small = tall_tile_plan(M, N, compute_units(), small);
-    small = few_tile_plan(M, K, N, compute_units(), norms, head, split_ws != nullptr, scratch_bytes, small);
+    const SmallPlan small = product_plan(g, M, K, N, compute_units(), norms, head, split_ws != nullptr, split_ws ? split_bytes : 0);
     if ((small.form >= 0 || small.few_rows > 0) && !delta_dbg) {
         GemmArgs a = args;
         if (!norms && small.parts < 2) a.partials = nullptr;

@@ -4,16 +4,13 @@ import ctypes
 import numpy as np
 import pytest
 
+from test_small_tile_plan import product_plan
 from test_staging_addresses import _load
 
 
-def few_plan(M, K, N, cu=256, norms=1, head=0, scratch=1 << 26):
-    lib = _load()
-    lib.dash_few_tile_plan.argtypes = [ctypes.c_int] * 6 + [ctypes.c_ulonglong, ctypes.POINTER(ctypes.c_int)]
-    lib.dash_few_tile_plan.restype = None
-    out = (ctypes.c_int * 4)()
-    lib.dash_few_tile_plan(M, K, N, cu, norms, head, scratch, out)
-    return tuple(out)
+def few_plan(*args, **kw):
+    p = product_plan(*args, **kw)
+    return p.few_rows, p.tiles, p.parts, p.per
 
 
 @pytest.mark.parametrize("bm", [16, 32, 48])

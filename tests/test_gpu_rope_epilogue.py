@@ -1,12 +1,10 @@
 """q/k/v projections with the rotary embedding in the product's epilogue, through every form the product takes."""
-import ctypes
-
 import numpy as np
 import pytest
 import torch
 
 from paper_2604_18103_amd import binding as B
-from test_small_tile_plan import _lib
+from test_small_tile_plan import form_of, product_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -23,19 +21,23 @@ def _rotate(u, pos, theta):
     return torch.cat([lo * c - hi * s, lo * s + hi * c], dim=2)
 
 
-# rows, width, query / key-value heads, head size: 64x64, 64x128 and 128x128 tiles (one and two workgroups per unit), K parts,
+# rows, width, query / key-value heads, head size: few-row, 64x64, 64x128 and 128x128 tiles (one and two workgroups per unit), K parts,
 # whole tiles, half tiles, left-over tiles in K parts
 SHAPES = [(1, 64, 1, 1, 64), (65, 512, 6, 1, 64), (129, 512, 4, 2, 128), (70, 3584, 4, 2, 128), (70, 3584, 6, 1, 64),
           (333, 1024, 28, 4, 128), (804, 1024, 28, 4, 128), (1300, 512, 28, 4, 128), (2500, 3584, 28, 4, 128),
           (3612, 3584, 28, 4, 128), (4700, 512, 24, 8, 64), (5100, 512, 28, 4, 128)]
 
 
-# the form each of these takes with the scratch left after the table: small form and its K parts (-1: large tiles), the large
-# tiles' K parts, whether half tiles are left over, and those in K parts
-PLANNED = [((65, 512, 6, 1, 64), (0, 1)), ((300, 1024, 28, 4, 64), (0, 1)), ((70, 3584, 6, 1, 64), (0, 8)),
-           ((70, 3584, 4, 2, 128), (0, 8)), ((16, 8192, 28, 4, 128), (1, 7)), ((600, 1024, 28, 4, 64), (1, 1)),
-           ((333, 1024, 28, 4, 128), (1, 1)), ((804, 1024, 56, 8, 64), (2, 1)), ((804, 1024, 28, 4, 128), (2, 1)),
-           ((2000, 512, 28, 4, 64), (3, 1)), ((1300, 512, 28, 4, 128), (3, 1)), ((300, 14336, 56, 8, 64), (-1, 7, False, 1)),
+# the form each of these takes with the scratch left after the table: small form (0 to 4) or rows of the few-row tiles (16, 32, 48) and its
+# K parts; -1 (large tiles), their K parts, whether half tiles are left over, and those in K parts
+PLANNED = [((65, 512, 6, 1, 64), (16, 1)), ((300, 1024, 28, 4, 64), (48, 1)), ((70, 3584, 6, 1, 64), (32, 7)),
+           ((70, 3584, 4, 2, 128), (48, 7)), ((16, 8192, 28, 4, 128), (16, 3)), ((1628, 832, 7, 1, 64), (0, 1)),
+           ((1089, 320, 1, 1, 64), (0, 1)), ((733, 832, 16, 2, 64), (0, 1)), ((252, 7360, 5, 1, 64), (0, 9)),
+           ((103, 5248, 16, 4, 64), (0, 5)), ((312, 3264, 4, 1, 128), (0, 4)), ((53, 2880, 32, 4, 128), (0, 3)),
+           ((600, 1024, 28, 4, 64), (1, 1)), ((333, 1024, 28, 4, 128), (1, 1)), ((208, 6080, 16, 4, 64), (1, 5)),
+           ((289, 2432, 16, 4, 128), (1, 2)), ((804, 1024, 56, 8, 64), (2, 1)), ((804, 1024, 28, 4, 128), (2, 1)),
+           ((2000, 512, 28, 4, 64), (3, 1)), ((1300, 512, 28, 4, 128), (3, 1)), ((1400, 2048, 28, 4, 128), (3, 1)),
+           ((1345, 1088, 52, 2, 64), (4, 1)), ((1200, 1024, 28, 4, 128), (4, 1)), ((300, 14336, 56, 8, 64), (-1, 7, False, 1)),
            ((300, 14336, 28, 4, 128), (-1, 7, False, 1)), ((2500, 3584, 56, 8, 64), (-1, 1, False, 1)),
            ((3612, 1024, 56, 8, 64), (-1, 1, True, 1)), ((5100, 512, 28, 4, 128), (-1, 1, True, 1)),
            ((3612, 3584, 56, 8, 64), (-1, 1, True, 6)), ((3612, 3584, 28, 4, 128), (-1, 1, True, 6))]
@@ -46,13 +48,11 @@ def test_every_form_against_fp64(shape, form):
     """Both head sizes in every form of the product: the partner column lies 32 or 64 columns away, in the same tile, the
     neighbouring wave's, or another lane's of the second pass."""
     n, d, hq, hkv, dh = shape
-    lib, out = _lib(), (ctypes.c_int * 5)()
-    lib.dash_product_plan.argtypes = [ctypes.c_int] * 6 + [ctypes.c_ulonglong, ctypes.POINTER(ctypes.c_int)]
     p = B.make_params(d, hq, hkv, dh, rule=B.RULE_NONE)
     scratch = B.qkv_workspace_bytes(p, n) - (n * (dh // 2) * 8 + 255) // 256 * 256
     units = torch.cuda.get_device_properties(0).multi_processor_count
-    lib.dash_product_plan(n, d, (hq + 2 * hkv) * dh, units, 0, dh, max(scratch, 1), out)
-    got = tuple(out)[:2] if form[0] >= 0 else (out[0], out[2], out[3] > 0, out[4])
+    plan = product_plan(n, d, (hq + 2 * hkv) * dh, units, 0, dh, max(scratch, 1))
+    got = (form_of(plan), plan.parts) if form_of(plan) >= 0 else (-1, plan.large_parts, plan.rest > 0, plan.rest_parts)
     assert got == form
     test_against_fp64(n, d, hq, hkv, dh)
 

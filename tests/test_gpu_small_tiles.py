@@ -1,5 +1,5 @@
 """The small-tile product in each of its forms, at the edges of the tiles and of the K groups, with every epilogue, against
-fp64 sums of the same bf16 operands."""
+fp64 sums of the same bf16 operands. The forms are what the launcher itself decides (product_plan)."""
 import ctypes
 
 import numpy as np
@@ -7,20 +7,22 @@ import pytest
 import torch
 
 from paper_2604_18103_amd import binding as B
-from test_small_tile_plan import _lib
+from test_small_tile_plan import _lib, form_of, product_plan
 
 pytestmark = pytest.mark.gpu
 
-# (rows, query heads of 64, width, the form (64x64, 64x128, 128x128 with one and with two workgroups per unit), K parts)
-PROJECTIONS = [(1, 1, 64, 0, 1), (65, 3, 200, 0, 1), (129, 8, 512, 0, 1), (70, 56, 3584, 1, 4), (333, 56, 3584, 1, 1),
-               (1300, 16, 1000, 1, 1), (16, 300, 520, 1, 50), (804, 56, 3584, 2, 1), (2200, 8, 1032, 2, 1),
-               (1601, 56, 3584, 3, 1), (5003, 9, 1096, 3, 1)]
+# (rows, query heads of 64, width, the form (0 to 4: 64x64, 64x128, 128x128 with one and with two workgroups per unit, 192x128; 16: few-row
+# tiles of 16 rows), K parts)
+PROJECTIONS = [(1, 1, 64, 16, 1), (65, 3, 200, 16, 1), (129, 8, 512, 16, 1), (16, 300, 520, 16, 19),
+               (149, 1, 3328, 0, 1), (1089, 5, 72, 0, 1), (2111, 9, 200, 0, 1), (293, 24, 3072, 0, 1), (632, 108, 1600, 0, 1),
+               (305, 50, 896, 0, 3), (359, 57, 544, 0, 4),
+               (333, 56, 3584, 1, 1), (1300, 16, 1000, 1, 1), (70, 56, 3584, 1, 4), (804, 56, 3584, 2, 1), (2200, 8, 1032, 2, 1),
+               (5003, 9, 1096, 3, 1), (1873, 46, 3216, 3, 1), (2459, 38, 2968, 3, 1), (1601, 56, 3584, 4, 1)]
 
 
-def _plan(M, K, N, norms, scratch):
-    out = (ctypes.c_int * 4)()
-    _lib().dash_small_plan(M, K, N, torch.cuda.get_device_properties(0).multi_processor_count, norms, scratch, out)
-    return tuple(out)
+def _plan(M, K, N, norms, scratch, head=0):
+    p = product_plan(M, K, N, torch.cuda.get_device_properties(0).multi_processor_count, norms, head, scratch)
+    return (form_of(p), *p[1:4])
 
 
 def _rand(rng, shape, scale=1.0):
@@ -52,7 +54,24 @@ def test_projection(n, heads, d, form, parts):
         assert float((part[..., e].double() - blocks).abs().max()) <= 1e-4 * float(blocks.max())
 
 
-@pytest.mark.parametrize("n,d,hq,hkv,m", [(70, 512, 6, 2, 704), (333, 1024, 8, 4, 1408), (1205, 512, 12, 2, 1472), (2300, 512, 8, 2, 2816)])
+# rows, width, heads of 64, key/value heads, feed-forward width: the forms of the q/k/v product over the concatenated weight, of the one over
+# w_q (plain store), of gate and up, and of the down projection
+FRONT_AND_FFN = {(70, 512, 6, 2, 704): (16, 16, 16, 16), (333, 1024, 8, 4, 1408): (32, 16, 1, 32), (1205, 512, 12, 2, 1472): (1, 0, 2, 0),
+                 (2300, 512, 8, 2, 2816): (1, 1, -1, 1), (149, 64, 52, 2, 1664): (0, 0, 0, 16), (1205, 512, 40, 2, 2240): (2, 2, 3, 0),
+                 (2000, 512, 36, 2, 1152): (3, 3, 3, 0), (900, 1024, 72, 4, 2816): (4, 4, 4, 0)}
+
+
+@pytest.mark.parametrize("n,d,hq,hkv,m", FRONT_AND_FFN)
+def test_forms_of_front_end_and_feed_forward(n, d, hq, hkv, m):
+    p = B.make_params(d, hq, hkv, 64, rule=B.RULE_NONE)
+    qkv, ffn = max(B.qkv_workspace_bytes(p, n), 256), B.ffn_workspace_bytes(p, n, m)
+    up256 = lambda v: -(-v // 256) * 256
+    ffn -= up256(n * d * 2) + up256(n * m * 2) + up256(n * B.norm_partials_per_row(p) * 8)  # what is left for the products
+    got = [_plan(n, d, N, 0, qkv)[0] for N in ((hq + 2 * hkv) * 64, hq * 64)] + [_plan(n, d, 2 * m, 0, ffn)[0], _plan(n, m, d, 0, ffn)[0]]
+    assert tuple(got) == FRONT_AND_FFN[n, d, hq, hkv, m]
+
+
+@pytest.mark.parametrize("n,d,hq,hkv,m", FRONT_AND_FFN)
 def test_front_end_and_feed_forward(n, d, hq, hkv, m):
     """The q/k/v routing, plain store and gating epilogues at rows and widths that end inside tiles. h is rounded to bf16 on
     the way as the library does it; results carry one bf16 rounding of a sum of d (or m) products."""

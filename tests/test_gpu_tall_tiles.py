@@ -1,4 +1,5 @@
-"""The 192 x 128 small-tile product with each of its epilogues, rows and columns ending inside tiles, against fp64."""
+"""The 192 x 128 small-tile product with the residual and norm and the q/k/v epilogues, rows and columns ending inside tiles, against fp64;
+plain store and gating: test_gpu_small_tiles.FRONT_AND_FFN."""
 import numpy as np
 import pytest
 

@@ -1,4 +1,5 @@
 """CPU check of the small-tile product: its staging addresses and tile map, and the choice of a form."""
+import collections
 import ctypes
 
 import numpy as np
@@ -13,9 +14,24 @@ def _lib():
     lib = _load()
     lib.dash_check_small_staging.argtypes = [ctypes.c_int] * 4 + [ctypes.POINTER(ctypes.c_longlong)]
     lib.dash_check_small_staging.restype = ctypes.c_int
-    lib.dash_small_plan.argtypes = [ctypes.c_int] * 5 + [ctypes.c_ulonglong, ctypes.POINTER(ctypes.c_int)]
-    lib.dash_small_plan.restype = None
+    lib.dash_product_plan.argtypes = [ctypes.c_int] * 6 + [ctypes.c_ulonglong, ctypes.POINTER(ctypes.c_int)]
+    lib.dash_product_plan.restype = None
     return lib
+
+
+Plan = collections.namedtuple("Plan", "form tiles parts per few_rows large_parts rest rest_parts")
+
+
+def product_plan(M, K, N, cu=256, norms=1, head=0, scratch=1 << 26):
+    """What the launcher decides about a product."""
+    out = (ctypes.c_int * 8)()
+    _lib().dash_product_plan(M, K, N, cu, norms, head, scratch, out)
+    return Plan(*out)
+
+
+def form_of(plan):
+    """0 to 4: the small form; 16, 32, 48: rows of the few-row tiles; -1: large tiles."""
+    return plan.few_rows or plan.form
 
 
 @pytest.mark.parametrize("form", FORMS)
@@ -48,14 +64,11 @@ def test_left_over_tiles_in_k_parts():
 
 
 def test_choice_of_a_form():
-    """Large products keep the large tiles; short ones take small tiles, along K in parts only where the tiles alone leave
-    the chip idle; without scratch none."""
-    lib = _lib()
-
+    """Large products keep the large tiles; short ones take small tiles or the few-row ones, along K in parts only where the tiles
+    alone leave the chip idle; without scratch none."""
     def plan(M, K, N, norms=1, scratch=1 << 30):
-        out = (ctypes.c_int * 4)()
-        lib.dash_small_plan(M, K, N, 256, norms, scratch, out)
-        return tuple(out)
+        p = product_plan(M, K, N, norms=norms, scratch=scratch)
+        return (form_of(p), *p[1:4])
 
     for M, K, N in ((16384, 3584, 3584), (8192, 3584, 4608), (4097, 3584, 3584), (32768, 3584, 37888), (8192, 18944, 3584)):
         assert plan(M, K, N)[0] == -1, (M, K, N)
@@ -92,14 +105,11 @@ def test_no_xcd_gets_more_than_an_eighth():
 def test_small_tiles_only_for_products_of_few_large_tiles():
     """Products of more than two large row tiles whose large tiles occupy more than half of the units keep them: several
     rounds of small tiles were up to 1.3 times as slow."""
-    lib = _lib()
-    out = (ctypes.c_int * 4)()
     rng = np.random.default_rng(11)
     shapes = [(513, 3584, 18944), (4700, 320, 3584), (8001, 320, 2112), (6600, 3584, 2080), (12001, 512, 6144)]
     shapes += [(int(rng.integers(1, 20000)), 64 * int(rng.integers(1, 300)), 8 * int(rng.integers(1, 5000))) for _ in range(400)]
     for M, K, N in shapes:
-        lib.dash_small_plan(M, K, N, 256, 1, 1 << 30, out)
+        p = product_plan(M, K, N, scratch=1 << 30)
         if M > 512 and 2 * (-(-M // 256)) * (-(-N // 256)) > 256:
-            assert out[0] == -1, (M, K, N, tuple(out))
-    lib.dash_small_plan(17, 3584, 37888, 256, 0, 1 << 30, out)
-    assert out[0] >= 0
+            assert p.form == -1 and p.few_rows in (0, 16, 32, 48) and (p.few_rows == 0 or M <= 1024), (M, K, N, p)
+    assert product_plan(17, 3584, 37888, norms=0, scratch=1 << 30).form >= 0

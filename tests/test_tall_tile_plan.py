@@ -3,17 +3,14 @@ import ctypes
 
 import numpy as np
 
-from test_small_tile_plan import _lib
+from test_small_tile_plan import _lib, product_plan
 
 TALL = 4
 
 
 def tall_plan(M, K, N, cu=256, norms=1, scratch=1 << 26):
-    lib, out = _lib(), (ctypes.c_int * 2)()
-    lib.dash_tall_tile_plan.argtypes = [ctypes.c_int] * 5 + [ctypes.c_ulonglong, ctypes.POINTER(ctypes.c_int)]
-    lib.dash_tall_tile_plan.restype = None
-    lib.dash_tall_tile_plan(M, K, N, cu, norms, scratch, out)
-    return tuple(out)
+    p = product_plan(M, K, N, cu, norms, 0, scratch)
+    return p.form, p.tiles
 
 
 def test_staging_loads_fetch_the_clamped_rows_and_columns():
