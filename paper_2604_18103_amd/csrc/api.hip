@@ -487,9 +487,9 @@ dash_status dash_attn_layer(const dash_layer_params* p, const void* x, const voi
     int32_t* counts = reinterpret_cast<int32_t*>(ws + w.counts_off);
     void* decide_ws = ws + w.decide_off;
 
-    // NONE / THRESHOLD, and TOPK of few rows: scores, decision and compaction run as one launch whose workgroups hand
-    // each other keys and the chunks' kept masks through words that have to start cleared: the attention kernel clears
-    // them on its way (TOPK of few rows hands nothing over)
+    // NONE / THRESHOLD, and TOPK of up to kFusedTopkRows rows: scores, decision and compaction run as one launch, whose workgroups hand
+    // each other the chunks' kept masks (TOPK: the rows' keys) through words that have to start cleared: the attention kernel clears
+    // them on its way (TOPK of the fewest rows hands nothing over)
     const bool topk = p->rule == DASH_RULE_TOPK, one_launch = !topk || n <= kFusedTopkRows;
     uint32_t* published = reinterpret_cast<uint32_t*>(ws + w.published_off);
     // how many norm pairs a row gets is known with the product's form: at most one per 64 columns

@@ -119,8 +119,9 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(
 // them).
 //
 // Waiting. Workgroups are dispatched in the order of their linear index (x fastest), and the publishers (c, 0) are the first of
-// the grid: a workgroup (c, y) waits for publishers (c', 0) with c' <= c only, which have a smaller linear index, are therefore
-// resident or done, and publish without having waited.
+// the grid: a workgroup (c, y) waits for publishers (c', 0) with c' <= c only, which have a smaller linear index and publish without
+// having waited. Each XCD takes its share of the grid in that order, at its own pace: where other streams' kernels fill one, its publishers
+// come later than readers elsewhere.
 // Every wait is bounded (kPubSpinLimit), and one that ends without its word fails the call: whoever gives up gathers nothing and writes
 // the survivor count -1.
 // The count is 0 when the kernel starts (cleared with the words), and its writer, one thread of the last chunk's publisher,
@@ -131,12 +132,12 @@ constexpr int kPubSpinLimit = 1 << 20;
 __device__ __forceinline__ unsigned long long wait_published(const unsigned long long* word, bool& bad) {
     unsigned long long v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     int spins = 0;
-    while (!(v & kPubReady)) {
+    while (!pub_ready(v)) {
         __builtin_amdgcn_s_sleep(4);
         if (++spins > kPubSpinLimit) break;
         v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (pub_bad(v)) bad = true;
+    if (!pub_ready(v)) bad = true;
     return v;
 }
 
@@ -169,9 +170,9 @@ __global__ __launch_bounds__(kCompactThreads) void score_decide_compact_kernel(
         }
         mask = __ballot(keep);
         if (tid == 0) {
-            __hip_atomic_store(published + 2 * chunk, pub_word0(mask, __popcll(mask), bad), __ATOMIC_RELAXED,
+            __hip_atomic_store(published + 2 * chunk, pub_word0(mask, __popcll(mask)), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(published + 2 * chunk + 1, pub_word1(mask, bad), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(published + 2 * chunk + 1, pub_word1(mask), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     } else {
         // the chunk's mask from its publisher (every lane reads the same two words: one request per wave)
@@ -486,9 +487,9 @@ size_t published_bytes(int n, bool topk) {
     return topk ? (size_t)n * sizeof(uint32_t) : (size_t)((n + kChunkRows - 1) / kChunkRows) * 2 * sizeof(unsigned long long);
 }
 
-// Scores, decision and compaction in one launch (TOPK: n <= kFusedTopkRows). `published` (published_bytes, 8-byte aligned) and
-// the count must have been cleared on this stream before (launch_flash_fwd does it for the layer call), except for
-// TOPK where few_topk holds, which hands nothing over.
+// Scores, decision and compaction in one launch (TOPK: n <= kFusedTopkRows). `published` (published_bytes, 8-byte aligned) must have been
+// cleared on this stream before (launch_flash_fwd does it for the layer call), except for TOPK where few_topk holds, which hands
+// nothing over; for NONE and THRESHOLD the count too.
 dash_status launch_score_decide_compact(const dash_layer_params& p, const NormSums& sums, int n, float* scores, uint8_t* halt, void* published, const int32_t* active_idx,
                                         const void* x_next, int row_bytes, void* x_compact, int32_t* new_active_idx,
                                         int32_t* n_active_out, hipStream_t s) {

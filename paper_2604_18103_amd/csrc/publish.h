@@ -1,26 +1,23 @@
 // The words through which the workgroups of the one-launch score + decision + compaction kernel (rules NONE and THRESHOLD) hand each other
-// the chunks' decisions, and what a reader takes from them. Plain C++ for the host and the device: the kernel uses these functions, and
-// a host program (staging_check.cpp) steps the same exchange with a key missing.
+// the chunks' decisions, and what a reader takes from them; and the keys of rule TOPK. Plain C++ for the host and the device: the kernels use
+// these functions, and host programs (publish_check.cpp) step the same exchanges with a word missing.
 //
 // Two 64-bit words per chunk of 64 rows, zero at the start, each valid on its own (one relaxed device-scope access each):
-//   word 0 = kept mask bits 0..31 | kept count << 32 | FAILED | READY      word 1 = kept mask bits 32..63 | FAILED | READY
-// FAILED: the publisher gave up and its mask means nothing (those of NONE and THRESHOLD wait for nothing and never do).
+//   word 0 = kept mask bits 0..31 | kept count << 32 | READY      word 1 = kept mask bits 32..63 | READY
+// A reader whose bounded wait ends without READY fails the call; publishers publish without having waited.
 #pragma once
 
 #include "staging_addr.h"
 
 namespace dash {
 
-constexpr unsigned long long kPubReady = 1ull << 62, kPubFailed = 1ull << 61;
+constexpr unsigned long long kPubReady = 1ull << 62;
 
-DASH_HD unsigned long long pub_word0(unsigned long long mask, int count, bool failed) {
-    return failed ? kPubReady | kPubFailed : (mask & 0xFFFFFFFFull) | ((unsigned long long)count << 32) | kPubReady;
+DASH_HD unsigned long long pub_word0(unsigned long long mask, int count) {
+    return (mask & 0xFFFFFFFFull) | ((unsigned long long)count << 32) | kPubReady;
 }
-DASH_HD unsigned long long pub_word1(unsigned long long mask, bool failed) {
-    return failed ? kPubReady | kPubFailed : (mask >> 32) | kPubReady;
-}
-// A word that never became READY (the bounded wait ended), or that says FAILED: the reader fails as well.
-DASH_HD bool pub_bad(unsigned long long w) { return (w & (kPubReady | kPubFailed)) != kPubReady; }
+DASH_HD unsigned long long pub_word1(unsigned long long mask) { return (mask >> 32) | kPubReady; }
+DASH_HD bool pub_ready(unsigned long long w) { return (w & kPubReady) != 0; }
 DASH_HD unsigned long long pub_mask(unsigned long long w0, unsigned long long w1) {
     return (w0 & 0xFFFFFFFFull) | ((w1 & 0xFFFFFFFFull) << 32);
 }

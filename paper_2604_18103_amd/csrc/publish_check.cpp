@@ -1,6 +1,6 @@
-// Host-side check of the exchange between the workgroups of the one-launch score + decision + compaction kernel (test
-// infrastructure, CPU only; part of the same small library as staging_check.cpp). Steps the kernel's protocol with the words
-// that the kernel uses (publish.h).
+// Host-side check of the exchanges between the workgroups of the one-launch score + decision + compaction kernels (test
+// infrastructure, CPU only; part of the same small library as staging_check.cpp). Steps the kernels' protocols with the words and
+// functions that they use (publish.h).
 #include <vector>
 
 #include "publish.h"
@@ -9,41 +9,46 @@ using namespace dash;
 
 extern "C" {
 
-// Steps the exchange of the one-launch TopK kernel over `chunks` chunks of 64 rows and `splits` column splits; chunk c keeps
-// c % 65 rows. late >= 0: that chunk's keys come only after every other publisher has given up waiting for them. Returns the
-// survivor count; gathered[c]: how many of chunk c's workgroups gathered rows.
-int dash_check_publish(int chunks, int splits, int late, int* gathered) {
+// Steps the exchange of the one-launch NONE / THRESHOLD kernel over `chunks` chunks of 64 rows and `splits` column splits; chunk c keeps
+// c % 65 rows. late >= 0: that chunk's publisher comes only after everybody that waits for its words has given up. backwards: the
+// others run from the last chunk to the first. Returns the survivor count; gathered[c]: how many of chunk c's workgroups gathered rows.
+int dash_check_publish(int chunks, int splits, int late, int backwards, int* gathered) {
     std::vector<unsigned long long> words((size_t)chunks * 2, 0);
     auto mask_of = [](int c) { return c % 65 == 64 ? ~0ull : (1ull << (c % 65)) - 1; };
-    for (int turn = 0; turn < 2; ++turn)  // the others first, then the late one, which finds every key
-        for (int c = 0; c < chunks; ++c) {
-            if ((c == late) != (turn == 1)) continue;
-            const bool missing = late >= 0 && c != late;
-            words[2 * c] |= pub_word0(mask_of(c), c % 65, missing);
-            words[2 * c + 1] |= pub_word1(mask_of(c), missing);
-        }
-    int n_out = 0;
-    for (int c = 0; c < chunks; ++c) {
+    auto publish = [&](int c) {
+        words[2 * c] = pub_word0(mask_of(c), c % 65);
+        words[2 * c + 1] = pub_word1(mask_of(c));
+    };
+    for (int c = 0; c < chunks; ++c) {  // publishers wait for nothing before they publish
         gathered[c] = 0;
-        for (int y = 0; y < splits; ++y) {
-            // the publisher knows whether it gave up; the others ask for the last chunk's word first, then for their own
-            bool failed = y == 0 ? late >= 0 && c != late
-                                 : pub_bad(words[2 * (chunks - 1)]) || pub_bad(words[2 * c]) || pub_bad(words[2 * c + 1]);
-            int base = 0;
-            for (int e = 0; e < c; ++e) {
-                failed = failed || pub_bad(words[2 * e]);
-                base += pub_count(words[2 * e]);
-            }
-            if (failed) {
-                n_out = -1;
-            } else {
-                if (y > 0 && pub_mask(words[2 * c], words[2 * c + 1]) != mask_of(c)) return -100;
-                ++gathered[c];
-            }
-            if (c == chunks - 1 && y == 0 && !failed && n_out == 0) n_out = base + c % 65;  // exchanges the 0
-        }
+        if (c != late) publish(c);
     }
-    return n_out;
+    int n_out = 0, wrong = 0;
+    auto rest_of = [&](int c, int y) {  // what a workgroup does once its own mask is there, or not
+        bool bad = y > 0 && !(pub_ready(words[2 * c]) && pub_ready(words[2 * c + 1]));
+        int base = 0;
+        for (int e = 0; e < c; ++e) {
+            bad = bad || !pub_ready(words[2 * e]);
+            base += pub_count(words[2 * e]);
+        }
+        if (bad) {
+            n_out = -1;
+            return;
+        }
+        if (y > 0 && pub_mask(words[2 * c], words[2 * c + 1]) != mask_of(c)) wrong = 1;
+        ++gathered[c];
+        if (c == chunks - 1 && y == 0 && n_out == 0) n_out = base + c % 65;  // exchanges the 0
+    };
+    for (int i = 0; i < chunks; ++i) {
+        const int c = backwards ? chunks - 1 - i : i;
+        for (int y = 0; y < splits; ++y)
+            if (c != late || y > 0) rest_of(c, y);
+    }
+    if (late >= 0) {
+        publish(late);
+        rest_of(late, 0);
+    }
+    return wrong ? -100 : n_out;
 }
 
 // Steps the keys' way into every thread of a one-launch TopK workgroup over n rows (take_keys); the words of rows [late0, late1) are still 0
