@@ -63,6 +63,26 @@ inline int splitk_parts(int tiles, int ksteps, int cu) {
     const int s = sa_min(cu / tiles, ksteps / kSplitMinSteps);
     return s < 2 ? 1 : s;
 }
+// Scratch bytes that let every product of up to M_cap rows with this K and N split as far as it would like to.
+constexpr int kSplitSizingUnits = 256;  // unit count assumed when sizing the scratch (the launch uses the real one)
+inline size_t gemm_splitk_bytes(int M_cap, int K, int N) {
+    const int nt = (N + kGN - 1) / kGN, ksteps = K / kGK;
+    size_t best = 0;
+    for (int mt = 1; mt <= (M_cap + kGM - 1) / kGM; ++mt) {
+        const int parts = splitk_parts(mt * nt, ksteps, kSplitSizingUnits);
+        if (parts < 2) break;  // more row tiles only split less
+        const size_t bytes = (size_t)parts * sa_min(mt * kGM, M_cap) * N * sizeof(float);
+        best = bytes > best ? bytes : best;
+    }
+    return (best + 255) / 256 * 256;
+}
+// The layer call's: as well the fine row norms of a small-tile projection (one pair per row and 64 columns); products of more than 1 MB of
+// them are no small ones, and one that finds less scratch takes the large tiles.
+inline size_t wo_scratch_bytes(int n, int K, int N) {
+    const size_t fine = ((size_t)n * ((N + 63) / 64) * 2 * sizeof(float) + 255) / 256 * 256, most = (size_t)1 << 20;
+    const size_t norms = fine < most ? fine : most, split = gemm_splitk_bytes(n, K, N);
+    return split > norms ? split : norms;
+}
 
 // Order in which the output tiles of a product are handed out ("tile index" below), and which workgroup takes which
 // index. Workgroup b of a launch runs on XCD b % 8, and each XCD has its own L2: what the 32 workgroups that an XCD

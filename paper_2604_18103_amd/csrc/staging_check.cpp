@@ -559,6 +559,8 @@ int dash_few_tail_parts(int n, int Hq, int head_dim, int cu, size_t scratch_byte
     *blocks_per_part = g.blocks_per_part;
     return g.parts;
 }
+// Bytes of the layer call's scratch that the projection and those parts share.
+size_t dash_wo_scratch_bytes(int n, int K, int N) { return wo_scratch_bytes(n, K, N); }
 // Whether the rows beyond the last whole tile take the few-row form (where dash_fa_form is 2).
 int dash_fa_few_tail(int n, int Hq, int head_dim, int cu) { return fa_few_tail(n, Hq, head_dim, cu); }
 

@@ -1451,20 +1451,6 @@ dash_status init_gemm_kernels() {
 
 // Split-K (staging_addr.h: splitk_parts, gemm_plan): each part writes fp32 sums to scratch, and a second kernel
 // adds the parts in a fixed order and applies the epilogue.
-constexpr int kSplitSizingUnits = 256;  // unit count assumed when sizing the scratch (the launch uses the real one)
-
-// Scratch bytes that let every product of up to M_cap rows with this K and N split as far as it would like to.
-size_t gemm_splitk_bytes(int M_cap, int K, int N) {
-    const int nt = (N + kGN - 1) / kGN, ksteps = K / kGK;
-    size_t best = 0;
-    for (int mt = 1; mt <= (M_cap + kGM - 1) / kGM; ++mt) {
-        const int parts = splitk_parts(mt * nt, ksteps, kSplitSizingUnits);
-        if (parts < 2) break;  // more row tiles only split less
-        const size_t rows = (size_t)min(mt * kGM, M_cap);
-        best = max(best, (size_t)parts * rows * N * sizeof(float));
-    }
-    return (best + 255) / 256 * 256;
-}
 
 struct GemmArgs {
     const __bf16 *A, *B;
@@ -1628,12 +1614,8 @@ static dash_status launch_gemm(const __bf16* A, const __bf16* B, int M, int K, i
     return launch_status();
 }
 
-// Fine row norms of a small-tile projection (one pair per row and 64 columns); products of more than 1 MB of them are no
-// small ones, and one that finds less scratch takes the large tiles.
 size_t wo_splitk_bytes(const dash_layer_params& p, int n) {
-    if (p.dtype != DASH_BF16) return 0;
-    const size_t fine = (size_t)n * ((p.d + 63) / 64) * 2 * sizeof(float);
-    return max(gemm_splitk_bytes(n, p.n_q_heads * p.head_dim, p.d), min((fine + 255) / 256 * 256, (size_t)1 << 20));
+    return p.dtype == DASH_BF16 ? wo_scratch_bytes(n, p.n_q_heads * p.head_dim, p.d) : 0;
 }
 
 dash_status launch_wo_residual_rownorm(const dash_layer_params& p, const void* o, const void* w_o,

@@ -11,6 +11,13 @@ def parts_of(n, hq, dh, cu, scratch):
     return _load().dash_few_tail_parts(n, hq, dh, cu, ctypes.c_size_t(scratch), ctypes.byref(per)), per.value
 
 
+def layer_scratch(n, K, N):
+    """Bytes that the layer call has for the parts: the projection's scratch."""
+    lib = _load()
+    lib.dash_wo_scratch_bytes.restype = ctypes.c_size_t
+    return lib.dash_wo_scratch_bytes(n, K, N)
+
+
 @pytest.mark.parametrize("dh", [64, 128])
 @pytest.mark.parametrize("hq", [1, 16, 28, 64, 300])
 def test_every_block_once(hq, dh):

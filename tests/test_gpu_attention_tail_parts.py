@@ -1,20 +1,22 @@
-"""Layer calls without a causal mask whose last rows' keys are cut over several workgroups, against fp64: the projection is the identity and
-x zero, so x_next holds the attention's result."""
+"""Layer calls without a causal mask whose last rows take the few-row form, their keys cut over several workgroups or not, against fp64: the
+projection is the identity and x zero, so x_next holds the attention's result."""
 import pytest
 
 torch = pytest.importorskip("torch")
 from paper_2604_18103_amd import binding as B
 from test_attention_form import ONE_AND_TAIL
-from test_attention_tail_parts import parts_of
+from test_attention_tail_parts import layer_scratch, parts_of
 from test_staging_addresses import _load
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,hq,hkv,dh,cut", [(4097, 16, 4, 64, True), (4129, 16, 4, 64, True), (8200, 16, 4, 64, True), (4319, 16, 4, 64, False),
-                                             (2305, 28, 4, 128, True), (2337, 28, 4, 128, True), (4609, 28, 4, 128, True)])
+# rows, query and key/value heads, head size, parts of the last rows' keys (more than half of the units in workgroups: not cut)
+@pytest.mark.parametrize("n,hq,hkv,dh,parts", [(4097, 16, 4, 64, 9), (4129, 16, 4, 64, 6), (8200, 16, 4, 64, 11), (4319, 16, 4, 64, 2),
+                                               (2785, 24, 8, 64, 1), (2305, 28, 4, 128, 5), (2337, 28, 4, 128, 4), (4609, 28, 4, 128, 7),
+                                               (2433, 28, 4, 128, 1)])
 @pytest.mark.parametrize("infinite", [None, slice(0, 1024), slice(2048, 5000)])
-def test_last_rows(n, hq, hkv, dh, cut, infinite):
+def test_last_rows(n, hq, hkv, dh, parts, infinite):
     """P and the result are rounded to bf16, 2.3e-3 of a row (test_gpu_attention_few): 3e-3 on the mean, 8e-3 on the largest. Keys without
     a finite score fill whole parts, the first ones and the last ones."""
     cu, d = torch.cuda.get_device_properties(0).multi_processor_count, hq * dh
@@ -26,8 +28,7 @@ def test_last_rows(n, hq, hkv, dh, cut, infinite):
     if infinite is not None:
         q[:, :, 0], k[:, :, 0] = 1.0, 0.0
         k[infinite, :, 0] = float("-inf")
-    if cut:
-        assert parts_of(n, hq, dh, cu, max(n * (d // 64) * 8, 1 << 18))[0] > 1
+    assert parts_of(n, hq, dh, cu, layer_scratch(n, d, d))[0] == parts
     x, idx = torch.zeros((n, d), dtype=torch.bfloat16, device="cuda"), torch.arange(n, dtype=torch.int32, device="cuda")
     B.dash_attn_layer(p, x, q, k, v, torch.eye(d, dtype=torch.bfloat16, device="cuda"), idx, n, buf)
     r0 = n - n % 256

@@ -17,9 +17,10 @@ def test_every_cut(n, kind):
         _layer(n, 128 if n % 2 else 1032, 1, min(k_keep, n), prot, kind, seed=n + i)
 
 
-@pytest.mark.parametrize("n,d,hq", [(256, 8192, 1), (257, 8192, 1), (512, 8192, 2), (512, 4096, 2), (257, 4104, 2), (400, 8192, 128), (257, 16384, 1)])
+@pytest.mark.parametrize("n,d,hq", [(256, 8192, 1), (257, 8192, 1), (512, 8192, 2), (512, 4096, 2), (257, 4104, 2), (400, 8192, 128), (257, 16384, 1),
+                                    (257, 2048, 1), (512, 2048, 1), (257, 2056, 1), (512, 2056, 1)])
 def test_wide_rows(n, d, hq):
-    """Up to 256 rows, and with 64 and more pairs of a row beyond that: words that are handed over, or not; with 128 heads the product's
+    """Up to 256 rows, and with 32 pairs of a row, 33 and more beyond that: keys that are handed over, or not; with 128 heads the product's
     large tiles leave fewer pairs than the width has columns of 64."""
     for i, (k_keep, prot, kind) in enumerate(((n // 3, (0, 0), "spread"), (n - 1, (5, 7), "spread"), (n // 2 + 5, (0, 0), "few"))):
         _layer(n, d, hq, k_keep, prot, kind, seed=n + i)

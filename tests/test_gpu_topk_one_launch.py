@@ -1,5 +1,5 @@
-"""The layer call's TOPK rule up to 768 rows, where scores, decision and compaction are one launch: against the oracle's
-TopK on the GPU's own scores, bit for bit."""
+"""The layer call's TOPK rule where scores, decision and compaction are one launch (up to 4096 rows, at lengths of chunks and a few hundred
+rows; longer ones: test_gpu_topk_compact.py): against the oracle's TopK on the GPU's own scores, bit for bit."""
 import numpy as np
 import pytest
 import torch
