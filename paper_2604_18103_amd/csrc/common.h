@@ -104,7 +104,7 @@ dash_status launch_score_rows(const float* delta, const void* x, int n, int d, i
 // TOPK in one launch with score and compaction up to this many rows (topk_compact_kernel), four keys per thread. Layer call in a graph,
 // score, selection and compaction one after the other (up to 768 rows: in one launch that ranked by counting) / this, us: width 512
 // 640 rows 24.9 / 23.1, 1000 28.0 / 26.0, 2000 34.6 / 32.8; 1024 600 25.1 / 22.9, 1500 36.0 / 34.2, 4000 76.9 / 76.4; 3584 700 58.0 / 52.5 (of which
-// 1.5 are the projection's), 2120 116.1 / 114.2, 4096 213.1 / 211.9. With eight keys per thread 6874 rows 465.6 / 465.0 and a chain's layer of
+// 1.5 are the projection's), 2120 116.1 / 114.2, 4096 213.1 / 211.9 (and 0.3 to 0.6 less since: topk_compact_kernel). With eight keys per thread 6874 rows 465.6 / 465.0 and a chain's layer of
 // them 685.7 / 687.2: there every workgroup's selection takes what the launches do.
 constexpr int kFusedTopkRows = 4096;
 // ... of these, up to this many without an exchange, every workgroup deciding about all rows itself (topk_compact_few_kernel): always up

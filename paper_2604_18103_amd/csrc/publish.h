@@ -24,8 +24,8 @@ DASH_HD unsigned long long pub_mask(unsigned long long w0, unsigned long long w1
 DASH_HD int pub_count(unsigned long long w0) { return (int)((w0 >> 32) & 0x7Full); }
 
 // Rule TOPK (topk_compact_kernel): one 32-bit word per row, its score's key, zero at the start. No key is 0, so a word is its own READY
-// flag. Keys u of a thread are rows u * stride + tid; a key whose word is still 0 when it has been asked for kKeyAsks times (a microsecond
-// or less each; they come after two to five) is made from its row's norm pairs, which the launch before has written. So nothing
+// flag. Keys u of a thread are rows u * stride + tid; a key whose word is still 0 when it has been asked for kKeyAsks times (a trip to
+// memory each: tens of microseconds in all, several times what the whole launch takes) is made from its row's norm pairs, which the launch before has written. So nothing
 // depends on when, or whether, the word's writer gets onto the chip: the XCDs take their workgroups each at its own pace, and beside
 // calls on other streams a writer may start long after those that ask for its words.
 // ask(row): the row's word; own(row): its key from the pairs; rest(): between two rounds of asking.
