@@ -1449,9 +1449,6 @@ dash_status init_gemm_kernels() {
     return err == hipSuccess && compute_units() > 0 ? DASH_OK : DASH_ERR_HIP;
 }
 
-// Split-K (staging_addr.h: splitk_parts, gemm_plan): each part writes fp32 sums to scratch, and a second kernel
-// adds the parts in a fixed order and applies the epilogue.
-
 struct GemmArgs {
     const __bf16 *A, *B;
     int M, K, N;
@@ -1483,7 +1480,7 @@ static void launch_few_tiles(const SmallPlan& g, const GemmArgs& a, hipStream_t 
     }
 }
 
-// Adds the K parts and applies the epilogue.
+// Adds the K parts (staging_addr.h: splitk_parts, gemm_plan), whose fp32 sums lie in the scratch, in a fixed order and applies the epilogue.
 template <int EPI>
 static void launch_splitk_reduce(const float* sums, int parts, const GemmArgs& a, hipStream_t s) {
     const int cols_per_wave = EPI == EPI_SWIGLU ? 1024 : 512;
